@@ -275,6 +275,20 @@ int fc_run_fused_static(const fc_graph *g, const fc_partition *p, const fc_buffe
 int fc_run_unfused(const fc_graph *g, const fc_buffer *bufs,
                    void *scratch, size_t scratch_bytes, void *hip_stream);
 
+/* fc_run_fused (p == NULL: fc_run_unfused) in two halves, for callers that run one program on
+ * the same buffers many times.  fc_bind does everything a run does on the host -- the checks, the
+ * choice of the kernels, the arguments and the sizes of their launches -- and enqueues nothing;
+ * fc_run_bound enqueues the launches.  The graph, the clustering and the buffer table are not
+ * needed after fc_bind; the device memory they name and the scratch buffer are, until the last run
+ * has finished.  A bound program belongs to the device that was current in fc_bind.  It is not
+ * changed by running: any number of threads and streams may run it, under the rule for runs that
+ * share a scratch buffer.  Same errors as fc_run_fused / fc_run_unfused; fc_unbind(NULL) does nothing. */
+typedef struct fc_bound fc_bound;
+int fc_bind(const fc_graph *g, const fc_partition *p, const fc_buffer *bufs, void *scratch, size_t scratch_bytes,
+            fc_bound **out);
+int fc_run_bound(const fc_bound *b, void *hip_stream);
+int fc_unbind(fc_bound *b);
+
 /* Status of the device work enqueued so far by fc_run_* calls that used `scratch`.
  *
  * Kernels whose workgroups hand partial results to each other (the last stage of a fold,

@@ -111,9 +111,12 @@ def lib() -> C.CDLL:
     L.fc_run_fused.argtypes = [PG, PP, C.POINTER(fc_buffer), C.c_void_p, C.c_size_t, C.c_void_p]
     L.fc_run_unfused.argtypes = [PG, C.POINTER(fc_buffer), C.c_void_p, C.c_size_t, C.c_void_p]
     L.fc_cluster_kernel.argtypes = [PG, PP, C.c_int32, C.c_char_p, C.c_size_t]
+    L.fc_bind.argtypes = [PG, PP, C.POINTER(fc_buffer), C.c_void_p, C.c_size_t, C.POINTER(C.c_void_p)]
+    L.fc_run_bound.argtypes = [C.c_void_p, C.c_void_p]
+    L.fc_unbind.argtypes = [C.c_void_p]
     L.fc_check.argtypes = [C.c_void_p, C.c_void_p]
     L.fc_run_fused_static.argtypes = [PG, PP, C.POINTER(fc_buffer), C.c_void_p]
-    for f in ("fc_check", "fc_run_fused_static", "fc_num_edges", "fc_plan", "fc_plan_weighted", "fc_plan_greedy", "fc_partition_trivial", "fc_partition_check", "fc_duplicate",
+    for f in ("fc_bind", "fc_run_bound", "fc_unbind", "fc_check", "fc_run_fused_static", "fc_num_edges", "fc_plan", "fc_plan_weighted", "fc_plan_greedy", "fc_partition_trivial", "fc_partition_check", "fc_duplicate",
               "fc_scratch_bytes", "fc_run_fused", "fc_run_unfused", "fc_cluster_kernel"):
         getattr(L, f).restype = C.c_int
     _lib = L
@@ -378,14 +381,29 @@ class BoundRun:
         self._sp, self._sb = _scratch(scratch)
         self._lib = lib()
 
+        # everything but the launches is done here (fc_bind).  What is wrong with the arguments is
+        # reported by the call, which then takes the way of fc_run_fused / fc_run_unfused.
+        handle = C.c_void_p()
+        rc = self._lib.fc_bind(self._g.ref(), C.byref(self._cp) if self._cp is not None else None, self._bufs,
+                               self._sp, self._sb, C.byref(handle))
+        self._handle = handle.value if rc == 0 else None
+        self._run = self._lib.fc_run_bound
+
     def __call__(self, stream: int = 0) -> None:
-        if self._cp is None:
+        if self._handle is not None:
+            rc = self._run(self._handle, stream)
+        elif self._cp is None:
             rc = self._lib.fc_run_unfused(self._g.ref(), self._bufs, self._sp, self._sb, stream or None)
         else:
             rc = self._lib.fc_run_fused(self._g.ref(), C.byref(self._cp), self._bufs, self._sp, self._sb,
                                         stream or None)
         if rc != 0:
             _check(rc)
+
+    def __del__(self):
+        handle, self._handle = getattr(self, "_handle", None), None
+        if handle is not None:
+            self._lib.fc_unbind(handle)
 
 
 def fc_check(scratch, stream: int = 0) -> None:

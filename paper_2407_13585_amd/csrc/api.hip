@@ -289,9 +289,11 @@ struct Prepared {
   std::shared_ptr<const fc::PreparedRun> run;
 };
 
-// use_static: run in the device's static scratch array instead of a buffer of the caller
+// use_static: run in the device's static scratch array instead of a buffer of the caller.
+// record: not NULL = keep the launches there instead of issuing them.
 static int run_common(const fc_graph *g, const fc_partition *p, const fc_buffer *bufs, void *scratch,
-                      size_t scratch_bytes, void *hip_stream, bool use_static = false) {
+                      size_t scratch_bytes, void *hip_stream, bool use_static = false,
+                      std::vector<fc::RecordedLaunch> *record = nullptr) {
   static std::mutex mu;
   static std::vector<Prepared> cache;        // most recently used first
   if (!g || g->n < 0 || (g->n > 0 && !g->nodes)) return fail(FC_E_ARG, "null graph");
@@ -346,7 +348,7 @@ static int run_common(const fc_graph *g, const fc_partition *p, const fc_buffer 
     if (rc != FC_OK) return fail(rc, err);
     scratch_bytes = FC_STATIC_SCRATCH_BYTES;
   }
-  int rc = fc::run_prepared(*run, bufs, scratch, scratch_bytes, static_cast<hipStream_t>(hip_stream), err);
+  int rc = fc::run_prepared(*run, bufs, scratch, scratch_bytes, static_cast<hipStream_t>(hip_stream), err, record);
   if (rc != FC_OK) return fail(rc, err);
   return FC_OK;
 }
@@ -368,6 +370,37 @@ int fc_run_fused_static(const fc_graph *g, const fc_partition *p, const fc_buffe
 
 int fc_run_unfused(const fc_graph *g, const fc_buffer *bufs, void *scratch, size_t scratch_bytes, void *hip_stream) {
   return guarded([&]() { return run_common(g, nullptr, bufs, scratch, scratch_bytes, hip_stream); });
+}
+
+struct fc_bound {
+  std::vector<fc::RecordedLaunch> launches;
+};
+
+int fc_bind(const fc_graph *g, const fc_partition *p, const fc_buffer *bufs, void *scratch, size_t scratch_bytes, fc_bound **out) {
+  return guarded([&]() {
+    if (!out) return fail(FC_E_ARG, "null result pointer");
+    *out = nullptr;
+    auto b = std::make_unique<fc_bound>();
+    int rc = run_common(g, p, bufs, scratch, scratch_bytes, nullptr, false, &b->launches);
+    if (rc == FC_OK) *out = b.release();
+    return rc;
+  });
+}
+
+int fc_run_bound(const fc_bound *b, void *hip_stream) {
+  return guarded([&]() {
+    if (!b) return fail(FC_E_ARG, "null bound program");
+    std::string err;
+    int rc = fc::issue_recorded(b->launches, static_cast<hipStream_t>(hip_stream), err);
+    return rc == FC_OK ? rc : fail(rc, err);
+  });
+}
+
+int fc_unbind(fc_bound *b) {
+  return guarded([&]() {
+    delete b;
+    return FC_OK;
+  });
 }
 
 int fc_check(void *scratch, void *hip_stream) {

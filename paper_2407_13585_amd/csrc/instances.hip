@@ -216,7 +216,7 @@ const std::vector<Instance> &registry() {
 static hipError_t launch_interp(const KArgs &a, const LaunchCtx &c) {
   // a fold of the cluster keeps a partial per workgroup; there may be kInterpFolds of them
   const unsigned cap = std::min<unsigned>(resident_grid(&interp_kernel<>), kMaxPartials / kInterpFolds);
-  return launch_k(&interp_kernel<>, grid_for(a.n, kBlock * kVec, cap), c.stream, a, c.ctl, c.partials);
+  return launch_k(&interp_kernel<>, grid_for(a.n, kBlock * kVec, cap), c, a, c.ctl, c.partials);
 }
 const Instance *interpreter_instance() {
   static const Instance inst = [] {

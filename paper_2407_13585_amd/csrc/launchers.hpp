@@ -32,21 +32,33 @@ unsigned grid_for(int n, int tile, unsigned cap) {
 // ---- launchers ------------------------------------------------------------
 // Launch through hipLaunchKernel so that the status returned is that of this
 // launch (hipGetLastError would also report an error an earlier, unrelated call
-// left behind on the thread).
+// left behind on the thread).  A program that is being bound (LaunchCtx::record) keeps
+// the launch instead.
 template <class... P, size_t... I>
-hipError_t launch_impl(void (*k)(P...), dim3 grid, dim3 block, hipStream_t s, std::tuple<P...> &vals,
+hipError_t launch_impl(void (*k)(P...), dim3 grid, dim3 block, const LaunchCtx &c, std::tuple<P...> &vals,
                        std::index_sequence<I...>) {
+  if (c.record) {
+    auto kept = std::make_shared<std::tuple<P...>>(vals);
+    RecordedLaunch r;
+    r.kernel = reinterpret_cast<const void *>(k);
+    r.grid = grid;
+    r.block = block;
+    r.args = {static_cast<void *>(&std::get<I>(*kept))...};
+    r.values = std::move(kept);
+    c.record->push_back(std::move(r));
+    return hipSuccess;
+  }
   void *ptrs[] = {static_cast<void *>(&std::get<I>(vals))...};
-  return hipLaunchKernel(reinterpret_cast<const void *>(k), grid, block, ptrs, 0, s);
+  return hipLaunchKernel(reinterpret_cast<const void *>(k), grid, block, ptrs, 0, c.stream);
 }
 template <class... P>
-hipError_t launch_k(void (*k)(P...), unsigned grid, hipStream_t s, int block, P... a) {
+hipError_t launch_k(void (*k)(P...), unsigned grid, const LaunchCtx &c, int block, P... a) {
   std::tuple<P...> vals(a...);
-  return launch_impl(k, dim3(grid), dim3(block), s, vals, std::index_sequence_for<P...>());
+  return launch_impl(k, dim3(grid), dim3(block), c, vals, std::index_sequence_for<P...>());
 }
 template <class... P>
-hipError_t launch_k(void (*k)(P...), unsigned grid, hipStream_t s, P... a) {
-  return launch_k(k, grid, s, (int)kBlock, a...);
+hipError_t launch_k(void (*k)(P...), unsigned grid, const LaunchCtx &c, P... a) {
+  return launch_k(k, grid, c, (int)kBlock, a...);
 }
 // the kernels that stride over tiles are launched with as many workgroups as are resident at once
 template <class... P>
@@ -57,19 +69,19 @@ unsigned resident_grid(void (*k)(P...)) {
 
 template <class E> hipError_t launch_store(const KArgs &a, const LaunchCtx &c) {
   if (a.n == 0) return hipSuccess;
-  return launch_k(&store_kernel<E>, grid_for(a.n, kTile, resident_grid(&store_kernel<E>)), c.stream, a);
+  return launch_k(&store_kernel<E>, grid_for(a.n, kTile, resident_grid(&store_kernel<E>)), c, a);
 }
 template <class Op, class E> hipError_t launch_fold(const KArgs &a, const LaunchCtx &c) {
-  return launch_k(&fold_kernel<Op, E>, grid_for(a.n, kTile, resident_grid(&fold_kernel<Op, E>)), c.stream, a, c.ctl,
+  return launch_k(&fold_kernel<Op, E>, grid_for(a.n, kTile, resident_grid(&fold_kernel<Op, E>)), c, a, c.ctl,
                   c.partials);
 }
 template <class ES, class Op, class EF> hipError_t launch_store_fold(const KArgs &a, const LaunchCtx &c) {
   return launch_k(&store_fold_kernel<ES, Op, EF>, grid_for(a.n, kTile, resident_grid(&store_fold_kernel<ES, Op, EF>)),
-                  c.stream, a, c.ctl, c.partials);
+                  c, a, c.ctl, c.partials);
 }
 template <class Op, class E> hipError_t launch_foldseg(const KArgs &a, const LaunchCtx &c) {
   if (a.aux == 0) return hipSuccess;
-  return launch_k(&foldseg_kernel<Op, E>, grid_for(a.aux, kBlock / 16, kMaxGrid * 8), c.stream, a);
+  return launch_k(&foldseg_kernel<Op, E>, grid_for(a.aux, kBlock / 16, kMaxGrid * 8), c, a);
 }
 // ---- column-blocked segmented fold: for tables of more than one and at most four L2s ----
 constexpr size_t kL2Bytes = 4u << 20;                 // L2 of one XCD
@@ -94,7 +106,7 @@ hipError_t launch_foldseg_blocked(const KArgs &a, const LaunchCtx &c) {
   grid = std::max(8u, std::min(grid, units * kQuarters / 8 * 8));
   const size_t elems = blocked_table_bytes<KT>(a) / 4;
   const int range_len = (int)(((elems + kQuarters - 1) / kQuarters + 31) / 32 * 32);    // whole 128-byte lines
-  return launch_k(&foldseg_blocked_kernel<Op, F, KV, KI, KT>, grid, c.stream, a, c.ctl, c.partials, c.status,
+  return launch_k(&foldseg_blocked_kernel<Op, F, KV, KI, KT>, grid, c, a, c.ctl, c.partials, c.status,
                   static_cast<unsigned long long *>(c.workspace), range_len);
 }
 
@@ -122,7 +134,7 @@ template <class Op, class E> hipError_t launch_fold_binned(const KArgs &a, const
   const size_t range_len = (binned_table_elems<E>(a) + kBins - 1) / kBins;
   const unsigned inv_range = (unsigned)(((1ull << 32) + range_len - 1) / range_len);
   const unsigned first = std::min(tiles, std::min<unsigned>(resident_grid(&bin_indices_kernel<Op, E>), kMaxPartials / 2));
-  hipError_t e = launch_k(&bin_indices_kernel<Op, E>, first, c.stream, a, c.ctl, c.partials, counts, entries, tiles, inv_range);
+  hipError_t e = launch_k(&bin_indices_kernel<Op, E>, first, c, a, c.ctl, c.partials, counts, entries, tiles, inv_range);
   if (e != hipSuccess) return e;
   // One workgroup per compute unit for the second kernel.  A compute unit's vector cache returns
   // data in request order, so its gathers (L2 hits) queue behind the entry reads (from memory) of
@@ -130,7 +142,7 @@ template <class Op, class E> hipError_t launch_fold_binned(const KArgs &a, const
   // gathers alone take 66 and the entry reads alone 27; with one or two it takes their sum.
   const int cus = device_compute_units();
   const unsigned second = std::max(8u, (unsigned)(cus > 0 ? cus : 256) / 8 * 8);
-  return launch_k(&fold_binned_kernel<Op, E>, second, c.stream, a, c.ctl, c.partials, static_cast<const int *>(counts),
+  return launch_k(&fold_binned_kernel<Op, E>, second, c, a, c.ctl, c.partials, static_cast<const int *>(counts),
                   static_cast<const int *>(entries), tiles, first);
 }
 
@@ -183,9 +195,9 @@ template <class Op, class E> hipError_t launch_fold_fine(const KArgs &a, const L
   const int cus = device_compute_units();
   const unsigned units = (unsigned)(cus > 0 ? cus : 256);
   const unsigned first = std::min(tiles, units);
-  hipError_t e = launch_k(&bin_fine_kernel<Op, E>, first, c.stream, (int)kFineBlock, a, c.ctl, c.partials, slots, tiles, cut);
+  hipError_t e = launch_k(&bin_fine_kernel<Op, E>, first, c, (int)kFineBlock, a, c.ctl, c.partials, slots, tiles, cut);
   if (e != hipSuccess) return e;
-  return launch_k(&fold_fine_kernel<Op, E>, std::min(cut.bins, units), c.stream, (int)kFineBlock, a, c.ctl, c.partials,
+  return launch_k(&fold_fine_kernel<Op, E>, std::min(cut.bins, units), c, (int)kFineBlock, a, c.ctl, c.partials,
                   static_cast<const unsigned *>(slots), tiles, cut, elems, first);
 }
 
@@ -258,7 +270,7 @@ hipError_t launch_foldseg_sorted(const KArgs &a, const LaunchCtx &c) {
   T *head = reinterpret_cast<T *>(w + s.head), *tail = reinterpret_cast<T *>(w + s.tail);
   const int cus = device_compute_units();
   const unsigned units = (unsigned)(cus > 0 ? cus : 256);
-  hipError_t e = launch_k(&seg_bin_kernel<KI>, std::min(p.tiles, units), c.stream, (int)kSegBlock, a, offsets, places,
+  hipError_t e = launch_k(&seg_bin_kernel<KI>, std::min(p.tiles, units), c, (int)kSegBlock, a, offsets, places,
                           list_place, list_index, list_count, p, elems);
   if (e != hipSuccess) return e;
   // A table range is read into LDS by every workgroup that works on it, and a workgroup fills the LDS of a compute
@@ -271,49 +283,49 @@ hipError_t launch_foldseg_sorted(const KArgs &a, const LaunchCtx &c) {
     for (unsigned q = 2; q <= 8; ++q)
       if (cost(q) < cost(parts) * 0.999) parts = q;
   }
-  e = launch_k(&seg_gather_kernel<T, KT>, p.cut.bins * parts, c.stream, (int)kSegBlock, a, static_cast<const unsigned short *>(offsets),
+  e = launch_k(&seg_gather_kernel<T, KT>, p.cut.bins * parts, c, (int)kSegBlock, a, static_cast<const unsigned short *>(offsets),
                gathered, first_row, p, elems, parts);
   if (e != hipSuccess) return e;
-  e = launch_k(&seg_rows_kernel<Op, F, KV, KT>, p.tiles, c.stream, (int)kSegRowsBlock, a, static_cast<const unsigned short *>(places),
+  e = launch_k(&seg_rows_kernel<Op, F, KV, KT>, p.tiles, c, (int)kSegRowsBlock, a, static_cast<const unsigned short *>(places),
                static_cast<const T *>(gathered), static_cast<const unsigned short *>(list_place), static_cast<const unsigned *>(list_index),
                static_cast<const unsigned *>(list_count), static_cast<const unsigned *>(first_row), head, tail, p);
   if (e != hipSuccess) return e;
-  return launch_k(&seg_join_kernel<Op>, (p.tiles + kBlock - 1) / kBlock, c.stream, a, static_cast<const unsigned *>(first_row),
+  return launch_k(&seg_join_kernel<Op>, (p.tiles + kBlock - 1) / kBlock, c, a, static_cast<const unsigned *>(first_row),
                   static_cast<const T *>(head), static_cast<const T *>(tail), p.tiles);
 }
 
 template <class EX, class EV, int Mode, bool Reverse = false> hipError_t launch_scan(const KArgs &a, const LaunchCtx &c) {
   long long tiles = std::max<long long>(1, ((long long)a.n + kScanTile - 1) / kScanTile);
   if (scan_status_words((size_t)tiles) > c.max_tiles) return hipErrorInvalidValue;
-  return launch_k(&scan_kernel<EX, EV, Mode, Reverse>, (unsigned)tiles, c.stream, kScanBlock, a, c.ctl, c.status, (unsigned)tiles);
+  return launch_k(&scan_kernel<EX, EV, Mode, Reverse>, (unsigned)tiles, c, kScanBlock, a, c.ctl, c.status, (unsigned)tiles);
 }
 // lanes per row by row length, as for the row folds
 template <class EX, bool Reverse = false, bool StoreX = false> hipError_t launch_scan_f32(const KArgs &a, const LaunchCtx &c) {
   long long tiles = std::max<long long>(1, ((long long)a.n + kScanFTile - 1) / kScanFTile);
   if (scan_status_words((size_t)tiles) > c.max_tiles) return hipErrorInvalidValue;
-  return launch_k(&scan_f32_kernel<EX, Reverse, StoreX>, (unsigned)tiles, c.stream, kScanBlock, a, c.ctl, c.status, (unsigned)tiles);
+  return launch_k(&scan_f32_kernel<EX, Reverse, StoreX>, (unsigned)tiles, c, kScanBlock, a, c.ctl, c.status, (unsigned)tiles);
 }
 template <class E, bool Reverse, bool StoreX = false> hipError_t launch_rowscan(const KArgs &a, const LaunchCtx &c) {
   if (a.aux == 0 || a.w == 0) return hipSuccess;
   if (a.w <= 64)
-    return launch_k(&rowscan_kernel<E, Reverse, 16, StoreX>, grid_for(a.aux, kBlock / 16, resident_grid(&rowscan_kernel<E, Reverse, 16, StoreX>)), c.stream, a);
+    return launch_k(&rowscan_kernel<E, Reverse, 16, StoreX>, grid_for(a.aux, kBlock / 16, resident_grid(&rowscan_kernel<E, Reverse, 16, StoreX>)), c, a);
   if (a.w <= 1024)
-    return launch_k(&rowscan_kernel<E, Reverse, kWave, StoreX>, grid_for(a.aux, kBlock / kWave, resident_grid(&rowscan_kernel<E, Reverse, kWave, StoreX>)), c.stream, a);
-  return launch_k(&rowscan_kernel<E, Reverse, kBlock, StoreX>, grid_for(a.aux, 1, resident_grid(&rowscan_kernel<E, Reverse, kBlock, StoreX>)), c.stream, a);
+    return launch_k(&rowscan_kernel<E, Reverse, kWave, StoreX>, grid_for(a.aux, kBlock / kWave, resident_grid(&rowscan_kernel<E, Reverse, kWave, StoreX>)), c, a);
+  return launch_k(&rowscan_kernel<E, Reverse, kBlock, StoreX>, grid_for(a.aux, 1, resident_grid(&rowscan_kernel<E, Reverse, kBlock, StoreX>)), c, a);
 }
 template <class EI, class EV, class EF, bool Add> hipError_t launch_scatter(const KArgs &a, const LaunchCtx &c) {
   if (a.n == 0) return hipSuccess;
-  return launch_k(&scatter_kernel<EI, EV, EF, Add>, grid_for(a.n, kTile, resident_grid(&scatter_kernel<EI, EV, EF, Add>)), c.stream, a);
+  return launch_k(&scatter_kernel<EI, EV, EF, Add>, grid_for(a.n, kTile, resident_grid(&scatter_kernel<EI, EV, EF, Add>)), c, a);
 }
 template <class E1, class E2> hipError_t launch_store2(const KArgs &a, const LaunchCtx &c) {
   if (a.n == 0) return hipSuccess;
-  return launch_k(&store2_kernel<E1, E2>, grid_for(a.n, kTile, resident_grid(&store2_kernel<E1, E2>)), c.stream, a);
+  return launch_k(&store2_kernel<E1, E2>, grid_for(a.n, kTile, resident_grid(&store2_kernel<E1, E2>)), c, a);
 }
 // lanes per row by row length: a 16-lane DPP row, a wave, or the whole workgroup
 template <class Op1, class Op2, class E, class RI> hipError_t launch_rowfold(const KArgs &a, const LaunchCtx &c) {
   if (a.aux == 0) return hipSuccess;
-  if (a.w <= 64) return launch_k(&rowfold_kernel<Op1, Op2, E, RI, 16>, grid_for(a.aux, kBlock / 16, kMaxGrid * 4), c.stream, a);
-  if (a.w <= 2048) return launch_k(&rowfold_kernel<Op1, Op2, E, RI, kWave>, grid_for(a.aux, kBlock / kWave, kMaxGrid * 4), c.stream, a);
+  if (a.w <= 64) return launch_k(&rowfold_kernel<Op1, Op2, E, RI, 16>, grid_for(a.aux, kBlock / 16, kMaxGrid * 4), c, a);
+  if (a.w <= 2048) return launch_k(&rowfold_kernel<Op1, Op2, E, RI, kWave>, grid_for(a.aux, kBlock / kWave, kMaxGrid * 4), c, a);
   if (a.aux < 1024 && a.w >= 4 * kTile) {
     // few long rows: cut every row into chunks (a multiple of the 128-bit stride) so that ~2048 workgroups run
     unsigned splits = std::min<unsigned>((unsigned)(a.w / kTile), std::max(1u, 2048u / (unsigned)a.aux));
@@ -321,11 +333,11 @@ template <class Op1, class Op2, class E, class RI> hipError_t launch_rowfold(con
     if (splits > 1) {
       unsigned chunk = (((unsigned)a.w + splits - 1) / splits + kBlock * kVec - 1) / (kBlock * kVec) * (kBlock * kVec);
       splits = ((unsigned)a.w + chunk - 1) / chunk;
-      return launch_k(&rowfold_split_kernel<Op1, Op2, E, RI>, (unsigned)a.aux * splits, c.stream, a, c.ctl, c.partials,
+      return launch_k(&rowfold_split_kernel<Op1, Op2, E, RI>, (unsigned)a.aux * splits, c, a, c.ctl, c.partials,
                       splits, chunk);
     }
   }
-  return launch_k(&rowfold_kernel<Op1, Op2, E, RI, kBlock>, grid_for(a.aux, 1, kMaxGrid * 4), c.stream, a);
+  return launch_k(&rowfold_kernel<Op1, Op2, E, RI, kBlock>, grid_for(a.aux, 1, kMaxGrid * 4), c, a);
 }
 
 // ---- signatures -----------------------------------------------------------

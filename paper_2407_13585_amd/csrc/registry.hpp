@@ -6,6 +6,7 @@
 #include <hip/hip_runtime_api.h>
 
 #include <map>
+#include <memory>
 #include <mutex>
 #include <string>
 #include <utility>
@@ -16,8 +17,21 @@ namespace fc {
 struct KArgs;
 struct Control;
 
+// One kernel launch (or, for a force whose result has a buffer of its own, one copy) of a program
+// bound to its buffers, ready to be issued: everything but the stream.
+struct RecordedLaunch {
+  const void *kernel = nullptr;   // NULL: copy `bytes` from `from` to `to`
+  dim3 grid, block;
+  std::shared_ptr<void> values;   // the argument values ...
+  std::vector<void *> args;       // ... and where each of them lies
+  void *to = nullptr;
+  const void *from = nullptr;
+  size_t bytes = 0;
+};
+
 struct LaunchCtx {
   hipStream_t stream;
+  std::vector<RecordedLaunch> *record;   // not NULL: launches are added here and not issued
   Control *ctl;                   // DEVICE: control block at the start of scratch
   unsigned long long *partials;             // DEVICE: per-workgroup partial results of a fold
   unsigned long long *status;     // DEVICE: tile status words of the single-pass scan

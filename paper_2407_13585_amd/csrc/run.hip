@@ -403,7 +403,7 @@ int prepare_run(PreparedRun &r, std::string &err) {
 }
 
 int run_prepared(const PreparedRun &r, const fc_buffer *bufs, void *scratch, size_t scratch_bytes, hipStream_t stream,
-                 std::string &err) {
+                 std::string &err, std::vector<RecordedLaunch> *record) {
   const Model &m = r.model;
   const Clustering &c = r.clustering;
   if (!bufs) { err = "null buffer table"; return FC_E_ARG; }
@@ -442,6 +442,7 @@ int run_prepared(const PreparedRun &r, const fc_buffer *bufs, void *scratch, siz
   }
   LaunchCtx ctx;
   ctx.stream = stream;
+  ctx.record = record;
   ctx.ctl = static_cast<Control *>(scratch);
   ctx.partials = reinterpret_cast<unsigned long long *>(static_cast<char *>(scratch) + kPartialsOffset);
   ctx.status = reinterpret_cast<unsigned long long *>(static_cast<char *>(scratch) + kStatusOffset);
@@ -449,32 +450,37 @@ int run_prepared(const PreparedRun &r, const fc_buffer *bufs, void *scratch, siz
   // what is left of scratch after the intermediates is the clusters' common workspace
   const size_t workspace_at = align_up(cursor, 256);
 
-  for (ClusterLaunch cl : r.launches) {
+  for (const ClusterLaunch &cl : r.launches) {
     if (cl.kind == ClusterLaunch::Alias) {
       if (bufs[cl.alias_node].ptr && bufs[cl.alias_node].ptr != ptr[cl.alias_of]) {
-        hipError_t e = hipMemcpyAsync(bufs[cl.alias_node].ptr, ptr[cl.alias_of], (size_t)m.bytes(cl.alias_node),
-                                      hipMemcpyDeviceToDevice, stream);
-        if (e != hipSuccess) { err = hipGetErrorString(e); return FC_E_HIP; }
+        RecordedLaunch copy;
+        copy.to = bufs[cl.alias_node].ptr;
+        copy.from = ptr[cl.alias_of];
+        copy.bytes = (size_t)m.bytes(cl.alias_node);
+        if (record) { record->push_back(copy); continue; }
+        const int rc = issue_recorded({copy}, stream, err);
+        if (rc != FC_OK) return rc;
       }
       continue;
     }
+    KArgs args = cl.args;
     for (size_t k = 0; k < cl.externals.size(); ++k) {
-      cl.args.in[k] = ptr[cl.externals[k]];
-      if (!cl.args.in[k]) { err = "array " + std::to_string(cl.externals[k]) + " read before it exists"; return FC_E_UNBOUND; }
+      args.in[k] = ptr[cl.externals[k]];
+      if (!args.in[k]) { err = "array " + std::to_string(cl.externals[k]) + " read before it exists"; return FC_E_UNBOUND; }
     }
-    if (cl.offsets_node >= 0) cl.args.in[kMaxIn - 1] = ptr[cl.offsets_node];
+    if (cl.offsets_node >= 0) args.in[kMaxIn - 1] = ptr[cl.offsets_node];
     for (int k = 0; k < kMaxOut; ++k)
       if (cl.out_nodes[k] >= 0) {
-        cl.args.out[k] = ptr[cl.out_nodes[k]];
-        if (!cl.args.out[k]) { err = "array " + std::to_string(cl.out_nodes[k]) + " has no buffer"; return FC_E_UNBOUND; }
+        args.out[k] = ptr[cl.out_nodes[k]];
+        if (!args.out[k]) { err = "array " + std::to_string(cl.out_nodes[k]) + " has no buffer"; return FC_E_UNBOUND; }
       }
     ctx.workspace = nullptr;
     if (cl.instance->workspace) {
-      const size_t need = cl.instance->workspace(cl.args);
+      const size_t need = cl.instance->workspace(args);
       if (workspace_at + need > scratch_bytes) { err = "scratch too small for the workspace of " + cl.sig; return FC_E_SCRATCH; }
       ctx.workspace = static_cast<char *>(scratch) + workspace_at;
     }
-    hipError_t e = cl.instance->launch(cl.args, ctx);
+    hipError_t e = cl.instance->launch(args, ctx);
     if (e != hipSuccess) {
       int count = -1, dev = -1;
       hipError_t e2 = hipGetDeviceCount(&count);
@@ -484,6 +490,15 @@ int run_prepared(const PreparedRun &r, const fc_buffer *bufs, void *scratch, siz
             std::to_string((int)e3) + ")";
       return FC_E_HIP;
     }
+  }
+  return FC_OK;
+}
+
+int issue_recorded(const std::vector<RecordedLaunch> &launches, hipStream_t stream, std::string &err) {
+  for (const RecordedLaunch &l : launches) {
+    const hipError_t e = l.kernel ? hipLaunchKernel(l.kernel, l.grid, l.block, const_cast<void **>(l.args.data()), 0, stream)
+                                  : hipMemcpyAsync(l.to, l.from, l.bytes, hipMemcpyDeviceToDevice, stream);
+    if (e != hipSuccess) { err = hipGetErrorString(e); return FC_E_HIP; }
   }
   return FC_OK;
 }

@@ -45,7 +45,11 @@ struct PreparedRun {
 
 int prepare_run(PreparedRun &r, std::string &err);
 
+// Resolves the buffers and issues the launches on `stream` or, if `record` is not NULL, adds them to it.
 int run_prepared(const PreparedRun &r, const fc_buffer *bufs, void *scratch, size_t scratch_bytes, hipStream_t stream,
-                 std::string &err);
+                 std::string &err, std::vector<RecordedLaunch> *record = nullptr);
+
+// Issues what run_prepared recorded.
+int issue_recorded(const std::vector<RecordedLaunch> &launches, hipStream_t stream, std::string &err);
 
 }  // namespace fc

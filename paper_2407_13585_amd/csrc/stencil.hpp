@@ -18,6 +18,7 @@
 #pragma once
 
 #include "kernels.hpp"
+#include "launchers.hpp"
 #include "registry.hpp"
 
 namespace fc {
@@ -157,13 +158,7 @@ hipError_t launch_stencil5(const KArgs &a, const LaunchCtx &c) {
   while ((long long)groups * ((a.h + band_rows - 1) / band_rows) > kMaxPartials - 8) band_rows *= 2;
   const int bands = std::max(1, (a.h + band_rows - 1) / band_rows);
   const int blocks = ((groups * bands + 7) / 8) * 8;
-  KArgs args = a;
-  Control *ctl = c.ctl;
-  unsigned long long *partials = c.partials;
-  int g = groups, b = bands, br = band_rows;
-  void *ptrs[] = {&args, &ctl, &partials, &g, &b, &br};
-  return hipLaunchKernel(reinterpret_cast<const void *>(&stencil5_kernel<F, FSlot, WithMax>), dim3(blocks),
-                         dim3(kBlock), ptrs, 0, c.stream);
+  return launch_k(&stencil5_kernel<F, FSlot, WithMax>, (unsigned)blocks, c, a, c.ctl, c.partials, groups, bands, band_rows);
 }
 
 }  // namespace fc

@@ -99,6 +99,23 @@ def test_run_checks_come_before_any_launch():
     expect("FC_E_SCRATCH", fc.fc_run_unfused, g, bufs, (0x10000000, B.FC_SCRATCH_CONTROL_BYTES))
 
 
+def test_a_bound_program_reports_the_errors_of_a_run_when_it_is_called():
+    # fc_bind checks what fc_run_fused checks and enqueues nothing (the fake buffers are never touched);
+    # BoundRun keeps the errors for its call, where fc_run_fused would report them
+    w = build(2, small=True)
+    g = w.graph
+    part = fc.fc_plan(g, "bytes")
+    fake = (0x10000000, 1 << 30)
+    bufs = {n.name: fake for n in g.nodes if n.kind == "input" or n.output}
+    assert B.BoundRun(g, part, bufs, fake)._handle is not None
+    for scratch in ((0, 0), (0x10000001, 1 << 30), (0x10000000, 1024)):
+        expect("FC_E_SCRATCH", B.BoundRun(g, part, bufs, scratch))
+    missing = dict(bufs)
+    del missing["idx"]
+    expect("FC_E_UNBOUND", B.BoundRun(g, part, missing, fake))
+    expect("FC_E_SCRATCH", B.BoundRun(g, None, bufs, (0x10000000, B.FC_SCRATCH_CONTROL_BYTES)))
+
+
 def test_scatter_that_reads_its_destination_is_refused():
     # the destination is updated in place; a scatter that took its values (or indices, or flags)
     # from the same array would read what it is overwriting
