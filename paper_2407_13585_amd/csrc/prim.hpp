@@ -177,13 +177,16 @@ __device__ __forceinline__ unsigned long long pack_word(unsigned value, unsigned
   return ((unsigned long long)value << 32) | (unsigned long long)((tag << 2) | state);
 }
 
+__device__ __forceinline__ bool word_ready(unsigned long long w, unsigned tag) {
+  return ((unsigned)w >> 2) == tag && ((unsigned)w & 3u) != 0u;
+}
+
 // Polls `p` until it carries `tag` with a non-zero state; returns the word, or 0
 // after kSpinLimit polls (and raises the error word).
 __device__ __forceinline__ unsigned long long wait_word(const unsigned long long *p, unsigned tag, Control *ctl) {
   for (unsigned spins = 0; spins < kSpinLimit; ++spins) {
     unsigned long long w = load_agent64(p);
-    unsigned lo = (unsigned)w;
-    if ((lo >> 2) == tag && (lo & 3u) != 0u) return w;
+    if (word_ready(w, tag)) return w;
     __builtin_amdgcn_s_sleep(1);
   }
   store_agent(&ctl->error, 1u);

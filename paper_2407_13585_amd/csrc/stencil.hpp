@@ -126,7 +126,7 @@ __global__ __launch_bounds__(kBlock) void stencil5_kernel(const KArgs a, Control
       }
     }
   }
-  if (WithMax) fold_finish<MaxF32>(m, a, 1, ctl, partials);
+  if (WithMax) fold_finish<MaxF32>(m, a, 1, ctl, partials, epoch_at_start(ctl));
 }
 
 template <class F, int FSlot, bool WithMax, int G0, int GStride>

@@ -159,6 +159,13 @@ def test_fold_sizes(n):
     run_all_modes(2, w)
 
 
+@pytest.mark.parametrize("n", [1023, 1024, 1028, 256 * 1024 + 5, (1 << 21) - 1, 1 << 21, (1 << 21) + 4, (1 << 21) + 7])
+def test_sizes_where_the_tile_changes(n):
+    # a group per lane below 2^21 elements, four above; one workgroup hands no partial over
+    run_all_modes(1, C.reverse_dot(n=n, seed=150 + n))
+    run_all_modes(4, C.compaction(n=n, seed=160 + n))
+
+
 @pytest.mark.parametrize("n", [1, 3, 4, 4095, 4096, 4097, 65536 + 17, 3 * 4096, (1 << 20) + 5])
 def test_compaction_sizes(n):
     run_all_modes(4, C.compaction(n=n, seed=300 + n))
