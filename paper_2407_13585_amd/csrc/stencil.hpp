@@ -5,16 +5,25 @@
 // orders inside one loop) and N, S, W, E are clamped unit shifts of a 2-D index.
 //
 // The generic element program would evaluate F five times per point and do
-// integer division for every index.  Here each wave walks down a strip of the
-// grid: a lane owns four adjacent columns, keeps rows r-1, r, r+1 of p in
-// registers, takes its west / east neighbours from the adjacent lanes with DPP
-// wave shifts, and evaluates F once per loaded element.  A wave's strip is 256
-// columns = eight whole 128-byte lines per row; the column left of the strip and
+// integer division for every index.  Here a wave takes units of four rows and 256
+// columns: a lane owns four adjacent columns, reads the unit's rows and the rows above
+// and below it, evaluates F once per loaded element, and takes its west / east neighbours
+// from the adjacent lanes with DPP wave shifts.  The column left of the strip and
 // the one right of it are read by lanes 0 and 63 with one extra 4-byte load per
-// row.  Those two lines are being read by the neighbouring waves at the same
-// time, so they come from the cache.  (Strips of 248 columns with the halo
-// inside the 128-bit loads straddled nine lines per row and fetched 17 % more
-// than the grid from HBM.)
+// row.  Rows may start on any 4-byte boundary: the 128-bit accesses of global memory need
+// no more.
+//
+// Bound by memory.  The rows above and below a unit, and the halo columns, are being read
+// by neighbouring waves at about the same time and come from the cache (ordinary loads;
+// F is evaluated 1.5 times per point, which the idle half of the issue slots takes).  Bands
+// as low as four rows keep what is in flight close together and give small grids enough
+// waves; before, a wave walked down 32 to 128 rows with three of them in registers: 8192 x 8192
+// 112 -> 98 us, 4096 x 4096 30.6 -> 22.4, 1024 x 1024 15.1 -> 6.3, 64 x 64 13.8 -> 5.1 (and grids
+// whose rows are no multiple of four went through the generic element program: 8192 x 8191
+// 269 -> 109 us, 1531 x 2477 22.4 -> 9.3).  Results are stored non-temporally: ordinary stores
+// leave dirty lines in the memory-side cache that the next kernel waits for (8192 x 8192 launched
+// back to back 104 - 120 us; inside the benchmark's step the stencil itself is faster with them,
+// 94 against 107 us, but the step is not, 607 against 602 us).
 #pragma once
 
 #include "kernels.hpp"
@@ -24,29 +33,30 @@
 namespace fc {
 
 constexpr int kStripCols = kWave * kVec;         // 256 output columns per wave
-constexpr int kBandRows = 32;                    // least rows per wave (a multiple of kRowsPerStep)
-constexpr int kMaxBandRows = 128;
-constexpr int kRowsPerStep = 4;                  // row loads in flight per lane
+constexpr int kBandRows = 4;                     // output rows of a unit
 
 struct Quad { float x, y, z, w; };
 
-// Row r (clamped to the grid) of the input at columns c .. c+3, before F.  W is a
-// multiple of four and c >= 0, so the 128-bit read is taken at min(c, W-4) and is
-// always inside the row.  Nothing here depends on the loaded value, so the row
-// reads of a step are issued back to back and are in flight together.
+// Row r (clamped to the grid) of the input at columns c .. c+3, before F; the 128-bit
+// read is taken at min(c, W-4) and so always inside the row (W >= 4, c >= 0).  Nothing
+// here depends on the loaded value, so the row reads of a step are issued back to back
+// and are in flight together.
 using RawRow = float __attribute__((ext_vector_type(4)));
+using RowInMemory = float __attribute__((ext_vector_type(4), aligned(4)));
 __device__ __forceinline__ RawRow load_row(const float *g, int r, int c, int H, int W) {
   r = min(max(r, 0), H - 1);
-  // non-temporal: the streamed grid must not displace the halo rows in L2 (measured: 18 % faster)
-  return __builtin_nontemporal_load(reinterpret_cast<const RawRow *>(g + (size_t)r * (size_t)W + min(c, W - kVec)));
+  return *reinterpret_cast<const RowInMemory *>(g + (size_t)r * (size_t)W + min(c, W - kVec));
 }
 
-// p = F(row); a lane right of the grid stands for the clamped column W-1
+// p = F(row).  `past` = how far (0 .. 3) the read was moved left to stay inside the row: columns right
+// of the grid stand for the clamped column W-1.
 template <class F>
-__device__ __forceinline__ Quad apply_row(const Slot &s, const RawRow &t, bool outside) {
-  const float w = F::apply(s, t.w);
-  if (outside) return {w, w, w, w};
-  return {F::apply(s, t.x), F::apply(s, t.y), F::apply(s, t.z), w};
+__device__ __forceinline__ Quad apply_row(const Slot &s, RawRow t, bool ragged, int past) {
+  if (ragged) {                                  // the same for the whole wave: its strip reaches past the grid
+    if (past & 1) { t.x = t.y; t.y = t.z; t.z = t.w; }
+    if (past & 2) { t.x = t.z; t.y = t.w; t.z = t.w; }
+  }
+  return {F::apply(s, t.x), F::apply(s, t.y), F::apply(s, t.z), F::apply(s, t.w)};
 }
 
 // p at the column left of the strip (lane 0) or right of it (lane 63), clamped to the grid
@@ -67,72 +77,79 @@ __device__ __forceinline__ float load_halo(const float *g, int r, int c0, int la
 // read from memory).  WithMax: also fold(max) over p into out[1].
 template <class F, int FSlot, bool WithMax>
 __global__ __launch_bounds__(kBlock) void stencil5_kernel(const KArgs a, Control *ctl, unsigned long long *partials,
-                                                          int n_groups, int n_bands, int band_rows) {
+                                                          int n_strips, int n_units) {
   const int H = a.h, W = a.w;
   const float *g = static_cast<const float *>(a.in[0]);
   float *out = static_cast<float *>(a.out[0]);
   const Slot &fs = a.p[FSlot];
+  const unsigned epoch = WithMax ? epoch_at_start(ctl) : 0u;
+  const int lane = lane_id();
 
   // workgroups are dealt round-robin to the 8 XCDs; give each XCD a contiguous
-  // range of (band, strip group) tiles so that halo rows are re-read from its own L2
-  const int n_blocks = n_groups * n_bands;
-  const int per_xcd = (n_blocks + 7) / 8;
-  const int logical = (int)(blockIdx.x % 8) * per_xcd + (int)(blockIdx.x / 8);
-  float m = -__builtin_inff();
-  if (logical < n_blocks) {
-    const int band = logical / n_groups, group = logical - band * n_groups;
-    const int strip = group * kWavesPerBlock + wave_id();
-    const int lane = lane_id();
+  // range of units (unit = band, strip), a wave a unit at a time, so that
+  // halo rows are re-read from its own L2
+  const int per_xcd = ((n_units + kWavesPerBlock - 1) / kWavesPerBlock + 7) / 8 * kWavesPerBlock;
+  const int first = (int)(blockIdx.x % 8) * per_xcd, end = min(first + per_xcd, n_units);
+  const int stride = (int)(gridDim.x / 8) * kWavesPerBlock;
+  RawRow raw[kBandRows + 2];                     // rows r0-1 .. r0+kBandRows of the unit that is worked on next
+  float hraw[kBandRows];
+  auto fetch = [&](int unit) {
+    const int band = unit / n_strips, strip = unit - band * n_strips, r0 = band * kBandRows;
     const int c0 = strip * kStripCols, c = c0 + lane * kVec;
-    const bool writes = c < W, outside = !writes;
-    const int r0 = band * band_rows, r1 = min(r0 + band_rows, H);
-    if (strip * kStripCols < W) {
-      Quad prev = apply_row<F>(fs, load_row(g, r0 - 1, c, H, W), outside);
-      Quad cur = apply_row<F>(fs, load_row(g, r0, c, H, W), outside);
-      float hcur = F::apply(fs, load_halo(g, r0, c0, lane, H, W));
-      for (int r = r0; r < r1; r += kRowsPerStep) {
-        RawRow raw[kRowsPerStep];
-        Quad nxt[kRowsPerStep];
-        float hnxt[kRowsPerStep];
 #pragma unroll
-        for (int k = 0; k < kRowsPerStep; ++k) hnxt[k] = load_halo(g, r + 1 + k, c0, lane, H, W);
+    for (int k = 0; k < kBandRows; ++k) hraw[k] = load_halo(g, r0 + k, c0, lane, H, W);
 #pragma unroll
-        for (int k = 0; k < kRowsPerStep; ++k) raw[k] = load_row(g, r + 1 + k, c, H, W);
+    for (int k = 0; k < kBandRows + 2; ++k) raw[k] = load_row(g, r0 + k - 1, c, H, W);
+  };
+  float m = -__builtin_inff();
+  const int unit0 = __builtin_amdgcn_readfirstlane(first + (int)(blockIdx.x / 8) * kWavesPerBlock + wave_id());
+  if (unit0 < end) fetch(unit0);
+  with_keep(a.keeps(0), [&](auto keep) {
+    for (int unit = unit0; unit < end; unit += stride) {
+      const int band = unit / n_strips, strip = unit - band * n_strips, r0 = band * kBandRows;
+      const int c0 = strip * kStripCols, c = c0 + lane * kVec;
+      const int mine = min(W - c, kVec);           // columns of the lane inside the grid (less than one: none)
+      const bool ragged = c0 + kStripCols > W;
+      const int past = min(max(c - (W - kVec), 0), kVec - 1);
+      Quad p[kBandRows + 2];
+      float h[kBandRows];
 #pragma unroll
-        for (int k = 0; k < kRowsPerStep; ++k) {
-          nxt[k] = apply_row<F>(fs, raw[k], outside);
-          hnxt[k] = F::apply(fs, hnxt[k]);
-        }
+      for (int k = 0; k < kBandRows + 2; ++k) p[k] = apply_row<F>(fs, raw[k], ragged, past);
 #pragma unroll
-        for (int k = 0; k < kRowsPerStep; ++k) {
-          const float left = lane_prev(hcur, cur.w);     // lane 0 keeps its halo value
-          const float right = lane_next(hcur, cur.x);    // lane 63 keeps its halo value
-          // (((p + N) + S) + W) + E, the order of add5
-          Quad o;
-          o.x = (((cur.x + prev.x) + nxt[k].x) + left) + cur.y;
-          o.y = (((cur.y + prev.y) + nxt[k].y) + cur.x) + cur.z;
-          o.z = (((cur.z + prev.z) + nxt[k].z) + cur.y) + cur.w;
-          o.w = (((cur.w + prev.w) + nxt[k].w) + cur.z) + right;
-          if (writes && r + k < r1) {
-            using V = float __attribute__((ext_vector_type(4)));
-            V t = {o.x, o.y, o.z, o.w};
-            *reinterpret_cast<V *>(out + (size_t)(r + k) * (size_t)W + c) = t;
-            if (WithMax) m = fmaxf(fmaxf(fmaxf(m, cur.x), fmaxf(cur.y, cur.z)), cur.w);
+      for (int k = 0; k < kBandRows; ++k) h[k] = F::apply(fs, hraw[k]);
+      if (unit + stride < end) fetch(unit + stride);
+#pragma unroll
+      for (int k = 0; k < kBandRows; ++k) {
+        const Quad &up = p[k], &cur = p[k + 1], &down = p[k + 2];
+        const float left = lane_prev(h[k], cur.w);     // lane 0 keeps its halo value
+        const float right = lane_next(h[k], cur.x);    // lane 63 keeps its halo value
+        // (((p + N) + S) + W) + E, the order of add5
+        RawRow o;
+        o.x = (((cur.x + up.x) + down.x) + left) + cur.y;
+        o.y = (((cur.y + up.y) + down.y) + cur.x) + cur.z;
+        o.z = (((cur.z + up.z) + down.z) + cur.y) + cur.w;
+        o.w = (((cur.w + up.w) + down.w) + cur.z) + right;
+        if (r0 + k < H) {
+          float *to = out + (size_t)(r0 + k) * (size_t)W + c;
+          if (mine == kVec) {
+            if (decltype(keep)::value) *reinterpret_cast<RowInMemory *>(to) = o; else __builtin_nontemporal_store(o, reinterpret_cast<RowInMemory *>(to));
+          } else {
+#pragma unroll
+            for (int q = 0; q < kVec - 1; ++q) if (q < mine) to[q] = o[q];
           }
-          prev = cur;
-          cur = nxt[k];
-          hcur = hnxt[k];
+          // columns past the grid repeat its last column
+          if (WithMax) m = fmaxf(fmaxf(fmaxf(m, cur.x), fmaxf(cur.y, cur.z)), cur.w);
         }
       }
     }
-  }
-  if (WithMax) fold_finish<MaxF32>(m, a, 1, ctl, partials, epoch_at_start(ctl));
+  });
+  if (WithMax) fold_finish<MaxF32>(m, a, 1, ctl, partials, epoch);
 }
 
 template <class F, int FSlot, bool WithMax, int G0, int GStride>
 bool stencil5_accept(const KArgs &a) {
   static const int want[4][2] = {{-1, 0}, {1, 0}, {0, -1}, {0, 1}};
-  if (a.h < 1 || a.w < 4 || (a.w % 4) != 0) return false;
+  if (a.h < 1 || a.w < kVec || a.w > 0x7fffffff - 4 * kStripCols) return false;     // columns past the row's end are counted in int
   for (int k = 0; k < 4; ++k) {
     const Slot &s = a.p[G0 + k * GStride];
     if (s.i[0] != want[k][0] || s.i[1] != want[k][1] || s.ext[0] != a.h || s.ext[1] != a.w) return false;
@@ -144,21 +161,13 @@ template <class F, int FSlot, bool WithMax>
 hipError_t launch_stencil5(const KArgs &a, const LaunchCtx &c) {
   if (a.n == 0 && !WithMax) return hipSuccess;
   const int strips = (a.w + kStripCols - 1) / kStripCols;
-  const int groups = (strips + kWavesPerBlock - 1) / kWavesPerBlock;
-  // Higher bands re-read fewer halo rows (two per band), lower bands give more
-  // workgroups: the bands are as high as they can be, up to kMaxBandRows, while the
-  // launch still has four workgroups per compute unit.  Measured at 8192 x 8192 inside
-  // the five-pipeline step: 96 us with 32-row bands (8 workgroups per CU), 94 us with
-  // 64 (4 per CU), 99 us with 48 (5.3 per CU, uneven), 102 us with 128 (2 per CU).
-  int band_rows = kBandRows;
-  const long long enough = 4LL * device_compute_units();
-  while (band_rows + kRowsPerStep <= kMaxBandRows &&
-         (long long)groups * ((a.h + band_rows + kRowsPerStep - 1) / (band_rows + kRowsPerStep)) >= enough)
-    band_rows += kRowsPerStep;
-  while ((long long)groups * ((a.h + band_rows - 1) / band_rows) > kMaxPartials - 8) band_rows *= 2;
-  const int bands = std::max(1, (a.h + band_rows - 1) / band_rows);
-  const int blocks = ((groups * bands + 7) / 8) * 8;
-  return launch_k(&stencil5_kernel<F, FSlot, WithMax>, (unsigned)blocks, c, a, c.ctl, c.partials, groups, bands, band_rows);
+  const int units = strips * ((a.h + kBandRows - 1) / kBandRows);
+  // A unit per wave and as many workgroups as the fold's partials allow: the hardware hands the next
+  // workgroup out as one ends, and what runs at a time is one front of adjacent units per XCD.  With 4
+  // workgroups per compute unit that walk over the units 8192 x 8192 takes the same 98 us, but
+  // 7000 x 8001 100 us instead of 91 and 4096 x 4096 24 us instead of 22.4.
+  const int blocks = std::min(std::max(8, ((units + kWavesPerBlock - 1) / kWavesPerBlock + 7) / 8 * 8), kMaxPartials - 8);
+  return launch_k(&stencil5_kernel<F, FSlot, WithMax>, (unsigned)blocks, c, a, c.ctl, c.partials, strips, units);
 }
 
 }  // namespace fc

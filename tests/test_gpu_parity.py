@@ -405,6 +405,17 @@ def test_stencil_shapes(hw):
     run_all_modes(5, C.stencil_max(h=hw[0], w=hw[1], seed=500 + hw[0] * 7 + hw[1]))
 
 
+@pytest.mark.parametrize("hw", [(4, 255), (5, 257), (8, 258), (9, 259), (3, 511), (13, 513), (1, 1030), (6, 5), (2, 6),
+                                (132003, 5)])
+def test_stencil_edges_of_strips_and_bands(hw):
+    # rows that start on any 4-byte boundary, strips that reach one to three columns past a 128-bit group,
+    # bands that end inside a unit; the tallest has more units than a launch has waves
+    w = C.stencil_max(h=hw[0], w=hw[1], seed=600 + hw[0] + hw[1])
+    g, part = plan(w.graph, True)
+    assert "rows-in-registers" in device_program(g, w.inputs, part).kernels()[0]
+    run_all_modes(5, w)
+
+
 def test_stencil_constant_grid_borders():
     w = C.stencil_max(grid=np.full((40, 500), F32(0.25)))
     res = run_all_modes(5, w)
