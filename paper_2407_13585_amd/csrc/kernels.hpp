@@ -1096,29 +1096,41 @@ __global__ __launch_bounds__(kFineBlock) void fold_fine_kernel(const KArgs a, Co
 }
 
 // ------------------------------------------------------------------ segmented fold
-// y[r] = fold(Op, E(k) for k in [off[r], off[r+1])).  One 16-lane DPP row per
-// segment: lanes stride through the segment, the row is reduced with row_shr
-// steps, lane 15 stores.  Offsets are external array kMaxIn-1.  An empty segment
-// yields the identity.
-template <class Op, class E>
+// y[r] = fold(Op, E(k) for k in [off[r], off[r+1])).  Offsets are external array
+// kMaxIn-1.  An empty segment yields the identity.
+//
+// L lanes take a row: they stride through it, U elements a lane in flight at a time, and combine
+// their sums with cross-lane moves.  Bound by the gathers of the element program (SpMV over a
+// table that fits L2: 236 G/s at most) behind a chain of three reads (offsets, index, table).
+// Ordinary loads: the lanes of neighbouring rows read a line of a stream a piece at a time
+// (non-temporal: 300001 rows of 16 elements 39 us instead of 26).  Elements past a row's end
+// are read at its last element instead of not at all, so that a lane's U reads are issued together.
+template <class Op, class E, int L, int U>
 __global__ __launch_bounds__(kBlock) void foldseg_kernel(const KArgs a) {
   using T = typename Op::T;
-  const int *off = static_cast<const int *>(a.in[kMaxIn - 1]);
+  const unsigned *off = static_cast<const unsigned *>(a.in[kMaxIn - 1]);
   T *y = static_cast<T *>(a.out[0]);
   const unsigned rows = (unsigned)a.aux;
-  const unsigned sub = threadIdx.x & 15u;
-  const unsigned rows_per_step = gridDim.x * (kBlock / 16);
-  // every lane of a wave runs the same number of steps so the DPP moves stay converged
+  const unsigned sub = threadIdx.x % L;
+  const unsigned rows_per_step = gridDim.x * (kBlock / L);
+  // every lane of a wave runs the same number of steps so the cross-lane moves stay converged
   const unsigned steps = (rows + rows_per_step - 1) / rows_per_step;
   for (unsigned s = 0; s < steps; ++s) {
-    unsigned r = s * rows_per_step + blockIdx.x * (kBlock / 16) + threadIdx.x / 16;
-    int lo = 0, hi = 0;
+    const unsigned r = s * rows_per_step + blockIdx.x * (kBlock / L) + threadIdx.x / L;
+    unsigned lo = 0, hi = 0;
     if (r < rows) { lo = off[r]; hi = off[r + 1]; }
     T acc = Op::identity();
     // unsigned: the step past a segment that ends at 2^31 - 1 must not wrap
-    for (unsigned k = (unsigned)lo + sub; k < (unsigned)hi; k += 16) acc = Op::apply(acc, E::template eval<0>(a, (int)k));
-    acc = row_scan_inclusive<Op>(acc);
-    if (sub == 15 && r < rows) y[r] = acc;
+    for (unsigned k = lo + sub; k < hi; k += L * U) {
+      T v[U];
+#pragma unroll
+      for (int u = 0; u < U; ++u) v[u] = E::template eval<0>(a, (int)min(k + u * L, hi - 1u));
+#pragma unroll
+      for (int u = 0; u < U; ++u) acc = Op::apply(acc, u == 0 || k + u * L < hi ? v[u] : Op::identity());
+    }
+#pragma unroll
+    for (int o = 1; o < L; o <<= 1) acc = Op::apply(acc, __shfl_xor(acc, o));
+    if (sub == 0 && r < rows) y[r] = acc;
   }
 }
 

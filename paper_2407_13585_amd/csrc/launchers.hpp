@@ -81,7 +81,18 @@ template <class ES, class Op, class EF> hipError_t launch_store_fold(const KArgs
 }
 template <class Op, class E> hipError_t launch_foldseg(const KArgs &a, const LaunchCtx &c) {
   if (a.aux == 0) return hipSuccess;
-  return launch_k(&foldseg_kernel<Op, E>, grid_for(a.aux, kBlock / 16, kMaxGrid * 8), c, a);
+  auto go = [&](auto kernel, int lanes) {
+    return launch_k(kernel, grid_for(a.aux, kBlock / lanes, 1u << 20), c, a);
+  };
+  constexpr int U = E::kNodes == 0 ? 1 : 4;             // an interpreted element program is a loop of its own
+  const double mean = (double)a.n / a.aux;
+  // Lanes by mean length, measured at 50000 and 300001 rows: as many as leave a lane two to four
+  // elements (3 elements a row: 9.4 us with 4 lanes, 11.6 with 8, 16.9 with 16; 16 elements: 27.1, 25.6,
+  // 26.2; 64 elements: 22.5, 19.4, 17.7; 500 elements: 26.2, 27.6, 21.7, with a wave 18.3).
+  if (mean < 12.0) return go(&foldseg_kernel<Op, E, 4, U>, 4);
+  if (mean < 32.0) return go(&foldseg_kernel<Op, E, 8, U>, 8);
+  if (mean < 256.0) return go(&foldseg_kernel<Op, E, 16, U>, 16);
+  return go(&foldseg_kernel<Op, E, kWave, U>, kWave);
 }
 // ---- column-blocked segmented fold: for tables of more than one and at most four L2s ----
 constexpr size_t kL2Bytes = 4u << 20;                 // L2 of one XCD

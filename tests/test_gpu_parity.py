@@ -221,6 +221,17 @@ def test_spmv_row_shapes(lengths):
     run_all_modes(3, w)
 
 
+@pytest.mark.parametrize("mean_len", [0.2, 11.9, 12.1, 31.0, 33.0, 255.0, 257.0])
+def test_spmv_lanes_by_row_length(mean_len):
+    # four, eight or sixteen lanes or a wave per row, by the mean length; rows around the number of elements the
+    # lanes take per step (16, 32, 64, 256), row counts off the rows of a workgroup
+    rows = 517
+    lengths = np.random.default_rng(int(mean_len * 10)).poisson(mean_len, size=rows)
+    lengths[:8] = [0, 1, 15, 16, 17, 33, 64, 65]
+    lengths[-3:] = [257, 0, 513]
+    run_all_modes(3, C.spmv(lengths=lengths, seed=900 + int(mean_len), ncols=3000))
+
+
 def test_spmv_skewed_rows():
     rng = np.random.default_rng(77)
     lengths = np.minimum(rng.zipf(1.5, size=5000), 20000).astype(np.int64)
