@@ -70,17 +70,21 @@ constexpr int kInterpDepth = 6;       // values below the top of the interpreter
 constexpr int kInterpGathers = 3;     // nesting of gathers it follows
 enum : unsigned char {
   kCodeEnd = 0,
-  kCodeIn,      // a = external array: push its element at the position
+  kCodeIn,      // a = external array: push its element at the position; b = 1 + k: it is array direct[k] of its
+                // element program, read at the element's own position (KArgs::direct)
   kCodeGen,     // a = index function, b = slot: push its value at the position
   kCodeMap,     // a = element function, b = slot, c = number of arguments: replace them by the result
   kCodeEnter,   // pop an index and make it the position
   kCodeLeave,   // back to the position before the matching kCodeEnter
+  kCodeLookup,  // a = external array, b = 1 + k: push its element at the index that array direct[k] holds
   kCodeStore,   // a = output array: pop a value into it at the element's own position
   kCodeFold,    // a = output array, b = reducer (kFold...), c = accumulator: pop a value into it
-  kCodeYield,   // the value on the stack is the result of this element program (Interp<K, T>)
-  kCodeDup      // push a copy of the top of the stack (an array with several consumers is computed once)
+  kCodeYield    // the value on the stack is the result of this element program (Interp<K, T>)
 };
+// in Code::op of a store or a fold: the value stays on the stack (an array with several consumers is computed once)
+constexpr unsigned char kCodeStays = 0x80;
 constexpr int kInterpFolds = 2;       // folds of one interpreted cluster
+constexpr int kInterpDirect = 4;      // arrays of an element program that are read ahead of its run
 enum : unsigned char { kFoldAddF32 = 0, kFoldMaxF32, kFoldMulF32, kFoldAddI32, kFoldMaxI32 };
 struct Code { unsigned char op, a, b, c; };
 
@@ -94,6 +98,11 @@ struct KArgs {    // arguments of one cluster launch
   Slot p[kMaxSlots];
   Code code[kMaxCode];      // kCodeEnd after the last instruction
   unsigned char root[kMaxRoots];   // where element program K of a cluster with another consumer starts in `code`
+  // External arrays that element program K reads at the element's own position (the first kInterpDirect of
+  // them): known before the program runs, so their reads are issued together and ahead of it.
+  unsigned char direct[kMaxRoots][kInterpDirect], n_direct[kMaxRoots];
+  unsigned char code_depth, code_gathers;   // values below the top of the stack and nested gathers that `code` needs
+  unsigned char n_folds, fold_op[kInterpFolds], fold_out[kInterpFolds];   // of a cluster that interp_kernel runs
   unsigned flags;           // kSinglePass: a fold of the cluster carries FC_NODE_SINGLE_PASS;
                             // kKeepOut << k: out[k] is read back by a later cluster of the program
   __host__ __device__ bool keeps(int k) const { return (flags >> (8 + k)) & 1u; }

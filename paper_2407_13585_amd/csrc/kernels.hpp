@@ -242,26 +242,12 @@ __device__ __forceinline__ void fold_finish(typename Op::T acc, const KArgs &a, 
   const unsigned tag = tag_of_epoch(epoch);
   if (threadIdx.x == 0) store_agent64(&partials[earlier + blockIdx.x], pack_word((unsigned)as_bits(r), tag, 1u));
   // the workgroup with the highest index is dispatched last; it waits for the
-  // partials of all others and combines them in index order, reading kTogether of them
-  // per thread in one round trip to memory (words that have not arrived are waited for)
+  // partials of all others and combines them in index order
   if (blockIdx.x == gridDim.x - 1) {
-    constexpr int kTogether = 4, kThreads = Waves * kWave;
-    const unsigned words = earlier + gridDim.x;
     T s = Op::identity();
-    for (unsigned k0 = threadIdx.x; k0 < words; k0 += kTogether * kThreads) {
-      unsigned long long w[kTogether];
-#pragma unroll
-      for (int u = 0; u < kTogether; ++u) {
-        w[u] = 0ull;
-        if (k0 + u * kThreads < words) w[u] = load_agent64(&partials[k0 + u * kThreads]);
-      }
-#pragma unroll
-      for (int u = 0; u < kTogether; ++u)
-        if (k0 + u * kThreads < words) {
-          if (!word_ready(w[u], tag)) w[u] = wait_word(&partials[k0 + u * kThreads], tag, ctl);
-          s = Op::apply(s, w[u] ? from_bits<T>((int)(unsigned)(w[u] >> 32)) : Op::identity());
-        }
-    }
+    for_tagged_words<Waves * kWave>(partials, earlier + gridDim.x, tag, ctl, [&](unsigned long long w) {
+      s = Op::apply(s, w ? from_bits<T>((int)(unsigned)(w >> 32)) : Op::identity());
+    });
     s = block_reduce<Op, Waves>(s, lds);
     if (threadIdx.x == 0) {
       *static_cast<T *>(a.out[out_slot]) = s;
@@ -330,35 +316,54 @@ __global__ __launch_bounds__(kBlock) void store_fold_kernel(const KArgs a, Contr
 // ------------------------------------------------------------------ interpreted elementwise clusters
 // Any cluster of maps, generates and gathers that ends in up to kMaxOut stored arrays
 // or in stored arrays and up to two folds, for which no kernel was compiled: the element
-// programs are run from KArgs::code, four elements per lane at a time.  The top of the
-// value stack stays in registers, what lies below in LDS (a column per lane: registers
-// cannot be indexed by a run-time number); the positions that gathers suspend are at most
-// kInterpGathers deep and stay in registers.  Every branch depends on the code only, which
+// programs are run from KArgs::code, four elements per lane at a time.  The value stack is in
+// registers (the compiler indexes them through the hardware's register index mode: the
+// index is the same for all lanes), as are the positions that gathers suspend, at most
+// kInterpGathers deep.  Every branch depends on the code only, which
 // is the same for all lanes.  Results are the same as a compiled instance's: the same
 // element functions, applied in the same order.  A fallback: several times the
-// instructions of a compiled instance per element, 4-byte accesses.
+// instructions of a compiled instance per element.
+// Bound by latency (a chain of one read after the other) unless the gathers are many; so the
+// arrays read at the element's own position are read together, ahead of the run
+// (KArgs::direct), and the next group's while this group's program runs.  Value stack in LDS and
+// reads where the code asks for them, as before: exp(-d) * t[i] stored and summed, 2^24 elements 95 us
+// (now 59; t of 4 KiB), 2^22 31.3 us (29.5; t of 256 KiB, whose gathers bound it), 4096 elements 9 us (7).
 // x[k][e]: argument k of element e; the function is picked once for the V elements
 template <int V>
-__device__ __forceinline__ void interp_map(int fn, const Slot &s, const unsigned (&x)[5][V], unsigned (&r)[V]) {
-  auto f = [&](int k, int e) { return from_bits<float>((int)x[k][e]); };
+__device__ __forceinline__ void interp_map1(int fn, const Slot &s, unsigned (&x)[V]) {
+  auto f = [&](int e) { return from_bits<float>((int)x[e]); };
   auto bits = [](float v) { return (unsigned)as_bits(v); };
-#define FC_EACH(expr) _Pragma("unroll") for (int e = 0; e < V; ++e) r[e] = (expr); break
+#define FC_EACH(expr) _Pragma("unroll") for (int e = 0; e < V; ++e) x[e] = (expr); break
   switch (fn) {
-    case FC_FN_IDENT: FC_EACH(x[0][e]);
-    case FC_FN_AFFINE: FC_EACH(bits(FnAffine::apply(s, f(0, e))));
-    case FC_FN_SIN_X_MUL_X: FC_EACH(bits(FnSinXMulX::apply(s, f(0, e))));
-    case FC_FN_SQ_PLUS_ONE: FC_EACH(bits(FnSqPlusOne::apply(s, f(0, e))));
-    case FC_FN_MUL2: FC_EACH(bits(FnMul2::apply(s, f(0, e), f(1, e))));
-    case FC_FN_ADD2: FC_EACH(bits(FnAdd2::apply(s, f(0, e), f(1, e))));
-    case FC_FN_ADD3: FC_EACH(bits(FnAdd3::apply(s, f(0, e), f(1, e), f(2, e))));
-    case FC_FN_ADD5: FC_EACH(bits(FnAdd5::apply(s, f(0, e), f(1, e), f(2, e), f(3, e), f(4, e))));
-    case FC_FN_EXP_NEG: FC_EACH(bits(FnExpNeg::apply(s, f(0, e))));
-    case FC_FN_MOD_EQ: FC_EACH((unsigned)FnModEq::apply(s, (int)x[0][e]));
+    case FC_FN_IDENT: break;
+    case FC_FN_AFFINE: FC_EACH(bits(FnAffine::apply(s, f(e))));
+    case FC_FN_SIN_X_MUL_X:                // one after the other: the reduction of large arguments takes many registers
+#pragma unroll 1
+      for (int i = 0; i < V; ++i) {        // the elements go round (an index known at run time would put them into memory)
+        const unsigned y = bits(FnSinXMulX::apply(s, f(0)));
+#pragma unroll
+        for (int e = 0; e + 1 < V; ++e) x[e] = x[e + 1];
+        x[V - 1] = y;
+      }
+      break;
+    case FC_FN_SQ_PLUS_ONE: FC_EACH(bits(FnSqPlusOne::apply(s, f(e))));
+    case FC_FN_EXP_NEG: FC_EACH(bits(FnExpNeg::apply(s, f(e))));
+    case FC_FN_MOD_EQ: FC_EACH((unsigned)FnModEq::apply(s, (int)x[e]));
     default: FC_EACH(0u);
+  }
+#undef FC_EACH
+}
+template <int V>
+__device__ __forceinline__ void interp_map2(int fn, const Slot &s, const unsigned (&x)[V], unsigned (&r)[V]) {
+#pragma unroll
+  for (int e = 0; e < V; ++e) {
+    const float a = from_bits<float>((int)x[e]), b = from_bits<float>((int)r[e]);
+    r[e] = (unsigned)as_bits(fn == FC_FN_MUL2 ? FnMul2::apply(s, a, b) : FnAdd2::apply(s, a, b));
   }
 }
 template <int V>
 __device__ __forceinline__ void interp_gen(int fn, const Slot &s, const KArgs &a, const int (&at)[V], unsigned (&r)[V]) {
+#define FC_EACH(expr) _Pragma("unroll") for (int e = 0; e < V; ++e) r[e] = (expr); break
   switch (fn) {
     case FC_FN_IOTA: FC_EACH((unsigned)GenIota::apply(s, a, at[e]));
     case FC_FN_IOTA_REV: FC_EACH((unsigned)GenIotaRev::apply(s, a, at[e]));
@@ -388,25 +393,69 @@ __device__ __forceinline__ unsigned interp_identity(int op) {
   }
 }
 
-// Runs the cluster's code for the V consecutive elements that start at `first` (V = 4: a
-// 128-bit group, `first` a multiple of four; V = 1: one element), so that the cost of
-// reading and decoding an instruction is shared by four elements.  `below` is this
-// lane's column of the value stack.
-// Starts at instruction `pc`; a kCodeYield ends the run with the program's values in `result`.
-template <int V, int Threads>
-__device__ __forceinline__ void interp_run(const KArgs &a, int pc, unsigned first, unsigned (*below)[kVec][Threads],
-                                           unsigned (&acc)[kInterpFolds], unsigned (&result)[V]) {
-  using Raw = unsigned __attribute__((ext_vector_type(4)));
-  int at[V];                                           // the positions element programs read at
-  int suspended[kInterpGathers][V];
-  unsigned top[V];
+// A lane runs a program for G 128-bit groups of elements at a time, which lie `apart` elements from each other,
+// or (G = 0) for one element, so that the cost of reading and decoding an instruction is shared.
+// What element program `root` reads at the elements' own positions, read ahead.
+template <int G> struct InterpAhead {
+  static constexpr int V = G ? G * kVec : 1;
+  unsigned v[kInterpDirect][V];
+  template <bool Stream> __device__ __forceinline__ void read(const KArgs &a, int root, unsigned first, unsigned apart) {
+    using Raw = unsigned __attribute__((ext_vector_type(4)));
 #pragma unroll
-  for (int e = 0; e < V; ++e) { at[e] = (int)first + e; top[e] = 0u; }
+    for (int k = 0; k < kInterpDirect; ++k)
+      if (k < a.n_direct[root]) {
+        const unsigned *p = static_cast<const unsigned *>(a.in[a.direct[root][k]]) + first;
+        if (G == 0) v[k][0] = p[0];
+#pragma unroll
+        for (int g = 0; g < G; ++g) {
+          const Raw *q = reinterpret_cast<const Raw *>(p + g * apart);
+          const Raw x = Stream ? __builtin_nontemporal_load(q) : *q;
+#pragma unroll
+          for (int c = 0; c < kVec; ++c) v[k][g * kVec + c] = x[c];
+        }
+      }
+  }
+  __device__ __forceinline__ unsigned get(int k, int e) const {   // k is the same in all lanes
+    static_assert(kInterpDirect == 4, "one value per array");
+    const unsigned a = v[0][e], b = v[1][e], c = v[2][e], d = v[3][e];                  // values: a choice of addresses would put v into memory
+    return k == 0 ? a : k == 1 ? b : k == 2 ? c : d;
+  }
+};
+
+// the stack columns of a workgroup in LDS
+template <int Threads>
+__device__ __forceinline__ unsigned (*interp_stack())[kVec][Threads] {
+  __shared__ unsigned below[kInterpDepth][kVec][Threads];
+  return below;
+}
+
+// Starts at instruction `pc`; a kCodeYield ends the run with the program's values in `result`.
+// Depth, Nest: values below the top of the stack and nested gathers that the code needs at most.  LdsThreads: threads
+// of the workgroup if the values below the top are to lie in LDS (a column per lane), or 0.
+template <int G, int Depth, int Nest, int LdsThreads>
+__device__ __forceinline__ void interp_run(const KArgs &a, int pc, unsigned first, unsigned apart, const InterpAhead<G> &ahead,
+                                           unsigned (&acc)[kInterpFolds], unsigned (&result)[InterpAhead<G>::V]) {
+  using Raw = unsigned __attribute__((ext_vector_type(4)));
+  constexpr int V = InterpAhead<G>::V;
+  auto own = [&](int e) { return (int)(first + (e / kVec) * apart + e % kVec); };      // the elements' own positions
+  int at[V];                                           // the positions element programs read at
+  int suspended[Nest > 1 ? Nest - 1 : 1][V];           // of the gathers around the innermost but one; outermost: own positions
+  unsigned top[V], below[LdsThreads ? 1 : Depth][V];   // an array of its own: as part of a struct it would be put into memory
+  unsigned (*column)[kVec][LdsThreads ? LdsThreads : 1] = nullptr;
+  if constexpr (LdsThreads != 0) column = interp_stack<LdsThreads>();
+#pragma unroll
+  for (int k = 0; k < (LdsThreads ? 1 : Depth); ++k)
+#pragma unroll
+    for (int e = 0; e < V; ++e) below[k][e] = 0u;
+  auto set_below = [&](int k, int e, unsigned x) { if (LdsThreads) column[k][e % kVec][threadIdx.x] = x; else below[k][e] = x; };
+  auto get_below = [&](int k, int e) { return LdsThreads ? column[k][e % kVec][threadIdx.x] : below[k][e]; };
+#pragma unroll
+  for (int e = 0; e < V; ++e) { at[e] = own(e); top[e] = 0u; }
   int gathers = 0, count = 0;                          // the same in every lane
   auto push_room = [&]() {
     if (count > 0) {
 #pragma unroll
-      for (int e = 0; e < V; ++e) below[count - 1][e][threadIdx.x] = top[e];
+      for (int e = 0; e < V; ++e) set_below(count - 1, e, top[e]);
     }
     ++count;
   };
@@ -414,28 +463,35 @@ __device__ __forceinline__ void interp_run(const KArgs &a, int pc, unsigned firs
     --count;
     if (count > 0) {
 #pragma unroll
-      for (int e = 0; e < V; ++e) top[e] = below[count - 1][e][threadIdx.x];
+      for (int e = 0; e < V; ++e) top[e] = get_below(count - 1, e);
     }
   };
-  for (; pc < kMaxCode; ++pc) {
-    const Code c = a.code[pc];
+  for (Code c = a.code[pc], next; pc < kMaxCode - 1; ++pc, c = next) {
+    next = a.code[pc + 1];                             // the last entry is kCodeEnd
     if (c.op == kCodeEnd) break;
     if (c.op == kCodeYield) {
 #pragma unroll
       for (int e = 0; e < V; ++e) result[e] = top[e];
       break;
     }
-    switch (c.op) {
+    switch (c.op & ~kCodeStays) {
       case kCodeIn: {
         push_room();
-        const unsigned *p = static_cast<const unsigned *>(a.in[c.a]);
-        if (V == 4 && gathers == 0) {                  // the elements' own positions: one 128-bit read
-          const Raw v = *reinterpret_cast<const Raw *>(p + first);
-          top[0] = v.x; if (V > 1) { top[1 % V] = v.y; top[2 % V] = v.z; top[3 % V] = v.w; }
+        if (c.b != 0) {
+#pragma unroll
+          for (int e = 0; e < V; ++e) top[e] = ahead.get(c.b - 1, e);
         } else {
+          const unsigned *p = static_cast<const unsigned *>(a.in[c.a]);
 #pragma unroll
           for (int e = 0; e < V; ++e) top[e] = p[at[e]];
         }
+        break;
+      }
+      case kCodeLookup: {
+        push_room();
+        const unsigned *p = static_cast<const unsigned *>(a.in[c.a]);
+#pragma unroll
+        for (int e = 0; e < V; ++e) top[e] = p[(int)ahead.get(c.b - 1, e)];
         break;
       }
       case kCodeGen:
@@ -443,22 +499,38 @@ __device__ __forceinline__ void interp_run(const KArgs &a, int pc, unsigned firs
         interp_gen<V>(c.a, a.p[c.b], a, at, top);
         break;
       case kCodeMap: {
-        const int nargs = c.c;
         // the last argument is the top of the stack, the others lie below it in order
-        unsigned x[5][V];
+        const int nargs = c.c;
+        if (nargs == 1) {
+          interp_map1<V>(c.a, a.p[c.b], top);
+        } else if (nargs == 2) {
+          unsigned x[V];
 #pragma unroll
-        for (int k = 0; k < 5; ++k)
+          for (int e = 0; e < V; ++e) x[e] = get_below(count - 2, e);
+          interp_map2<V>(c.a, a.p[c.b], x, top);
+        } else {
+          // add3 and add5: sums from the left
+          unsigned x[V];
 #pragma unroll
-          for (int e = 0; e < V; ++e)
-            x[k][e] = k >= nargs ? 0u : k == nargs - 1 ? top[e] : below[count - nargs + k][e][threadIdx.x];
+          for (int e = 0; e < V; ++e) x[e] = get_below(count - nargs, e);
+          for (int k = count - nargs + 1; k < count; ++k) {
+#pragma unroll
+            for (int e = 0; e < V; ++e) {
+              const unsigned y = k == count - 1 ? top[e] : get_below(min(k, Depth - 1), e);
+              x[e] = (unsigned)as_bits(FnAdd2::apply(a.p[c.b], from_bits<float>((int)x[e]), from_bits<float>((int)y)));
+            }
+          }
+#pragma unroll
+          for (int e = 0; e < V; ++e) top[e] = x[e];
+        }
         count -= nargs - 1;
-        interp_map<V>(c.a, a.p[c.b], x, top);
         break;
       }
       case kCodeEnter: {
 #pragma unroll
         for (int e = 0; e < V; ++e) {
-          if (gathers == 0) suspended[0][e] = at[e]; else if (gathers == 1) suspended[1][e] = at[e]; else suspended[2][e] = at[e];
+          if (Nest > 1 && gathers == 1) suspended[0][e] = at[e];
+          if (Nest > 2 && gathers == 2) suspended[Nest > 2 ? 1 : 0][e] = at[e];
           at[e] = (int)top[e];
         }
         ++gathers;
@@ -468,25 +540,32 @@ __device__ __forceinline__ void interp_run(const KArgs &a, int pc, unsigned firs
       case kCodeLeave:
         --gathers;
 #pragma unroll
-        for (int e = 0; e < V; ++e) at[e] = gathers == 0 ? suspended[0][e] : gathers == 1 ? suspended[1][e] : suspended[2][e];
+        for (int e = 0; e < V; ++e)
+          at[e] = Nest > 2 && gathers == 2 ? suspended[Nest > 2 ? 1 : 0][e] : Nest > 1 && gathers == 1 ? suspended[0][e] : own(e);
         break;
       case kCodeStore: {
         unsigned *p = static_cast<unsigned *>(a.out[c.a]) + first;
-        if (V == 4) {
-          *reinterpret_cast<Raw *>(p) = Raw{top[0], top[1 % V], top[2 % V], top[3 % V]};
-        } else {
-          p[0] = top[0];
+        if (G == 0) p[0] = top[0];
+#pragma unroll
+        for (int g = 0; g < G; ++g) {
+          const Raw x = {top[(g * kVec) % V], top[(g * kVec + 1) % V], top[(g * kVec + 2) % V], top[(g * kVec + 3) % V]};
+          Raw *q = reinterpret_cast<Raw *>(p + g * apart);
+          if (a.keeps(c.a)) {
+            asm volatile("" ::: "memory");             // keeps the two stores apart: merged, both would be ordinary
+            *q = x;
+          } else {
+            __builtin_nontemporal_store(x, q);
+          }
         }
-        pop();
+        if (!(c.op & kCodeStays)) pop();
         break;
       }
-      case kCodeDup: push_room(); break;               // the top goes below and stays the top
       default: {                                        // kCodeFold
         unsigned v = c.c == 0 ? acc[0] : acc[1];
 #pragma unroll
         for (int e = 0; e < V; ++e) v = interp_fold(c.b, v, top[e]);
         if (c.c == 0) acc[0] = v; else acc[1] = v;
-        pop();
+        if (!(c.op & kCodeStays)) pop();
         break;
       }
     }
@@ -504,28 +583,42 @@ __device__ __forceinline__ unsigned interp_block_reduce(int op, unsigned v, unsi
   }
 }
 
-template <class Tag = void>            // a template only so that every translation unit may see the definition
-__global__ __launch_bounds__(kBlock) void interp_kernel(const KArgs a, Control *ctl, unsigned long long *partials) {
-  __shared__ unsigned below[kInterpDepth][kVec][kBlock];
+// G groups a lane at a time where there are that many elements, single groups and elements for the rest.
+template <int G, int Depth, int Nest>
+__global__ __launch_bounds__(kBlock, 4) void interp_kernel(const KArgs a, Control *ctl, unsigned long long *partials) {
   __shared__ unsigned lds[kWavesPerBlock + 1];
   const unsigned n = (unsigned)a.n, n4 = n & ~3u;
+  const unsigned epoch = epoch_at_start(ctl);
   // the folds of the cluster (at most kInterpFolds), each with an accumulator of its own
-  int n_folds = 0, fold_op[kInterpFolds] = {0, 0}, fold_out[kInterpFolds] = {0, 0};
-  for (int pc = 0; pc < kMaxCode && a.code[pc].op != kCodeEnd; ++pc)
-    if (a.code[pc].op == kCodeFold) {
-      const int k = a.code[pc].c == 0 ? 0 : 1;
-      if (k == 0) { fold_op[0] = a.code[pc].b; fold_out[0] = a.code[pc].a; } else { fold_op[1] = a.code[pc].b; fold_out[1] = a.code[pc].a; }
-      n_folds = n_folds > k + 1 ? n_folds : k + 1;
-    }
+  const int n_folds = a.n_folds, fold_op[kInterpFolds] = {a.fold_op[0], a.fold_op[1]};
   unsigned acc[kInterpFolds] = {interp_identity(fold_op[0]), interp_identity(fold_op[1])};
-  unsigned none4[kVec], none1[1];
-  for (unsigned i = (blockIdx.x * kBlock + threadIdx.x) * kVec; i < n4; i += gridDim.x * kBlock * kVec)
-    interp_run<kVec, kBlock>(a, 0, i, below, acc, none4);
-  if (blockIdx.x == 0 && threadIdx.x < n - n4) interp_run<1, kBlock>(a, 0, n4 + threadIdx.x, below, acc, none1);
+  constexpr unsigned kGroup = kBlock * kVec, kTileOf = kGroup * G;
+  unsigned none[InterpAhead<G>::V], none4[kVec], none1[1];
+  const unsigned whole = n4 / kTileOf * kTileOf;
+  for (unsigned base = blockIdx.x * kTileOf; base < (G > 1 ? whole : n4); base += gridDim.x * kTileOf) {
+    const unsigned i = base + threadIdx.x * kVec;
+    if (G == 1 && i >= n4) break;
+    InterpAhead<G> ahead;
+    ahead.template read<true>(a, 0, i, kGroup);
+    interp_run<G, Depth, Nest, 0>(a, 0, i, kGroup, ahead, acc, none);
+  }
+  // what is left is less than a tile: the first G workgroups take a group a lane of it
+  if (G > 1) {
+    const unsigned i = whole + blockIdx.x * kGroup + threadIdx.x * kVec;
+    if (i < n4) {
+      InterpAhead<1> ahead;
+      ahead.template read<true>(a, 0, i, kGroup);
+      interp_run<1, Depth, Nest, 0>(a, 0, i, kGroup, ahead, acc, none4);
+    }
+  }
+  if (blockIdx.x == 0 && threadIdx.x < n - n4) {
+    InterpAhead<0> ahead;
+    ahead.template read<false>(a, 0, n4 + threadIdx.x, 0u);
+    interp_run<0, Depth, Nest, 0>(a, 0, n4 + threadIdx.x, 0u, ahead, acc, none1);
+  }
   if (n_folds == 0) return;                              // the same for the whole grid
   // as fold_finish, for up to two accumulators under one tag: fold k keeps its partials at
   // [k * gridDim.x, (k + 1) * gridDim.x); the last workgroup combines them and takes the next tag
-  const unsigned epoch = load_agent(&ctl->epoch);
   const unsigned tag = tag_of_epoch(epoch);
   for (int k = 0; k < n_folds; ++k) {
     const unsigned r = interp_block_reduce(k == 0 ? fold_op[0] : fold_op[1], k == 0 ? acc[0] : acc[1], lds);
@@ -535,12 +628,11 @@ __global__ __launch_bounds__(kBlock) void interp_kernel(const KArgs a, Control *
   for (int k = 0; k < n_folds; ++k) {
     const int op = k == 0 ? fold_op[0] : fold_op[1];
     unsigned s = interp_identity(op);
-    for (unsigned j = threadIdx.x; j < gridDim.x; j += kBlock) {
-      const unsigned long long w = wait_word(&partials[(size_t)k * gridDim.x + j], tag, ctl);
+    for_tagged_words<kBlock>(partials + (size_t)k * gridDim.x, gridDim.x, tag, ctl, [&](unsigned long long w) {
       s = interp_fold(op, s, w ? (unsigned)(w >> 32) : interp_identity(op));
-    }
+    });
     s = interp_block_reduce(op, s, lds);
-    if (threadIdx.x == 0) static_cast<unsigned *>(a.out[k == 0 ? fold_out[0] : fold_out[1]])[0] = s;
+    if (threadIdx.x == 0) static_cast<unsigned *>(a.out[k == 0 ? a.fold_out[0] : a.fold_out[1]])[0] = s;
   }
   if (threadIdx.x == 0) store_agent(&ctl->epoch, epoch + 1u);
 }
@@ -548,27 +640,27 @@ __global__ __launch_bounds__(kBlock) void interp_kernel(const KArgs a, Control *
 // Element program K of a cluster as an expression node: evaluated by running its code
 // (KArgs::code from KArgs::root[K] to the kCodeYield).  With it every skeleton of this
 // file has an instance that takes any element program: what the matcher cannot pair with a
-// compiled element program runs through these.  Threads = threads of the workgroup (the
-// lanes' stack columns live in LDS).
-template <int Threads>
-__device__ __forceinline__ unsigned (*interp_stack())[kVec][Threads] {
-  __shared__ unsigned below[kInterpDepth][kVec][Threads];
-  return below;
-}
-template <int K, class T, int Threads = kBlock>
+// compiled element program runs through these.
+// LdsThreads: threads of the workgroup if the value stack is to lie in LDS (the scan kernels: the tile a lane
+// holds fills its registers), or 0.
+template <int K, class T, int LdsThreads = 0>
 struct Interp {
   using R = T;
   static constexpr int kNodes = 0;                     // the code names its parameter slots itself
   static constexpr bool kMirror = false;
   template <int Base, bool Stream = false> static __device__ __forceinline__ T eval(const KArgs &a, int i) {
     unsigned r[1] = {0u}, none[kInterpFolds] = {0u, 0u};
-    interp_run<1, Threads>(a, a.root[K], (unsigned)i, interp_stack<Threads>(), none, r);
+    InterpAhead<0> ahead;
+    ahead.template read<false>(a, K, (unsigned)i, 0u);
+    interp_run<0, kInterpDepth, kInterpGathers, LdsThreads>(a, a.root[K], (unsigned)i, 0u, ahead, none, r);
     return from_bits<T>((int)r[0]);
   }
   // i is a multiple of four (the callers read 128-bit groups)
   template <int Base> static __device__ __forceinline__ Vec4<T> eval4(const KArgs &a, int i) {
     unsigned r[kVec] = {0u, 0u, 0u, 0u}, none[kInterpFolds] = {0u, 0u};
-    interp_run<kVec, Threads>(a, a.root[K], (unsigned)i, interp_stack<Threads>(), none, r);
+    InterpAhead<1> ahead;
+    ahead.template read<false>(a, K, (unsigned)i, 0u);
+    interp_run<1, kInterpDepth, kInterpGathers, LdsThreads>(a, a.root[K], (unsigned)i, 0u, ahead, none, r);
     return Vec4<T>{{from_bits<T>((int)r[0]), from_bits<T>((int)r[1]), from_bits<T>((int)r[2]), from_bits<T>((int)r[3])}};
   }
   static void sig(std::string &s) { s += std::string("*") + DtypeName<T>::s(); }
@@ -2081,8 +2173,11 @@ struct ScanPayload {
   }
 };
 
+// waves per SIMD asked of the compiler: an interpreted element program (it has no nodes of its own) needs the registers
+template <class EX> struct ScanWaves { static constexpr int value = EX::kNodes == 0 ? 4 : 8; };
+
 template <class EX, class EV, int Mode, bool Reverse>
-__global__ __launch_bounds__(kScanBlock, 8) void scan_kernel(const KArgs a, Control *ctl, unsigned long long *status,
+__global__ __launch_bounds__(kScanBlock, ScanWaves<EX>::value) void scan_kernel(const KArgs a, Control *ctl, unsigned long long *status,
                                                              unsigned n_tiles) {
   __shared__ int lds_wave[kScanWaves];
   __shared__ int lds_sum[kScanWaves];
@@ -2290,7 +2385,7 @@ __device__ __forceinline__ float scan_block_sum_f32(float v, float *lds) {
 }
 
 template <class EX, bool Reverse, bool StoreX = false>
-__global__ __launch_bounds__(kScanBlock) void scan_f32_kernel(const KArgs a, Control *ctl, unsigned long long *status,
+__global__ __launch_bounds__(kScanBlock, ScanWaves<EX>::value) void scan_f32_kernel(const KArgs a, Control *ctl, unsigned long long *status,
                                                               unsigned n_tiles) {
   static_assert(std::is_same<typename EX::R, float>::value, "fp32 stream");
   __shared__ float lds_wave[kScanWaves];

@@ -193,4 +193,22 @@ __device__ __forceinline__ unsigned long long wait_word(const unsigned long long
   return 0ull;
 }
 
+// use(word) for this thread's share of `count` tagged words, in a fixed order (0: a wait gave up); four words
+// a thread are read in one round trip to memory, those that have not arrived are waited for.
+template <int Threads, class F>
+__device__ __forceinline__ void for_tagged_words(const unsigned long long *p, unsigned count, unsigned tag, Control *ctl, F &&use) {
+  constexpr int kTogether = 4;
+  for (unsigned k0 = threadIdx.x; k0 < count; k0 += kTogether * Threads) {
+    unsigned long long w[kTogether];
+#pragma unroll
+    for (int u = 0; u < kTogether; ++u) {
+      w[u] = 0ull;
+      if (k0 + u * Threads < count) w[u] = load_agent64(p + k0 + u * Threads);
+    }
+#pragma unroll
+    for (int u = 0; u < kTogether; ++u)
+      if (k0 + u * Threads < count) use(word_ready(w[u], tag) ? w[u] : wait_word(p + k0 + u * Threads, tag, ctl));
+  }
+}
+
 }  // namespace fc

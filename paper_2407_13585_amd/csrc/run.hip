@@ -31,14 +31,16 @@ struct Builder {
     if (n_code >= kMaxCode - 1) { code_ok = false; return; }   // the last entry stays kCodeEnd
     args.code[n_code++] = Code{op, (unsigned char)a, (unsigned char)b, (unsigned char)c};
     switch (op) {
-      case kCodeIn: case kCodeGen: ++on_stack; break;
+      case kCodeIn: case kCodeGen: case kCodeLookup: ++on_stack; break;
       case kCodeMap: on_stack -= c - 1; break;
       case kCodeEnter: --on_stack; if (++gathers > kInterpGathers) code_ok = false; break;
       case kCodeLeave: --gathers; break;
-      case kCodeDup: ++on_stack; break;
-      default: --on_stack; break;                              // store, fold, yield
+      default: if (!(op & kCodeStays)) --on_stack; break;      // store, fold, yield
     }
     if (on_stack > kInterpDepth + 1 || on_stack < 0) code_ok = false;
+    if (!code_ok) return;
+    args.code_depth = (unsigned char)std::max<int>(args.code_depth, on_stack - 1);
+    args.code_gathers = (unsigned char)std::max<int>(args.code_gathers, gathers);
   }
 
   Builder(const Model &m_, const Clustering &c_, const std::vector<int> &mem)
@@ -66,6 +68,18 @@ struct Builder {
     return true;
   }
 
+  // 1 + the place of external array k among the arrays that the element program under way reads at
+  // the element's own position, or 0: below a gather, or no place left
+  int direct_slot(int k) {
+    const int r = n_roots > 0 ? n_roots - 1 : 0;        // an elementwise cluster has one program and no root()
+    if (gathers != 0 || r >= kMaxRoots) return 0;
+    int s = 0;
+    while (s < args.n_direct[r] && args.direct[r][s] != k) ++s;
+    if (s == kInterpDirect) return 0;
+    if (s == args.n_direct[r]) args.direct[r][args.n_direct[r]++] = (unsigned char)k;
+    return 1 + s;
+  }
+
   // Element program number n_roots of a cluster whose consumer is not elementwise: its
   // signature goes to `sig` as always; `any` receives the signature of the instance that
   // takes any element program of this type (it runs the code between root[k] and the yield).
@@ -88,7 +102,7 @@ struct Builder {
       int k = external(a);
       if (k >= kMaxIn - 1) return fail("too many external arrays");
       sig += "in" + std::to_string(k) + (nd.dtype == FC_F32 ? ":f32" : ":i32");
-      emit(kCodeIn, k);
+      emit(kCodeIn, k, direct_slot(k));
       return true;
     }
     switch (nd.kind) {
@@ -109,9 +123,26 @@ struct Builder {
         sig += "gather(";
         if (!expr(nd.arg[0], sig)) return false;
         sig += ",";
-        emit(kCodeEnter);
-        if (!expr(nd.arg[1], sig)) return false;
-        emit(kCodeLeave);
+        {
+          // an array read at the element's own position that is the index into another array: one instruction
+          const int at = n_code - 1;
+          const bool lookup = code_ok && at >= 0 && args.code[at].op == kCodeIn && args.code[at].b != 0 &&
+                              !in_cluster.count(nd.arg[0]) && !in_cluster.count(nd.arg[1]);
+          if (lookup) {
+            --on_stack;
+            ++gathers;                 // the source is not read at the element's own position: no place among the direct arrays
+            if (!expr(nd.arg[1], sig)) return false;
+            --gathers;
+            if (code_ok) {
+              args.code[at] = Code{kCodeLookup, args.code[n_code - 1].a, args.code[at].b, 0};
+              args.code[--n_code] = Code{kCodeEnd, 0, 0, 0};
+            }
+          } else {
+            emit(kCodeEnter);
+            if (!expr(nd.arg[1], sig)) return false;
+            emit(kCodeLeave);
+          }
+        }
         sig += ")";
         return true;
       default:
@@ -300,10 +331,8 @@ int plan_cluster(const Model &m, const Clustering &c, const std::vector<int> &me
         if (m.nodes[folds[f]].arg[0] == array)
           ops.push_back(Code{kCodeFold, (unsigned char)(stores.size() + f),
                              (unsigned char)reducer_code(m.nodes[folds[f]].fn, m.nodes[folds[f]].dtype), (unsigned char)f});
-      for (size_t k = 0; k < ops.size(); ++k) {
-        if (k + 1 < ops.size()) b.emit(kCodeDup);
-        b.emit(ops[k].op, ops[k].a, ops[k].b, ops[k].c);
-      }
+      for (size_t k = 0; k < ops.size(); ++k)
+        b.emit((unsigned char)(ops[k].op | (k + 1 < ops.size() ? kCodeStays : 0)), ops[k].a, ops[k].b, ops[k].c);
     };
     std::set<int> computed;
     for (size_t k = 0; k < stores.size(); ++k) {
@@ -335,6 +364,11 @@ int plan_cluster(const Model &m, const Clustering &c, const std::vector<int> &me
       if (!set_n(m.size(fd.arg[0]))) return unsupported("iteration sizes differ inside a cluster");
       if (stores.empty() && f == 0) shape_from(fd.arg[0]);
       out.out_nodes[stores.size() + f] = folds[f];
+    }
+    b.args.n_folds = (unsigned char)folds.size();
+    for (size_t f = 0; f < folds.size(); ++f) {
+      b.args.fold_op[f] = (unsigned char)reducer_code(m.nodes[folds[f]].fn, m.nodes[folds[f]].dtype);
+      b.args.fold_out[f] = (unsigned char)(stores.size() + f);
     }
     interpretable = b.code_ok && b.on_stack == 0 && reducer_ok;
   }

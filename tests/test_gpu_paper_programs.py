@@ -450,6 +450,37 @@ def fused_and_unfused(g, ins):
     return fused, unfused, name
 
 
+@pytest.mark.parametrize("n", [1, 3, 1020, 1024, 1025, (1 << 20) - 4, 1 << 20, (1 << 20) + 3, (1 << 20) + 1028, (1 << 20) + 2047])
+def test_interpreted_cluster_sizes(n):
+    # one group of four elements a lane below 2^20 elements, two above, the rest of the last tile shared out among the
+    # first workgroups; a lookup in a table shorter than a group, five
+    # arrays read directly (four are read ahead), a value stored and folded twice
+    rng = np.random.default_rng(n)
+    g = Graph()
+    g.add("i", "input", "i32", (n,))
+    g.add("t", "input", "f32", (7,))
+    for k in "abcd":
+        g.add(k, "input", "f32", (n,))
+    g.add("v", "gather", "f32", (n,), args=("i", "t"))
+    g.add("e", "map", "f32", (n,), fn="exp_neg", args=("a",))
+    g.add("w", "map", "f32", (n,), fn="mul2", args=("e", "v"), output=True)
+    g.add("u", "map", "f32", (n,), fn="add3", args=("b", "c", "d"), output=True)
+    g.add("s", "fold", "f32", (1,), fn="add", args=("w",), output=True)
+    g.add("m", "fold", "f32", (1,), fn="max", args=("w",), output=True)
+    ins = {k: rng.uniform(0.0, 1.0, n).astype(F32) for k in "abcd"}
+    ins.update(i=rng.integers(0, 7, n).astype(np.int32), t=rng.uniform(0.5, 1.0, 7).astype(F32))
+    part = fc().fc_partition_check(g, [0 if nd.kind == "input" else 1 for nd in g.nodes])
+    assert "interpreted" in fc().fc_cluster_kernel(g, part, 0)
+    env = evaluate(g, ins)
+    fused, unfused = device_program(g, ins, part), device_program(g, ins, None)
+    for prog in (fused, unfused):
+        prog.run()
+    for out in ("w", "u", "m"):
+        P.assert_bit_exact(fused.fetch(out), unfused.fetch(out), f"n={n} {out}")
+    P.assert_fold(fused.fetch("s"), env["s"], f"n={n} fold")
+    assert fused.control_words()[1] == 0
+
+
 def test_every_consumer_takes_any_element_program():
     # segmented folds, scatters, scans (alone and as a compaction), row folds and row scans over
     # random element programs that no instance was compiled for: the instances over Interp<K, T> run
