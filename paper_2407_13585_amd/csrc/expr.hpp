@@ -8,11 +8,12 @@
 //
 // Every expression type offers
 //   eval(args, i)     value at iteration index i
-//   eval4(args, i)    values at i .. i+3 (i a multiple of 4), 128-bit loads on leaves
+//   eval4(args, i)    values at i .. i+3, 128-bit loads on leaves (i may be any position: 128-bit
+//                     accesses of global memory need 4-byte alignment only, see Quad128)
 //   sig(std::string&) the textual signature the host matcher compares against
 //   kNodes            number of combinator nodes in the tree (parameter slots)
 //   kMirror           the tree reads an array through `reverse` as well (tile order, kernels.hpp)
-//   eval4_pair(args, i, ip, at_i, at_ip)   values at the 128-bit groups i and ip, where ip is
+//   eval4_pair(args, i, ip, at_i, at_ip)   values at the groups of four i and ip, where ip is
 //                     the mirror image of i (ip = n - 4 - i); see for_each_mirrored_pair
 //   mirrors_whole(args, n)   every `reverse` of the tree runs over exactly n elements
 // Parameter slots are numbered in pre-order, leaves included.
@@ -111,6 +112,8 @@ constexpr unsigned kSinglePass = 1u;
 constexpr unsigned kKeepOut = 1u << 8;
 
 template <class T> struct Vec4 { T v[4]; };
+// four elements in memory, at any 4-byte boundary: one 128-bit access
+template <class T> using Quad128 = T __attribute__((ext_vector_type(4), aligned(4)));
 
 template <class T> struct DtypeName;
 template <> struct DtypeName<float> { static const char *s() { return "f32"; } };
@@ -195,8 +198,7 @@ struct In {
     return Stream ? __builtin_nontemporal_load(p) : *p;
   }
   template <int Base> static __device__ __forceinline__ Vec4<T> eval4(const KArgs &a, int i) {
-    using V = T __attribute__((ext_vector_type(4)));
-    V v = __builtin_nontemporal_load(reinterpret_cast<const V *>(static_cast<const T *>(a.in[K]) + i));
+    const Quad128<T> v = __builtin_nontemporal_load(reinterpret_cast<const Quad128<T> *>(static_cast<const T *>(a.in[K]) + i));
     return Vec4<T>{{v.x, v.y, v.z, v.w}};
   }
   template <int Base>
@@ -344,7 +346,7 @@ struct Gather {
 
 // `reverse` (section 2, gather: the index is generate(n-1-i)): the source is read
 // backwards, so four consecutive results are one 128-bit read of the source,
-// taken in the opposite order, whenever the extent is a multiple of four.
+// taken in the opposite order.
 template <class ES>
 struct Gather<Gen<GenIotaRev>, ES> {
   using R = typename ES::R;
@@ -358,17 +360,12 @@ struct Gather<Gen<GenIotaRev>, ES> {
   template <int Base> static __device__ __forceinline__ Vec4<R> eval4(const KArgs &a, int i) {
     const int total = a.p[Base + 1].ext[0] * a.p[Base + 1].ext[1];
     Vec4<R> r;
-    if ((total & 3) == 0) {
-      Vec4<R> v = ES::template eval4<Base + 1 + EI::kNodes>(a, total - 4 - i);
+    const Vec4<R> v = ES::template eval4<Base + 1 + EI::kNodes>(a, total - 4 - i);
 #pragma unroll
-      for (int c = 0; c < 4; ++c) r.v[c] = v.v[3 - c];
-    } else {
-#pragma unroll
-      for (int c = 0; c < 4; ++c) r.v[c] = ES::template eval<Base + 1 + EI::kNodes>(a, total - 1 - (i + c));
-    }
+    for (int c = 0; c < 4; ++c) r.v[c] = v.v[3 - c];
     return r;
   }
-  // Over exactly n elements (mirrors_whole, n a multiple of four) the group that `reverse` reads
+  // Over exactly n elements (mirrors_whole) the group that `reverse` reads
   // for position i is the one at ip taken backwards, and the other way round: the source is
   // evaluated at the same two groups as a direct read of it, with the roles swapped, so that the
   // reads of an array which the program takes forwards and backwards coincide (same addresses in
@@ -392,6 +389,12 @@ struct Gather<Gen<GenIotaRev>, ES> {
   }
 };
 
+// Does the element program read at positions that an array holds (any gather but `reverse`)?
+template <class E> struct ReadsAnywhere { static constexpr bool value = false; };
+template <class F, class... E> struct ReadsAnywhere<Map<F, E...>> { static constexpr bool value = (ReadsAnywhere<E>::value || ... || false); };
+template <class EI, class ES> struct ReadsAnywhere<Gather<EI, ES>> { static constexpr bool value = true; };
+template <class ES> struct ReadsAnywhere<Gather<Gen<GenIotaRev>, ES>> { static constexpr bool value = ReadsAnywhere<ES>::value; };
+
 // KeepLoads<E>::type is E with every external array read by ordinary loads
 // instead of non-temporal ones.  Streams are read non-temporally so that they do
 // not displace gathered arrays from the caches; a program that reads one array
@@ -401,8 +404,7 @@ struct Gather<Gen<GenIotaRev>, ES> {
 template <int K, class T>
 struct InKeep : In<K, T> {
   template <int Base> static __device__ __forceinline__ Vec4<T> eval4(const KArgs &a, int i) {
-    using V = T __attribute__((ext_vector_type(4)));
-    V v = *reinterpret_cast<const V *>(static_cast<const T *>(a.in[K]) + i);
+    const Quad128<T> v = *reinterpret_cast<const Quad128<T> *>(static_cast<const T *>(a.in[K]) + i);
     return Vec4<T>{{v.x, v.y, v.z, v.w}};
   }
 };

@@ -26,8 +26,8 @@ constexpr int kTile = kBlock * kVec * kUnroll;     // 4096 elements per workgrou
 // under a run-time condition is merged with its twin and loses the non-temporal mark.
 template <bool Keep, class T>
 __device__ __forceinline__ void store4(T *p, const Vec4<T> &v) {
-  using V = T __attribute__((ext_vector_type(4)));
-  V x = {v.v[0], v.v[1], v.v[2], v.v[3]};
+  using V = Quad128<T>;
+  const V x = {v.v[0], v.v[1], v.v[2], v.v[3]};
   if (Keep) *reinterpret_cast<V *>(p) = x; else __builtin_nontemporal_store(x, reinterpret_cast<V *>(p));
 }
 // runs body(std::true_type) or body(std::false_type): the two forms of a kernel's loop
@@ -70,14 +70,14 @@ __device__ __forceinline__ void for_each_group_of(unsigned n4, L &&load, U &&use
     }
   }
 }
-// Short arrays are spread over four times as many workgroups, a group per lane: below kSpreadBelow
-// elements tiles of 4096 do not give every compute unit the waves that hide its latency.  Fold over
-// a gather (GPU time a pass): 100003 elements 6.8 -> 4.4 us, 400000 11.4 -> 7.2, 10^6 12.9 -> 11.0.
-constexpr unsigned kSpreadBelow = 1u << 21;
-__host__ __device__ inline int tile_of(unsigned n) { return (n & ~3u) < kSpreadBelow ? kBlock * kVec : kTile; }
-template <class L, class U>
+// Short arrays are spread over four times as many workgroups, a group per lane: tiles of 4096 do not give
+// every compute unit the waves that hide its latency.  Fold over a gather (GPU time a pass): 100003
+// elements 6.8 -> 4.4 us, 400000 11.4 -> 7.2, 10^6 12.9 -> 11.0.  A program that only streams has less to
+// hide and more to lose in the last stage of its fold: 300001 elements 4.4 -> 3.8 us, 10^6 4.6 -> 5.3.
+template <class... E> struct SpreadBelow { static constexpr unsigned value = (ReadsAnywhere<E>::value || ...) ? 1u << 21 : 1u << 19; };
+template <class... E, class L, class U>
 __device__ __forceinline__ void for_each_group(unsigned n4, L &&load, U &&use) {
-  if (n4 < kSpreadBelow) for_each_group_of<1>(n4, load, use); else for_each_group_of<kUnroll>(n4, load, use);
+  if (n4 < SpreadBelow<E...>::value) for_each_group_of<1>(n4, load, use); else for_each_group_of<kUnroll>(n4, load, use);
 }
 
 // The same for element programs that read an array forwards and through
@@ -91,6 +91,12 @@ __device__ __forceinline__ void for_each_group(unsigned n4, L &&load, U &&use) {
 // (measured at 2^16 elements: 8.3 us plain, 9.8 us mirrored), so the kernels take
 // this path from kMirrorMin elements on.
 constexpr unsigned kMirrorMin = 1u << 20;
+// elements a workgroup takes per step of the loops above and below
+template <class... E> int tile_of(unsigned n) {
+  const unsigned n4 = n & ~3u;
+  if ((E::kMirror || ...) && n4 >= kMirrorMin) return 2 * kTile;
+  return n4 < SpreadBelow<E...>::value ? kBlock * kVec : kTile;
+}
 template <class L, class U>
 __device__ __forceinline__ void for_each_mirrored_group(unsigned n4, L &&load, U &&use) {
   const unsigned half = ((n4 / 4 + 1) / 2) * 4;     // the first half, the middle group included
@@ -121,43 +127,47 @@ __device__ __forceinline__ void for_each_mirrored_group(unsigned n4, L &&load, U
   }
 }
 
-// The same pairing when every `reverse` of the element program runs over exactly the n4 elements
-// of the iteration space (E::mirrors_whole): the groups at i and at n4-4-i are evaluated together
+// The same pairing when every `reverse` of the element program runs over exactly the n elements
+// of the iteration space (E::mirrors_whole): the groups at i and at n-4-i are evaluated together
 // (eval4_pair), every array read of the pair is issued once, so the streams can be read
 // non-temporally like any other and a full tile has all its reads in flight.  Measured on the
 // reversed dot product at 2^26 elements: 52 us with for_each_mirrored_group, 43 us this way; a
-// read-only pass over as many bytes takes 39 us.
-template <class L, class U>
-__device__ __forceinline__ void for_each_mirrored_pair(unsigned n4, L &&load_pair, U &&use) {
-  const unsigned half = ((n4 / 4 + 1) / 2) * 4;     // the first half, the middle group included
+// read-only pass over as many bytes takes 39 us.  n need not be a multiple of anything: the
+// mirrored group starts on any 4-byte boundary, and the elements in the middle that no pair covers
+// (fewer than eight) go to one(i).  10000019 elements: 13.4 us with for_each_mirrored_group and the reverse
+// read an element at a time, 8.9 us this way.
+template <class L, class U, class O>
+__device__ __forceinline__ void for_each_mirrored_pair(unsigned n, L &&load_pair, U &&use, O &&one) {
+  const unsigned half = n / 8 * 4;                  // groups of the first half, each with its mirror image
   for (unsigned base = blockIdx.x * kTile; base < half; base += gridDim.x * kTile) {
     decltype(load_pair(0u, 0u)) v[kUnroll];
     const unsigned i0 = base + threadIdx.x * kVec;
     if (base + kTile <= half) {
 #pragma unroll
-      for (int u = 0; u < kUnroll; ++u) v[u] = load_pair(i0 + u * (kBlock * kVec), n4 - 4 - (i0 + u * (kBlock * kVec)));
+      for (int u = 0; u < kUnroll; ++u) v[u] = load_pair(i0 + u * (kBlock * kVec), n - 4 - (i0 + u * (kBlock * kVec)));
 #pragma unroll
       for (int u = 0; u < kUnroll; ++u) {
-        const unsigned i = i0 + u * (kBlock * kVec), ip = n4 - 4 - i;
+        const unsigned i = i0 + u * (kBlock * kVec);
         use(i, v[u].first);
-        if (ip != i) use(ip, v[u].second);
+        use(n - 4 - i, v[u].second);
       }
     } else {
 #pragma unroll
       for (int u = 0; u < kUnroll; ++u) {
         const unsigned i = i0 + u * (kBlock * kVec);
-        if (i < half) v[u] = load_pair(i, n4 - 4 - i);
+        if (i < half) v[u] = load_pair(i, n - 4 - i);
       }
 #pragma unroll
       for (int u = 0; u < kUnroll; ++u) {
-        const unsigned i = i0 + u * (kBlock * kVec), ip = n4 - 4 - i;
+        const unsigned i = i0 + u * (kBlock * kVec);
         if (i < half) {
           use(i, v[u].first);
-          if (ip != i) use(ip, v[u].second);
+          use(n - 4 - i, v[u].second);
         }
       }
     }
   }
+  if (blockIdx.x == 0 && threadIdx.x < n - 2 * half) one(half + threadIdx.x);
 }
 // the two groups of a pair, evaluated together
 template <class E>
@@ -167,26 +177,34 @@ __device__ __forceinline__ Two<Vec4<typename E::R>, Vec4<typename E::R>> eval_pa
   return r;
 }
 
+// whether a kernel over n elements takes them in mirrored pairs
+template <class E> __device__ __forceinline__ bool mirrored_pairs(const KArgs &a, unsigned n) {
+  if constexpr (E::kMirror) return n >= kMirrorMin && E::template mirrors_whole<0>(a, (int)n);
+  return false;
+}
+
 // ------------------------------------------------------------------ elementwise: out[i] = E(i)
 template <class E>
 __global__ __launch_bounds__(kBlock) void store_kernel(const KArgs a) {
   using T = typename E::R;
   T *out = static_cast<T *>(a.out[0]);
   const unsigned n = (unsigned)a.n, n4 = n & ~3u;
+  const bool pairs = mirrored_pairs<E>(a, n);
   with_keep(a.keeps(0), [&](auto keep) {
     auto use = [&](unsigned i, const Vec4<T> &v) { store4<decltype(keep)::value>(out + i, v); };
     if constexpr (E::kMirror) {
-      if (n4 >= kMirrorMin && n == n4 && E::template mirrors_whole<0>(a, (int)n))
-        for_each_mirrored_pair(n4, [&](unsigned i, unsigned ip) { return eval_pair<E>(a, i, ip); }, use);
+      if (pairs)
+        for_each_mirrored_pair(n, [&](unsigned i, unsigned ip) { return eval_pair<E>(a, i, ip); }, use,
+                               [&](unsigned i) { out[i] = E::template eval<0>(a, (int)i); });
       else if (n4 >= kMirrorMin)
         for_each_mirrored_group(n4, [&](unsigned i) { return KeepLoads<E>::type::template eval4<0>(a, (int)i); }, use);
       else
-        for_each_group(n4, [&](unsigned i) { return E::template eval4<0>(a, (int)i); }, use);
+        for_each_group<E>(n4, [&](unsigned i) { return E::template eval4<0>(a, (int)i); }, use);
     } else {
-      for_each_group(n4, [&](unsigned i) { return E::template eval4<0>(a, (int)i); }, use);
+      for_each_group<E>(n4, [&](unsigned i) { return E::template eval4<0>(a, (int)i); }, use);
     }
   });
-  if (blockIdx.x == 0 && threadIdx.x < n - n4) out[n4 + threadIdx.x] = E::template eval<0>(a, (int)(n4 + threadIdx.x));
+  if (!pairs && blockIdx.x == 0 && threadIdx.x < n - n4) out[n4 + threadIdx.x] = E::template eval<0>(a, (int)(n4 + threadIdx.x));
 }
 
 // two arrays written in one pass (diagonal fusion: a value is forwarded to the next
@@ -211,7 +229,7 @@ __global__ __launch_bounds__(kBlock) void store2_kernel(const KArgs a) {
       for_each_mirrored_group(
           n4, [&](unsigned i) { return Both{K1::template eval4<0>(a, (int)i), K2::template eval4<E1::kNodes>(a, (int)i)}; }, use);
     else
-      for_each_group(
+      for_each_group<E1, E2>(
           n4, [&](unsigned i) { return Both{E1::template eval4<0>(a, (int)i), E2::template eval4<E1::kNodes>(a, (int)i)}; }, use);
   });
   if (blockIdx.x == 0 && threadIdx.x < n - n4) {
@@ -266,17 +284,19 @@ __global__ __launch_bounds__(kBlock) void fold_kernel(const KArgs a, Control *ct
 #pragma unroll
     for (int c = 0; c < 4; ++c) acc = Op::apply(acc, v.v[c]);
   };
+  const bool pairs = mirrored_pairs<E>(a, n);
   if constexpr (E::kMirror) {
-    if (n4 >= kMirrorMin && n == n4 && E::template mirrors_whole<0>(a, (int)n))
-      for_each_mirrored_pair(n4, [&](unsigned i, unsigned ip) { return eval_pair<E>(a, i, ip); }, use);
+    if (pairs)
+      for_each_mirrored_pair(n, [&](unsigned i, unsigned ip) { return eval_pair<E>(a, i, ip); }, use,
+                             [&](unsigned i) { acc = Op::apply(acc, E::template eval<0>(a, (int)i)); });
     else if (n4 >= kMirrorMin)
       for_each_mirrored_group(n4, [&](unsigned i) { return KeepLoads<E>::type::template eval4<0>(a, (int)i); }, use);
     else
-      for_each_group(n4, [&](unsigned i) { return E::template eval4<0>(a, (int)i); }, use);
+      for_each_group<E>(n4, [&](unsigned i) { return E::template eval4<0>(a, (int)i); }, use);
   } else {
-    for_each_group(n4, [&](unsigned i) { return E::template eval4<0>(a, (int)i); }, use);
+    for_each_group<E>(n4, [&](unsigned i) { return E::template eval4<0>(a, (int)i); }, use);
   }
-  if (blockIdx.x == 0 && threadIdx.x < n - n4) acc = Op::apply(acc, E::template eval<0>(a, (int)(n4 + threadIdx.x)));
+  if (!pairs && blockIdx.x == 0 && threadIdx.x < n - n4) acc = Op::apply(acc, E::template eval<0>(a, (int)(n4 + threadIdx.x)));
   fold_finish<Op>(acc, a, 0, ctl, partials, epoch);
 }
 
@@ -302,7 +322,7 @@ __global__ __launch_bounds__(kBlock) void store_fold_kernel(const KArgs a, Contr
       for_each_mirrored_group(
           n4, [&](unsigned i) { return Both{KS::template eval4<0>(a, (int)i), KF::template eval4<ES::kNodes>(a, (int)i)}; }, use);
     else
-      for_each_group(
+      for_each_group<ES, EF>(
           n4, [&](unsigned i) { return Both{ES::template eval4<0>(a, (int)i), EF::template eval4<ES::kNodes>(a, (int)i)}; }, use);
   });
   if (blockIdx.x == 0 && threadIdx.x < n - n4) {
@@ -2575,7 +2595,7 @@ __global__ __launch_bounds__(kBlock) void scatter_kernel(const KArgs a) {
   struct Item { Vec4<int> f, j; Vec4<V> v; };
   V *dest = static_cast<V *>(a.out[0]);
   const unsigned n = (unsigned)a.n, n4 = n & ~3u;
-  for_each_group(
+  for_each_group<EI, EV, EF>(
       n4,
       [&](unsigned i) {
         return Item{EF::template eval4<EI::kNodes + EV::kNodes>(a, (int)i), EI::template eval4<0>(a, (int)i),

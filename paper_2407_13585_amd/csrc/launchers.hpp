@@ -69,14 +69,14 @@ unsigned resident_grid(void (*k)(P...)) {
 
 template <class E> hipError_t launch_store(const KArgs &a, const LaunchCtx &c) {
   if (a.n == 0) return hipSuccess;
-  return launch_k(&store_kernel<E>, grid_for(a.n, tile_of((unsigned)a.n), resident_grid(&store_kernel<E>)), c, a);
+  return launch_k(&store_kernel<E>, grid_for(a.n, tile_of<E>((unsigned)a.n), resident_grid(&store_kernel<E>)), c, a);
 }
 template <class Op, class E> hipError_t launch_fold(const KArgs &a, const LaunchCtx &c) {
-  return launch_k(&fold_kernel<Op, E>, grid_for(a.n, tile_of((unsigned)a.n), resident_grid(&fold_kernel<Op, E>)), c, a, c.ctl,
+  return launch_k(&fold_kernel<Op, E>, grid_for(a.n, tile_of<E>((unsigned)a.n), resident_grid(&fold_kernel<Op, E>)), c, a, c.ctl,
                   c.partials);
 }
 template <class ES, class Op, class EF> hipError_t launch_store_fold(const KArgs &a, const LaunchCtx &c) {
-  return launch_k(&store_fold_kernel<ES, Op, EF>, grid_for(a.n, tile_of((unsigned)a.n), resident_grid(&store_fold_kernel<ES, Op, EF>)),
+  return launch_k(&store_fold_kernel<ES, Op, EF>, grid_for(a.n, tile_of<ES, EF>((unsigned)a.n), resident_grid(&store_fold_kernel<ES, Op, EF>)),
                   c, a, c.ctl, c.partials);
 }
 template <class Op, class E> hipError_t launch_foldseg(const KArgs &a, const LaunchCtx &c) {
@@ -326,11 +326,11 @@ template <class E, bool Reverse, bool StoreX = false> hipError_t launch_rowscan(
 }
 template <class EI, class EV, class EF, bool Add> hipError_t launch_scatter(const KArgs &a, const LaunchCtx &c) {
   if (a.n == 0) return hipSuccess;
-  return launch_k(&scatter_kernel<EI, EV, EF, Add>, grid_for(a.n, tile_of((unsigned)a.n), resident_grid(&scatter_kernel<EI, EV, EF, Add>)), c, a);
+  return launch_k(&scatter_kernel<EI, EV, EF, Add>, grid_for(a.n, tile_of<EI, EV, EF>((unsigned)a.n), resident_grid(&scatter_kernel<EI, EV, EF, Add>)), c, a);
 }
 template <class E1, class E2> hipError_t launch_store2(const KArgs &a, const LaunchCtx &c) {
   if (a.n == 0) return hipSuccess;
-  return launch_k(&store2_kernel<E1, E2>, grid_for(a.n, tile_of((unsigned)a.n), resident_grid(&store2_kernel<E1, E2>)), c, a);
+  return launch_k(&store2_kernel<E1, E2>, grid_for(a.n, tile_of<E1, E2>((unsigned)a.n), resident_grid(&store2_kernel<E1, E2>)), c, a);
 }
 // lanes per row by row length: a 16-lane DPP row, a wave, or the whole workgroup
 template <class Op1, class Op2, class E, class RI> hipError_t launch_rowfold(const KArgs &a, const LaunchCtx &c) {

@@ -159,9 +159,11 @@ def test_fold_sizes(n):
     run_all_modes(2, w)
 
 
-@pytest.mark.parametrize("n", [1023, 1024, 1028, 256 * 1024 + 5, (1 << 21) - 1, 1 << 21, (1 << 21) + 4, (1 << 21) + 7])
+@pytest.mark.parametrize("n", [1023, 1024, 1028, 256 * 1024 + 5, (1 << 19) - 4, (1 << 19) + 1, (1 << 20) - 1, (1 << 20) + 2,
+                               (1 << 21) - 1, 1 << 21, (1 << 21) + 4, (1 << 21) + 7])
 def test_sizes_where_the_tile_changes(n):
-    # a group per lane below 2^21 elements, four above; one workgroup hands no partial over
+    # a group per lane in short arrays, four in long ones, mirrored pairs from 2^20 elements on (whatever is left in
+    # the middle element by element); one workgroup hands no partial over
     run_all_modes(1, C.reverse_dot(n=n, seed=150 + n))
     run_all_modes(4, C.compaction(n=n, seed=160 + n))
 
