@@ -23,6 +23,7 @@
 
 #include <string>
 #include <tuple>
+#include <type_traits>
 #include <utility>
 
 #include "prim.hpp"
@@ -452,5 +453,128 @@ template <int KI, class ES> struct GatherChain<Gather<In<KI, int>, ES>> {
     return Inner::template from_leaf<Base + 2>(a, x);
   }
 };
+
+// ------------------------------------------------------------------ kernel arguments
+// A launch writes its arguments across the bus a cache line at a time, and a small program's pass costs little
+// else: a kernel of 48 bytes of arguments takes the host 2.6 us to launch, one of 376 bytes 3.3 to 3.7, one of 1432 (KArgs
+// as a whole) 3.3 to 3.9.  So the kernels whose element programs are compiled take the parts of KArgs
+// these programs use, as Packed<...>, and open() puts them back where the program looks for them (registers:
+// every index is known when the kernel is compiled).
+template <int K, class T, int LdsThreads> struct Interp;        // kernels.hpp: reads KArgs::code, needs all of it
+
+// the fields of a Slot as words: f[0], f[1], i[0], i[1], ext[0], ext[1], m[0], m[1], m[2]
+constexpr int kSlotWords = 9;
+constexpr unsigned kWordsF = 3u, kWordsI = 3u << 2, kWordsExt = 3u << 4, kWordsM01 = 3u << 6, kWordM2 = 1u << 8;
+template <class F> struct SlotUse { static constexpr unsigned value = 0; };
+template <> struct SlotUse<FnAffine> { static constexpr unsigned value = kWordsF; };
+template <> struct SlotUse<FnModEq> { static constexpr unsigned value = 1u << 3 | kWordsM01 | kWordM2; };
+template <> struct SlotUse<GenIotaRev> { static constexpr unsigned value = kWordsExt; };
+template <> struct SlotUse<GenClampShift2D> { static constexpr unsigned value = kWordsI | kWordsExt | kWordsM01; };
+template <> struct SlotUse<GenRowOf2D> { static constexpr unsigned value = kWordsM01; };
+template <> struct SlotUse<GenConst> { static constexpr unsigned value = 1u << 2; };
+
+struct WordList {
+  int n = 0;
+  short at[kMaxSlots * kSlotWords + 8] = {};
+  constexpr void add(int w) { at[n++] = (short)w; }
+  constexpr void add_slot(int slot, unsigned use) {
+    for (int k = 0; k < kSlotWords; ++k) if (use >> k & 1u) add(slot * kSlotWords + k);
+  }
+};
+
+// what element program E reads: external arrays 0 .. ins-1, words of its slots, or everything
+template <class E> struct Needs {
+  static constexpr int ins = 0;
+  static constexpr bool all = false;
+  template <int Base> static constexpr void words(WordList &) {}
+};
+template <int K, class T, int L> struct Needs<Interp<K, T, L>> : Needs<void> { static constexpr bool all = true; };
+template <int K, class T> struct Needs<In<K, T>> : Needs<void> { static constexpr int ins = K + 1; };
+template <class G> struct Needs<Gen<G>> : Needs<void> {
+  template <int Base> static constexpr void words(WordList &l) { l.add_slot(Base, SlotUse<G>::value); }
+};
+constexpr int most_of() { return 0; }
+template <class... I> constexpr int most_of(int a, I... b) { const int m = most_of(b...); return a > m ? a : m; }
+template <class F, class... E> struct Needs<Map<F, E...>> {
+  static constexpr int ins = most_of(Needs<E>::ins...);
+  static constexpr bool all = (Needs<E>::all || ... || false);
+  template <int Base, int... K> static constexpr void words_(WordList &l, std::integer_sequence<int, K...>) {
+    (Needs<E>::template words<ChildBase<Base + 1, K, E...>::value>(l), ...);
+  }
+  template <int Base> static constexpr void words(WordList &l) {
+    l.add_slot(Base, SlotUse<F>::value);
+    words_<Base>(l, std::make_integer_sequence<int, sizeof...(E)>());
+  }
+};
+template <class EI, class ES> struct Needs<Gather<EI, ES>> {
+  static constexpr int ins = most_of(Needs<EI>::ins, Needs<ES>::ins);
+  static constexpr bool all = Needs<EI>::all || Needs<ES>::all;
+  template <int Base> static constexpr void words(WordList &l) {
+    Needs<EI>::template words<Base + 1>(l);
+    Needs<ES>::template words<Base + 1 + EI::kNodes>(l);
+  }
+};
+
+// Head: numbers of KArgs the kernel itself reads.  Outs: bit k = it writes out[k].  E: its element programs, whose slots
+// follow each other.
+constexpr unsigned kHeadN = 1u, kHeadW = 2u, kHeadH = 4u, kHeadAux = 8u, kHeadFlags = 16u, kHeadOffsets = 32u;
+template <unsigned Head, unsigned Outs, bool All, class... E> struct PackedArgs {
+  static constexpr int kIns = most_of(Needs<E>::ins...) + ((Head & kHeadOffsets) ? 1 : 0);
+  static constexpr int kOuts = __builtin_popcount(Outs);
+  static constexpr int kHeadWord = kMaxSlots * kSlotWords;
+  template <int Base, class E0, class... R> static constexpr void add_programs(WordList &l) {
+    Needs<E0>::template words<Base>(l);
+    if constexpr (sizeof...(R) != 0) add_programs<Base + E0::kNodes, R...>(l);
+  }
+  static constexpr WordList make_list() {
+    WordList l;
+    for (int k = 0; k < 5; ++k) if (Head >> k & 1u) l.add(kHeadWord + k);
+    if constexpr (sizeof...(E) != 0) add_programs<0, E...>(l);
+    return l;
+  }
+  static constexpr WordList kList = make_list();
+  const void *in[kIns ? kIns : 1];
+  void *out[kOuts ? kOuts : 1];
+  unsigned word[kList.n ? kList.n : 1];
+
+  // word W of KArgs, read or written
+  template <int W, class A, class V> static __host__ __device__ __forceinline__ void visit(A &a, V &&v) {
+    if constexpr (W >= kHeadWord) {
+      constexpr int k = W - kHeadWord;
+      if constexpr (k == 0) v(a.n); else if constexpr (k == 1) v(a.w); else if constexpr (k == 2) v(a.h); else if constexpr (k == 3) v(a.aux); else v(a.flags);
+    } else {
+      constexpr int s = W / kSlotWords, k = W % kSlotWords;
+      if constexpr (k < 2) v(a.p[s].f[k]); else if constexpr (k < 4) v(a.p[s].i[k - 2]); else if constexpr (k < 6) v(a.p[s].ext[k - 4]); else v(a.p[s].m[k - 6]);
+    }
+  }
+  template <int... I> void pack_words(const KArgs &a, std::integer_sequence<int, I...>) {
+    (visit<kList.at[I]>(a, [&](const auto &x) { word[I] = __builtin_bit_cast(unsigned, x); }), ...);
+  }
+  template <int... I> __device__ __forceinline__ void open_words(KArgs &a, std::integer_sequence<int, I...>) const {
+    (visit<kList.at[I]>(a, [&](auto &x) { x = __builtin_bit_cast(typename std::remove_reference<decltype(x)>::type, word[I]); }), ...);
+  }
+  PackedArgs(const KArgs &a) {
+    for (int k = 0; k < kIns; ++k) in[k] = a.in[k];
+    if (Head & kHeadOffsets) in[kIns - 1] = a.in[kMaxIn - 1];
+    for (int k = 0, o = 0; k < kMaxOut; ++k) if (Outs >> k & 1u) out[o++] = a.out[k];
+    pack_words(a, std::make_integer_sequence<int, kList.n>());
+  }
+  __device__ __forceinline__ KArgs open() const {
+    KArgs a;
+#pragma unroll
+    for (int k = 0; k < kIns; ++k) a.in[(Head & kHeadOffsets) && k == kIns - 1 ? kMaxIn - 1 : k] = in[k];
+    int o = 0;
+#pragma unroll
+    for (int k = 0; k < kMaxOut; ++k) if (Outs >> k & 1u) a.out[k] = out[o++];
+    open_words(a, std::make_integer_sequence<int, kList.n>());
+    return a;
+  }
+};
+template <unsigned Head, unsigned Outs, class... E> struct PackedArgs<Head, Outs, true, E...> {
+  KArgs args;
+  PackedArgs(const KArgs &a) : args(a) {}
+  __device__ __forceinline__ const KArgs &open() const { return args; }
+};
+template <unsigned Head, unsigned Outs, class... E> using Packed = PackedArgs<Head, Outs, (Needs<E>::all || ... || false), E...>;
 
 }  // namespace fc

@@ -37,6 +37,18 @@ using Stencil5 = Map<FnAdd5, ExpNeg0, ShiftedExp, ShiftedExp, ShiftedExp, Shifte
 using ShiftedIn = Gather<Gen<GenClampShift2D>, F0>;
 using Stencil5Mat = Map<FnAdd5, F0, ShiftedIn, ShiftedIn, ShiftedIn, ShiftedIn>;
 
+// what the host has to write per launch for the kernels of small programs: one cache line (see Packed)
+template <class... P> constexpr size_t argument_bytes(void (*)(P...)) {
+  size_t at = 0;
+  ((at = (at + alignof(P) - 1) / alignof(P) * alignof(P) + sizeof(P)), ...);
+  return at;
+}
+static_assert(argument_bytes(&fold_kernel<AddF32, ReverseDot>) <= 64 && argument_bytes(&fold_kernel<AddF32, PermGather>) <= 64 &&
+                  argument_bytes(&scan_kernel<ModFlag, I0, kScatter | kCount, false>) <= 64 &&
+                  argument_bytes(&stencil5_kernel<FnExpNeg, 1, true>) <= 64 &&
+                  argument_bytes(&foldseg_kernel<AddF32, SpmvTerm, 4, 4>) <= 64,
+              "arguments of the fused pipelines");
+
 // specialised instances come first: they share the signature of a generic one
 // and take over when their accept() passes
 void append_stencil_instances(std::vector<Instance> &r) {

@@ -185,7 +185,8 @@ template <class E> __device__ __forceinline__ bool mirrored_pairs(const KArgs &a
 
 // ------------------------------------------------------------------ elementwise: out[i] = E(i)
 template <class E>
-__global__ __launch_bounds__(kBlock) void store_kernel(const KArgs a) {
+__global__ __launch_bounds__(kBlock) void store_kernel(const Packed<kHeadN | kHeadFlags, 1u, E> packed) {
+  const KArgs &a = packed.open();
   using T = typename E::R;
   T *out = static_cast<T *>(a.out[0]);
   const unsigned n = (unsigned)a.n, n4 = n & ~3u;
@@ -210,7 +211,8 @@ __global__ __launch_bounds__(kBlock) void store_kernel(const KArgs a) {
 // two arrays written in one pass (diagonal fusion: a value is forwarded to the next
 // combinator in registers and stored as well; section 1, Fig. "Three types of fusion")
 template <class E1, class E2>
-__global__ __launch_bounds__(kBlock) void store2_kernel(const KArgs a) {
+__global__ __launch_bounds__(kBlock) void store2_kernel(const Packed<kHeadN | kHeadFlags, 3u, E1, E2> packed) {
+  const KArgs &a = packed.open();
   using T1 = typename E1::R;
   using T2 = typename E2::R;
   using K1 = typename KeepLoads<E1>::type;
@@ -275,7 +277,8 @@ __device__ __forceinline__ void fold_finish(typename Op::T acc, const KArgs &a, 
 }
 
 template <class Op, class E>
-__global__ __launch_bounds__(kBlock) void fold_kernel(const KArgs a, Control *ctl, unsigned long long *partials) {
+__global__ __launch_bounds__(kBlock) void fold_kernel(const Packed<kHeadN, 1u, E> packed, Control *ctl, unsigned long long *partials) {
+  const KArgs &a = packed.open();
   const unsigned epoch = epoch_at_start(ctl);
   using T = typename Op::T;
   const unsigned n = (unsigned)a.n, n4 = n & ~3u;
@@ -302,7 +305,8 @@ __global__ __launch_bounds__(kBlock) void fold_kernel(const KArgs a, Control *ct
 
 // out[0][i] = ES(i) and out[1] = fold(Op, EF(i)) in one pass
 template <class ES, class Op, class EF>
-__global__ __launch_bounds__(kBlock) void store_fold_kernel(const KArgs a, Control *ctl, unsigned long long *partials) {
+__global__ __launch_bounds__(kBlock) void store_fold_kernel(const Packed<kHeadN | kHeadFlags, 3u, ES, EF> packed, Control *ctl, unsigned long long *partials) {
+  const KArgs &a = packed.open();
   const unsigned epoch = epoch_at_start(ctl);
   using T = typename Op::T;
   using S = typename ES::R;
@@ -1218,7 +1222,8 @@ __global__ __launch_bounds__(kFineBlock) void fold_fine_kernel(const KArgs a, Co
 // (non-temporal: 300001 rows of 16 elements 39 us instead of 26).  Elements past a row's end
 // are read at its last element instead of not at all, so that a lane's U reads are issued together.
 template <class Op, class E, int L, int U>
-__global__ __launch_bounds__(kBlock) void foldseg_kernel(const KArgs a) {
+__global__ __launch_bounds__(kBlock) void foldseg_kernel(const Packed<kHeadAux | kHeadOffsets, 1u, E> packed) {
+  const KArgs &a = packed.open();
   using T = typename Op::T;
   const unsigned *off = static_cast<const unsigned *>(a.in[kMaxIn - 1]);
   T *y = static_cast<T *>(a.out[0]);
@@ -2000,6 +2005,8 @@ template <class EX, int Mode> struct ScanParks {
   static constexpr int cap = value ? kScanTile / 2 : 1;
 };
 
+// tiles of a scan of n elements (an empty array has one, which writes the total)
+__host__ __device__ constexpr unsigned scan_tiles(unsigned n, unsigned tile) { return n == 0 ? 1u : (n - 1u) / tile + 1u; }
 // number of status words a launch over n_tiles tiles uses (tile words, then group words)
 __host__ __device__ inline size_t scan_status_words(size_t n_tiles) {
   return ((n_tiles + 15) / 16) * 16 + (n_tiles + kScanGroup - 1) / kScanGroup;
@@ -2193,12 +2200,16 @@ struct ScanPayload {
   }
 };
 
+// the arrays a scan of this mode writes
+template <int Mode> constexpr unsigned kScanOuts = ((Mode & kScatter) ? 1u : 0u) | ((Mode & kOffs) ? 2u : 0u) | ((Mode & kCount) ? 4u : 0u) | ((Mode & kStoreX) ? 8u : 0u);
+
 // waves per SIMD asked of the compiler: an interpreted element program (it has no nodes of its own) needs the registers
 template <class EX> struct ScanWaves { static constexpr int value = EX::kNodes == 0 ? 4 : 8; };
 
 template <class EX, class EV, int Mode, bool Reverse>
-__global__ __launch_bounds__(kScanBlock, ScanWaves<EX>::value) void scan_kernel(const KArgs a, Control *ctl, unsigned long long *status,
-                                                             unsigned n_tiles) {
+__global__ __launch_bounds__(kScanBlock, ScanWaves<EX>::value) void scan_kernel(const Packed<kHeadN, kScanOuts<Mode>, EX, EV> packed, Control *ctl, unsigned long long *status) {
+  const KArgs &a = packed.open();
+  const unsigned n_tiles = scan_tiles((unsigned)a.n, kScanTile);
   __shared__ int lds_wave[kScanWaves];
   __shared__ int lds_sum[kScanWaves];
   using P = ScanPayload<EX, EV, Mode, Reverse>;
@@ -2405,8 +2416,9 @@ __device__ __forceinline__ float scan_block_sum_f32(float v, float *lds) {
 }
 
 template <class EX, bool Reverse, bool StoreX = false>
-__global__ __launch_bounds__(kScanBlock, ScanWaves<EX>::value) void scan_f32_kernel(const KArgs a, Control *ctl, unsigned long long *status,
-                                                              unsigned n_tiles) {
+__global__ __launch_bounds__(kScanBlock, ScanWaves<EX>::value) void scan_f32_kernel(const Packed<kHeadN, StoreX ? 10u : 2u, EX> packed, Control *ctl, unsigned long long *status) {
+  const KArgs &a = packed.open();
+  const unsigned n_tiles = scan_tiles((unsigned)a.n, kScanFTile);
   static_assert(std::is_same<typename EX::R, float>::value, "fp32 stream");
   __shared__ float lds_wave[kScanWaves];
   __shared__ float lds_sum[kScanWaves];
@@ -2590,7 +2602,8 @@ template <> __device__ __forceinline__ void scatter_one<true, float>(float *dest
 }
 
 template <class EI, class EV, class EF, bool Add>
-__global__ __launch_bounds__(kBlock) void scatter_kernel(const KArgs a) {
+__global__ __launch_bounds__(kBlock) void scatter_kernel(const Packed<kHeadN, 1u, EI, EV, EF> packed) {
+  const KArgs &a = packed.open();
   using V = typename EV::R;
   struct Item { Vec4<int> f, j; Vec4<V> v; };
   V *dest = static_cast<V *>(a.out[0]);

@@ -51,14 +51,14 @@ hipError_t launch_impl(void (*k)(P...), dim3 grid, dim3 block, const LaunchCtx &
   void *ptrs[] = {static_cast<void *>(&std::get<I>(vals))...};
   return hipLaunchKernel(reinterpret_cast<const void *>(k), grid, block, ptrs, 0, c.stream);
 }
-template <class... P>
-hipError_t launch_k(void (*k)(P...), unsigned grid, const LaunchCtx &c, int block, P... a) {
-  std::tuple<P...> vals(a...);
+template <class... P, class... A>
+hipError_t launch_threads(void (*k)(P...), unsigned grid, const LaunchCtx &c, int block, const A &...a) {
+  std::tuple<P...> vals(static_cast<P>(a)...);          // KArgs becomes the kernel's PackedArgs here
   return launch_impl(k, dim3(grid), dim3(block), c, vals, std::index_sequence_for<P...>());
 }
-template <class... P>
-hipError_t launch_k(void (*k)(P...), unsigned grid, const LaunchCtx &c, P... a) {
-  return launch_k(k, grid, c, (int)kBlock, a...);
+template <class... P, class... A>
+hipError_t launch_k(void (*k)(P...), unsigned grid, const LaunchCtx &c, const A &...a) {
+  return launch_threads(k, grid, c, (int)kBlock, a...);
 }
 // the kernels that stride over tiles are launched with as many workgroups as are resident at once
 template <class... P>
@@ -206,9 +206,9 @@ template <class Op, class E> hipError_t launch_fold_fine(const KArgs &a, const L
   const int cus = device_compute_units();
   const unsigned units = (unsigned)(cus > 0 ? cus : 256);
   const unsigned first = std::min(tiles, units);
-  hipError_t e = launch_k(&bin_fine_kernel<Op, E>, first, c, (int)kFineBlock, a, c.ctl, c.partials, slots, tiles, cut);
+  hipError_t e = launch_threads(&bin_fine_kernel<Op, E>, first, c, (int)kFineBlock, a, c.ctl, c.partials, slots, tiles, cut);
   if (e != hipSuccess) return e;
-  return launch_k(&fold_fine_kernel<Op, E>, std::min(cut.bins, units), c, (int)kFineBlock, a, c.ctl, c.partials,
+  return launch_threads(&fold_fine_kernel<Op, E>, std::min(cut.bins, units), c, (int)kFineBlock, a, c.ctl, c.partials,
                   static_cast<const unsigned *>(slots), tiles, cut, elems, first);
 }
 
@@ -281,7 +281,7 @@ hipError_t launch_foldseg_sorted(const KArgs &a, const LaunchCtx &c) {
   T *head = reinterpret_cast<T *>(w + s.head), *tail = reinterpret_cast<T *>(w + s.tail);
   const int cus = device_compute_units();
   const unsigned units = (unsigned)(cus > 0 ? cus : 256);
-  hipError_t e = launch_k(&seg_bin_kernel<KI>, std::min(p.tiles, units), c, (int)kSegBlock, a, offsets, places,
+  hipError_t e = launch_threads(&seg_bin_kernel<KI>, std::min(p.tiles, units), c, (int)kSegBlock, a, offsets, places,
                           list_place, list_index, list_count, p, elems);
   if (e != hipSuccess) return e;
   // A table range is read into LDS by every workgroup that works on it, and a workgroup fills the LDS of a compute
@@ -294,10 +294,10 @@ hipError_t launch_foldseg_sorted(const KArgs &a, const LaunchCtx &c) {
     for (unsigned q = 2; q <= 8; ++q)
       if (cost(q) < cost(parts) * 0.999) parts = q;
   }
-  e = launch_k(&seg_gather_kernel<T, KT>, p.cut.bins * parts, c, (int)kSegBlock, a, static_cast<const unsigned short *>(offsets),
+  e = launch_threads(&seg_gather_kernel<T, KT>, p.cut.bins * parts, c, (int)kSegBlock, a, static_cast<const unsigned short *>(offsets),
                gathered, first_row, p, elems, parts);
   if (e != hipSuccess) return e;
-  e = launch_k(&seg_rows_kernel<Op, F, KV, KT>, p.tiles, c, (int)kSegRowsBlock, a, static_cast<const unsigned short *>(places),
+  e = launch_threads(&seg_rows_kernel<Op, F, KV, KT>, p.tiles, c, (int)kSegRowsBlock, a, static_cast<const unsigned short *>(places),
                static_cast<const T *>(gathered), static_cast<const unsigned short *>(list_place), static_cast<const unsigned *>(list_index),
                static_cast<const unsigned *>(list_count), static_cast<const unsigned *>(first_row), head, tail, p);
   if (e != hipSuccess) return e;
@@ -306,15 +306,15 @@ hipError_t launch_foldseg_sorted(const KArgs &a, const LaunchCtx &c) {
 }
 
 template <class EX, class EV, int Mode, bool Reverse = false> hipError_t launch_scan(const KArgs &a, const LaunchCtx &c) {
-  long long tiles = std::max<long long>(1, ((long long)a.n + kScanTile - 1) / kScanTile);
-  if (scan_status_words((size_t)tiles) > c.max_tiles) return hipErrorInvalidValue;
-  return launch_k(&scan_kernel<EX, EV, Mode, Reverse>, (unsigned)tiles, c, kScanBlock, a, c.ctl, c.status, (unsigned)tiles);
+  const unsigned tiles = scan_tiles((unsigned)a.n, kScanTile);
+  if (scan_status_words(tiles) > c.max_tiles) return hipErrorInvalidValue;
+  return launch_threads(&scan_kernel<EX, EV, Mode, Reverse>, tiles, c, kScanBlock, a, c.ctl, c.status);
 }
 // lanes per row by row length, as for the row folds
 template <class EX, bool Reverse = false, bool StoreX = false> hipError_t launch_scan_f32(const KArgs &a, const LaunchCtx &c) {
-  long long tiles = std::max<long long>(1, ((long long)a.n + kScanFTile - 1) / kScanFTile);
-  if (scan_status_words((size_t)tiles) > c.max_tiles) return hipErrorInvalidValue;
-  return launch_k(&scan_f32_kernel<EX, Reverse, StoreX>, (unsigned)tiles, c, kScanBlock, a, c.ctl, c.status, (unsigned)tiles);
+  const unsigned tiles = scan_tiles((unsigned)a.n, kScanFTile);
+  if (scan_status_words(tiles) > c.max_tiles) return hipErrorInvalidValue;
+  return launch_threads(&scan_f32_kernel<EX, Reverse, StoreX>, tiles, c, kScanBlock, a, c.ctl, c.status);
 }
 template <class E, bool Reverse, bool StoreX = false> hipError_t launch_rowscan(const KArgs &a, const LaunchCtx &c) {
   if (a.aux == 0 || a.w == 0) return hipSuccess;

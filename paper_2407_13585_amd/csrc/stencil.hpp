@@ -76,8 +76,10 @@ __device__ __forceinline__ float load_halo(const float *g, int r, int c0, int la
 // F: element function of the shared producer (FnExpNeg, or FnIdentF when p is
 // read from memory).  WithMax: also fold(max) over p into out[1].
 template <class F, int FSlot, bool WithMax>
-__global__ __launch_bounds__(kBlock) void stencil5_kernel(const KArgs a, Control *ctl, unsigned long long *partials,
-                                                          int n_strips, int n_units) {
+__global__ __launch_bounds__(kBlock) void stencil5_kernel(const Packed<kHeadH | kHeadW | kHeadFlags, WithMax ? 3u : 1u, In<0, float>> packed,
+                                                          Control *ctl, unsigned long long *partials, int n_strips, int n_units) {
+  static_assert(SlotUse<F>::value == 0, "the shared producer takes no parameters");
+  const KArgs &a = packed.open();
   const int H = a.h, W = a.w;
   const float *g = static_cast<const float *>(a.in[0]);
   float *out = static_cast<float *>(a.out[0]);
