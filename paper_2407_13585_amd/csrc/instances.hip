@@ -44,7 +44,7 @@ template <class... P> constexpr size_t argument_bytes(void (*)(P...)) {
   return at;
 }
 static_assert(argument_bytes(&fold_kernel<AddF32, ReverseDot>) <= 64 && argument_bytes(&fold_kernel<AddF32, PermGather>) <= 64 &&
-                  argument_bytes(&scan_kernel<ModFlag, I0, kScatter | kCount, false>) <= 64 &&
+                  argument_bytes(&scan_kernel<ModFlag, I0, kScatter | kCount, false, kScanAcc>) <= 64 &&
                   argument_bytes(&stencil5_kernel<FnExpNeg, 1, true>) <= 64 &&
                   argument_bytes(&foldseg_kernel<AddF32, SpmvTerm, 4, 4>) <= 64,
               "arguments of the fused pipelines");

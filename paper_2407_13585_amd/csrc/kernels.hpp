@@ -1990,9 +1990,13 @@ __global__ __launch_bounds__(kBlock) void seg_join_kernel(const KArgs a, const u
 // collision-free indices: plain stores, no atomics), kCount stores the total.
 constexpr int kScanBlock = 512;                       // threads per workgroup of the scan kernels
 constexpr int kScanWaves = kScanBlock / kWave;
-constexpr int kScanItems = 24;                        // per lane: six 128-bit accesses (measured best of 16..32)
-constexpr int kScanAcc = kScanItems / kVec;
-constexpr int kScanTile = kScanBlock * kScanItems;    // 12288 elements
+// 128-bit accesses per lane, hence elements per tile: kScanAcc in long arrays (six, measured best of four to
+// eight), kScanShortAcc in short ones, where the pass lasts as long as one tile's serial work (GPU time of a pass,
+// two accesses against six: compaction of 300007 elements 4.8 against 6.3 us, of 2 x 10^6 6.0 against 7.3, of 4 x 10^6
+// 8.2 against 8.8, of 1.7 x 10^7 23.5 against 17.9; int32 scan of 10^6 4.8 against 5.6, of 2 x 10^6 6.9 against 6.5)
+constexpr int kScanAcc = 6, kScanShortAcc = 2;
+template <bool Parks> constexpr unsigned kScanShortBelow = Parks ? 1u << 22 : 3u << 19;
+constexpr int scan_tile(int acc) { return kScanBlock * kVec * acc; }
 constexpr int kScanGroup = 256;                       // tiles per group
 constexpr int kOffs = 1, kScatter = 2, kCount = 4;
 constexpr int kStoreX = 8;                            // the scanned stream is a result too: stored to out[3] (diagonal fusion)
@@ -2000,9 +2004,9 @@ constexpr int kStoreX = 8;                            // the scanned stream is a
 // scattered, the offsets are not stored) parks the kept elements of a tile in
 // LDS (see scan_kernel); the other forms hold the tile in registers across the
 // wait.  The LDS buffer takes half a tile; a tile that keeps more uses registers.
-template <class EX, int Mode> struct ScanParks {
+template <class EX, int Mode, int Acc> struct ScanParks {
   static constexpr bool value = (Mode & kScatter) != 0 && (Mode & kOffs) == 0 && YieldsZeroOne<EX>::value;
-  static constexpr int cap = value ? kScanTile / 2 : 1;
+  static constexpr int cap = value ? scan_tile(Acc) / 2 : 1;
 };
 
 // tiles of a scan of n elements (an empty array has one, which writes the total)
@@ -2117,15 +2121,16 @@ struct TaggedPairs {
 // Registers bound how many tiles are in flight, and tiles in flight bound
 // bandwidth, so a scanned stream of zeros and ones (a predicate) is kept as one
 // bit per element -- a single register for the 24 elements of a lane.
-template <class EX, class EV, int Mode, bool Reverse>
+template <class EX, class EV, int Mode, bool Reverse, int Acc>
 struct ScanPayload {
   using V = typename EV::R;
+  static constexpr unsigned kTileOf = (unsigned)scan_tile(Acc);
   static constexpr bool kScat = (Mode & kScatter) != 0;
   static constexpr bool kBits = YieldsZeroOne<EX>::value;
-  static_assert(kScanItems <= 32, "one bit per element in a 32-bit register");
-  int x[kBits ? 1 : kScanAcc][4];
+  static_assert(Acc * kVec <= 32, "one bit per element in a 32-bit register");
+  int x[kBits ? 1 : Acc][4];
   unsigned bits;
-  V val[kScat ? kScanAcc : 1][4];
+  V val[kScat ? Acc : 1][4];
 
   // element c of access j of the scanned stream; positions past the end of the array read 0
   __device__ __forceinline__ int flag(int j, int c) const {
@@ -2134,19 +2139,19 @@ struct ScanPayload {
   __device__ __forceinline__ void set(int j, int c, int v) {
     if (kBits) bits |= (unsigned)(v != 0) << (j * 4 + c); else x[kBits ? 0 : j][c] = v;
   }
-  // wave-striped layout: a wave owns kWave * kScanItems consecutive elements; access j
+  // wave-striped layout: a wave owns kWave * kVec * Acc consecutive elements; access j
   // of a lane covers elements base + j*256 + lane*4 .. +3 (fully coalesced).
   // A tile that lies wholly inside the array takes a path without any
   // per-lane condition, so that its 128-bit reads are issued back to back and
   // are all in flight together; the last tile (and scanr of a length that is not a
   // multiple of four) takes the guarded path.
   __device__ __forceinline__ void load(const KArgs &a, unsigned tile, unsigned n) {
-    const unsigned wbase = tile * kScanTile + wave_id() * (kWave * kScanItems);
+    const unsigned wbase = tile * kTileOf + wave_id() * (kWave * kVec * Acc);
     bits = 0u;
-    if (!Reverse && (unsigned long long)(tile + 1) * kScanTile <= n) {
+    if (!Reverse && (unsigned long long)(tile + 1) * kTileOf <= n) {
       if (kScat) {
 #pragma unroll
-        for (int j = 0; j < kScanAcc; ++j) {
+        for (int j = 0; j < Acc; ++j) {
           Vec4<V> u = EV::template eval4<EX::kNodes>(a, (int)(wbase + j * (kWave * kVec) + lane_id() * kVec));
 #pragma unroll
           for (int c = 0; c < 4; ++c) val[kScat ? j : 0][c] = u.v[c];
@@ -2154,49 +2159,62 @@ struct ScanPayload {
       }
       if (kScat && FlagOfValue<EX, EV>::value) {
 #pragma unroll
-        for (int j = 0; j < kScanAcc; ++j)
+        for (int j = 0; j < Acc; ++j)
 #pragma unroll
           for (int c = 0; c < 4; ++c) set(j, c, FlagOfValue<EX, EV>::apply(a, val[kScat ? j : 0][c]));
       } else {
-        Vec4<int> v[kScanAcc];
+        Vec4<int> v[Acc];
 #pragma unroll
-        for (int j = 0; j < kScanAcc; ++j)
+        for (int j = 0; j < Acc; ++j)
           v[j] = EX::template eval4<0>(a, (int)(wbase + j * (kWave * kVec) + lane_id() * kVec));
 #pragma unroll
-        for (int j = 0; j < kScanAcc; ++j)
+        for (int j = 0; j < Acc; ++j)
 #pragma unroll
           for (int c = 0; c < 4; ++c) set(j, c, v[j].v[c]);
       }
       return;
     }
-    if (Reverse && !kScat && (n & 3u) == 0u && (unsigned long long)(tile + 1) * kScanTile <= n) {
+    if (Reverse && !kScat && (unsigned long long)(tile + 1) * kTileOf <= n) {
       // scanr of a whole tile: the group at position i of the pass is elements n-4-i .. n-1-i
-      // taken backwards, one 128-bit read when the length is a multiple of four
-      Vec4<int> v[kScanAcc];
+      // taken backwards, one 128-bit read
+      Vec4<int> v[Acc];
 #pragma unroll
-      for (int j = 0; j < kScanAcc; ++j)
+      for (int j = 0; j < Acc; ++j)
         v[j] = EX::template eval4<0>(a, (int)(n - 4 - (wbase + j * (kWave * kVec) + lane_id() * kVec)));
 #pragma unroll
-      for (int j = 0; j < kScanAcc; ++j)
+      for (int j = 0; j < Acc; ++j)
 #pragma unroll
         for (int c = 0; c < 4; ++c) set(j, c, v[j].v[3 - c]);
       return;
     }
+    // Positions past the end are evaluated at the last element and count as zero: without a condition in front of
+    // them the reads of a lane are in flight together.
+    if (n == 0u) {
 #pragma unroll
-    for (int j = 0; j < kScanAcc; ++j) {
-      const unsigned i = wbase + j * (kWave * kVec) + lane_id() * kVec;
+      for (int j = 0; j < Acc; ++j)
+#pragma unroll
+        for (int c = 0; c < 4; ++c) { set(j, c, 0); if (kScat) val[kScat ? j : 0][c] = V(0); }
+      return;
+    }
+    int got[Acc][4];
+#pragma unroll
+    for (int j = 0; j < Acc; ++j)
 #pragma unroll
       for (int c = 0; c < 4; ++c) {
-        // scanr walks the array from its end: position i + c of the pass is element n - 1 - (i + c)
-        const int e = Reverse ? (int)(n - 1 - (i + c)) : (int)(i + c);
-        const bool in = i + c < n;
-        if (kScat) val[kScat ? j : 0][c] = in ? EV::template eval<EX::kNodes>(a, e) : V(0);
-        if (kScat && FlagOfValue<EX, EV>::value)
-          set(j, c, in ? FlagOfValue<EX, EV>::apply(a, val[kScat ? j : 0][c]) : 0);
-        else
-          set(j, c, in ? EX::template eval<0>(a, e) : 0);
+        const unsigned i = min(wbase + j * (kWave * kVec) + lane_id() * kVec + c, n - 1u);
+        // scanr walks the array from its end: position i of the pass is element n - 1 - i
+        const int e = Reverse ? (int)(n - 1u - i) : (int)i;
+        if (kScat) val[kScat ? j : 0][c] = EV::template eval<EX::kNodes>(a, e);
+        if (!(kScat && FlagOfValue<EX, EV>::value)) got[j][c] = EX::template eval<0>(a, e);
       }
-    }
+#pragma unroll
+    for (int j = 0; j < Acc; ++j)
+#pragma unroll
+      for (int c = 0; c < 4; ++c) {
+        const bool in = wbase + j * (kWave * kVec) + lane_id() * kVec + c < n;
+        const int x_here = kScat && FlagOfValue<EX, EV>::value ? FlagOfValue<EX, EV>::apply(a, val[kScat ? j : 0][c]) : got[j][c];
+        set(j, c, in ? x_here : 0);
+      }
   }
 };
 
@@ -2206,16 +2224,17 @@ template <int Mode> constexpr unsigned kScanOuts = ((Mode & kScatter) ? 1u : 0u)
 // waves per SIMD asked of the compiler: an interpreted element program (it has no nodes of its own) needs the registers
 template <class EX> struct ScanWaves { static constexpr int value = EX::kNodes == 0 ? 4 : 8; };
 
-template <class EX, class EV, int Mode, bool Reverse>
-__global__ __launch_bounds__(kScanBlock, ScanWaves<EX>::value) void scan_kernel(const Packed<kHeadN, kScanOuts<Mode>, EX, EV> packed, Control *ctl, unsigned long long *status) {
+template <class EX, class EV, int Mode, bool Reverse, int Acc>
+__global__ __launch_bounds__(kScanBlock, ScanWaves<EX>::value) void scan_kernel(const Packed<(Mode & kOffs) ? kHeadN | kHeadFlags : kHeadN, kScanOuts<Mode>, EX, EV> packed, Control *ctl, unsigned long long *status) {
   const KArgs &a = packed.open();
-  const unsigned n_tiles = scan_tiles((unsigned)a.n, kScanTile);
+  constexpr unsigned kTileOf = (unsigned)scan_tile(Acc);
+  const unsigned n_tiles = scan_tiles((unsigned)a.n, kTileOf);
   __shared__ int lds_wave[kScanWaves];
   __shared__ int lds_sum[kScanWaves];
-  using P = ScanPayload<EX, EV, Mode, Reverse>;
+  using P = ScanPayload<EX, EV, Mode, Reverse, Acc>;
   using V = typename EV::R;
-  constexpr bool kPark = ScanParks<EX, Mode>::value;
-  constexpr int kParkCap = ScanParks<EX, Mode>::cap;
+  constexpr bool kPark = ScanParks<EX, Mode, Acc>::value;
+  constexpr int kParkCap = ScanParks<EX, Mode, Acc>::cap;
   __shared__ V parked[kParkCap];
   const unsigned n = (unsigned)a.n;
   const int lane = lane_id(), wave = wave_id();
@@ -2229,10 +2248,10 @@ __global__ __launch_bounds__(kScanBlock, ScanWaves<EX>::value) void scan_kernel(
   if (Mode & kStoreX) {
     // the scanned stream is stored as well as scanned: straight from the registers it was loaded into
     int *xs = static_cast<int *>(a.out[3]);
-    const unsigned base = tile * kScanTile + wave * (kWave * kScanItems);
-    const bool whole = (unsigned long long)(tile + 1) * kScanTile <= n && (!Reverse || (n & 3u) == 0u);
+    const unsigned base = tile * kTileOf + wave * (kWave * kVec * Acc);
+    const bool whole = (unsigned long long)(tile + 1) * kTileOf <= n;
 #pragma unroll
-    for (int j = 0; j < kScanAcc; ++j) {
+    for (int j = 0; j < Acc; ++j) {
       const unsigned i = base + j * (kWave * kVec) + lane * kVec;
       const Vec4<int> v = {{cur.flag(j, 0), cur.flag(j, 1), cur.flag(j, 2), cur.flag(j, 3)}};
       if (whole) {
@@ -2244,20 +2263,20 @@ __global__ __launch_bounds__(kScanBlock, ScanWaves<EX>::value) void scan_kernel(
     }
   }
   {
-    const unsigned wbase = tile * kScanTile + wave * (kWave * kScanItems);
-    int s[kScanAcc];
+    const unsigned wbase = tile * kTileOf + wave * (kWave * kVec * Acc);
+    int s[Acc];
 #pragma unroll
-    for (int j = 0; j < kScanAcc; ++j) {
+    for (int j = 0; j < Acc; ++j) {
       int f[4];
 #pragma unroll
       for (int c = 0; c < 4; ++c) f[c] = cur.flag(j, c);
       s[j] = (f[0] + f[1]) + (f[2] + f[3]);
     }
     // exclusive prefix of each access inside the wave
-    int excl[kScanAcc];
+    int excl[Acc];
     int carry = 0;
 #pragma unroll
-    for (int j = 0; j < kScanAcc; ++j) {
+    for (int j = 0; j < Acc; ++j) {
       int inc = wave_scan_inclusive<AddI32>(s[j]);
       excl[j] = carry + inc - s[j];
       carry += __builtin_amdgcn_readlane(inc, 63);
@@ -2286,7 +2305,7 @@ __global__ __launch_bounds__(kScanBlock, ScanWaves<EX>::value) void scan_kernel(
       // a tile's loading phase, which waits for nothing.  Which wave stays rotates
       // with the tile, so that the waiting waves spread over the four SIMDs.
 #pragma unroll
-      for (int j = 0; j < kScanAcc; ++j) {
+      for (int j = 0; j < Acc; ++j) {
         int o = wave_excl + excl[j];
 #pragma unroll
         for (int c = 0; c < 4; ++c) {
@@ -2361,34 +2380,36 @@ __global__ __launch_bounds__(kScanBlock, ScanWaves<EX>::value) void scan_kernel(
       store_agent(&ctl->epoch, epoch + 1u);
     }
 
+    with_keep(!(Mode & kOffs) || a.keeps(1), [&](auto keep) {
 #pragma unroll
-    for (int j = 0; j < kScanAcc; ++j) {
-      unsigned i = wbase + j * (kWave * kVec) + lane * kVec;
-      int f[4];
+      for (int j = 0; j < Acc; ++j) {
+        unsigned i = wbase + j * (kWave * kVec) + lane * kVec;
+        int f[4];
 #pragma unroll
-      for (int c = 0; c < 4; ++c) f[c] = cur.flag(j, c);
-      int o[4];
-      o[0] = tile_excl + wave_excl + excl[j];
-      o[1] = o[0] + f[0];
-      o[2] = o[1] + f[1];
-      o[3] = o[2] + f[2];
-      if (Mode & kOffs) {
-        int *offs = static_cast<int *>(a.out[1]);
-        if (!Reverse && i + 3 < n) {
-          store4<true>(offs + i, Vec4<int>{{o[0], o[1], o[2], o[3]}});
-        } else if (Reverse && (n & 3u) == 0u && i + 3 < n) {
-          store4<true>(offs + (n - 4 - i), Vec4<int>{{o[3], o[2], o[1], o[0]}});
-        } else {
+        for (int c = 0; c < 4; ++c) f[c] = cur.flag(j, c);
+        int o[4];
+        o[0] = tile_excl + wave_excl + excl[j];
+        o[1] = o[0] + f[0];
+        o[2] = o[1] + f[1];
+        o[3] = o[2] + f[2];
+        if (Mode & kOffs) {
+          int *offs = static_cast<int *>(a.out[1]);
+          if (!Reverse && i + 3 < n) {
+            store4<decltype(keep)::value>(offs + i, Vec4<int>{{o[0], o[1], o[2], o[3]}});
+          } else if (Reverse && i + 3 < n) {
+            store4<decltype(keep)::value>(offs + (n - 4 - i), Vec4<int>{{o[3], o[2], o[1], o[0]}});
+          } else {
 #pragma unroll
-          for (int c = 0; c < 4; ++c) if (i + c < n) offs[Reverse ? n - 1 - (i + c) : i + c] = o[c];
+            for (int c = 0; c < 4; ++c) if (i + c < n) offs[Reverse ? n - 1 - (i + c) : i + c] = o[c];
+          }
+        }
+        if (Mode & kScatter) {
+          V *dest = static_cast<V *>(a.out[0]);
+#pragma unroll
+          for (int c = 0; c < 4; ++c) if (f[c] != 0) dest[o[c]] = cur.val[P::kScat ? j : 0][c];
         }
       }
-      if (Mode & kScatter) {
-        V *dest = static_cast<V *>(a.out[0]);
-#pragma unroll
-        for (int c = 0; c < 4; ++c) if (f[c] != 0) dest[o[c]] = cur.val[P::kScat ? j : 0][c];
-      }
-    }
+    });
   }
 }
 
@@ -2400,9 +2421,10 @@ __global__ __launch_bounds__(kScanBlock, ScanWaves<EX>::value) void scan_kernel(
 // a tile, the tiles of a group, the groups), so a launch gives the same bits every
 // time; the order is not the sequential one, so a prefix differs from the
 // sequential fp32 sum by rounding, within the bound of any summation order.
-constexpr int kScanFItems = 16;                       // per lane: four 128-bit accesses
-constexpr int kScanFAcc = kScanFItems / kVec;
-constexpr int kScanFTile = kScanBlock * kScanFItems;  // 8192 elements
+// As above, with a step in between: four accesses up to kScanFLong elements (4 x 10^6: 7.4 us against 8.8 with six,
+// 8 x 10^6: 12.3 against 11.7, 6.7 x 10^7: 98.6 against 94.1).
+constexpr int kScanFAcc = 4;
+constexpr unsigned kScanFLong = 6u << 20;
 
 __device__ __forceinline__ float scan_block_sum_f32(float v, float *lds) {
   float w = wave_reduce<AddF32>(v);
@@ -2415,10 +2437,11 @@ __device__ __forceinline__ float scan_block_sum_f32(float v, float *lds) {
   return r;
 }
 
-template <class EX, bool Reverse, bool StoreX = false>
-__global__ __launch_bounds__(kScanBlock, ScanWaves<EX>::value) void scan_f32_kernel(const Packed<kHeadN, StoreX ? 10u : 2u, EX> packed, Control *ctl, unsigned long long *status) {
+template <class EX, bool Reverse, bool StoreX = false, int Acc = kScanFAcc>
+__global__ __launch_bounds__(kScanBlock, ScanWaves<EX>::value) void scan_f32_kernel(const Packed<kHeadN | kHeadFlags, StoreX ? 10u : 2u, EX> packed, Control *ctl, unsigned long long *status) {
   const KArgs &a = packed.open();
-  const unsigned n_tiles = scan_tiles((unsigned)a.n, kScanFTile);
+  constexpr unsigned kTileOf = (unsigned)scan_tile(Acc);
+  const unsigned n_tiles = scan_tiles((unsigned)a.n, kTileOf);
   static_assert(std::is_same<typename EX::R, float>::value, "fp32 stream");
   __shared__ float lds_wave[kScanWaves];
   __shared__ float lds_sum[kScanWaves];
@@ -2429,15 +2452,15 @@ __global__ __launch_bounds__(kScanBlock, ScanWaves<EX>::value) void scan_f32_ker
   unsigned long long *group_word = status + ((n_tiles + 15) / 16) * 16;
   float *offs = static_cast<float *>(a.out[1]);
   const unsigned tile = blockIdx.x;
-  const unsigned wbase = tile * kScanFTile + wave * (kWave * kScanFItems);
+  const unsigned wbase = tile * kTileOf + wave * (kWave * kVec * Acc);
   // position i of the pass is element i, for scanr element n - 1 - i; positions past the end read 0
   // a whole tile is read and written in 128-bit groups; for scanr the group at position i is
-  // elements n-4-i .. n-1-i taken backwards, which is a group only if n is a multiple of four
-  const bool whole = (size_t)(tile + 1) * kScanFTile <= n && (!Reverse || (n & 3u) == 0u);
-  float x[kScanFAcc][kVec];
+  // elements n-4-i .. n-1-i taken backwards
+  const bool whole = (size_t)(tile + 1) * kTileOf <= n;
+  float x[Acc][kVec];
   if (whole) {
 #pragma unroll
-    for (int j = 0; j < kScanFAcc; ++j) {
+    for (int j = 0; j < Acc; ++j) {
       const unsigned i = wbase + j * (kWave * kVec) + lane * kVec;
       const Vec4<float> v = EX::template eval4<0>(a, (int)(Reverse ? n - 4 - i : i));
 #pragma unroll
@@ -2445,18 +2468,24 @@ __global__ __launch_bounds__(kScanBlock, ScanWaves<EX>::value) void scan_f32_ker
     }
   } else {
 #pragma unroll
-    for (int j = 0; j < kScanFAcc; ++j)
+    for (int j = 0; j < Acc; ++j)
 #pragma unroll
       for (int c = 0; c < kVec; ++c) {
+        // past the end: evaluated at the last element (no condition in front of the reads), then nothing
         const unsigned i = wbase + j * (kWave * kVec) + lane * kVec + c;
-        x[j][c] = i < n ? EX::template eval<0>(a, (int)(Reverse ? n - 1 - i : i)) : 0.0f;
+        x[j][c] = 0.0f;
+        if (n != 0u) x[j][c] = EX::template eval<0>(a, (int)(Reverse ? n - 1 - min(i, n - 1u) : min(i, n - 1u)));
       }
+#pragma unroll
+    for (int j = 0; j < Acc; ++j)
+#pragma unroll
+      for (int c = 0; c < kVec; ++c) if (wbase + j * (kWave * kVec) + lane * kVec + c >= n) x[j][c] = 0.0f;
   }
   if (StoreX) {
     // the scanned array is a result as well: stored from the registers it was loaded into
     float *xs = static_cast<float *>(a.out[3]);
 #pragma unroll
-    for (int j = 0; j < kScanFAcc; ++j) {
+    for (int j = 0; j < Acc; ++j) {
       const unsigned i = wbase + j * (kWave * kVec) + lane * kVec;
       if (whole) {
         if (Reverse)
@@ -2471,10 +2500,10 @@ __global__ __launch_bounds__(kScanBlock, ScanWaves<EX>::value) void scan_f32_ker
     }
   }
   // exclusive prefix of each access inside the wave
-  float excl[kScanFAcc];
+  float excl[Acc];
   float carry = 0.0f;
 #pragma unroll
-  for (int j = 0; j < kScanFAcc; ++j) {
+  for (int j = 0; j < Acc; ++j) {
     const float s = (x[j][0] + x[j][1]) + (x[j][2] + x[j][3]);
     const float inc = wave_scan_inclusive<AddF32>(s);
     excl[j] = carry + lane_prev(0.0f, inc);
@@ -2506,25 +2535,27 @@ __global__ __launch_bounds__(kScanBlock, ScanWaves<EX>::value) void scan_f32_ker
   const float sum_before = sum_group + sum_tagged_words<kScanBlock, float>(group_word, group, tag, ctl);
   const float tile_excl = scan_block_sum_f32(sum_before, lds_sum);
   if (tile == n_tiles - 1 && threadIdx.x == 0) store_agent(&ctl->epoch, epoch + 1u);
+  with_keep(a.keeps(1), [&](auto keep) {
 #pragma unroll
-  for (int j = 0; j < kScanFAcc; ++j) {
-    const unsigned i = wbase + j * (kWave * kVec) + lane * kVec;
-    Vec4<float> o;
-    o.v[0] = tile_excl + (wave_excl + excl[j]);
-    o.v[1] = o.v[0] + x[j][0];
-    o.v[2] = o.v[1] + x[j][1];
-    o.v[3] = o.v[2] + x[j][2];
-    if (whole) {
-      if (Reverse)
-        store4<true>(offs + (n - 4 - i), Vec4<float>{{o.v[3], o.v[2], o.v[1], o.v[0]}});
-      else
-        store4<true>(offs + i, o);
-    } else {
+    for (int j = 0; j < Acc; ++j) {
+      const unsigned i = wbase + j * (kWave * kVec) + lane * kVec;
+      Vec4<float> o;
+      o.v[0] = tile_excl + (wave_excl + excl[j]);
+      o.v[1] = o.v[0] + x[j][0];
+      o.v[2] = o.v[1] + x[j][1];
+      o.v[3] = o.v[2] + x[j][2];
+      if (whole) {
+        if (Reverse)
+          store4<decltype(keep)::value>(offs + (n - 4 - i), Vec4<float>{{o.v[3], o.v[2], o.v[1], o.v[0]}});
+        else
+          store4<decltype(keep)::value>(offs + i, o);
+      } else {
 #pragma unroll
-      for (int c = 0; c < kVec; ++c)
-        if (i + c < n) offs[Reverse ? n - 1 - (i + c) : i + c] = o.v[c];
+        for (int c = 0; c < kVec; ++c)
+          if (i + c < n) offs[Reverse ? n - 1 - (i + c) : i + c] = o.v[c];
+      }
     }
-  }
+  });
 }
 
 // ------------------------------------------------------------------ row scans

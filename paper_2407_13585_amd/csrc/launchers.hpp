@@ -305,17 +305,30 @@ hipError_t launch_foldseg_sorted(const KArgs &a, const LaunchCtx &c) {
                   static_cast<const T *>(head), static_cast<const T *>(tail), p.tiles);
 }
 
-template <class EX, class EV, int Mode, bool Reverse = false> hipError_t launch_scan(const KArgs &a, const LaunchCtx &c) {
-  const unsigned tiles = scan_tiles((unsigned)a.n, kScanTile);
+template <class EX, class EV, int Mode, bool Reverse, int Acc> hipError_t launch_scan_of(const KArgs &a, const LaunchCtx &c) {
+  const unsigned tiles = scan_tiles((unsigned)a.n, (unsigned)scan_tile(Acc));
   if (scan_status_words(tiles) > c.max_tiles) return hipErrorInvalidValue;
-  return launch_threads(&scan_kernel<EX, EV, Mode, Reverse>, tiles, c, kScanBlock, a, c.ctl, c.status);
+  return launch_threads(&scan_kernel<EX, EV, Mode, Reverse, Acc>, tiles, c, kScanBlock, a, c.ctl, c.status);
+}
+template <class EX, class EV, int Mode, bool Reverse = false> hipError_t launch_scan(const KArgs &a, const LaunchCtx &c) {
+  if constexpr (EX::kNodes != 0) {                     // interpreted element programs: one kernel each, the compiler has enough to do
+    if ((unsigned)a.n < (ScanParks<EX, Mode, kScanAcc>::value ? kScanShortBelow<true> : kScanShortBelow<false>))
+      return launch_scan_of<EX, EV, Mode, Reverse, kScanShortAcc>(a, c);
+  }
+  return launch_scan_of<EX, EV, Mode, Reverse, kScanAcc>(a, c);
+}
+template <class EX, bool Reverse, bool StoreX, int Acc> hipError_t launch_scan_f32_of(const KArgs &a, const LaunchCtx &c) {
+  const unsigned tiles = scan_tiles((unsigned)a.n, (unsigned)scan_tile(Acc));
+  if (scan_status_words(tiles) > c.max_tiles) return hipErrorInvalidValue;
+  return launch_threads(&scan_f32_kernel<EX, Reverse, StoreX, Acc>, tiles, c, kScanBlock, a, c.ctl, c.status);
+}
+template <class EX, bool Reverse = false, bool StoreX = false> hipError_t launch_scan_f32(const KArgs &a, const LaunchCtx &c) {
+  // (interpreted element programs too: the tile fixes the order of the sums, and with it the bits of the result)
+  if ((unsigned)a.n < kScanShortBelow<false>) return launch_scan_f32_of<EX, Reverse, StoreX, kScanShortAcc>(a, c);
+  if ((unsigned)a.n >= kScanFLong) return launch_scan_f32_of<EX, Reverse, StoreX, kScanAcc>(a, c);
+  return launch_scan_f32_of<EX, Reverse, StoreX, kScanFAcc>(a, c);
 }
 // lanes per row by row length, as for the row folds
-template <class EX, bool Reverse = false, bool StoreX = false> hipError_t launch_scan_f32(const KArgs &a, const LaunchCtx &c) {
-  const unsigned tiles = scan_tiles((unsigned)a.n, kScanFTile);
-  if (scan_status_words(tiles) > c.max_tiles) return hipErrorInvalidValue;
-  return launch_threads(&scan_f32_kernel<EX, Reverse, StoreX>, tiles, c, kScanBlock, a, c.ctl, c.status);
-}
 template <class E, bool Reverse, bool StoreX = false> hipError_t launch_rowscan(const KArgs &a, const LaunchCtx &c) {
   if (a.aux == 0 || a.w == 0) return hipSuccess;
   if (a.w <= 64)

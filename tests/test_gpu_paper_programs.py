@@ -221,6 +221,36 @@ def test_scans_of_fp32():
         assert all(k.startswith("rowscan") for k in prog.kernels())
 
 
+@pytest.mark.parametrize("n", [0, 4095, 4096, 4097, 256 * 4096 - 1, 256 * 4096 + 4099, (3 << 19) - 3, 3 << 19, (3 << 19) + 5,
+                               (1 << 22) - 1, (1 << 22) + 2, (6 << 20) - 1, (6 << 20) + 3])
+def test_scans_where_the_tile_changes(n):
+    # tiles of 4096 elements in short arrays, 8192 (fp32) and 12288 above: lengths around the tiles, around 256 of
+    # them, and around the lengths where the tile changes; both directions, also of odd lengths; integers
+    # exact, the compaction (whose tile changes at 2^22) as well
+    rng = np.random.default_rng(n)
+    g = Graph()
+    g.add("x", "input", "f32", (n,))
+    g.add("k", "input", "i32", (n,))
+    g.add("d", "input", "i32", (n,))
+    for name, kind, arg in (("fl", "scanl", "x"), ("fr", "scanr", "x"), ("il", "scanl", "k"), ("ir", "scanr", "k")):
+        g.add(name, kind, "f32" if arg == "x" else "i32", (n,), fn="add", args=(arg,), output=True)
+    g.add("flags", "map", "i32", (n,), fn="mod_eq", iparam=(3, 1), args=("k",))
+    g.add("offs", "scanl", "i32", (n,), fn="add", args=("flags",))
+    g.add("count", "fold", "i32", (1,), fn="add", args=("flags",), output=True)
+    g.add("out", "scatter", "i32", (n,), fn="overwrite", args=("d", "offs", "k", "flags"), output=True)
+    ins = {"x": rng.standard_normal(n).astype(F32), "k": rng.integers(0, 100, n).astype(np.int32), "d": np.full(n, -7, np.int32)}
+    env = evaluate(g, ins)
+    prog = device_program(g, ins, fc().fc_plan(g, "bytes", executable=True))
+    assert any("+scatter" in k and "+count" in k for k in prog.kernels())
+    prog.run()
+    for name in ("il", "ir", "count", "out"):
+        P.assert_bit_exact(prog.fetch(name), env[name], f"n={n} {name}")
+    for name, rev in (("fl", False), ("fr", True)):
+        got, tol = prog.fetch(name).astype(np.float64), 1e-5 * prefix_scale(ins["x"], rev) + 1e-30
+        assert np.all(np.abs(got - env[name].astype(np.float64)) <= tol), (n, name)
+    assert prog.control_words()[1] == 0
+
+
 def test_programs_whose_optimum_has_no_kernel_run_with_an_executable_plan():
     # the cheapest legal clustering of these programs contains a cluster the library has no
     # kernel for; planned with FC_PLAN_EXECUTABLE they run fused as far as the kernels go
