@@ -152,6 +152,12 @@ template <class F, int FSlot, bool WithMax, int G0, int GStride>
 bool stencil5_accept(const KArgs &a) {
   static const int want[4][2] = {{-1, 0}, {1, 0}, {0, -1}, {0, 1}};
   if (a.h < 1 || a.w < kVec || a.w > 0x7fffffff - 4 * kStripCols) return false;     // columns past the row's end are counted in int
+  // A narrow grid leaves most lanes of a strip idle, and the generic element program, which takes points in storage
+  // order, is faster there: 4.2 x 10^6 points in rows of 4 take 242 us here and 20 there, of 17 66 and 21, of 33 41 and 21,
+  // of 66 (3.9 columns of the strip for one of the grid) 21 and 21, of 129 13 and 20.  Unless the units are few enough to run all at
+  // once: 2.6 x 10^5 points in rows of 33 (1986 units) take 6.7 us here and 8.4 there, of 17 (3855) 8.4 and 8.2.
+  const long long strips = (a.w + kStripCols - 1) / kStripCols, units = strips * ((a.h + kBandRows - 1) / kBandRows);
+  if (units > 2048 && strips * kStripCols * 2 > 7LL * a.w) return false;
   for (int k = 0; k < 4; ++k) {
     const Slot &s = a.p[G0 + k * GStride];
     if (s.i[0] != want[k][0] || s.i[1] != want[k][1] || s.ext[0] != a.h || s.ext[1] != a.w) return false;

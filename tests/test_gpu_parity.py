@@ -419,7 +419,7 @@ def test_stencil_shapes(hw):
 
 
 @pytest.mark.parametrize("hw", [(4, 255), (5, 257), (8, 258), (9, 259), (3, 511), (13, 513), (1, 1030), (6, 5), (2, 6),
-                                (132003, 5)])
+                                (132003, 74)])
 def test_stencil_edges_of_strips_and_bands(hw):
     # rows that start on any 4-byte boundary, strips that reach one to three columns past a 128-bit group,
     # bands that end inside a unit; the tallest has more units than a launch has waves
@@ -427,6 +427,16 @@ def test_stencil_edges_of_strips_and_bands(hw):
     g, part = plan(w.graph, True)
     assert "rows-in-registers" in device_program(g, w.inputs, part).kernels()[0]
     run_all_modes(5, w)
+
+
+@pytest.mark.parametrize("h,w,strips", [(8192, 17, True), (8193, 17, False), (8193, 73, False), (8193, 74, True),
+                                        (8193, 4, False)])
+def test_stencil_of_narrow_grids(h, w, strips):
+    # many rows of few columns run the generic element program, 2048 units of four rows or fewer the strips
+    x = C.stencil_max(h=h, w=w, seed=700 + h + w)
+    g, part = plan(x.graph, True)
+    assert ("rows-in-registers" in device_program(g, x.inputs, part).kernels()[0]) == strips
+    run_all_modes(5, x)
 
 
 def test_stencil_constant_grid_borders():
