@@ -89,8 +89,12 @@ template <class Op, class E> hipError_t launch_foldseg(const KArgs &a, const Lau
   // Lanes by mean length, measured at 50000 and 300001 rows: as many as leave a lane two to four
   // elements (3 elements a row: 9.4 us with 4 lanes, 11.6 with 8, 16.9 with 16; 16 elements: 27.1, 25.6,
   // 26.2; 64 elements: 22.5, 19.4, 17.7; 500 elements: 26.2, 27.6, 21.7, with a wave 18.3).
-  if (mean < 12.0) return go(&foldseg_kernel<Op, E, 4, U>, 4);
-  if (mean < 32.0) return go(&foldseg_kernel<Op, E, 8, U>, 8);
+  // An interpreted program takes one element a lane and step, so a row far above the mean lasts in proportion to
+  // the lanes that are missing: it keeps sixteen.
+  if constexpr (U > 1) {
+    if (mean < 12.0) return go(&foldseg_kernel<Op, E, 4, U>, 4);
+    if (mean < 32.0) return go(&foldseg_kernel<Op, E, 8, U>, 8);
+  }
   if (mean < 256.0) return go(&foldseg_kernel<Op, E, 16, U>, 16);
   return go(&foldseg_kernel<Op, E, kWave, U>, kWave);
 }

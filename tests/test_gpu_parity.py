@@ -234,6 +234,15 @@ def test_spmv_lanes_by_row_length(mean_len):
     run_all_modes(3, C.spmv(lengths=lengths, seed=900 + int(mean_len), ncols=3000))
 
 
+@pytest.mark.parametrize("mean_len,own", [(3, 128), (20, 256), (100, 512)])
+def test_spmv_rows_shared_by_the_wave(mean_len, own):
+    # rows longer than `own` are taken by the whole wave from there: at that length, one past it, around the 256
+    # elements the wave takes per step, several in one wave, the first and the last row
+    lengths = np.random.default_rng(mean_len).poisson(mean_len, size=1003)
+    lengths[[0, 5, 6, 7, 8, 400, 401, 1002]] = [own + 1, own, own + 2, own + 255, own + 256, own + 257, 2500, 700]
+    run_all_modes(3, C.spmv(lengths=lengths, seed=950 + mean_len, ncols=3000))
+
+
 def test_spmv_skewed_rows():
     rng = np.random.default_rng(77)
     lengths = np.minimum(rng.zipf(1.5, size=5000), 20000).astype(np.int64)
