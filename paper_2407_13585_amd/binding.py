@@ -368,6 +368,22 @@ def fc_run_unfused(graph, buffers: Dict[str, object], scratch, stream: int = 0) 
     _check(lib().fc_run_unfused(g.ref(), _buffers(g, buffers), sp, sb, stream or None))
 
 
+class _BoundHandle:
+    """The one owner of a program bound by fc_bind: whatever shares it shares the program, and the last
+    one to go releases it (fc_unbind).  It cannot be copied itself."""
+
+    __slots__ = ("value", "_lib")
+
+    def __init__(self, library, value: int):
+        self.value, self._lib = value, library
+
+    def __reduce_ex__(self, protocol):
+        raise TypeError("a bound program cannot be copied or pickled")
+
+    def __del__(self):
+        self._lib.fc_unbind(self.value)
+
+
 class BoundRun:
     """fc_run_fused / fc_run_unfused with the arguments marshalled once: for callers that run
     one program on the same buffers many times.  partition None = fc_run_unfused."""
@@ -386,12 +402,12 @@ class BoundRun:
         handle = C.c_void_p()
         rc = self._lib.fc_bind(self._g.ref(), C.byref(self._cp) if self._cp is not None else None, self._bufs,
                                self._sp, self._sb, C.byref(handle))
-        self._handle = handle.value if rc == 0 else None
+        self._handle = _BoundHandle(self._lib, handle.value) if rc == 0 else None    # a copy of this object shares it
         self._run = self._lib.fc_run_bound
 
     def __call__(self, stream: int = 0) -> None:
         if self._handle is not None:
-            rc = self._run(self._handle, stream)
+            rc = self._run(self._handle.value, stream)
         elif self._cp is None:
             rc = self._lib.fc_run_unfused(self._g.ref(), self._bufs, self._sp, self._sb, stream or None)
         else:
@@ -399,11 +415,6 @@ class BoundRun:
                                         stream or None)
         if rc != 0:
             _check(rc)
-
-    def __del__(self):
-        handle, self._handle = getattr(self, "_handle", None), None
-        if handle is not None:
-            self._lib.fc_unbind(handle)
 
 
 def fc_check(scratch, stream: int = 0) -> None:

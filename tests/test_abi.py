@@ -116,6 +116,34 @@ def test_a_bound_program_reports_the_errors_of_a_run_when_it_is_called():
     expect("FC_E_SCRATCH", B.BoundRun(g, None, bufs, (0x10000000, B.FC_SCRATCH_CONTROL_BYTES)))
 
 
+def test_a_copy_of_a_bound_program_shares_it(monkeypatch):
+    # fc_unbind runs once, when the last of the objects that share the program has gone (the fake buffers are
+    # never touched: nothing is launched)
+    import copy
+    import gc
+    L = B.lib()
+    unbind, released = L.fc_unbind, []
+
+    def record(handle):
+        released.append(handle)
+        return unbind(handle) if released.count(handle) == 1 else 0      # a second release would end the process
+
+    monkeypatch.setattr(L, "fc_unbind", record)
+    w = build(2, small=True)
+    fake = (0x10000000, 1 << 30)
+    bufs = {n.name: fake for n in w.graph.nodes if n.kind == "input" or n.output}
+    first = B.BoundRun(w.graph, fc.fc_plan(w.graph, "bytes"), bufs, fake)
+    second = copy.copy(first)
+    del first
+    gc.collect()
+    after_first = len(released)
+    del second
+    gc.collect()
+    assert (after_first, len(released)) == (0, 1)
+    with pytest.raises(TypeError):
+        copy.copy(B.BoundRun(w.graph, fc.fc_plan(w.graph, "bytes"), bufs, fake)._handle)
+
+
 def test_scatter_that_reads_its_destination_is_refused():
     # the destination is updated in place; a scatter that took its values (or indices, or flags)
     # from the same array would read what it is overwriting
