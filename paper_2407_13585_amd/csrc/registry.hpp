@@ -24,6 +24,7 @@ struct RecordedLaunch {
   dim3 grid, block;
   std::shared_ptr<void> values;   // the argument values ...
   std::vector<void *> args;       // ... and where each of them lies
+  std::string what;               // signature of the cluster, for the message of a launch that fails
   void *to = nullptr;
   const void *from = nullptr;
   size_t bytes = 0;

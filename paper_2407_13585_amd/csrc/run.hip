@@ -436,6 +436,15 @@ int prepare_run(PreparedRun &r, std::string &err) {
   return FC_OK;
 }
 
+static std::string launch_error(const std::string &sig, hipError_t e) {
+  int count = -1, dev = -1;
+  hipError_t e2 = hipGetDeviceCount(&count);
+  hipError_t e3 = hipGetDevice(&dev);
+  return std::string("launch of ") + sig + ": " + hipGetErrorString(e) + " (devices visible to the library: " +
+         std::to_string(count) + ", current " + std::to_string(dev) + ", status " + std::to_string((int)e2) + "/" +
+         std::to_string((int)e3) + ")";
+}
+
 int run_prepared(const PreparedRun &r, const fc_buffer *bufs, void *scratch, size_t scratch_bytes, hipStream_t stream,
                  std::string &err, std::vector<RecordedLaunch> *record) {
   const Model &m = r.model;
@@ -514,16 +523,10 @@ int run_prepared(const PreparedRun &r, const fc_buffer *bufs, void *scratch, siz
       if (workspace_at + need > scratch_bytes) { err = "scratch too small for the workspace of " + cl.sig; return FC_E_SCRATCH; }
       ctx.workspace = static_cast<char *>(scratch) + workspace_at;
     }
+    const size_t recorded = record ? record->size() : 0;
     hipError_t e = cl.instance->launch(args, ctx);
-    if (e != hipSuccess) {
-      int count = -1, dev = -1;
-      hipError_t e2 = hipGetDeviceCount(&count);
-      hipError_t e3 = hipGetDevice(&dev);
-      err = std::string("launch of ") + cl.sig + ": " + hipGetErrorString(e) + " (devices visible to the library: " +
-            std::to_string(count) + ", current " + std::to_string(dev) + ", status " + std::to_string((int)e2) + "/" +
-            std::to_string((int)e3) + ")";
-      return FC_E_HIP;
-    }
+    if (e != hipSuccess) { err = launch_error(cl.sig, e); return FC_E_HIP; }
+    for (size_t k = recorded; record && k < record->size(); ++k) (*record)[k].what = cl.sig;
   }
   return FC_OK;
 }
@@ -532,7 +535,7 @@ int issue_recorded(const std::vector<RecordedLaunch> &launches, hipStream_t stre
   for (const RecordedLaunch &l : launches) {
     const hipError_t e = l.kernel ? hipLaunchKernel(l.kernel, l.grid, l.block, const_cast<void **>(l.args.data()), 0, stream)
                                   : hipMemcpyAsync(l.to, l.from, l.bytes, hipMemcpyDeviceToDevice, stream);
-    if (e != hipSuccess) { err = hipGetErrorString(e); return FC_E_HIP; }
+    if (e != hipSuccess) { err = l.kernel ? launch_error(l.what, e) : hipGetErrorString(e); return FC_E_HIP; }
   }
   return FC_OK;
 }

@@ -116,6 +116,25 @@ def test_a_bound_program_reports_the_errors_of_a_run_when_it_is_called():
     expect("FC_E_SCRATCH", B.BoundRun(g, None, bufs, (0x10000000, B.FC_SCRATCH_CONTROL_BYTES)))
 
 
+def test_a_bound_program_names_the_launch_that_failed():
+    # without a device every launch fails on the host; the message is the same on both ways to it
+    import torch
+    if torch.cuda.device_count() != 0:
+        pytest.skip("the made-up buffers are for a machine on which nothing can be launched")
+    fake = (0x10000000, 1 << 30)
+    for cfg in (1, 2, 3, 4, 5):
+        w = build(cfg, small=True)
+        bufs = {n.name: fake for n in w.graph.nodes if n.kind == "input" or n.output}
+        part = fc.fc_plan(w.graph, "bytes")
+        said = []
+        for call in (lambda: fc.fc_run_fused(w.graph, part, bufs, fake), B.BoundRun(w.graph, part, bufs, fake)):
+            with pytest.raises(fc.FcError) as e:
+                call()
+            assert e.value.name == "FC_E_HIP"
+            said.append(str(e.value))
+        assert said[0] == said[1] and "launch of " in said[0]
+
+
 def test_a_copy_of_a_bound_program_shares_it(monkeypatch):
     # fc_unbind runs once, when the last of the objects that share the program has gone (the fake buffers are
     # never touched: nothing is launched)
@@ -132,6 +151,8 @@ def test_a_copy_of_a_bound_program_shares_it(monkeypatch):
     w = build(2, small=True)
     fake = (0x10000000, 1 << 30)
     bufs = {n.name: fake for n in w.graph.nodes if n.kind == "input" or n.output}
+    gc.collect()                                       # what earlier tests left behind
+    released.clear()
     first = B.BoundRun(w.graph, fc.fc_plan(w.graph, "bytes"), bufs, fake)
     second = copy.copy(first)
     del first
