@@ -113,8 +113,11 @@ constexpr unsigned kSinglePass = 1u;
 constexpr unsigned kKeepOut = 1u << 8;
 
 template <class T> struct Vec4 { T v[4]; };
-// four elements in memory, at any 4-byte boundary: one 128-bit access
-template <class T> using Quad128 = T __attribute__((ext_vector_type(4), aligned(4)));
+// Four elements in memory, at any 4-byte boundary: one 128-bit access.  A typedef: the compiler drops `aligned`
+// from an alias declaration, and the type would promise 16 bytes.
+template <class T> struct Quad128Of { typedef T type __attribute__((ext_vector_type(4), aligned(4))); };
+template <class T> using Quad128 = typename Quad128Of<T>::type;
+static_assert(alignof(Quad128<float>) == 4 && alignof(Quad128<int>) == 4 && alignof(Quad128<unsigned>) == 4, "any 4-byte boundary");
 
 template <class T> struct DtypeName;
 template <> struct DtypeName<float> { static const char *s() { return "f32"; } };

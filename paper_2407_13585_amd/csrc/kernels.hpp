@@ -422,9 +422,9 @@ __device__ __forceinline__ unsigned interp_identity(int op) {
 // What element program `root` reads at the elements' own positions, read ahead.
 template <int G> struct InterpAhead {
   static constexpr int V = G ? G * kVec : 1;
+  using Group = Quad128<unsigned>;                     // a scan from the right reads groups at n - 4 - i, n of any length
   unsigned v[kInterpDirect][V];
   template <bool Stream> __device__ __forceinline__ void read(const KArgs &a, int root, unsigned first, unsigned apart) {
-    using Raw = unsigned __attribute__((ext_vector_type(4)));
 #pragma unroll
     for (int k = 0; k < kInterpDirect; ++k)
       if (k < a.n_direct[root]) {
@@ -432,8 +432,8 @@ template <int G> struct InterpAhead {
         if (G == 0) v[k][0] = p[0];
 #pragma unroll
         for (int g = 0; g < G; ++g) {
-          const Raw *q = reinterpret_cast<const Raw *>(p + g * apart);
-          const Raw x = Stream ? __builtin_nontemporal_load(q) : *q;
+          const Group *q = reinterpret_cast<const Group *>(p + g * apart);
+          const Group x = Stream ? __builtin_nontemporal_load(q) : *q;
 #pragma unroll
           for (int c = 0; c < kVec; ++c) v[k][g * kVec + c] = x[c];
         }
@@ -679,7 +679,7 @@ struct Interp {
     interp_run<0, kInterpDepth, kInterpGathers, LdsThreads>(a, a.root[K], (unsigned)i, 0u, ahead, none, r);
     return from_bits<T>((int)r[0]);
   }
-  // i is a multiple of four (the callers read 128-bit groups)
+  // i may be any position, as for the compiled element programs
   template <int Base> static __device__ __forceinline__ Vec4<T> eval4(const KArgs &a, int i) {
     unsigned r[kVec] = {0u, 0u, 0u, 0u}, none[kInterpFolds] = {0u, 0u};
     InterpAhead<1> ahead;
@@ -2142,7 +2142,7 @@ struct TaggedPairs {
 // What a lane holds of one tile between loading it and writing its results.
 // Registers bound how many tiles are in flight, and tiles in flight bound
 // bandwidth, so a scanned stream of zeros and ones (a predicate) is kept as one
-// bit per element -- a single register for the 24 elements of a lane.
+// bit per element -- a single register for the 24 (or 8) elements of a lane.
 template <class EX, class EV, int Mode, bool Reverse, int Acc>
 struct ScanPayload {
   using V = typename EV::R;
@@ -2165,8 +2165,8 @@ struct ScanPayload {
   // of a lane covers elements base + j*256 + lane*4 .. +3 (fully coalesced).
   // A tile that lies wholly inside the array takes a path without any
   // per-lane condition, so that its 128-bit reads are issued back to back and
-  // are all in flight together; the last tile (and scanr of a length that is not a
-  // multiple of four) takes the guarded path.
+  // are all in flight together (scanr reads groups that start at any element); the last
+  // tile, and scanr with a scatter, take the guarded path.
   __device__ __forceinline__ void load(const KArgs &a, unsigned tile, unsigned n) {
     const unsigned wbase = tile * kTileOf + wave_id() * (kWave * kVec * Acc);
     bits = 0u;

@@ -42,7 +42,7 @@ struct Quad { float x, y, z, w; };
 // here depends on the loaded value, so the row reads of a step are issued back to back
 // and are in flight together.
 using RawRow = float __attribute__((ext_vector_type(4)));
-using RowInMemory = float __attribute__((ext_vector_type(4), aligned(4)));
+using RowInMemory = Quad128<float>;              // rows start on any 4-byte boundary
 __device__ __forceinline__ RawRow load_row(const float *g, int r, int c, int H, int W) {
   r = min(max(r, 0), H - 1);
   return *reinterpret_cast<const RowInMemory *>(g + (size_t)r * (size_t)W + min(c, W - kVec));

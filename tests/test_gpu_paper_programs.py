@@ -251,6 +251,33 @@ def test_scans_where_the_tile_changes(n):
     assert prog.control_words()[1] == 0
 
 
+@pytest.mark.parametrize("tile", [4096, 8192, 12288])
+@pytest.mark.parametrize("past", [0, 1, 2, 3])
+def test_interpreted_scans_from_the_right_of_any_length(tile, past):
+    # a whole tile is evaluated in groups of four that start at n - 4 - i: at every position of a 128-bit boundary;
+    # the array read at the element's own position and one read through a gather
+    n = (1600000 // tile + 3) * tile + past if tile != 4096 else 3 * tile + past
+    rng = np.random.default_rng(n)
+    g = Graph()
+    g.add("x", "input", "f32", (n,))
+    g.add("i", "input", "i32", (n,))
+    g.add("t", "input", "i32", (1000,))
+    g.add("a", "map", "f32", (n,), fn="sq_plus_one", args=("x",))
+    g.add("b", "map", "f32", (n,), fn="affine", fparam=(0.5, -0.75), args=("a",))
+    g.add("r", "scanr", "f32", (n,), fn="add", args=("b",), output=True)
+    g.add("c", "gather", "i32", (n,), args=("i", "t"))
+    g.add("q", "scanr", "i32", (n,), fn="add", args=("c",), output=True)
+    ins = {"x": rng.uniform(-1.0, 1.0, n).astype(F32),
+           "i": rng.integers(0, 1000, n).astype(np.int32), "t": rng.integers(-50, 50, 1000).astype(np.int32)}
+    env = evaluate(g, ins)
+    prog = device_program(g, ins, fc().fc_plan(g, "bytes", executable=True))
+    assert sum("element programs interpreted" in k for k in prog.kernels()) == 2, prog.kernels()
+    prog.run()
+    P.assert_bit_exact(prog.fetch("q"), env["q"], f"n={n} q")
+    got, tol = prog.fetch("r").astype(np.float64), 1e-5 * prefix_scale(env["b"], True) + 1e-30
+    assert np.all(np.abs(got - env["r"].astype(np.float64)) <= tol), n
+
+
 def test_programs_whose_optimum_has_no_kernel_run_with_an_executable_plan():
     # the cheapest legal clustering of these programs contains a cluster the library has no
     # kernel for; planned with FC_PLAN_EXECUTABLE they run fused as far as the kernels go
