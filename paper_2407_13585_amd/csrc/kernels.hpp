@@ -1216,13 +1216,17 @@ __global__ __launch_bounds__(kFineBlock) void fold_fine_kernel(const KArgs a, Co
 // kMaxIn-1.  An empty segment yields the identity.
 //
 // L lanes take a row: they stride through it, U elements a lane in flight at a time, and combine
-// their sums with cross-lane moves.  Bound by the gathers of the element program (SpMV over a
+// their sums with cross-lane moves.  Each of the U elements in flight goes to a sum of its own, so that a row
+// is never added up in fewer than sixteen sums (in one sum a lane, as before, rows of 100 to 256 elements
+// among short ones rounded 1.1 to 1.4 times as much as with sixteen lanes; the time is the same, 300001 rows of 7
+// 12.2 us against 12.4, a row of 20000 29.6 against 32.1).
+// Bound by the gathers of the element program (SpMV over a
 // table that fits L2: 236 G/s at most) behind a chain of three reads (offsets, index, table).
 // Ordinary loads: the lanes of neighbouring rows read a line of a stream a piece at a time
 // (non-temporal: 300001 rows of 16 elements 39 us instead of 26).  Elements past a row's end
 // are read at its last element instead of not at all, so that a lane's U reads are issued together.
 // A row of 20000 elements among 10^5 of three: 240 us with sixteen lanes an element at a time, 321 with four lanes,
-// 33 with the whole wave on what is left of it (interpreted, sixteen lanes: 2034 us alone, 511 with the wave).
+// 30 with the whole wave on what is left of it (interpreted, sixteen lanes: 2034 us alone, 511 with the wave).
 template <class Op, class E, int L, int U>
 __global__ __launch_bounds__(kBlock) void foldseg_kernel(const Packed<kHeadAux | kHeadOffsets, 1u, E> packed) {
   const KArgs &a = packed.open();
@@ -1238,35 +1242,39 @@ __global__ __launch_bounds__(kBlock) void foldseg_kernel(const Packed<kHeadAux |
     const unsigned r = s * rows_per_step + blockIdx.x * (kBlock / L) + threadIdx.x / L;
     unsigned lo = 0, hi = 0;
     if (r < rows) { lo = off[r]; hi = off[r + 1]; }
-    T acc = Op::identity();
-    // elements from .. to - 1, by `Lanes` lanes
+    // the sum of elements from .. to - 1, by `Lanes` lanes with U sums each
     auto take = [&](auto lanes, unsigned lane, unsigned from, unsigned to) {
       constexpr unsigned Lanes = decltype(lanes)::value;
+      T acc[U];
+#pragma unroll
+      for (int u = 0; u < U; ++u) acc[u] = Op::identity();
       // unsigned: the step past a segment that ends at 2^31 - 1 must not wrap
       for (unsigned k = from + lane; k < to; k += Lanes * U) {
         T v[U];
 #pragma unroll
         for (int u = 0; u < U; ++u) v[u] = E::template eval<0>(a, (int)min(k + u * Lanes, to - 1u));
 #pragma unroll
-        for (int u = 0; u < U; ++u) acc = Op::apply(acc, u == 0 || k + u * Lanes < to ? v[u] : Op::identity());
+        for (int u = 0; u < U; ++u) acc[u] = Op::apply(acc[u], u == 0 || k + u * Lanes < to ? v[u] : Op::identity());
       }
+#pragma unroll
+      for (int h = U / 2; h > 0; h /= 2)
+#pragma unroll
+        for (int u = 0; u < h; ++u) acc[u] = Op::apply(acc[u], acc[u + h]);
+      T sum = acc[0];
+#pragma unroll
+      for (unsigned o = 1; o < Lanes; o <<= 1) sum = Op::apply(sum, __shfl_xor(sum, (int)o));
+      return sum;
     };
     // A row far above the mean is taken by its own lanes up to kOwn elements and by the whole wave from there.
     constexpr unsigned kOwn = L * U * 8;
     const bool longer = L < kWave && hi > lo && hi - lo > kOwn;
-    take(std::integral_constant<unsigned, L>(), sub, lo, longer ? lo + kOwn : hi);
-#pragma unroll
-    for (int o = 1; o < L; o <<= 1) acc = Op::apply(acc, __shfl_xor(acc, o));
+    T acc = take(std::integral_constant<unsigned, L>(), sub, lo, longer ? lo + kOwn : hi);
     if constexpr (L < kWave) {
       for (unsigned long long left = __ballot(longer && sub == 0); left != 0; left &= left - 1) {
         const int src = __builtin_ctzll(left);
         const unsigned from = (unsigned)__shfl((int)lo, src) + kOwn, to = (unsigned)__shfl((int)hi, src);
-        const T own = acc;
-        acc = Op::identity();
-        take(std::integral_constant<unsigned, kWave>(), (unsigned)lane_id(), from, to);
-#pragma unroll
-        for (int o = 1; o < kWave; o <<= 1) acc = Op::apply(acc, __shfl_xor(acc, o));
-        acc = lane_id() == src ? Op::apply(own, acc) : own;
+        const T rest = take(std::integral_constant<unsigned, kWave>(), (unsigned)lane_id(), from, to);
+        if (lane_id() == src) acc = Op::apply(acc, rest);
       }
     }
     if (sub == 0 && r < rows) y[r] = acc;

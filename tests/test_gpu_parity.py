@@ -243,6 +243,28 @@ def test_spmv_rows_shared_by_the_wave(mean_len, own):
     run_all_modes(3, C.spmv(lengths=lengths, seed=950 + mean_len, ncols=3000))
 
 
+@pytest.mark.parametrize("mean_len,own", [(3, 128), (20, 256), (100, 512)])
+def test_spmv_rows_are_added_up_in_sixteen_sums_or_more(mean_len, own):
+    # the first term of every row is 2^24 and the others are 1, which a sum that holds the first one loses: a row of
+    # k elements in s sums of at most ceil(k / s) terms, combined pairwise, is off by at most (ceil(k / s) + log2 s) half
+    # units of 2^24, here with s = 16; the exact sum itself may need one more rounding
+    lengths = np.random.default_rng(mean_len).poisson(mean_len, size=1003) + 1
+    lengths[[0, 5, 6, 7, 400, 401, 1002]] = [own, own - 1, own + 1, own + 255, own // 2, own // 4 * 3, 2500]
+    w = C.spmv(lengths=lengths, seed=970 + mean_len, ncols=3000)
+    off = w.inputs["off"]
+    w.inputs["x"][:] = 1.0
+    w.inputs["vals"][:] = 1.0
+    w.inputs["vals"][off[:-1]] = 2.0 ** 24
+    exact = 2.0 ** 24 + (lengths - 1)
+    bound = (-(-lengths // 16) + 4 + 1) * exact * 2.0 ** -24
+    g, part = plan(w.graph, True)
+    prog = device_program(g, w.inputs, part)
+    assert "{" not in prog.kernels()[0], prog.kernels()      # the kernel that takes the rows in place
+    prog.run()
+    off_by = np.abs(prog.fetch("y").astype(np.float64) - exact)
+    assert np.all(off_by <= bound), (off_by - bound).max()
+
+
 def test_spmv_skewed_rows():
     rng = np.random.default_rng(77)
     lengths = np.minimum(rng.zipf(1.5, size=5000), 20000).astype(np.int64)
