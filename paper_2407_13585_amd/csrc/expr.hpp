@@ -78,7 +78,7 @@ enum : unsigned char {
   kCodeMap,     // a = element function, b = slot, c = number of arguments: replace them by the result
   kCodeEnter,   // pop an index and make it the position
   kCodeLeave,   // back to the position before the matching kCodeEnter
-  kCodeLookup,  // a = external array, b = 1 + k: push its element at the index that array direct[k] holds
+  kCodeLookup,  // a = external array, b = 1 + k: push its element at the index that array direct[k] (c) holds
   kCodeStore,   // a = output array: pop a value into it at the element's own position
   kCodeFold,    // a = output array, b = reducer (kFold...), c = accumulator: pop a value into it
   kCodeYield    // the value on the stack is the result of this element program (Interp<K, T>)
@@ -99,12 +99,20 @@ struct KArgs {    // arguments of one cluster launch
   int aux;                  // skeleton specific (rows of a segmented fold, ...)
   Slot p[kMaxSlots];
   Code code[kMaxCode];      // kCodeEnd after the last instruction
-  unsigned char root[kMaxRoots];   // where element program K of a cluster with another consumer starts in `code`
+  unsigned root[kMaxRoots];        // where element program K of a cluster with another consumer starts in `code`
   // External arrays that element program K reads at the element's own position (the first kInterpDirect of
   // them): known before the program runs, so their reads are issued together and ahead of it.
   unsigned char direct[kMaxRoots][kInterpDirect], n_direct[kMaxRoots];
   unsigned char code_depth, code_gathers;   // values below the top of the stack and nested gathers that `code` needs
   unsigned char n_folds, fold_op[kInterpFolds], fold_out[kInterpFolds];   // of a cluster that interp_kernel runs
+  // An instruction as one word: at an index that is the same for all lanes a scalar read, where the compiler may read
+  // four bytes through the vector unit (row scans of 2^24 interpreted elements 107 us, with words 101).  The kernel that
+  // reads ahead of the run has scalar reads as it is, and came out slower with words (fold of 2^24 elements 35.7, 37.7).
+  __device__ __forceinline__ Code code_word(int pc) const {
+    unsigned word;
+    __builtin_memcpy(&word, __builtin_assume_aligned(&code[pc], 4), sizeof(word));
+    return {(unsigned char)word, (unsigned char)(word >> 8), (unsigned char)(word >> 16), (unsigned char)(word >> 24)};
+  }
   unsigned flags;           // kSinglePass: a fold of the cluster carries FC_NODE_SINGLE_PASS;
                             // kKeepOut << k: out[k] is read back by a later cluster of the program
   __host__ __device__ bool keeps(int k) const { return (flags >> (8 + k)) & 1u; }
@@ -463,7 +471,7 @@ template <int KI, class ES> struct GatherChain<Gather<In<KI, int>, ES>> {
 // as a whole) 3.3 to 3.9.  So the kernels whose element programs are compiled take the parts of KArgs
 // these programs use, as Packed<...>, and open() puts them back where the program looks for them (registers:
 // every index is known when the kernel is compiled).
-template <int K, class T, int LdsThreads> struct Interp;        // kernels.hpp: reads KArgs::code, needs all of it
+template <int K, class T, int LdsThreads, bool Early, int Columns> struct Interp;        // kernels.hpp: reads KArgs::code, needs all of it
 
 // the fields of a Slot as words: f[0], f[1], i[0], i[1], ext[0], ext[1], m[0], m[1], m[2]
 constexpr int kSlotWords = 9;
@@ -491,7 +499,7 @@ template <class E> struct Needs {
   static constexpr bool all = false;
   template <int Base> static constexpr void words(WordList &) {}
 };
-template <int K, class T, int L> struct Needs<Interp<K, T, L>> : Needs<void> { static constexpr bool all = true; };
+template <int K, class T, int L, bool Early, int C> struct Needs<Interp<K, T, L, Early, C>> : Needs<void> { static constexpr bool all = true; };
 template <int K, class T> struct Needs<In<K, T>> : Needs<void> { static constexpr int ins = K + 1; };
 template <class G> struct Needs<Gen<G>> : Needs<void> {
   template <int Base> static constexpr void words(WordList &l) { l.add_slot(Base, SlotUse<G>::value); }

@@ -9,15 +9,17 @@ void append_generic_row_instances(std::vector<Instance> &r) {
   using XF0 = Interp<0, float>;
   using XI0 = Interp<0, int>;
   using XI1 = Interp<1, int>;
-  r.push_back(rowscan_<XI0>());
-  r.push_back(rowscan_<XI0, true>());
-  r.push_back(rowscan_<XF0>());
-  r.push_back(rowscan_<XF0, true>());
+  using SF0 = Interp<0, float, kBlock, false, 1>;      // the row scans evaluate one element a lane
+  using SI0 = Interp<0, int, kBlock, false, 1>;
+  r.push_back(rowscan_<SI0>());
+  r.push_back(rowscan_<SI0, true>());
+  r.push_back(rowscan_<SF0>());
+  r.push_back(rowscan_<SF0, true>());
   // the scanned array stored as well
-  r.push_back(rowscan_<XI0, false, true>());
-  r.push_back(rowscan_<XI0, true, true>());
-  r.push_back(rowscan_<XF0, false, true>());
-  r.push_back(rowscan_<XF0, true, true>());
+  r.push_back(rowscan_<SI0, false, true>());
+  r.push_back(rowscan_<SI0, true, true>());
+  r.push_back(rowscan_<SF0, false, true>());
+  r.push_back(rowscan_<SF0, true, true>());
   r.push_back(rowfold_<AddF32, NoSecondOp, XF0>());
   r.push_back(rowfold_<MulF32, NoSecondOp, XF0>());
   r.push_back(rowfold_<MaxF32, NoSecondOp, XF0>());

@@ -342,16 +342,17 @@ __global__ __launch_bounds__(kBlock) void store_fold_kernel(const Packed<kHeadN 
 // or in stored arrays and up to two folds, for which no kernel was compiled: the element
 // programs are run from KArgs::code, four elements per lane at a time.  The value stack is in
 // registers (the compiler indexes them through the hardware's register index mode: the
-// index is the same for all lanes), as are the positions that gathers suspend, at most
-// kInterpGathers deep.  Every branch depends on the code only, which
+// index is the same for all lanes) or in LDS, the positions that gathers suspend, at most
+// kInterpGathers deep, in registers.  Every branch depends on the code only, which
 // is the same for all lanes.  Results are the same as a compiled instance's: the same
 // element functions, applied in the same order.  A fallback: several times the
 // instructions of a compiled instance per element.
-// Bound by latency (a chain of one read after the other) unless the gathers are many; so the
-// arrays read at the element's own position are read together, ahead of the run
-// (KArgs::direct), and the next group's while this group's program runs.  Value stack in LDS and
-// reads where the code asks for them, as before: exp(-d) * t[i] stored and summed, 2^24 elements 95 us
-// (now 59; t of 4 KiB), 2^22 31.3 us (29.5; t of 256 KiB, whose gathers bound it), 4096 elements 9 us (7).
+// Bound by latency (a chain of one read after the other) unless the gathers are many; so in the kernel for
+// programs that need few registers the arrays read at the element's own position are read together, ahead of the run
+// (KArgs::direct).  Value stack in LDS and reads where the code asks for them, as before: exp(-d) * t[i] stored and
+// summed, 2^24 elements 95 us (now 59; t of 4 KiB), 2^22 31.3 us (29.5; t of 256 KiB), 4096 elements 9 us (7).
+// Programs with a deeper stack or nested gathers keep the stack in LDS and read where the code asks: with 128 registers a lane
+// there are two to three times fewer waves to hide the chain (sum of five maps, 2^22 elements: 28 us against 47).
 // x[k][e]: argument k of element e; the function is picked once for the V elements
 template <int V>
 __device__ __forceinline__ void interp_map1(int fn, const Slot &s, unsigned (&x)[V]) {
@@ -420,59 +421,71 @@ __device__ __forceinline__ unsigned interp_identity(int op) {
 // A lane runs a program for G 128-bit groups of elements at a time, which lie `apart` elements from each other,
 // or (G = 0) for one element, so that the cost of reading and decoding an instruction is shared.
 // What element program `root` reads at the elements' own positions, read ahead.
-template <int G> struct InterpAhead {
+template <int G, bool Early> struct InterpAhead {
   static constexpr int V = G ? G * kVec : 1;
   using Group = Quad128<unsigned>;                     // a scan from the right reads groups at n - 4 - i, n of any length
-  unsigned v[kInterpDirect][V];
-  template <bool Stream> __device__ __forceinline__ void read(const KArgs &a, int root, unsigned first, unsigned apart) {
+  unsigned v[Early ? kInterpDirect : 1][V];
+  template <bool Stream> static __device__ __forceinline__ void read_one(const void *array, unsigned first, unsigned apart, unsigned (&x)[V]) {
+    const unsigned *p = static_cast<const unsigned *>(array) + first;
+    if (G == 0) x[0] = p[0];
 #pragma unroll
-    for (int k = 0; k < kInterpDirect; ++k)
-      if (k < a.n_direct[root]) {
-        const unsigned *p = static_cast<const unsigned *>(a.in[a.direct[root][k]]) + first;
-        if (G == 0) v[k][0] = p[0];
+    for (int g = 0; g < G; ++g) {
+      const Group *q = reinterpret_cast<const Group *>(p + g * apart);
+      const Group y = Stream ? __builtin_nontemporal_load(q) : *q;
 #pragma unroll
-        for (int g = 0; g < G; ++g) {
-          const Group *q = reinterpret_cast<const Group *>(p + g * apart);
-          const Group x = Stream ? __builtin_nontemporal_load(q) : *q;
-#pragma unroll
-          for (int c = 0; c < kVec; ++c) v[k][g * kVec + c] = x[c];
-        }
-      }
+      for (int c = 0; c < kVec; ++c) x[g * kVec + c] = y[c];
+    }
   }
-  __device__ __forceinline__ unsigned get(int k, int e) const {   // k is the same in all lanes
-    static_assert(kInterpDirect == 4, "one value per array");
-    const unsigned a = v[0][e], b = v[1][e], c = v[2][e], d = v[3][e];                  // values: a choice of addresses would put v into memory
-    return k == 0 ? a : k == 1 ? b : k == 2 ? c : d;
+  template <bool Stream> __device__ __forceinline__ void read(const KArgs &a, int root, unsigned first, unsigned apart) {
+    if constexpr (Early) {
+#pragma unroll
+      for (int k = 0; k < kInterpDirect; ++k)
+        if (k < a.n_direct[root]) read_one<Stream>(a.in[a.direct[root][k]], first, apart, v[k]);
+    }
+  }
+  // x: array number k of those read ahead, which is external array `array`; both are the same in all lanes
+  __device__ __forceinline__ void get(const KArgs &a, int array, unsigned first, unsigned apart, int k, unsigned (&x)[V]) const {
+    if constexpr (Early) {
+      static_assert(kInterpDirect == 4, "one value per array");
+#pragma unroll
+      for (int e = 0; e < V; ++e) {
+        const unsigned v0 = v[0][e], v1 = v[1][e], v2 = v[2][e], v3 = v[3][e];             // values: a choice of addresses would put v into memory
+        x[e] = k == 0 ? v0 : k == 1 ? v1 : k == 2 ? v2 : v3;
+      }
+    } else {
+      read_one<false>(a.in[array], first, apart, x);
+    }
   }
 };
 
-// the stack columns of a workgroup in LDS
-template <int Threads>
-__device__ __forceinline__ unsigned (*interp_stack())[kVec][Threads] {
-  __shared__ unsigned below[kInterpDepth][kVec][Threads];
+// the stack columns of a workgroup in LDS, for Columns elements a lane
+template <int Threads, int Columns>
+__device__ __forceinline__ unsigned (*interp_stack())[Columns][Threads] {
+  __shared__ unsigned below[kInterpDepth][Columns][Threads];
   return below;
 }
 
 // Starts at instruction `pc`; a kCodeYield ends the run with the program's values in `result`.
 // Depth, Nest: values below the top of the stack and nested gathers that the code needs at most.  LdsThreads: threads
 // of the workgroup if the values below the top are to lie in LDS (a column per lane), or 0.
-template <int G, int Depth, int Nest, int LdsThreads>
-__device__ __forceinline__ void interp_run(const KArgs &a, int pc, unsigned first, unsigned apart, const InterpAhead<G> &ahead,
-                                           unsigned (&acc)[kInterpFolds], unsigned (&result)[InterpAhead<G>::V]) {
+template <int G, int Depth, int Nest, int LdsThreads, bool Early, int Columns = kVec>
+__device__ __forceinline__ void interp_run(const KArgs &a, int pc, unsigned first, unsigned apart, const InterpAhead<G, Early> &ahead,
+                                           unsigned (&acc)[kInterpFolds], unsigned (&result)[InterpAhead<G, Early>::V]) {
   using Raw = unsigned __attribute__((ext_vector_type(4)));
-  constexpr int V = InterpAhead<G>::V;
+  constexpr int V = InterpAhead<G, Early>::V;
   auto own = [&](int e) { return (int)(first + (e / kVec) * apart + e % kVec); };      // the elements' own positions
   int at[V];                                           // the positions element programs read at
   int suspended[Nest > 1 ? Nest - 1 : 1][V];           // of the gathers around the innermost but one; outermost: own positions
   unsigned top[V], below[LdsThreads ? 1 : Depth][V];   // an array of its own: as part of a struct it would be put into memory
-  unsigned (*column)[kVec][LdsThreads ? LdsThreads : 1] = nullptr;
-  if constexpr (LdsThreads != 0) column = interp_stack<LdsThreads>();
+  unsigned (*column)[Columns][LdsThreads ? LdsThreads : 1] = nullptr;
+  if constexpr (LdsThreads != 0) column = interp_stack<LdsThreads, Columns>();
+  static_assert(LdsThreads == 0 || V <= Columns, "a column for each element");
 #pragma unroll
   for (int k = 0; k < (LdsThreads ? 1 : Depth); ++k)
 #pragma unroll
     for (int e = 0; e < V; ++e) below[k][e] = 0u;
-  auto set_below = [&](int k, int e, unsigned x) { if (LdsThreads) column[k][e % kVec][threadIdx.x] = x; else below[k][e] = x; };
-  auto get_below = [&](int k, int e) { return LdsThreads ? column[k][e % kVec][threadIdx.x] : below[k][e]; };
+  auto set_below = [&](int k, int e, unsigned x) { if (LdsThreads) column[k][e % Columns][threadIdx.x] = x; else below[k][e] = x; };
+  auto get_below = [&](int k, int e) { return LdsThreads ? column[k][e % Columns][threadIdx.x] : below[k][e]; };
 #pragma unroll
   for (int e = 0; e < V; ++e) { at[e] = own(e); top[e] = 0u; }
   int gathers = 0, count = 0;                          // the same in every lane
@@ -490,8 +503,9 @@ __device__ __forceinline__ void interp_run(const KArgs &a, int pc, unsigned firs
       for (int e = 0; e < V; ++e) top[e] = get_below(count - 1, e);
     }
   };
-  for (Code c = a.code[pc], next; pc < kMaxCode - 1; ++pc, c = next) {
-    next = a.code[pc + 1];                             // the last entry is kCodeEnd
+  constexpr bool kFetch = Early || V > 1;              // the next instruction is fetched while one is worked on
+  for (Code c = Early ? a.code[pc] : a.code_word(pc), next; pc < kMaxCode - 1; ++pc, c = kFetch ? next : a.code_word(pc)) {
+    if (kFetch) next = Early ? a.code[pc + 1] : a.code_word(pc + 1);             // the last entry is kCodeEnd
     if (c.op == kCodeEnd) break;
     if (c.op == kCodeYield) {
 #pragma unroll
@@ -502,8 +516,7 @@ __device__ __forceinline__ void interp_run(const KArgs &a, int pc, unsigned firs
       case kCodeIn: {
         push_room();
         if (c.b != 0) {
-#pragma unroll
-          for (int e = 0; e < V; ++e) top[e] = ahead.get(c.b - 1, e);
+          ahead.get(a, c.a, first, apart, c.b - 1, top);
         } else {
           const unsigned *p = static_cast<const unsigned *>(a.in[c.a]);
 #pragma unroll
@@ -514,8 +527,9 @@ __device__ __forceinline__ void interp_run(const KArgs &a, int pc, unsigned firs
       case kCodeLookup: {
         push_room();
         const unsigned *p = static_cast<const unsigned *>(a.in[c.a]);
+        ahead.get(a, c.c, first, apart, c.b - 1, top);
 #pragma unroll
-        for (int e = 0; e < V; ++e) top[e] = p[(int)ahead.get(c.b - 1, e)];
+        for (int e = 0; e < V; ++e) top[e] = p[(int)top[e]];
         break;
       }
       case kCodeGen:
@@ -608,8 +622,8 @@ __device__ __forceinline__ unsigned interp_block_reduce(int op, unsigned v, unsi
 }
 
 // G groups a lane at a time where there are that many elements, single groups and elements for the rest.
-template <int G, int Depth, int Nest>
-__global__ __launch_bounds__(kBlock, 4) void interp_kernel(const KArgs a, Control *ctl, unsigned long long *partials) {
+template <int G, int Depth, int Nest, int LdsThreads, bool Early>
+__global__ __launch_bounds__(kBlock, LdsThreads ? 1 : 4) void interp_kernel(const KArgs a, Control *ctl, unsigned long long *partials) {
   __shared__ unsigned lds[kWavesPerBlock + 1];
   const unsigned n = (unsigned)a.n, n4 = n & ~3u;
   const unsigned epoch = epoch_at_start(ctl);
@@ -617,28 +631,28 @@ __global__ __launch_bounds__(kBlock, 4) void interp_kernel(const KArgs a, Contro
   const int n_folds = a.n_folds, fold_op[kInterpFolds] = {a.fold_op[0], a.fold_op[1]};
   unsigned acc[kInterpFolds] = {interp_identity(fold_op[0]), interp_identity(fold_op[1])};
   constexpr unsigned kGroup = kBlock * kVec, kTileOf = kGroup * G;
-  unsigned none[InterpAhead<G>::V], none4[kVec], none1[1];
+  unsigned none[InterpAhead<G, Early>::V], none4[kVec], none1[1];
   const unsigned whole = n4 / kTileOf * kTileOf;
   for (unsigned base = blockIdx.x * kTileOf; base < (G > 1 ? whole : n4); base += gridDim.x * kTileOf) {
     const unsigned i = base + threadIdx.x * kVec;
     if (G == 1 && i >= n4) break;
-    InterpAhead<G> ahead;
+    InterpAhead<G, Early> ahead;
     ahead.template read<true>(a, 0, i, kGroup);
-    interp_run<G, Depth, Nest, 0>(a, 0, i, kGroup, ahead, acc, none);
+    interp_run<G, Depth, Nest, LdsThreads, Early>(a, 0, i, kGroup, ahead, acc, none);
   }
   // what is left is less than a tile: the first G workgroups take a group a lane of it
   if (G > 1) {
     const unsigned i = whole + blockIdx.x * kGroup + threadIdx.x * kVec;
     if (i < n4) {
-      InterpAhead<1> ahead;
+      InterpAhead<1, Early> ahead;
       ahead.template read<true>(a, 0, i, kGroup);
-      interp_run<1, Depth, Nest, 0>(a, 0, i, kGroup, ahead, acc, none4);
+      interp_run<1, Depth, Nest, LdsThreads, Early>(a, 0, i, kGroup, ahead, acc, none4);
     }
   }
   if (blockIdx.x == 0 && threadIdx.x < n - n4) {
-    InterpAhead<0> ahead;
+    InterpAhead<0, Early> ahead;
     ahead.template read<false>(a, 0, n4 + threadIdx.x, 0u);
-    interp_run<0, Depth, Nest, 0>(a, 0, n4 + threadIdx.x, 0u, ahead, acc, none1);
+    interp_run<0, Depth, Nest, LdsThreads, Early>(a, 0, n4 + threadIdx.x, 0u, ahead, acc, none1);
   }
   if (n_folds == 0) return;                              // the same for the whole grid
   // as fold_finish, for up to two accumulators under one tag: fold k keeps its partials at
@@ -665,26 +679,29 @@ __global__ __launch_bounds__(kBlock, 4) void interp_kernel(const KArgs a, Contro
 // (KArgs::code from KArgs::root[K] to the kCodeYield).  With it every skeleton of this
 // file has an instance that takes any element program: what the matcher cannot pair with a
 // compiled element program runs through these.
-// LdsThreads: threads of the workgroup if the value stack is to lie in LDS (the scan kernels: the tile a lane
-// holds fills its registers), or 0.
-template <int K, class T, int LdsThreads = 0>
+// LdsThreads: threads of the workgroup if the value stack is to lie in LDS, or 0; Columns: elements a lane that the
+// stack has room for (1: only eval is used).  Early: the arrays at the element's own position are read ahead of the run.
+// The stack in LDS and reads where the code asks for them: in registers, stack and reads ahead leave two to four waves
+// a SIMD, too few to hide the interpreter's chain (2^24 elements: row folds of 32 elements 61 us against 115 with
+// registers and reads ahead, row scans of 32 84 / 107, segmented folds of 16 elements a row 338 / 484, fp32 scans 38 / 68).
+template <int K, class T, int LdsThreads = kBlock, bool Early = false, int Columns = kVec>
 struct Interp {
   using R = T;
   static constexpr int kNodes = 0;                     // the code names its parameter slots itself
   static constexpr bool kMirror = false;
   template <int Base, bool Stream = false> static __device__ __forceinline__ T eval(const KArgs &a, int i) {
     unsigned r[1] = {0u}, none[kInterpFolds] = {0u, 0u};
-    InterpAhead<0> ahead;
+    InterpAhead<0, Early> ahead;
     ahead.template read<false>(a, K, (unsigned)i, 0u);
-    interp_run<0, kInterpDepth, kInterpGathers, LdsThreads>(a, a.root[K], (unsigned)i, 0u, ahead, none, r);
+    interp_run<0, kInterpDepth, kInterpGathers, LdsThreads, Early, Columns>(a, (int)a.root[K], (unsigned)i, 0u, ahead, none, r);
     return from_bits<T>((int)r[0]);
   }
   // i may be any position, as for the compiled element programs
   template <int Base> static __device__ __forceinline__ Vec4<T> eval4(const KArgs &a, int i) {
     unsigned r[kVec] = {0u, 0u, 0u, 0u}, none[kInterpFolds] = {0u, 0u};
-    InterpAhead<1> ahead;
+    InterpAhead<1, Early> ahead;
     ahead.template read<false>(a, K, (unsigned)i, 0u);
-    interp_run<1, kInterpDepth, kInterpGathers, LdsThreads>(a, a.root[K], (unsigned)i, 0u, ahead, none, r);
+    interp_run<1, kInterpDepth, kInterpGathers, LdsThreads, Early, Columns>(a, (int)a.root[K], (unsigned)i, 0u, ahead, none, r);
     return Vec4<T>{{from_bits<T>((int)r[0]), from_bits<T>((int)r[1]), from_bits<T>((int)r[2]), from_bits<T>((int)r[3])}};
   }
   static void sig(std::string &s) { s += std::string("*") + DtypeName<T>::s(); }
@@ -1260,7 +1277,9 @@ __global__ __launch_bounds__(kBlock) void foldseg_kernel(const Packed<kHeadAux |
       for (int h = U / 2; h > 0; h /= 2)
 #pragma unroll
         for (int u = 0; u < h; ++u) acc[u] = Op::apply(acc[u], acc[u + h]);
-      T sum = acc[0];
+      T sum = acc[0];                                      // the last of the lanes gets the result
+      if constexpr (Lanes == kWave) return wave_reduce<Op>(sum);
+      if constexpr (Lanes == 16) return row_scan_inclusive<Op>(sum);
 #pragma unroll
       for (unsigned o = 1; o < Lanes; o <<= 1) sum = Op::apply(sum, __shfl_xor(sum, (int)o));
       return sum;
@@ -1270,14 +1289,14 @@ __global__ __launch_bounds__(kBlock) void foldseg_kernel(const Packed<kHeadAux |
     const bool longer = L < kWave && hi > lo && hi - lo > kOwn;
     T acc = take(std::integral_constant<unsigned, L>(), sub, lo, longer ? lo + kOwn : hi);
     if constexpr (L < kWave) {
-      for (unsigned long long left = __ballot(longer && sub == 0); left != 0; left &= left - 1) {
+      for (unsigned long long left = __ballot(longer && sub == L - 1); left != 0; left &= left - 1) {
         const int src = __builtin_ctzll(left);
         const unsigned from = (unsigned)__shfl((int)lo, src) + kOwn, to = (unsigned)__shfl((int)hi, src);
         const T rest = take(std::integral_constant<unsigned, kWave>(), (unsigned)lane_id(), from, to);
         if (lane_id() == src) acc = Op::apply(acc, rest);
       }
     }
-    if (sub == 0 && r < rows) y[r] = acc;
+    if (sub == L - 1 && r < rows) y[r] = acc;
   }
 }
 
@@ -2169,6 +2188,49 @@ struct ScanPayload {
   __device__ __forceinline__ void set(int j, int c, int v) {
     if (kBits) bits |= (unsigned)(v != 0) << (j * 4 + c); else x[kBits ? 0 : j][c] = v;
   }
+  // Interpreted element programs: one copy of the interpreter in a loop that stays one, whose results go round (in
+  // copies for every access the code is too long for the compiler to keep the tile in registers: the compaction
+  // of 2^22 mapped elements 163 us), and no run for positions past the end.
+  __device__ __forceinline__ void load_interpreted(const KArgs &a, unsigned wbase, bool whole, unsigned n) {
+#pragma unroll
+    for (int j = 0; j < Acc; ++j)
+#pragma unroll
+      for (int c = 0; c < 4; ++c) { x[kBits ? 0 : j][c] = 0; if (kScat) val[kScat ? j : 0][c] = V(0); }
+#pragma unroll 1
+    for (int j = 0; j < Acc; ++j) {
+      const unsigned i = wbase + j * (kWave * kVec) + lane_id() * kVec;
+      Vec4<int> got = {{0, 0, 0, 0}};
+      Vec4<V> here = {{V(0), V(0), V(0), V(0)}};
+      if (whole) {
+        if (kScat) here = EV::template eval4<EX::kNodes>(a, (int)(Reverse ? n - 4 - i : i));
+        got = EX::template eval4<0>(a, (int)(Reverse ? n - 4 - i : i));
+        if (Reverse) {
+          got = Vec4<int>{{got.v[3], got.v[2], got.v[1], got.v[0]}};
+          if (kScat) here = Vec4<V>{{here.v[3], here.v[2], here.v[1], here.v[0]}};
+        }
+      } else {
+#pragma unroll 1
+        for (int c = 0; c < 4; ++c) {
+          const int e = Reverse ? (int)(n - 1u - (i + c)) : (int)(i + c);
+          int g = 0;
+          V h = V(0);
+          if (i + c < n) {
+            if (kScat) h = EV::template eval<EX::kNodes>(a, e);
+            g = EX::template eval<0>(a, e);
+          }
+          got = Vec4<int>{{got.v[1], got.v[2], got.v[3], g}};
+          if (kScat) here = Vec4<V>{{here.v[1], here.v[2], here.v[3], h}};
+        }
+      }
+#pragma unroll
+      for (int k = 0; k < Acc; ++k)
+#pragma unroll
+        for (int c = 0; c < 4; ++c) {
+          x[kBits ? 0 : k][c] = k + 1 < Acc ? x[kBits ? 0 : k + 1][c] : got.v[c];
+          if (kScat) val[kScat ? k : 0][c] = k + 1 < Acc ? val[kScat ? k + 1 : 0][c] : here.v[c];
+        }
+    }
+  }
   // wave-striped layout: a wave owns kWave * kVec * Acc consecutive elements; access j
   // of a lane covers elements base + j*256 + lane*4 .. +3 (fully coalesced).
   // A tile that lies wholly inside the array takes a path without any
@@ -2178,6 +2240,10 @@ struct ScanPayload {
   __device__ __forceinline__ void load(const KArgs &a, unsigned tile, unsigned n) {
     const unsigned wbase = tile * kTileOf + wave_id() * (kWave * kVec * Acc);
     bits = 0u;
+    if constexpr (EX::kNodes == 0) {
+      load_interpreted(a, wbase, (unsigned long long)(tile + 1) * kTileOf <= n, n);
+      return;
+    }
     if (!Reverse && (unsigned long long)(tile + 1) * kTileOf <= n) {
       if (kScat) {
 #pragma unroll
@@ -2488,7 +2554,33 @@ __global__ __launch_bounds__(kScanBlock, ScanWaves<EX>::value) void scan_f32_ker
   // elements n-4-i .. n-1-i taken backwards
   const bool whole = (size_t)(tile + 1) * kTileOf <= n;
   float x[Acc][kVec];
-  if (whole) {
+  if constexpr (EX::kNodes == 0) {
+    // interpreted: one copy of the interpreter, as in ScanPayload
+#pragma unroll
+    for (int j = 0; j < Acc; ++j)
+#pragma unroll
+      for (int c = 0; c < kVec; ++c) x[j][c] = 0.0f;
+#pragma unroll 1
+    for (int j = 0; j < Acc; ++j) {
+      const unsigned i = wbase + j * (kWave * kVec) + lane * kVec;
+      Vec4<float> v = {{0.0f, 0.0f, 0.0f, 0.0f}};
+      if (whole) {
+        v = EX::template eval4<0>(a, (int)(Reverse ? n - 4 - i : i));
+        if (Reverse) v = Vec4<float>{{v.v[3], v.v[2], v.v[1], v.v[0]}};
+      } else {
+#pragma unroll 1
+        for (int c = 0; c < kVec; ++c) {
+          float y = 0.0f;
+          if (i + c < n) y = EX::template eval<0>(a, (int)(Reverse ? n - 1u - (i + c) : i + c));
+          v = Vec4<float>{{v.v[1], v.v[2], v.v[3], y}};
+        }
+      }
+#pragma unroll
+      for (int k = 0; k < Acc; ++k)
+#pragma unroll
+        for (int c = 0; c < kVec; ++c) x[k][c] = k + 1 < Acc ? x[k + 1][c] : v.v[c];
+    }
+  } else if (whole) {
 #pragma unroll
     for (int j = 0; j < Acc; ++j) {
       const unsigned i = wbase + j * (kWave * kVec) + lane * kVec;

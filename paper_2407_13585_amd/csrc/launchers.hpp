@@ -81,10 +81,11 @@ template <class ES, class Op, class EF> hipError_t launch_store_fold(const KArgs
 }
 template <class Op, class E> hipError_t launch_foldseg(const KArgs &a, const LaunchCtx &c) {
   if (a.aux == 0) return hipSuccess;
-  auto go = [&](auto kernel, int lanes) {
-    return launch_k(kernel, grid_for(a.aux, kBlock / lanes, 1u << 20), c, a);
-  };
   constexpr int U = E::kNodes == 0 ? 1 : 4;             // an interpreted element program is a loop of its own
+  // interpreted: as many workgroups as take some steps each (1.4 x 10^6 rows of 3 elements 258 us, a step each 276)
+  auto go = [&](auto kernel, int lanes) {
+    return launch_k(kernel, grid_for(a.aux, kBlock / lanes, U == 1 ? kMaxGrid * 8 : 1u << 20), c, a);
+  };
   const double mean = (double)a.n / a.aux;
   // Lanes by mean length, measured at 50000 and 300001 rows: as many as leave a lane two to four
   // elements (3 elements a row: 9.4 us with 4 lanes, 11.6 with 8, 16.9 with 16; 16 elements: 27.1, 25.6,
@@ -327,9 +328,10 @@ template <class EX, bool Reverse, bool StoreX, int Acc> hipError_t launch_scan_f
   return launch_threads(&scan_f32_kernel<EX, Reverse, StoreX, Acc>, tiles, c, kScanBlock, a, c.ctl, c.status);
 }
 template <class EX, bool Reverse = false, bool StoreX = false> hipError_t launch_scan_f32(const KArgs &a, const LaunchCtx &c) {
-  // (interpreted element programs too: the tile fixes the order of the sums, and with it the bits of the result)
   if ((unsigned)a.n < kScanShortBelow<false>) return launch_scan_f32_of<EX, Reverse, StoreX, kScanShortAcc>(a, c);
-  if ((unsigned)a.n >= kScanFLong) return launch_scan_f32_of<EX, Reverse, StoreX, kScanAcc>(a, c);
+  if constexpr (EX::kNodes != 0) {                     // an interpreted program has no reads to hide (2^24 elements 45 us with four, 49 with six)
+    if ((unsigned)a.n >= kScanFLong) return launch_scan_f32_of<EX, Reverse, StoreX, kScanAcc>(a, c);
+  }
   return launch_scan_f32_of<EX, Reverse, StoreX, kScanFAcc>(a, c);
 }
 // lanes per row by row length, as for the row folds

@@ -85,7 +85,7 @@ struct Builder {
   // takes any element program of this type (it runs the code between root[k] and the yield).
   int n_roots = 0;
   bool root(int a, std::string &sig, std::string &any) {
-    if (n_roots >= kMaxRoots || n_code > 255) code_ok = false; else args.root[n_roots] = (unsigned char)n_code;
+    if (n_roots >= kMaxRoots || n_code > 255) code_ok = false; else args.root[n_roots] = (unsigned)n_code;
     ++n_roots;
     if (!expr(a, sig)) return false;
     emit(kCodeYield);
@@ -134,7 +134,7 @@ struct Builder {
             if (!expr(nd.arg[1], sig)) return false;
             --gathers;
             if (code_ok) {
-              args.code[at] = Code{kCodeLookup, args.code[n_code - 1].a, args.code[at].b, 0};
+              args.code[at] = Code{kCodeLookup, args.code[n_code - 1].a, args.code[at].b, args.code[at].a};
               args.code[--n_code] = Code{kCodeEnd, 0, 0, 0};
             }
           } else {
