@@ -407,26 +407,6 @@ template <class F, class... E> struct ReadsAnywhere<Map<F, E...>> { static const
 template <class EI, class ES> struct ReadsAnywhere<Gather<EI, ES>> { static constexpr bool value = true; };
 template <class ES> struct ReadsAnywhere<Gather<Gen<GenIotaRev>, ES>> { static constexpr bool value = ReadsAnywhere<ES>::value; };
 
-// KeepLoads<E>::type is E with every external array read by ordinary loads
-// instead of non-temporal ones.  Streams are read non-temporally so that they do
-// not displace gathered arrays from the caches; a program that reads one array
-// forwards and mirrored wants the opposite: the second read of a line should find
-// it (measured on the reversed dot product at 2^26 elements: 1.37x the array's
-// bytes fetched with non-temporal loads, 1.00x with ordinary ones).
-template <int K, class T>
-struct InKeep : In<K, T> {
-  template <int Base> static __device__ __forceinline__ Vec4<T> eval4(const KArgs &a, int i) {
-    const Quad128<T> v = *reinterpret_cast<const Quad128<T> *>(static_cast<const T *>(a.in[K]) + i);
-    return Vec4<T>{{v.x, v.y, v.z, v.w}};
-  }
-};
-template <class E> struct KeepLoads { using type = E; };
-template <int K, class T> struct KeepLoads<In<K, T>> { using type = InKeep<K, T>; };
-template <class F, class... E> struct KeepLoads<Map<F, E...>> { using type = Map<F, typename KeepLoads<E>::type...>; };
-template <class EI, class ES> struct KeepLoads<Gather<EI, ES>> {
-  using type = Gather<typename KeepLoads<EI>::type, typename KeepLoads<ES>::type>;
-};
-
 // GatherChain<E> describes an element program that is a chain of one-argument maps over one
 // gather whose index is an external array read in order and whose source is again a chain of
 // one-argument maps over one external array (the table).  Its value at a position depends on

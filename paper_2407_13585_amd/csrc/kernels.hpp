@@ -80,16 +80,11 @@ __device__ __forceinline__ void for_each_group(unsigned n4, L &&load, U &&use) {
   if (n4 < SpreadBelow<E...>::value) for_each_group_of<1>(n4, load, use); else for_each_group_of<kUnroll>(n4, load, use);
 }
 
-// The same for element programs that read an array forwards and through
-// `reverse` (two traversal orders of one array in one loop, section 3.3
-// `simple5`).  Position i reads a[i] and a[n-1-i]; position n-1-i reads the same
-// two.  A lane therefore takes the 128-bit group at i together with its mirror
-// image at n4-4-i: the two groups issue the same two 128-bit reads, the second
-// pair hits in the vector cache, and the array comes from HBM once instead of
-// twice.  Every group of [0, n4) is used once.  Short arrays stay in the caches
-// whatever the order and are better spread over twice as many workgroups
-// (measured at 2^16 elements: 8.3 us plain, 9.8 us mirrored), so the kernels take
-// this path from kMirrorMin elements on.
+// Element programs that read an array forwards and through `reverse` (two traversal orders of one array in one
+// loop, section 3.3 reading two): a lane takes the 128-bit group at i together with its mirror image at n-4-i
+// (for_each_mirrored_pair), so that the array comes from HBM once instead of twice.  Short arrays stay in the caches
+// whatever the order and are better spread over twice as many workgroups (measured at 2^16 elements: 8.3 us
+// plain, 9.8 us mirrored), so the kernels take this path from kMirrorMin elements on.
 constexpr unsigned kMirrorMin = 1u << 20;
 // elements a workgroup takes per step of the loops above and below
 template <class... E> int tile_of(unsigned n) {
@@ -97,45 +92,16 @@ template <class... E> int tile_of(unsigned n) {
   if ((E::kMirror || ...) && n4 >= kMirrorMin) return 2 * kTile;
   return n4 < SpreadBelow<E...>::value ? kBlock * kVec : kTile;
 }
-template <class L, class U>
-__device__ __forceinline__ void for_each_mirrored_group(unsigned n4, L &&load, U &&use) {
-  const unsigned half = ((n4 / 4 + 1) / 2) * 4;     // the first half, the middle group included
-  // Every tile takes the guarded form here, on purpose: the second read of a line has
-  // to reach the vector cache while the first is still on its way, and that works best
-  // with few reads in flight per lane.  Measured on the reversed dot product at 2^26
-  // elements: 51 us in this form (the compiler waits after each group and its mirror
-  // image), 55 us with the sixteen reads of a tile issued back to back, 61 us with the
-  // mirror images read after the groups have been used.
-  for (unsigned base = blockIdx.x * kTile; base < half; base += gridDim.x * kTile) {
-    decltype(load(0u)) v[kUnroll][2];
-#pragma unroll
-    for (int u = 0; u < kUnroll; ++u) {
-      const unsigned i = base + u * (kBlock * kVec) + threadIdx.x * kVec;
-      if (i < half) {
-        v[u][0] = load(i);
-        v[u][1] = load(n4 - 4 - i);
-      }
-    }
-#pragma unroll
-    for (int u = 0; u < kUnroll; ++u) {
-      const unsigned i = base + u * (kBlock * kVec) + threadIdx.x * kVec;
-      if (i < half) {
-        use(i, v[u][0]);
-        if (n4 - 4 - i != i) use(n4 - 4 - i, v[u][1]);
-      }
-    }
-  }
-}
-
-// The same pairing when every `reverse` of the element program runs over exactly the n elements
-// of the iteration space (E::mirrors_whole): the groups at i and at n-4-i are evaluated together
-// (eval4_pair), every array read of the pair is issued once, so the streams can be read
+// For programs whose every `reverse` runs over exactly the n elements of the iteration space (E::mirrors_whole;
+// any gather has the size of its index array, so this fails only below another gather): the groups at i and
+// at n-4-i are evaluated together (eval4_pair), every array read of the pair is issued once, so the streams can be read
 // non-temporally like any other and a full tile has all its reads in flight.  Measured on the
-// reversed dot product at 2^26 elements: 52 us with for_each_mirrored_group, 43 us this way; a
+// reversed dot product at 2^26 elements: 52 us with each position's reads issued on their own (the second
+// read of a line from the vector cache), 43 us this way; a
 // read-only pass over as many bytes takes 39 us.  n need not be a multiple of anything: the
 // mirrored group starts on any 4-byte boundary, and the elements in the middle that no pair covers
-// (fewer than eight) go to one(i).  10000019 elements: 13.4 us with for_each_mirrored_group and the reverse
-// read an element at a time, 8.9 us this way.
+// (fewer than eight) go to one(i).  10000019 elements: 13.4 us with the reverse read an element at a time, 8.9 us
+// this way.
 template <class L, class U, class O>
 __device__ __forceinline__ void for_each_mirrored_pair(unsigned n, L &&load_pair, U &&use, O &&one) {
   const unsigned half = n / 8 * 4;                  // groups of the first half, each with its mirror image
@@ -197,8 +163,6 @@ __global__ __launch_bounds__(kBlock) void store_kernel(const Packed<kHeadN | kHe
       if (pairs)
         for_each_mirrored_pair(n, [&](unsigned i, unsigned ip) { return eval_pair<E>(a, i, ip); }, use,
                                [&](unsigned i) { out[i] = E::template eval<0>(a, (int)i); });
-      else if (n4 >= kMirrorMin)
-        for_each_mirrored_group(n4, [&](unsigned i) { return KeepLoads<E>::type::template eval4<0>(a, (int)i); }, use);
       else
         for_each_group<E>(n4, [&](unsigned i) { return E::template eval4<0>(a, (int)i); }, use);
     } else {
@@ -215,8 +179,6 @@ __global__ __launch_bounds__(kBlock) void store2_kernel(const Packed<kHeadN | kH
   const KArgs &a = packed.open();
   using T1 = typename E1::R;
   using T2 = typename E2::R;
-  using K1 = typename KeepLoads<E1>::type;
-  using K2 = typename KeepLoads<E2>::type;
   using Both = Two<Vec4<T1>, Vec4<T2>>;
   T1 *out1 = static_cast<T1 *>(a.out[0]);
   T2 *out2 = static_cast<T2 *>(a.out[1]);
@@ -227,12 +189,8 @@ __global__ __launch_bounds__(kBlock) void store2_kernel(const Packed<kHeadN | kH
       store4<decltype(keep)::value>(out1 + i, v.first);
       store4<decltype(keep)::value>(out2 + i, v.second);
     };
-    if ((E1::kMirror || E2::kMirror) && n4 >= kMirrorMin)
-      for_each_mirrored_group(
-          n4, [&](unsigned i) { return Both{K1::template eval4<0>(a, (int)i), K2::template eval4<E1::kNodes>(a, (int)i)}; }, use);
-    else
-      for_each_group<E1, E2>(
-          n4, [&](unsigned i) { return Both{E1::template eval4<0>(a, (int)i), E2::template eval4<E1::kNodes>(a, (int)i)}; }, use);
+    for_each_group<E1, E2>(
+        n4, [&](unsigned i) { return Both{E1::template eval4<0>(a, (int)i), E2::template eval4<E1::kNodes>(a, (int)i)}; }, use);
   });
   if (blockIdx.x == 0 && threadIdx.x < n - n4) {
     int i = (int)(n4 + threadIdx.x);
@@ -292,8 +250,6 @@ __global__ __launch_bounds__(kBlock) void fold_kernel(const Packed<kHeadN, 1u, E
     if (pairs)
       for_each_mirrored_pair(n, [&](unsigned i, unsigned ip) { return eval_pair<E>(a, i, ip); }, use,
                              [&](unsigned i) { acc = Op::apply(acc, E::template eval<0>(a, (int)i)); });
-    else if (n4 >= kMirrorMin)
-      for_each_mirrored_group(n4, [&](unsigned i) { return KeepLoads<E>::type::template eval4<0>(a, (int)i); }, use);
     else
       for_each_group<E>(n4, [&](unsigned i) { return E::template eval4<0>(a, (int)i); }, use);
   } else {
@@ -310,8 +266,6 @@ __global__ __launch_bounds__(kBlock) void store_fold_kernel(const Packed<kHeadN 
   const unsigned epoch = epoch_at_start(ctl);
   using T = typename Op::T;
   using S = typename ES::R;
-  using KS = typename KeepLoads<ES>::type;
-  using KF = typename KeepLoads<EF>::type;
   using Both = Two<Vec4<S>, Vec4<T>>;
   S *out = static_cast<S *>(a.out[0]);
   const unsigned n = (unsigned)a.n, n4 = n & ~3u;
@@ -322,12 +276,8 @@ __global__ __launch_bounds__(kBlock) void store_fold_kernel(const Packed<kHeadN 
 #pragma unroll
       for (int c = 0; c < 4; ++c) acc = Op::apply(acc, v.second.v[c]);
     };
-    if ((ES::kMirror || EF::kMirror) && n4 >= kMirrorMin)
-      for_each_mirrored_group(
-          n4, [&](unsigned i) { return Both{KS::template eval4<0>(a, (int)i), KF::template eval4<ES::kNodes>(a, (int)i)}; }, use);
-    else
-      for_each_group<ES, EF>(
-          n4, [&](unsigned i) { return Both{ES::template eval4<0>(a, (int)i), EF::template eval4<ES::kNodes>(a, (int)i)}; }, use);
+    for_each_group<ES, EF>(
+        n4, [&](unsigned i) { return Both{ES::template eval4<0>(a, (int)i), EF::template eval4<ES::kNodes>(a, (int)i)}; }, use);
   });
   if (blockIdx.x == 0 && threadIdx.x < n - n4) {
     int i = (int)(n4 + threadIdx.x);
