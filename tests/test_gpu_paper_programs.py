@@ -109,7 +109,7 @@ def test_scan_then_gather_and_scanr():
     rng = np.random.default_rng(5)
     g = PG.scan_then_gather()
     check(g, random_inputs(g, rng, {"is": PG.N, "xs": 100}), exact=("bs",), expect_clusters=2)
-    # scanr reads whole tiles in mirrored 128-bit groups when the length is a multiple of four
+    # scanr reads whole tiles in mirrored 128-bit groups, which start at any element
     for n in (1, 5, 4097, 100003, 100004, 3 * 12288, 12288 + 8):
         g = Graph()
         g.add("x", "input", "i32", (n,))
@@ -169,8 +169,8 @@ def test_scans_of_fp32():
     # prefix sums of fp32 arrays: the same single pass with the aggregates travelling as bit
     # patterns.  The kernel adds in a fixed tree order, the reference sums exactly and rounds once:
     # every prefix within 1e-5 of the magnitudes summed (the bound of the folds).  Lengths around
-    # the tile (8192), the 128-bit group and the group of 256 tiles; scanr with a length that is
-    # and is not a multiple of four (mirrored 128-bit reads, or element by element).
+    # the tile (8192), the 128-bit group and the group of 256 tiles; scanr with lengths that are
+    # and are not multiples of four (its mirrored 128-bit groups then start off a 128-bit boundary).
     rng = np.random.default_rng(12)
     for n in (1, 3, 8191, 8192, 8193, 100003, 100004, (1 << 21) + 8192 * 3 + 5, 1 << 22):
         g = Graph()

@@ -1,7 +1,7 @@
 """Parity of the HIP path (through the C ABI) with the CPU oracle, on the GPU.
 
-Every case runs the same seeded inputs through oracle.interp.evaluate and through
-fc_run_fused / fc_run_unfused and compares element by element under the rules of
+Every case runs the same seeded inputs through oracle.interp.evaluate and through a program bound by
+fc_bind (fused, or one kernel per combinator; fc_run_fused and fc_run_unfused are compared with it) and compares element by element under the rules of
 tests/parity.py.
 """
 import numpy as np
@@ -265,6 +265,37 @@ def test_spmv_rows_are_added_up_in_sixteen_sums_or_more(mean_len, own):
     assert np.all(off_by <= bound), (off_by - bound).max()
 
 
+@pytest.mark.parametrize("fn", ["add", "max"])
+@pytest.mark.parametrize("mean_len", [3, 100])
+def test_interpreted_rows_shared_by_the_wave(fn, mean_len):
+    # an interpreted term takes sixteen lanes a row and the whole wave from 128 elements on: rows of 128 elements,
+    # one more, around the 64 a wave takes per step, several in one wave, the first and the last row
+    lengths = np.random.default_rng(mean_len).poisson(mean_len, size=1003)
+    lengths[[0, 4, 5, 6, 7, 8, 9, 400, 1002]] = [129, 128, 128 + 63, 128 + 64, 128 + 65, 3000, 127, 5000, 700]
+    rng = np.random.default_rng(30 + mean_len)
+    n, ncols = int(lengths.sum()), 3000
+    g = Graph()
+    g.add("x", "input", "f32", (ncols,))
+    g.add("col", "input", "i32", (n,))
+    g.add("vals", "input", "f32", (n,))
+    g.add("off", "input", "i32", (len(lengths) + 1,))
+    g.add("e", "map", "f32", (ncols,), fn="sq_plus_one", args=("x",))
+    g.add("g", "gather", "f32", (n,), args=("col", "e"))
+    g.add("p", "map", "f32", (n,), fn="mul2", args=("vals", "g"))
+    g.add("y", "foldseg", "f32", (len(lengths),), fn=fn, args=("p", "off"), output=True)
+    ins = {"x": rng.uniform(-1.0, 1.0, ncols).astype(F32), "col": rng.integers(0, ncols, n).astype(np.int32),
+           "vals": rng.uniform(-1.0, 1.0, n).astype(F32), "off": np.concatenate([[0], np.cumsum(lengths)]).astype(np.int32)}
+    env = evaluate(g, ins)
+    g2, part = plan(g, True)
+    prog = device_program(g2, ins, part)
+    assert len(prog.kernels()) == 1 and "element programs interpreted" in prog.kernels()[0], prog.kernels()
+    prog.run()
+    if fn == "max":
+        P.assert_bit_exact(prog.fetch("y"), env["y"], "max")
+    else:
+        P.assert_segmented(prog.fetch("y"), env["y"], env["p"], ins["off"], "add")
+
+
 def test_spmv_skewed_rows():
     rng = np.random.default_rng(77)
     lengths = np.minimum(rng.zipf(1.5, size=5000), 20000).astype(np.int64)
@@ -522,11 +553,12 @@ def test_two_streams_each_with_its_own_scratch():
         assert words[1] == 0 and words[0] >= 6
 
 
-def test_step_replays_from_a_hip_graph():
-    # fc_run_fused only enqueues kernels (no allocation, no host synchronisation, no memset), so a
-    # caller can capture a step into a HIP graph.  Captured here: the five pipelines at small sizes
-    # plus the two kernels that hand data over through scratch (column-blocked SpMV, fold over sorted
-    # gather indices).  Every replay runs on other input values, with eager copies and
+@pytest.mark.parametrize("bound", [True, False])
+def test_step_replays_from_a_hip_graph(bound):
+    # fc_run_bound and fc_run_fused only enqueue kernels (no allocation, no host synchronisation, no
+    # memset), so a caller can capture a step into a HIP graph.  Captured here, through the one or the
+    # other: the five pipelines at small sizes plus the two kernels that hand data over through scratch
+    # (column-blocked SpMV, fold over sorted gather indices).  Every replay runs on other input values, with eager copies and
     # synchronisations in between, and is checked against the oracle.
     import torch
     rng = np.random.default_rng(77)
@@ -542,14 +574,21 @@ def test_step_replays_from_a_hip_graph():
         g, part = plan(w.graph, dup)
         progs.append(device_program(g, w.inputs, part))
     assert "column-blocked" in progs[5].kernels()[0] and "binned" in progs[6].kernels()[0]
+
+    def run(p):
+        if bound:
+            p.run()
+        else:
+            fc().fc_run_fused(p.cg, p.partition, p.buffers, p.scratch, torch.cuda.current_stream().cuda_stream)
+
     for p in progs:                                           # first launches outside the capture
-        p.run()
+        run(p)
     torch.cuda.synchronize()
     graph = torch.cuda.CUDAGraph()
     side = torch.cuda.Stream()
     with torch.cuda.graph(graph, stream=side):
         for p in progs:
-            p.run()
+            run(p)
     for rep in range(3):
         for (cfg, w, dup), p in zip(items, progs):
             for name, a in list(w.inputs.items()):
@@ -563,6 +602,42 @@ def test_step_replays_from_a_hip_graph():
             env = evaluate(w.graph, w.inputs)
             compare(cfg, w, env, p, w.graph.outputs(), f"replay{rep}")
             assert p.control_words()[1] == 0
+
+
+@pytest.mark.parametrize("cfg", [1, 2, 3, 4, 5, "force"])
+def test_direct_runs_give_the_results_of_a_bound_program(cfg):
+    # fc_run_fused and fc_run_unfused, which issue every launch from the call's own arguments, against the program
+    # bound once and run twice; the unfused arm with every intermediate in a buffer of the caller
+    import torch
+    if cfg == "force":                                       # its result in a buffer of its own: a copy among the launches
+        g = Graph()
+        g.add("x", "input", "f32", (10007,))
+        g.add("y", "map", "f32", (10007,), fn="sq_plus_one", args=("x",), output=True)
+        g.add("f", "force", "f32", (10007,), args=("y",), output=True)
+        g.add("r", "fold", "f32", (1,), fn="add", args=("f",), output=True)
+        w = C.Workload("force", g, {"x": np.random.default_rng(3).standard_normal(10007).astype(F32)}, 10007, "elements", 0, 0)
+    else:
+        w = build(cfg, small=True)
+    g, part = plan(w.graph, True)
+    stream = torch.cuda.current_stream().cuda_stream
+    for graph, p, bind in ((g, part, []), (w.graph, None, [n.name for n in w.graph.nodes if n.kind != "input"])):
+        bound = device_program(graph, w.inputs, p, bind=bind)
+        direct = device_program(graph, w.inputs, p, bind=bind)         # its tensors only
+        names = w.graph.outputs() + bind
+        for rep in range(2):
+            for prog in (bound, direct):
+                if cfg == 4:
+                    prog.upload("dest", w.inputs["dest"])
+            bound.run()
+            if p is None:
+                fc().fc_run_unfused(graph, direct.buffers, direct.scratch, stream)
+            else:
+                fc().fc_run_fused(graph, p, direct.buffers, direct.scratch, stream)
+            torch.cuda.synchronize()
+            for name in names:
+                P.assert_bit_exact(direct.fetch(name), bound.fetch(name), f"{w.name} rep={rep} {name}")
+        fc().fc_check(direct.scratch, stream)
+        assert direct.control_words()[0] == bound.control_words()[0]
 
 
 def test_fusion_rule_clusters_execute():

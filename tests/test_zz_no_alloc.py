@@ -38,8 +38,8 @@ def test_static_scratch_gives_the_results_of_a_caller_buffer():
             g = fc.fc_duplicate(w.graph)[0] if dup else w.graph
             part = fc.fc_plan(g, "bytes")
             assert fc.fc_scratch_bytes(g, part) <= B.FC_STATIC_SCRATCH_BYTES
-            ref = DeviceProgram(g, w.inputs, part)         # its own scratch buffer, fc_run_fused
-            ref.run()
+            ref = DeviceProgram(g, w.inputs, part)         # its own scratch buffer
+            fc.fc_run_fused(g, part, ref.buffers, ref.scratch, stream)
             got = DeviceProgram(g, w.inputs, part)         # used for its input and output tensors only
             for rep in range(2):
                 for o in g.outputs():
