@@ -21,9 +21,11 @@
 // 112 -> 98 us, 4096 x 4096 30.6 -> 22.4, 1024 x 1024 15.1 -> 6.3, 64 x 64 13.8 -> 5.1 (and grids
 // whose rows are no multiple of four went through the generic element program: 8192 x 8191
 // 269 -> 109 us, 1531 x 2477 22.4 -> 9.3).  Results are stored non-temporally: ordinary stores
-// leave dirty lines in the memory-side cache that the next kernel waits for (8192 x 8192 launched
-// back to back 104 - 120 us; inside the benchmark's step the stencil itself is faster with them,
-// 94 against 107 us, but the step is not, 607 against 602 us).
+// leave dirty lines in the memory-side cache that the next kernel waits for.  What the choice costs depends on what ran
+// before (8192 x 8192, us, before / now / now with ordinary stores): grids in turn 110 / 94 / 105, after idle 113 / 98
+// / 105, after a compaction 115 / 105 / 110; but right after a kernel that leaves dirty lines of its own
+// (a copy of 512 MiB) 95 / 119 / 101, where the two together take 316 / 306 / 300, with a fill 197 / 209 / 193; the
+// output the next call's input 98 / 97 / 108, 5800 x 5800 53 / 58 / 49, 4096 x 4096 31 / 32 / 24.
 #pragma once
 
 #include "kernels.hpp"
@@ -170,10 +172,12 @@ hipError_t launch_stencil5(const KArgs &a, const LaunchCtx &c) {
   if (a.n == 0 && !WithMax) return hipSuccess;
   const int strips = (a.w + kStripCols - 1) / kStripCols;
   const int units = strips * ((a.h + kBandRows - 1) / kBandRows);
-  // A unit per wave and as many workgroups as the fold's partials allow: the hardware hands the next
-  // workgroup out as one ends, and what runs at a time is one front of adjacent units per XCD.  With 4
-  // workgroups per compute unit that walk over the units 8192 x 8192 takes the same 98 us, but
-  // 7000 x 8001 100 us instead of 91 and 4096 x 4096 24 us instead of 22.4.
+  // A unit per wave, up to a round of the XCDs fewer workgroups than the fold has partials (the form without the fold
+  // keeps to the same number): the hardware hands the next workgroup out as one ends, and what runs at a time is one
+  // front of adjacent units per XCD; in larger grids a wave takes several units, a grid's length apart.  8192 workgroups, which
+  // give every wave of 8192 x 8192 two units, are slower than these 8184, which leave eight units per XCD for a
+  // third turn: 99.5 us against 94.7.  With 4 workgroups per compute unit that walk over the units 8192 x 8192 takes 98 us,
+  // but 7000 x 8001 100 us instead of 91 and 4096 x 4096 24 us instead of 22.4.
   const int blocks = std::min(std::max(8, ((units + kWavesPerBlock - 1) / kWavesPerBlock + 7) / 8 * 8), kMaxPartials - 8);
   return launch_k(&stencil5_kernel<F, FSlot, WithMax>, (unsigned)blocks, c, a, c.ctl, c.partials, strips, units);
 }
