@@ -113,8 +113,10 @@ struct KArgs {    // arguments of one cluster launch
     __builtin_memcpy(&word, __builtin_assume_aligned(&code[pc], 4), sizeof(word));
     return {(unsigned char)word, (unsigned char)(word >> 8), (unsigned char)(word >> 16), (unsigned char)(word >> 24)};
   }
+  unsigned grid;            // workgroups of the launch (see below, kernel arguments)
   unsigned flags;           // kSinglePass: a fold of the cluster carries FC_NODE_SINGLE_PASS;
                             // kKeepOut << k: out[k] is read back by a later cluster of the program
+  void set_grid(unsigned workgroups) { grid = workgroups; }
   __host__ __device__ bool keeps(int k) const { return (flags >> (8 + k)) & 1u; }
 };
 constexpr unsigned kSinglePass = 1u;
@@ -450,7 +452,10 @@ template <int KI, class ES> struct GatherChain<Gather<In<KI, int>, ES>> {
 // else: a kernel of 48 bytes of arguments takes the host 2.6 us to launch, one of 376 bytes 3.3 to 3.7, one of 1432 (KArgs
 // as a whole) 3.3 to 3.9.  So the kernels whose element programs are compiled take the parts of KArgs
 // these programs use, as Packed<...>, and open() puts them back where the program looks for them (registers:
-// every index is known when the kernel is compiled).
+// every index is known when the kernel is compiled).  The number of workgroups is one of the arguments: a kernel that
+// asks for gridDim has another 256 bytes of arguments that the launch fills in (an empty kernel of 48 bytes of arguments
+// 2.42 us a launch without and 2.85 with them, of 64 bytes 2.42 and 3.07; a call of a bound program of one kernel
+// 2.64 to 2.70 us on the host without, 2.66 to 2.88 with them).
 template <int K, class T, int LdsThreads, bool Early, int Columns> struct Interp;        // kernels.hpp: reads KArgs::code, needs all of it
 
 // the fields of a Slot as words: f[0], f[1], i[0], i[1], ext[0], ext[1], m[0], m[1], m[2]
@@ -526,6 +531,7 @@ template <unsigned Head, unsigned Outs, bool All, class... E> struct PackedArgs 
   static constexpr WordList kList = make_list();
   const void *in[kIns ? kIns : 1];
   void *out[kOuts ? kOuts : 1];
+  unsigned grid;
   unsigned word[kList.n ? kList.n : 1];
 
   // word W of KArgs, read or written
@@ -550,6 +556,7 @@ template <unsigned Head, unsigned Outs, bool All, class... E> struct PackedArgs 
     for (int k = 0, o = 0; k < kMaxOut; ++k) if (Outs >> k & 1u) out[o++] = a.out[k];
     pack_words(a, std::make_integer_sequence<int, kList.n>());
   }
+  void set_grid(unsigned workgroups) { grid = workgroups; }
   __device__ __forceinline__ KArgs open() const {
     KArgs a;
 #pragma unroll
@@ -557,6 +564,7 @@ template <unsigned Head, unsigned Outs, bool All, class... E> struct PackedArgs 
     int o = 0;
 #pragma unroll
     for (int k = 0; k < kMaxOut; ++k) if (Outs >> k & 1u) a.out[k] = out[o++];
+    a.grid = grid;
     open_words(a, std::make_integer_sequence<int, kList.n>());
     return a;
   }
@@ -564,6 +572,7 @@ template <unsigned Head, unsigned Outs, bool All, class... E> struct PackedArgs 
 template <unsigned Head, unsigned Outs, class... E> struct PackedArgs<Head, Outs, true, E...> {
   KArgs args;
   PackedArgs(const KArgs &a) : args(a) {}
+  void set_grid(unsigned workgroups) { args.set_grid(workgroups); }
   __device__ __forceinline__ const KArgs &open() const { return args; }
 };
 template <unsigned Head, unsigned Outs, class... E> using Packed = PackedArgs<Head, Outs, (Needs<E>::all || ... || false), E...>;

@@ -52,9 +52,9 @@ __device__ __forceinline__ void store4_lds(T *p, const Vec4<T> &v) {
 template <class A, class B> struct Two { A first; B second; };
 
 template <int Unroll, class L, class U>
-__device__ __forceinline__ void for_each_group_of(unsigned n4, L &&load, U &&use) {
+__device__ __forceinline__ void for_each_group_of(unsigned n4, unsigned grid, L &&load, U &&use) {
   constexpr unsigned kStep = kBlock * kVec * Unroll;
-  for (unsigned base = blockIdx.x * kStep; base < n4; base += gridDim.x * kStep) {
+  for (unsigned base = blockIdx.x * kStep; base < n4; base += grid * kStep) {
     const unsigned i0 = base + threadIdx.x * kVec;
     decltype(load(0u)) v[Unroll];
     if (base + kStep <= n4) {
@@ -76,8 +76,8 @@ __device__ __forceinline__ void for_each_group_of(unsigned n4, L &&load, U &&use
 // hide and more to lose in the last stage of its fold: 300001 elements 4.4 -> 3.8 us, 10^6 4.6 -> 5.3.
 template <class... E> struct SpreadBelow { static constexpr unsigned value = (ReadsAnywhere<E>::value || ...) ? 1u << 21 : 1u << 19; };
 template <class... E, class L, class U>
-__device__ __forceinline__ void for_each_group(unsigned n4, L &&load, U &&use) {
-  if (n4 < SpreadBelow<E...>::value) for_each_group_of<1>(n4, load, use); else for_each_group_of<kUnroll>(n4, load, use);
+__device__ __forceinline__ void for_each_group(unsigned n4, unsigned grid, L &&load, U &&use) {
+  if (n4 < SpreadBelow<E...>::value) for_each_group_of<1>(n4, grid, load, use); else for_each_group_of<kUnroll>(n4, grid, load, use);
 }
 
 // Element programs that read an array forwards and through `reverse` (two traversal orders of one array in one
@@ -103,9 +103,9 @@ template <class... E> int tile_of(unsigned n) {
 // (fewer than eight) go to one(i).  10000019 elements: 13.4 us with the reverse read an element at a time, 8.9 us
 // this way.
 template <class L, class U, class O>
-__device__ __forceinline__ void for_each_mirrored_pair(unsigned n, L &&load_pair, U &&use, O &&one) {
+__device__ __forceinline__ void for_each_mirrored_pair(unsigned n, unsigned grid, L &&load_pair, U &&use, O &&one) {
   const unsigned half = n / 8 * 4;                  // groups of the first half, each with its mirror image
-  for (unsigned base = blockIdx.x * kTile; base < half; base += gridDim.x * kTile) {
+  for (unsigned base = blockIdx.x * kTile; base < half; base += grid * kTile) {
     decltype(load_pair(0u, 0u)) v[kUnroll];
     const unsigned i0 = base + threadIdx.x * kVec;
     if (base + kTile <= half) {
@@ -161,12 +161,12 @@ __global__ __launch_bounds__(kBlock) void store_kernel(const Packed<kHeadN | kHe
     auto use = [&](unsigned i, const Vec4<T> &v) { store4<decltype(keep)::value>(out + i, v); };
     if constexpr (E::kMirror) {
       if (pairs)
-        for_each_mirrored_pair(n, [&](unsigned i, unsigned ip) { return eval_pair<E>(a, i, ip); }, use,
+        for_each_mirrored_pair(n, a.grid, [&](unsigned i, unsigned ip) { return eval_pair<E>(a, i, ip); }, use,
                                [&](unsigned i) { out[i] = E::template eval<0>(a, (int)i); });
       else
-        for_each_group<E>(n4, [&](unsigned i) { return E::template eval4<0>(a, (int)i); }, use);
+        for_each_group<E>(n4, a.grid, [&](unsigned i) { return E::template eval4<0>(a, (int)i); }, use);
     } else {
-      for_each_group<E>(n4, [&](unsigned i) { return E::template eval4<0>(a, (int)i); }, use);
+      for_each_group<E>(n4, a.grid, [&](unsigned i) { return E::template eval4<0>(a, (int)i); }, use);
     }
   });
   if (!pairs && blockIdx.x == 0 && threadIdx.x < n - n4) out[n4 + threadIdx.x] = E::template eval<0>(a, (int)(n4 + threadIdx.x));
@@ -190,7 +190,7 @@ __global__ __launch_bounds__(kBlock) void store2_kernel(const Packed<kHeadN | kH
       store4<decltype(keep)::value>(out2 + i, v.second);
     };
     for_each_group<E1, E2>(
-        n4, [&](unsigned i) { return Both{E1::template eval4<0>(a, (int)i), E2::template eval4<E1::kNodes>(a, (int)i)}; }, use);
+        n4, a.grid, [&](unsigned i) { return Both{E1::template eval4<0>(a, (int)i), E2::template eval4<E1::kNodes>(a, (int)i)}; }, use);
   });
   if (blockIdx.x == 0 && threadIdx.x < n - n4) {
     int i = (int)(n4 + threadIdx.x);
@@ -213,7 +213,7 @@ __device__ __forceinline__ void fold_finish(typename Op::T acc, const KArgs &a, 
   using T = typename Op::T;
   __shared__ T lds[Waves + 1];
   T r = block_reduce<Op, Waves>(acc, lds);
-  if (gridDim.x == 1 && earlier == 0) {            // nothing to hand over, no tag used
+  if (a.grid == 1 && earlier == 0) {            // nothing to hand over, no tag used
     if (threadIdx.x == 0) *static_cast<T *>(a.out[out_slot]) = r;
     return;
   }
@@ -221,9 +221,9 @@ __device__ __forceinline__ void fold_finish(typename Op::T acc, const KArgs &a, 
   if (threadIdx.x == 0) store_agent64(&partials[earlier + blockIdx.x], pack_word((unsigned)as_bits(r), tag, 1u));
   // the workgroup with the highest index is dispatched last; it waits for the
   // partials of all others and combines them in index order
-  if (blockIdx.x == gridDim.x - 1) {
+  if (blockIdx.x == a.grid - 1) {
     T s = Op::identity();
-    for_tagged_words<Waves * kWave>(partials, earlier + gridDim.x, tag, ctl, [&](unsigned long long w) {
+    for_tagged_words<Waves * kWave>(partials, earlier + a.grid, tag, ctl, [&](unsigned long long w) {
       s = Op::apply(s, w ? from_bits<T>((int)(unsigned)(w >> 32)) : Op::identity());
     });
     s = block_reduce<Op, Waves>(s, lds);
@@ -248,12 +248,12 @@ __global__ __launch_bounds__(kBlock) void fold_kernel(const Packed<kHeadN, 1u, E
   const bool pairs = mirrored_pairs<E>(a, n);
   if constexpr (E::kMirror) {
     if (pairs)
-      for_each_mirrored_pair(n, [&](unsigned i, unsigned ip) { return eval_pair<E>(a, i, ip); }, use,
+      for_each_mirrored_pair(n, a.grid, [&](unsigned i, unsigned ip) { return eval_pair<E>(a, i, ip); }, use,
                              [&](unsigned i) { acc = Op::apply(acc, E::template eval<0>(a, (int)i)); });
     else
-      for_each_group<E>(n4, [&](unsigned i) { return E::template eval4<0>(a, (int)i); }, use);
+      for_each_group<E>(n4, a.grid, [&](unsigned i) { return E::template eval4<0>(a, (int)i); }, use);
   } else {
-    for_each_group<E>(n4, [&](unsigned i) { return E::template eval4<0>(a, (int)i); }, use);
+    for_each_group<E>(n4, a.grid, [&](unsigned i) { return E::template eval4<0>(a, (int)i); }, use);
   }
   if (!pairs && blockIdx.x == 0 && threadIdx.x < n - n4) acc = Op::apply(acc, E::template eval<0>(a, (int)(n4 + threadIdx.x)));
   fold_finish<Op>(acc, a, 0, ctl, partials, epoch);
@@ -277,7 +277,7 @@ __global__ __launch_bounds__(kBlock) void store_fold_kernel(const Packed<kHeadN 
       for (int c = 0; c < 4; ++c) acc = Op::apply(acc, v.second.v[c]);
     };
     for_each_group<ES, EF>(
-        n4, [&](unsigned i) { return Both{ES::template eval4<0>(a, (int)i), EF::template eval4<ES::kNodes>(a, (int)i)}; }, use);
+        n4, a.grid, [&](unsigned i) { return Both{ES::template eval4<0>(a, (int)i), EF::template eval4<ES::kNodes>(a, (int)i)}; }, use);
   });
   if (blockIdx.x == 0 && threadIdx.x < n - n4) {
     int i = (int)(n4 + threadIdx.x);
@@ -583,7 +583,7 @@ __global__ __launch_bounds__(kBlock, LdsThreads ? 1 : 4) void interp_kernel(cons
   constexpr unsigned kGroup = kBlock * kVec, kTileOf = kGroup * G;
   unsigned none[InterpAhead<G, Early>::V], none4[kVec], none1[1];
   const unsigned whole = n4 / kTileOf * kTileOf;
-  for (unsigned base = blockIdx.x * kTileOf; base < (G > 1 ? whole : n4); base += gridDim.x * kTileOf) {
+  for (unsigned base = blockIdx.x * kTileOf; base < (G > 1 ? whole : n4); base += a.grid * kTileOf) {
     const unsigned i = base + threadIdx.x * kVec;
     if (G == 1 && i >= n4) break;
     InterpAhead<G, Early> ahead;
@@ -606,17 +606,17 @@ __global__ __launch_bounds__(kBlock, LdsThreads ? 1 : 4) void interp_kernel(cons
   }
   if (n_folds == 0) return;                              // the same for the whole grid
   // as fold_finish, for up to two accumulators under one tag: fold k keeps its partials at
-  // [k * gridDim.x, (k + 1) * gridDim.x); the last workgroup combines them and takes the next tag
+  // [k * a.grid, (k + 1) * a.grid); the last workgroup combines them and takes the next tag
   const unsigned tag = tag_of_epoch(epoch);
   for (int k = 0; k < n_folds; ++k) {
     const unsigned r = interp_block_reduce(k == 0 ? fold_op[0] : fold_op[1], k == 0 ? acc[0] : acc[1], lds);
-    if (threadIdx.x == 0) store_agent64(&partials[(size_t)k * gridDim.x + blockIdx.x], pack_word(r, tag, 1u));
+    if (threadIdx.x == 0) store_agent64(&partials[(size_t)k * a.grid + blockIdx.x], pack_word(r, tag, 1u));
   }
-  if (blockIdx.x != gridDim.x - 1) return;
+  if (blockIdx.x != a.grid - 1) return;
   for (int k = 0; k < n_folds; ++k) {
     const int op = k == 0 ? fold_op[0] : fold_op[1];
     unsigned s = interp_identity(op);
-    for_tagged_words<kBlock>(partials + (size_t)k * gridDim.x, gridDim.x, tag, ctl, [&](unsigned long long w) {
+    for_tagged_words<kBlock>(partials + (size_t)k * a.grid, a.grid, tag, ctl, [&](unsigned long long w) {
       s = interp_fold(op, s, w ? (unsigned)(w >> 32) : interp_identity(op));
     });
     s = interp_block_reduce(op, s, lds);
@@ -717,7 +717,7 @@ __global__ __launch_bounds__(kBlock) void bin_indices_kernel(const KArgs a, Cont
   const unsigned wave = (unsigned)wave_id(), lane = (unsigned)lane_id();
   constexpr unsigned kNone = 0xffu;                    // range of a position past the end
   T acc = Op::identity();
-  for (unsigned tile = blockIdx.x; tile < tiles; tile += gridDim.x) {
+  for (unsigned tile = blockIdx.x; tile < tiles; tile += a.grid) {
     unsigned filled = 0;                               // thread b < kBins: entries in slot (b, tile) so far
     for (unsigned pass = 0; pass < (unsigned)kBinPasses; ++pass) {
       const unsigned first = tile * kBinTile + pass * kBinPass;
@@ -830,7 +830,7 @@ __global__ __launch_bounds__(kBlock) void fold_binned_kernel(const KArgs a, Cont
   using Leaf = typename C::Leaf;
   constexpr unsigned kXcds = 8;                        // workgroup b runs on XCD b % 8
   constexpr int kPastL2 = 0x12;                        // cache policy of the buffer loads: sc1 | nt
-  const unsigned xcd = blockIdx.x % kXcds, team = blockIdx.x / kXcds, teams = gridDim.x / kXcds;
+  const unsigned xcd = blockIdx.x % kXcds, team = blockIdx.x / kXcds, teams = a.grid / kXcds;
   const unsigned wave = (unsigned)wave_id(), lane = (unsigned)lane_id();
   // raw buffer views: byte offsets, and an offset past the end reads as zero without a memory access
   const unsigned slots = kBins * tiles;
@@ -1005,7 +1005,7 @@ __global__ __launch_bounds__(kFineBlock) void bin_fine_kernel(const KArgs a, Con
   clear_counters();
   for (unsigned q = threadIdx.x; q < kChunks; q += kFineBlock) image[q] = nothing;
   __syncthreads();
-  for (unsigned tile = blockIdx.x; tile < tiles; tile += gridDim.x) {
+  for (unsigned tile = blockIdx.x; tile < tiles; tile += a.grid) {
     const unsigned base = tile * kFineTile + threadIdx.x * kVec;
     // rank of every element among the wave's elements of its range (range << 16 | rank is kept).  An index
     // outside the table (undefined anyway) gets the last range, so that everything stays inside LDS.
@@ -1064,7 +1064,7 @@ __global__ __launch_bounds__(kFineBlock) void bin_fine_kernel(const KArgs a, Con
           if (left >> c & 1u) acc = Op::apply(acc, val);
         }
       }
-      v[u] = fetch_group(tile + gridDim.x, u);
+      v[u] = fetch_group(tile + a.grid, u);
     }
     __syncthreads();
     // the image goes to the tile's slots as it is, 128 bits a thread and step, and is emptied on the way;
@@ -1129,7 +1129,7 @@ __global__ __launch_bounds__(kFineBlock) void fold_fine_kernel(const KArgs a, Co
   RawI v[kAhead];
 #pragma unroll
   for (int u = 0; u < kAhead; ++u) v[u] = fetch_group(blockIdx.x, u);
-  for (unsigned b = blockIdx.x; b < cut.bins; b += gridDim.x) {
+  for (unsigned b = blockIdx.x; b < cut.bins; b += a.grid) {
     const unsigned lo = b * cut.range;
     const unsigned len = min(cut.range, elems - lo), len4 = len & ~3u;
     // the range's slots lie one behind the other: one stream of 128-bit groups
@@ -1157,7 +1157,7 @@ __global__ __launch_bounds__(kFineBlock) void fold_fine_kernel(const KArgs a, Co
       if (i < len4) *reinterpret_cast<RawI *>(&slice[i]) = val;
       if (u < kInFlight)
         w[u] = __builtin_bit_cast(Raw, __builtin_amdgcn_raw_buffer_load_b128(slot_buf, (int)((threadIdx.x + u * kFineBlock) * 16u), 0, kStream));
-      v[u] = fetch_group(b + gridDim.x, u);
+      v[u] = fetch_group(b + a.grid, u);
     }
     if (threadIdx.x < len - len4) slice[len4 + threadIdx.x] = C::template from_leaf<0>(a, table[lo + len4 + threadIdx.x]);
     __syncthreads();
@@ -1202,7 +1202,7 @@ __global__ __launch_bounds__(kBlock) void foldseg_kernel(const Packed<kHeadAux |
   T *y = static_cast<T *>(a.out[0]);
   const unsigned rows = (unsigned)a.aux;
   const unsigned sub = threadIdx.x % L;
-  const unsigned rows_per_step = gridDim.x * (kBlock / L);
+  const unsigned rows_per_step = a.grid * (kBlock / L);
   // every lane of a wave runs the same number of steps so the cross-lane moves stay converged
   const unsigned steps = (rows + rows_per_step - 1) / rows_per_step;
   for (unsigned s = 0; s < steps; ++s) {
@@ -1305,7 +1305,7 @@ __global__ __launch_bounds__(kBlock) void foldseg_blocked_kernel(const KArgs a, 
   T *y = static_cast<T *>(a.out[0]);
   const unsigned rows = (unsigned)a.aux;
   const unsigned n_units = (rows + kBlockedRows - 1) / kBlockedRows;
-  const unsigned q = blockIdx.x % kQuarters, team = blockIdx.x / kQuarters, teams = gridDim.x / kQuarters;
+  const unsigned q = blockIdx.x % kQuarters, team = blockIdx.x / kQuarters, teams = a.grid / kQuarters;
   const unsigned lo_col = q * (unsigned)range_len;
   const unsigned epoch = load_agent(&ctl->epoch);
   const unsigned tag = tag_of_epoch(epoch);
@@ -1457,8 +1457,8 @@ __global__ __launch_bounds__(kBlock) void foldseg_blocked_kernel(const KArgs a, 
   if (prev != ~0u && q == prev % kQuarters) combine(prev, sums_of[(iter & 1) ^ 1]);
   // every workgroup has taken its tag once its word is out; the last one then moves the epoch on
   if (threadIdx.x == 0) store_agent64(&partials[blockIdx.x], pack_word(0u, tag, 1u));
-  if (blockIdx.x == gridDim.x - 1) {
-    for (unsigned k = threadIdx.x; k < gridDim.x; k += kBlock) (void)wait_word(&partials[k], tag, ctl);
+  if (blockIdx.x == a.grid - 1) {
+    for (unsigned k = threadIdx.x; k < a.grid; k += kBlock) (void)wait_word(&partials[k], tag, ctl);
     __syncthreads();
     if (threadIdx.x == 0) store_agent(&ctl->epoch, epoch + 1u);
   }
@@ -1557,7 +1557,7 @@ __global__ __launch_bounds__(kSegBlock) void seg_bin_kernel(const KArgs a, unsig
   for (unsigned q = threadIdx.x; q < words / 4u; q += kSegBlock) image[q] = nothing;
   if (threadIdx.x == 0) listed = 0u;
   __syncthreads();
-  for (unsigned tile = blockIdx.x; tile < tiles; tile += gridDim.x) {
+  for (unsigned tile = blockIdx.x; tile < tiles; tile += a.grid) {
     if (threadIdx.x == 0) listed = 0u;                      // read last before the barrier that ended the tile before; added to after the next two
     const unsigned first = threadIdx.x * kVec;              // this thread's first position in the tile, group 0
     const unsigned base = tile * kSegTile;
@@ -1627,7 +1627,7 @@ __global__ __launch_bounds__(kSegBlock) void seg_bin_kernel(const KArgs a, unsig
           waiting += more;
         }
       }
-      v[u] = fetch_group(tile + gridDim.x, u);
+      v[u] = fetch_group(tile + a.grid, u);
     }
     if (waiting != 0u) append();
     __syncthreads();
@@ -1710,7 +1710,7 @@ __global__ __launch_bounds__(kSegBlock) void seg_gather_kernel(const KArgs a, co
     {
       const unsigned *row_start = reinterpret_cast<const unsigned *>(a.in[kMaxIn - 1]);
       const unsigned rows = (unsigned)a.aux;
-      for (unsigned t = blockIdx.x * kSegWaves + (unsigned)wave_id(); t < plan.tiles; t += gridDim.x * kSegWaves) {
+      for (unsigned t = blockIdx.x * kSegWaves + (unsigned)wave_id(); t < plan.tiles; t += a.grid * kSegWaves) {
         const unsigned r = wave_rows_below(row_start, rows, t * kSegTile);
         if (lane_id() == 0) first_row[t] = r;
       }
@@ -2647,7 +2647,7 @@ __global__ __launch_bounds__(kBlock) void rowscan_kernel(const KArgs a) {
   // unsigned throughout: the steps past the last row and past a row's end must not wrap
   const unsigned rows = (unsigned)a.aux, w = (unsigned)a.w;
   const unsigned sub = threadIdx.x % L, which = threadIdx.x / L;
-  for (unsigned r0 = blockIdx.x * kRows; r0 < rows; r0 += gridDim.x * kRows) {
+  for (unsigned r0 = blockIdx.x * kRows; r0 < rows; r0 += a.grid * kRows) {
     const unsigned r = r0 + which;
     T carry = T();
     // every lane runs the same number of steps, so DPP and the barriers stay converged
@@ -2712,7 +2712,7 @@ __global__ __launch_bounds__(kBlock) void scatter_kernel(const Packed<kHeadN, 1u
   V *dest = static_cast<V *>(a.out[0]);
   const unsigned n = (unsigned)a.n, n4 = n & ~3u;
   for_each_group<EI, EV, EF>(
-      n4,
+      n4, a.grid,
       [&](unsigned i) {
         return Item{EF::template eval4<EI::kNodes + EV::kNodes>(a, (int)i), EI::template eval4<0>(a, (int)i),
                     EV::template eval4<EI::kNodes>(a, (int)i)};
@@ -2756,9 +2756,9 @@ __global__ __launch_bounds__(kBlock) void rowfold_kernel(const KArgs a) {
   const unsigned rows = (unsigned)a.aux, m = (unsigned)a.w;
   constexpr unsigned kRowsPerBlock = kBlock / L;
   const unsigned sub = threadIdx.x % L;
-  const unsigned steps = (rows + gridDim.x * kRowsPerBlock - 1) / (gridDim.x * kRowsPerBlock);
+  const unsigned steps = (rows + a.grid * kRowsPerBlock - 1) / (a.grid * kRowsPerBlock);
   for (unsigned s = 0; s < steps; ++s) {          // same trip count for every thread: barriers and DPP stay converged
-    const unsigned r = (s * gridDim.x + blockIdx.x) * kRowsPerBlock + threadIdx.x / L;
+    const unsigned r = (s * a.grid + blockIdx.x) * kRowsPerBlock + threadIdx.x / L;
     T acc1 = Op1::identity();
     typename Op2::T acc2 = Op2::identity();
     if (r < rows) {
@@ -2849,9 +2849,9 @@ __global__ __launch_bounds__(kBlock) void rowfold_split_kernel(const KArgs a, Co
     static_cast<T *>(a.out[0])[r] = s1;
     if (kTwo) static_cast<U *>(a.out[1])[r] = s2;
   }
-  if (blockIdx.x == gridDim.x - 1) {
+  if (blockIdx.x == a.grid - 1) {
     // every workgroup has taken its tag once its word is visible
-    for (unsigned k = threadIdx.x; k < gridDim.x; k += kBlock) (void)wait_word(&partials[k], tag, ctl);
+    for (unsigned k = threadIdx.x; k < a.grid; k += kBlock) (void)wait_word(&partials[k], tag, ctl);
     __syncthreads();
     if (threadIdx.x == 0) store_agent(&ctl->epoch, epoch + 1u);
   }

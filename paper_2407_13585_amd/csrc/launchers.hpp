@@ -54,6 +54,7 @@ hipError_t launch_impl(void (*k)(P...), dim3 grid, dim3 block, const LaunchCtx &
 template <class... P, class... A>
 hipError_t launch_threads(void (*k)(P...), unsigned grid, const LaunchCtx &c, int block, const A &...a) {
   std::tuple<P...> vals(static_cast<P>(a)...);          // KArgs becomes the kernel's PackedArgs here
+  std::get<0>(vals).set_grid(grid);                     // every kernel's first argument is one of the two
   return launch_impl(k, dim3(grid), dim3(block), c, vals, std::index_sequence_for<P...>());
 }
 template <class... P, class... A>

@@ -94,7 +94,7 @@ __global__ __launch_bounds__(kBlock) void stencil5_kernel(const Packed<kHeadH | 
   // halo rows are re-read from its own L2
   const int per_xcd = ((n_units + kWavesPerBlock - 1) / kWavesPerBlock + 7) / 8 * kWavesPerBlock;
   const int first = (int)(blockIdx.x % 8) * per_xcd, end = min(first + per_xcd, n_units);
-  const int stride = (int)(gridDim.x / 8) * kWavesPerBlock;
+  const int stride = (int)(a.grid / 8) * kWavesPerBlock;
   RawRow raw[kBandRows + 2];                     // rows r0-1 .. r0+kBandRows of the unit that is worked on next
   float hraw[kBandRows];
   auto fetch = [&](int unit) {
