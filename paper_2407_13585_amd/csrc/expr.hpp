@@ -81,7 +81,8 @@ enum : unsigned char {
   kCodeLookup,  // a = external array, b = 1 + k: push its element at the index that array direct[k] (c) holds
   kCodeStore,   // a = output array: pop a value into it at the element's own position
   kCodeFold,    // a = output array, b = reducer (kFold...), c = accumulator: pop a value into it
-  kCodeYield    // the value on the stack is the result of this element program (Interp<K, T>)
+  kCodeYield,   // the value on the stack is the result of this element program (Interp<K, T>)
+  kCodeTable    // push what kCodeLookup would, from where the kernel has left it (interp_table_kernel)
 };
 // in Code::op of a store or a fold: the value stays on the stack (an array with several consumers is computed once)
 constexpr unsigned char kCodeStays = 0x80;
@@ -90,32 +91,36 @@ constexpr int kInterpDirect = 4;      // arrays of an element program that are r
 enum : unsigned char { kFoldAddF32 = 0, kFoldMaxF32, kFoldMulF32, kFoldAddI32, kFoldMaxI32 };
 struct Code { unsigned char op, a, b, c; };
 
+// What an interpreted program needs before its first read of an array comes first, in as few cache lines as it fits: a
+// launch finds its arguments in no cache.
 struct KArgs {    // arguments of one cluster launch
+  int n;                    // iteration size
+  unsigned grid;            // workgroups of the launch (see below, kernel arguments)
+  unsigned flags;           // kSinglePass: a fold of the cluster carries FC_NODE_SINGLE_PASS;
+                            // kKeepOut << k: out[k] is read back by a later cluster of the program
+  unsigned char n_folds, fold_op[kInterpFolds], fold_out[kInterpFolds];   // of a cluster that interp_kernel runs
+  unsigned char code_depth, code_gathers;   // values below the top of the stack and nested gathers that `code` needs
+  const void *ahead[kInterpDirect];         // the arrays direct[0] names, where the kernel's launch has put them
   const void *in[kMaxIn];   // external arrays read by the cluster
   void *out[kMaxOut];       // arrays the cluster writes
-  int n;                    // iteration size
+  Code code[kMaxCode];      // kCodeEnd after the last instruction
   int w;                    // inner extent of 2-D index functions (1 for 1-D)
   int h;                    // outer extent
   int aux;                  // skeleton specific (rows of a segmented fold, ...)
+  unsigned lookup_elems;    // elements of the array that the first kCodeLookup reads from, 0: there is none
   Slot p[kMaxSlots];
-  Code code[kMaxCode];      // kCodeEnd after the last instruction
   unsigned root[kMaxRoots];        // where element program K of a cluster with another consumer starts in `code`
   // External arrays that element program K reads at the element's own position (the first kInterpDirect of
   // them): known before the program runs, so their reads are issued together and ahead of it.
   unsigned char direct[kMaxRoots][kInterpDirect], n_direct[kMaxRoots];
-  unsigned char code_depth, code_gathers;   // values below the top of the stack and nested gathers that `code` needs
-  unsigned char n_folds, fold_op[kInterpFolds], fold_out[kInterpFolds];   // of a cluster that interp_kernel runs
   // An instruction as one word: at an index that is the same for all lanes a scalar read, where the compiler may read
-  // four bytes through the vector unit (row scans of 2^24 interpreted elements 107 us, with words 101).  The kernel that
-  // reads ahead of the run has scalar reads as it is, and came out slower with words (fold of 2^24 elements 35.7, 37.7).
+  // four bytes through the vector unit (row scans of 2^24 interpreted elements 107 us, with words 101).  The scatters, which
+  // read ahead of the run, have scalar reads as it is.
   __device__ __forceinline__ Code code_word(int pc) const {
     unsigned word;
     __builtin_memcpy(&word, __builtin_assume_aligned(&code[pc], 4), sizeof(word));
     return {(unsigned char)word, (unsigned char)(word >> 8), (unsigned char)(word >> 16), (unsigned char)(word >> 24)};
   }
-  unsigned grid;            // workgroups of the launch (see below, kernel arguments)
-  unsigned flags;           // kSinglePass: a fold of the cluster carries FC_NODE_SINGLE_PASS;
-                            // kKeepOut << k: out[k] is read back by a later cluster of the program
   void set_grid(unsigned workgroups) { grid = workgroups; }
   __host__ __device__ bool keeps(int k) const { return (flags >> (8 + k)) & 1u; }
 };

@@ -225,30 +225,6 @@ const std::vector<Instance> &registry() {
   return r;
 }
 
-template <int G, int Depth, int Nest, int LdsThreads, bool Early> static hipError_t launch_interp_as(const KArgs &a, const LaunchCtx &c) {
-  // a fold of the cluster keeps a partial per workgroup; there may be kInterpFolds of them
-  const unsigned cap = std::min<unsigned>(resident_grid(&interp_kernel<G, Depth, Nest, LdsThreads, Early>), kMaxPartials / kInterpFolds);
-  // never less than the G workgroups that share out what is left behind the last whole tile
-  return launch_k(&interp_kernel<G, Depth, Nest, LdsThreads, Early>, std::max<unsigned>(grid_for(a.n, kBlock * kVec * G, cap), G), c, a, c.ctl, c.partials);
-}
-static hipError_t launch_interp(const KArgs &a, const LaunchCtx &c) {
-  // Two groups a lane where the program's values fit the registers that way and the chip is full: of 2^22
-  // elements 20.4 us instead of 25.8 (table of 4 KiB), of 10^6 the same 10.6.  Programs that need no more
-  // than two values below the top of the stack take a variant with more workgroups on a compute unit.
-  const bool small_code = a.code_depth <= 2 && a.code_gathers <= 1;
-  if (small_code && a.n >= (1 << 20)) return launch_interp_as<2, 2, 1, 0, true>(a, c);
-  if (small_code) return launch_interp_as<1, 2, 1, 0, true>(a, c);
-  return launch_interp_as<1, kInterpDepth, kInterpGathers, kBlock, false>(a, c);
-}
-const Instance *interpreter_instance() {
-  static const Instance inst = [] {
-    Instance i{"", &launch_interp};
-    i.variant = "interpreted";
-    return i;
-  }();
-  return &inst;
-}
-
 const Instance *find_instance(const std::string &sig, const KArgs &a) {
   for (const Instance &i : registry())
     if (i.sig == sig && (!i.accept || i.accept(a))) return &i;

@@ -290,18 +290,15 @@ __global__ __launch_bounds__(kBlock) void store_fold_kernel(const Packed<kHeadN 
 // ------------------------------------------------------------------ interpreted elementwise clusters
 // Any cluster of maps, generates and gathers that ends in up to kMaxOut stored arrays
 // or in stored arrays and up to two folds, for which no kernel was compiled: the element
-// programs are run from KArgs::code, four elements per lane at a time.  The value stack is in
-// registers (the compiler indexes them through the hardware's register index mode: the
-// index is the same for all lanes) or in LDS, the positions that gathers suspend, at most
+// programs are run from KArgs::code, four elements per lane at a time.  The value stack is in LDS (or, for the
+// scatters, in registers, which the compiler indexes through the hardware's register index mode: the
+// index is the same for all lanes), the positions that gathers suspend, at most
 // kInterpGathers deep, in registers.  Every branch depends on the code only, which
 // is the same for all lanes.  Results are the same as a compiled instance's: the same
 // element functions, applied in the same order.  A fallback: several times the
-// instructions of a compiled instance per element.
-// Bound by latency (a chain of one read after the other) unless the gathers are many; so in the kernel for
-// programs that need few registers the arrays read at the element's own position are read together, ahead of the run
-// (KArgs::direct).  Value stack in LDS and reads where the code asks for them, as before: exp(-d) * t[i] stored and
-// summed, 2^24 elements 95 us (now 59; t of 4 KiB), 2^22 31.3 us (29.5; t of 256 KiB), 4096 elements 9 us (7).
-// Programs with a deeper stack or nested gathers keep the stack in LDS and read where the code asks: with 128 registers a lane
+// instructions of a compiled instance per element.  The kernels of such clusters are in interp.hpp.
+// Bound by latency (a chain of one read after the other) unless the gathers are many.  Programs with a deep
+// stack or nested gathers keep the stack in LDS and read where the code asks: with 128 registers a lane
 // there are two to three times fewer waves to hide the chain (sum of five maps, 2^22 elements: 28 us against 47).
 // x[k][e]: argument k of element e; the function is picked once for the V elements
 template <int V>
@@ -561,65 +558,39 @@ __device__ __forceinline__ void interp_run(const KArgs &a, int pc, unsigned firs
 }
 
 // Workgroup reduction with the reducer picked at run time (the same for the whole grid).
+template <int Waves>
 __device__ __forceinline__ unsigned interp_block_reduce(int op, unsigned v, unsigned *lds) {
   switch (op) {
-    case kFoldAddF32: return (unsigned)as_bits(block_reduce<AddF32>(from_bits<float>((int)v), reinterpret_cast<float *>(lds)));
-    case kFoldMaxF32: return (unsigned)as_bits(block_reduce<MaxF32>(from_bits<float>((int)v), reinterpret_cast<float *>(lds)));
-    case kFoldMulF32: return (unsigned)as_bits(block_reduce<MulF32>(from_bits<float>((int)v), reinterpret_cast<float *>(lds)));
-    case kFoldAddI32: return (unsigned)block_reduce<AddI32>((int)v, reinterpret_cast<int *>(lds));
-    default: return (unsigned)block_reduce<MaxI32>((int)v, reinterpret_cast<int *>(lds));
+    case kFoldAddF32: return (unsigned)as_bits(block_reduce<AddF32, Waves>(from_bits<float>((int)v), reinterpret_cast<float *>(lds)));
+    case kFoldMaxF32: return (unsigned)as_bits(block_reduce<MaxF32, Waves>(from_bits<float>((int)v), reinterpret_cast<float *>(lds)));
+    case kFoldMulF32: return (unsigned)as_bits(block_reduce<MulF32, Waves>(from_bits<float>((int)v), reinterpret_cast<float *>(lds)));
+    case kFoldAddI32: return (unsigned)block_reduce<AddI32, Waves>((int)v, reinterpret_cast<int *>(lds));
+    default: return (unsigned)block_reduce<MaxI32, Waves>((int)v, reinterpret_cast<int *>(lds));
   }
 }
 
-// G groups a lane at a time where there are that many elements, single groups and elements for the rest.
-template <int G, int Depth, int Nest, int LdsThreads, bool Early>
-__global__ __launch_bounds__(kBlock, LdsThreads ? 1 : 4) void interp_kernel(const KArgs a, Control *ctl, unsigned long long *partials) {
-  __shared__ unsigned lds[kWavesPerBlock + 1];
-  const unsigned n = (unsigned)a.n, n4 = n & ~3u;
-  const unsigned epoch = epoch_at_start(ctl);
-  // the folds of the cluster (at most kInterpFolds), each with an accumulator of its own
+// The end of an interpreted cluster: its folds (at most kInterpFolds), each with an accumulator of its own, as
+// fold_finish but for up to two of them under one tag: fold k keeps its partials at [k * grid, (k + 1) * grid);
+// the last workgroup combines them and takes the next tag.
+template <int Waves>
+__device__ __forceinline__ void interp_finish(const KArgs &a, const unsigned (&acc)[kInterpFolds], Control *ctl, unsigned long long *partials,
+                                              unsigned epoch) {
+  __shared__ unsigned lds[Waves + 1];
   const int n_folds = a.n_folds, fold_op[kInterpFolds] = {a.fold_op[0], a.fold_op[1]};
-  unsigned acc[kInterpFolds] = {interp_identity(fold_op[0]), interp_identity(fold_op[1])};
-  constexpr unsigned kGroup = kBlock * kVec, kTileOf = kGroup * G;
-  unsigned none[InterpAhead<G, Early>::V], none4[kVec], none1[1];
-  const unsigned whole = n4 / kTileOf * kTileOf;
-  for (unsigned base = blockIdx.x * kTileOf; base < (G > 1 ? whole : n4); base += a.grid * kTileOf) {
-    const unsigned i = base + threadIdx.x * kVec;
-    if (G == 1 && i >= n4) break;
-    InterpAhead<G, Early> ahead;
-    ahead.template read<true>(a, 0, i, kGroup);
-    interp_run<G, Depth, Nest, LdsThreads, Early>(a, 0, i, kGroup, ahead, acc, none);
-  }
-  // what is left is less than a tile: the first G workgroups take a group a lane of it
-  if (G > 1) {
-    const unsigned i = whole + blockIdx.x * kGroup + threadIdx.x * kVec;
-    if (i < n4) {
-      InterpAhead<1, Early> ahead;
-      ahead.template read<true>(a, 0, i, kGroup);
-      interp_run<1, Depth, Nest, LdsThreads, Early>(a, 0, i, kGroup, ahead, acc, none4);
-    }
-  }
-  if (blockIdx.x == 0 && threadIdx.x < n - n4) {
-    InterpAhead<0, Early> ahead;
-    ahead.template read<false>(a, 0, n4 + threadIdx.x, 0u);
-    interp_run<0, Depth, Nest, LdsThreads, Early>(a, 0, n4 + threadIdx.x, 0u, ahead, acc, none1);
-  }
   if (n_folds == 0) return;                              // the same for the whole grid
-  // as fold_finish, for up to two accumulators under one tag: fold k keeps its partials at
-  // [k * a.grid, (k + 1) * a.grid); the last workgroup combines them and takes the next tag
   const unsigned tag = tag_of_epoch(epoch);
   for (int k = 0; k < n_folds; ++k) {
-    const unsigned r = interp_block_reduce(k == 0 ? fold_op[0] : fold_op[1], k == 0 ? acc[0] : acc[1], lds);
+    const unsigned r = interp_block_reduce<Waves>(k == 0 ? fold_op[0] : fold_op[1], k == 0 ? acc[0] : acc[1], lds);
     if (threadIdx.x == 0) store_agent64(&partials[(size_t)k * a.grid + blockIdx.x], pack_word(r, tag, 1u));
   }
   if (blockIdx.x != a.grid - 1) return;
   for (int k = 0; k < n_folds; ++k) {
     const int op = k == 0 ? fold_op[0] : fold_op[1];
     unsigned s = interp_identity(op);
-    for_tagged_words<kBlock>(partials + (size_t)k * a.grid, a.grid, tag, ctl, [&](unsigned long long w) {
+    for_tagged_words<Waves * kWave>(partials + (size_t)k * a.grid, a.grid, tag, ctl, [&](unsigned long long w) {
       s = interp_fold(op, s, w ? (unsigned)(w >> 32) : interp_identity(op));
     });
-    s = interp_block_reduce(op, s, lds);
+    s = interp_block_reduce<Waves>(op, s, lds);
     if (threadIdx.x == 0) static_cast<unsigned *>(a.out[k == 0 ? a.fold_out[0] : a.fold_out[1]])[0] = s;
   }
   if (threadIdx.x == 0) store_agent(&ctl->epoch, epoch + 1u);

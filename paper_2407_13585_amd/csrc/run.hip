@@ -136,6 +136,7 @@ struct Builder {
             if (code_ok) {
               args.code[at] = Code{kCodeLookup, args.code[n_code - 1].a, args.code[at].b, args.code[at].a};
               args.code[--n_code] = Code{kCodeEnd, 0, 0, 0};
+              if (args.lookup_elems == 0) args.lookup_elems = (unsigned)m.size(nd.arg[1]);
             }
           } else {
             emit(kCodeEnter);

@@ -507,6 +507,75 @@ def fused_and_unfused(g, ins):
     return fused, unfused, name
 
 
+@pytest.mark.parametrize("n, elems", [
+    (2 * 256 * 4096 - 4, 39935), (2 * 256 * 4096, 39936), (2 * 256 * 4096 + 4, 39937), (2 * 256 * 4096 + 3 * 4096 + 3, 8192),
+    (3 * 256 * 4096 + 1, 8195), (4 * 256 * 4096 + 4097, 60001), ((1 << 20) + 300001, 39940), (8000003, 1021), ((1 << 20) + 5, 7)])
+def test_interpreted_lookups_from_lds(n, elems):
+    # tables that end before, at and behind what LDS holds of them; arrays that end before, at and behind the slabs of
+    # 4096 elements the workgroups take two and one at a time; an index array that is read for itself as well.  The last
+    # is too small for LDS.  Stored arrays bit for bit as one kernel per combinator leaves them; the sum within
+    # 1e-5 of the sum of the magnitudes, the bound of the folds.
+    rng = np.random.default_rng(n)
+    g = Graph()
+    g.add("i", "input", "i32", (n,))
+    g.add("t", "input", "f32", (elems,))
+    g.add("d", "input", "f32", (n,))
+    g.add("v", "gather", "f32", (n,), args=("i", "t"))
+    g.add("e", "map", "f32", (n,), fn="exp_neg", args=("d",))
+    g.add("w", "map", "f32", (n,), fn="mul2", args=("e", "v"), output=True)
+    g.add("u", "map", "i32", (n,), fn="mod_eq", iparam=(3, 1), args=("i",), output=True)
+    g.add("s", "fold", "f32", (1,), fn="add", args=("w",), output=True)
+    g.add("m", "fold", "f32", (1,), fn="max", args=("w",), output=True)
+    ins = {"i": rng.integers(0, elems, n).astype(np.int32), "t": rng.uniform(0.5, 1.0, elems).astype(F32), "d": rng.uniform(0.0, 4.0, n).astype(F32)}
+    ins["i"][:4] = ins["i"][-4:] = (0, elems - 1, min(elems - 1, 39935), min(elems - 1, 39936))
+    fused, unfused, name = fused_and_unfused(g, ins)
+    assert "interpreted" in name
+    w = unfused.fetch("w")
+    for _ in range(2):
+        for out in ("w", "u", "m"):
+            P.assert_bit_exact(fused.fetch(out), unfused.fetch(out), out)
+        assert abs(float(fused.fetch("s")[0]) - w.astype(np.float64).sum()) <= 1e-5 * w.astype(np.float64).sum()
+        fused.run()
+    assert [int(x) for x in fused.control_words()[:2]] == [3, 0]
+
+
+@pytest.mark.parametrize("shape", ["three", "add3", "computed_index", "five"])
+@pytest.mark.parametrize("n", [1021, (1 << 20) + 1029, 3 * (1 << 20) + 7])
+def test_interpreted_programs_of_every_form(shape, n):
+    # the forms a short program is told apart by: three arrays, two values below the top of the stack, a gather whose
+    # index or source is computed, and an array past the four that are read ahead; below and above 2^20 elements
+    rng = np.random.default_rng(n)
+    g = Graph()
+    for k in "abcde":
+        g.add(k, "input", "f32", (n,))
+    g.add("i", "input", "i32", (n,))
+    m = lambda name, fn, *args, **kw: g.add(name, "map", "f32", (n,), fn=fn, args=args, **kw)
+    m("x", "exp_neg", "a")
+    if shape == "three":
+        m("y", "mul2", "b", "c")
+        m("w", "add2", "x", "y", output=True)
+    elif shape == "add3":
+        m("w", "add3", "x", "b", "c", output=True)
+    elif shape == "computed_index":
+        g.add("j", "generate", "i32", (n,), fn="iota_rev")
+        g.add("v", "gather", "f32", (n,), args=("i", "x"))
+        g.add("r", "gather", "f32", (n,), args=("j", "b"))
+        m("w", "mul2", "v", "r", output=True)
+    else:
+        m("y", "mul2", "x", "b")
+        m("z", "add2", "y", "c")
+        m("q", "mul2", "z", "d")
+        m("w", "add2", "q", "e", output=True)
+    g.add("s", "fold", "f32", (1,), fn="add", args=("w",), output=True)
+    ins = {k: rng.uniform(0.0, 1.0, n).astype(F32) for k in "abcde"}
+    ins["i"] = rng.integers(0, n, n).astype(np.int32)
+    fused, unfused, name = fused_and_unfused(g, ins)
+    assert "interpreted" in name
+    P.assert_bit_exact(fused.fetch("w"), unfused.fetch("w"), shape)
+    w = unfused.fetch("w").astype(np.float64)
+    assert abs(float(fused.fetch("s")[0]) - w.sum()) <= 1e-5 * w.sum()
+
+
 @pytest.mark.parametrize("n", [1, 3, 1020, 1024, 1025, (1 << 20) - 4, 1 << 20, (1 << 20) + 3, (1 << 20) + 1028, (1 << 20) + 2047])
 def test_interpreted_cluster_sizes(n):
     # one group of four elements a lane below 2^20 elements, two above, the rest of the last tile shared out among the
