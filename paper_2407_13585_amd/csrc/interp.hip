@@ -33,13 +33,12 @@ hipError_t launch_interp(const KArgs &args, const LaunchCtx &c) {
     enters |= a.code[k].op == kCodeEnter;
     if (a.code[k].op == kCodeLookup) lookup = k;
   }
-  // Two groups a lane where the chip is full: of 2^22 elements 17.6 us, of 10^6 8.0 (one group 20.9 and 8.0); never less
-  // than the workgroups that share out what is left behind the last whole tile.  Programs of two arrays at most, one value
-  // below the top of the stack and no other gathers than lookups leave the registers for the next tile's arrays (exp(-d) * t stored
-  // and summed, 2^24 elements: 40 us, with the general form 54); the others have them read when the tile before is done.
+  // Two groups a lane where the chip is full (the sharing of an instruction's cost begins to count there).  Programs of two
+  // arrays at most, one value below the top of the stack and no other gathers than lookups leave the registers for the next
+  // tile's arrays; the others have them read when the tile before is done.
   const bool two = a.n >= (1 << 20);
   if (a.n_direct[0] > 2 || a.code_depth > 1 || enters)
-    return two ? launch_interp_as(&interp_short_kernel<2, 4, 2, true, false>, kBlock * kVec * 2, 2, a, c)
+    return two ? launch_interp_as(&interp_short_kernel<2, 4, 2, true, false>, kBlock * kVec * 2, 3, a, c)
                : launch_interp_as(&interp_short_kernel<1, 4, 2, true, false>, kBlock * kVec, 1, a, c);
   if (lookup < kMaxCode && table_pays((unsigned)a.n, a.lookup_elems)) {
     a.code[lookup].op = kCodeTable;
@@ -48,7 +47,7 @@ hipError_t launch_interp(const KArgs &args, const LaunchCtx &c) {
     return launch_threads(&interp_table_kernel, std::min(slabs, (unsigned)(cus > 0 ? cus : 256)), c, kTableBlock, a, c.ctl, c.partials,
                           (int)a.code[lookup].a, a.lookup_elems);
   }
-  return two ? launch_interp_as(&interp_short_kernel<2, 2, 1, false, true>, kBlock * kVec * 2, 2, a, c)
+  return two ? launch_interp_as(&interp_short_kernel<2, 2, 1, false, true>, kBlock * kVec * 2, 3, a, c)
              : launch_interp_as(&interp_short_kernel<1, 2, 1, false, true>, kBlock * kVec, 1, a, c);
 }
 
