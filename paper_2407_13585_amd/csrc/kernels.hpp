@@ -1443,8 +1443,10 @@ __global__ __launch_bounds__(kBlock) void foldseg_blocked_kernel(const KArgs a, 
 // a table, and a row has an element or none in a range that small: the gathered values have to go
 // back to their positions before rows can be added up.  Four kernels, all streaming:
 //
-//  1. seg_bin_kernel sorts every tile of kSegTile positions by table range, as bin_fine_kernel
-//     does (an LDS counter per wave and range, the tile's slots built in LDS as they go to memory),
+//  1. seg_bin_kernel sorts every tile of kSegTile positions by table range (an LDS counter per range, the
+//     tile's slots built in LDS as they go to memory, two tiles in turn so that one goes to memory while the
+//     next is sorted: one barrier a tile; 2^26 elements, before with a counter per wave and range, three passes over
+//     them and three barriers: 113 us, now 101 of which 567 MB take 90 at the rate of a copy),
 //     and keeps two 16-bit numbers per element, in two arrays: the offset inside the range and the
 //     position inside the tile (offsets slot after slot for every range, positions tile after tile).
 //     An element that finds its slot full (a few in a thousand of evenly spread indices; most
@@ -1458,14 +1460,14 @@ __global__ __launch_bounds__(kBlock) void foldseg_blocked_kernel(const KArgs a, 
 //     tile's last row when the row goes on, are kept per tile,
 //  4. and seg_join_kernel adds those up, tile after tile, for the rows that cross a tile boundary.
 //
-// Every element has one place at every stage and every sum a fixed order: the same bits on every
+// Every value goes back to its position and every sum has a fixed order: the same bits on every
 // launch.  Bytes per element: 4 + 4 (first kernel), 2 + 4 (second), 4 + 2 + 4 (third), times the
 // slots' slack (a slot holds little more than the mean of a uniform spread: what overflows is listed).
 constexpr int kSegBlock = 1024;                        // threads per workgroup of the first two kernels
 constexpr int kSegWaves = kSegBlock / kWave;
 constexpr int kSegTile = 16384;                        // positions per tile: 14-bit positions, a tile of values is 64 KiB of LDS
 constexpr int kSegVecs = kSegTile / (kSegBlock * kVec);      // 128-bit reads per thread and tile
-constexpr int kSegImageWords = 24576;                  // words of a tile's slots in LDS at most (96 KiB)
+constexpr int kSegImageWords = 18432;                  // words of a tile's slots in LDS at most (72 KiB, twice)
 constexpr int kSegMaxBins = 512;
 constexpr int kSegRowsBlock = 512;                     // threads per workgroup of the third kernel: two workgroups per compute unit
 constexpr int kSegRowsStaged = 2048;                   // row starts of a tile kept in LDS (a tile of 16-element rows has 1024)
@@ -1489,11 +1491,11 @@ __global__ __launch_bounds__(kSegBlock) void seg_bin_kernel(const KArgs a, unsig
                                                             const SegPlan plan, unsigned elems) {
   using Raw = int __attribute__((ext_vector_type(4)));
   using Chunk = unsigned __attribute__((ext_vector_type(4)));
-  __shared__ unsigned cursor[kSegWaves][kSegMaxBins];       // per (wave, range): the count, then the wave's first place in the slot
-  __shared__ Chunk image[kSegImageWords / 4];               // the tile's slots: offset | position << 16 per element
-  __shared__ unsigned listed;                               // elements on the tile's list so far
+  // Two of each, for even and odd tiles: a tile is sorted into one image while the one before goes to memory.
+  __shared__ unsigned cursor[2][kSegMaxBins];               // per range: places of the slot taken so far
+  __shared__ Chunk image[2][kSegImageWords / 4];            // the tile's slots: offset | position << 16 per element
+  __shared__ unsigned listed[2];                            // elements on the tile's list so far
   __shared__ unsigned list_wait[kSegWaves][kWave][2];       // per wave: (position, index) of elements that wait to go onto the list together
-  unsigned *entry = reinterpret_cast<unsigned *>(image);
   const int *index = static_cast<const int *>(a.in[KI]);
   const FineCut cut = plan.cut;
   const unsigned cap = plan.cap, tiles = plan.tiles, bins = cut.bins;
@@ -1507,32 +1509,33 @@ __global__ __launch_bounds__(kSegBlock) void seg_bin_kernel(const KArgs a, unsig
     const unsigned i = tile * kSegTile + threadIdx.x * kVec + u * (kSegBlock * kVec);
     return __builtin_amdgcn_raw_buffer_load_b128(index_buf, tile < tiles && i < n ? (int)(i * 4u) : (int)kPastEnd, 0, 0x2);
   };
+  // Workgroups go to the XCDs in turn: two tiles next to each other, whose slots share cache lines, to the same one (103 -> 101 us)
+  const unsigned tile0 = a.grid % 16u == 0u ? blockIdx.x / 16u * 16u + blockIdx.x % 8u * 2u + blockIdx.x / 8u % 2u : blockIdx.x;
   const Chunk nothing = {kSegNothing, kSegNothing, kSegNothing, kSegNothing};
   Raw v[kSegVecs];
 #pragma unroll
-  for (int u = 0; u < kSegVecs; ++u) v[u] = fetch_group(blockIdx.x, u);
-  auto clear_counters = [&]() {                             // a wave its own, of the ranges there are
-    for (unsigned b = (unsigned)lane_id(); b < bins; b += kWave) cursor[wave][b] = 0u;
-  };
+  for (int u = 0; u < kSegVecs; ++u) v[u] = fetch_group(tile0, u);
   // where the groups of eight entries that this thread copies out lie in a range's run of slots: worked out once
-  constexpr int kCopies = kSegImageWords / 8 / kSegBlock;
-  static_assert(kCopies * kSegBlock * 8 == kSegImageWords, "whole steps");
+  constexpr int kCopies = (kSegImageWords / 8 + kSegBlock - 1) / kSegBlock;
   unsigned copy_to[kCopies];                                // b * tiles * cap + part, without the tile's share
 #pragma unroll
   for (int k = 0; k < kCopies; ++k) {
     const unsigned q = threadIdx.x + k * kSegBlock, b = q * 8u / cap, part = q * 8u - b * cap;
     copy_to[k] = b * tiles * cap + part;
   }
-  // between tiles the counters are zero, every place of the image holds nothing and the list is empty
-  clear_counters();
-  for (unsigned q = threadIdx.x; q < words / 4u; q += kSegBlock) image[q] = nothing;
-  if (threadIdx.x == 0) listed = 0u;
+  // a tile finds its counters zero, every place of its image holding nothing and its list empty
+  for (unsigned b = threadIdx.x; b < 2u * kSegMaxBins; b += kSegBlock) cursor[b / kSegMaxBins][b % kSegMaxBins] = 0u;
+  for (unsigned q = threadIdx.x; q < words / 4u; q += kSegBlock) image[0][q] = image[1][q] = nothing;
+  if (threadIdx.x < 2u) listed[threadIdx.x] = 0u;
   __syncthreads();
-  for (unsigned tile = blockIdx.x; tile < tiles; tile += a.grid) {
-    if (threadIdx.x == 0) listed = 0u;                      // read last before the barrier that ended the tile before; added to after the next two
+  unsigned half = 0u;
+  for (unsigned tile = tile0; tile < tiles; tile += a.grid, half ^= 1u) {
     const unsigned first = threadIdx.x * kVec;              // this thread's first position in the tile, group 0
     const unsigned base = tile * kSegTile;
-    // rank of every element among the wave's elements of its range (range << 16 | rank is kept).  An index
+    unsigned *count = cursor[half], *entry = reinterpret_cast<unsigned *>(image[half]);
+    // The next place of its range's slot for every element (range << 16 | place is kept).  The waves take the places
+    // as they come, so where in a slot an element stands differs from launch to launch, and which elements of a full slot go onto the list;
+    // its value goes back to its position all the same, and the rows are added up by position.  An index
     // outside the table (undefined anyway) gets the last range, so that everything stays inside LDS.
     unsigned where[kSegVecs][kVec];
     const unsigned here = n - base;                         // positions of this tile that exist (or more)
@@ -1543,23 +1546,9 @@ __global__ __launch_bounds__(kSegBlock) void seg_bin_kernel(const KArgs a, unsig
         const unsigned b = min(__umulhi((unsigned)v[u][c], cut.magic) >> cut.shift, bins - 1u);
         where[u][c] = b << 16;
         if (first + u * (kSegBlock * kVec) + c < here)
-          where[u][c] |= __hip_atomic_fetch_add(&cursor[wave][b], 1u, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_WAVEFRONT);
+          where[u][c] |= __hip_atomic_fetch_add(&count[b], 1u, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_WORKGROUP);
       }
     }
-    __syncthreads();
-    // inside a range's slot the waves in order: thread t < bins turns the counts of range t into first places
-    if (threadIdx.x < bins) {
-      unsigned count[kSegWaves];                              // all read before any is written: one round trip to LDS, not sixteen
-#pragma unroll
-      for (int w = 0; w < kSegWaves; ++w) count[w] = cursor[w][threadIdx.x];
-      unsigned run = 0;
-#pragma unroll
-      for (int w = 0; w < kSegWaves; ++w) {
-        cursor[w][threadIdx.x] = run;
-        run += count[w];
-      }
-    }
-    __syncthreads();
     // Every element to its place in the image, or with its index onto the list: a wave collects such
     // elements in LDS (places from a ballot, no atomic in the way) and appends them to the tile's list sixty-
     // four at a time at most, reserving the places with one atomic.  As a group is done with, the same
@@ -1567,7 +1556,7 @@ __global__ __launch_bounds__(kSegBlock) void seg_bin_kernel(const KArgs a, unsig
     unsigned waiting = 0;                                     // elements in this wave's part of list_wait: the same in all lanes
     auto append = [&]() {                                     // the whole wave, converged
       unsigned at_list = 0;
-      if (lane_id() == 0) at_list = atomicAdd(&listed, waiting);
+      if (lane_id() == 0) at_list = atomicAdd(&listed[half], waiting);
       at_list = (unsigned)__builtin_amdgcn_readfirstlane((int)at_list);
       if ((unsigned)lane_id() < waiting) {
         list_place[(size_t)base + at_list + (unsigned)lane_id()] = (unsigned short)list_wait[wave][lane_id()][0];
@@ -1582,7 +1571,7 @@ __global__ __launch_bounds__(kSegBlock) void seg_bin_kernel(const KArgs a, unsig
         const unsigned at = first + u * (kSegBlock * kVec) + c;
         const unsigned b = where[u][c] >> 16;
         const unsigned offset = min((unsigned)v[u][c] - b * cut.range, cut.range - 1u);
-        const unsigned place = cursor[wave][b] + (where[u][c] & 0xffffu);
+        const unsigned place = where[u][c] & 0xffffu;
         const bool real = at < here;
         if (real && place < cap) entry[b * cap + place] = offset | (at << 16);
         const bool over = real && place >= cap;
@@ -1608,9 +1597,9 @@ __global__ __launch_bounds__(kSegBlock) void seg_bin_kernel(const KArgs a, unsig
     for (int k = 0; k < kCopies; ++k) {
       const unsigned q = threadIdx.x + k * kSegBlock;
       if (q < words / 8u) {
-        const Chunk lo = image[2u * q], hi = image[2u * q + 1u];
-        image[2u * q] = nothing;
-        image[2u * q + 1u] = nothing;
+        const Chunk lo = image[half][2u * q], hi = image[half][2u * q + 1u];
+        image[half][2u * q] = nothing;
+        image[half][2u * q + 1u] = nothing;
         const size_t at = (size_t)copy_to[k] + (size_t)tile * cap;
         Chunk o, p;
         o[0] = (lo[0] & 0xffffu) | (lo[1] << 16);
@@ -1625,11 +1614,13 @@ __global__ __launch_bounds__(kSegBlock) void seg_bin_kernel(const KArgs a, unsig
         *reinterpret_cast<Chunk *>(places + (size_t)tile * words + q * 8u) = p;
       }
     }
-    // No barrier here.  A wave goes on to rank the next tile in its own counters, which it clears itself;
-    // the counts are not looked at by others, and the image and the list not written to again, before the
-    // barriers that follow the ranking, which no wave passes before all are done with this tile.
-    clear_counters();
-    if (threadIdx.x == 0) list_count[tile] = listed;          // settled before the barrier above
+    // The one barrier of a tile is the one above: behind it everything of this half has been written, and everything of
+    // the other half, which the next tile goes to, was read and emptied before it.
+    for (unsigned b = threadIdx.x; b < bins; b += kSegBlock) count[b] = 0u;
+    if (threadIdx.x == 0) {
+      list_count[tile] = listed[half];
+      listed[half] = 0u;
+    }
   }
 }
 
@@ -1772,19 +1763,26 @@ __global__ __launch_bounds__(kSegRowsBlock) void seg_rows_kernel(const KArgs a, 
   }
   // The elements on the tile's list (those that found their slot full) are asked for now as well, a thread
   // an element: count, then position and index, then the table element -- three round trips in a row that
-  // are over by the time the slots have been put in place.
+  // are over by the time the slots have been put in place.  The last waits for what was asked for before it, so it comes
+  // after the first slots; the row starts, used last, are asked for here too (2^26 elements: 145 us before, 140 now).
   const unsigned listed = list_count[tile];
-  unsigned listed_place = 0;
+  unsigned listed_place = 0, listed_index = 0;
   T listed_value = T();
   if (threadIdx.x < listed) {
     listed_place = list_place[(size_t)t_lo + threadIdx.x];
-    listed_value = table[list_index[(size_t)t_lo + threadIdx.x]];
+    listed_index = list_index[(size_t)t_lo + threadIdx.x];
   }
   // the first row that starts in this tile and in the next (the last tile takes the empty rows at the end);
   // the row before reaches into the tile if it ends behind the tile's first position (start[rows] is the
   // number of elements)
   const unsigned row_lo = first_row[tile], row_hi = tile + 1u < tiles ? first_row[tile + 1u] : rows;
   const unsigned r_first = row_lo - (row_lo > 0u && start[row_lo] > t_lo ? 1u : 0u);
+  // where the first kSegRowsStaged of the tile's rows start
+  const unsigned staged = min(row_hi - r_first, (unsigned)kSegRowsStaged);
+  constexpr int kLoads = kSegRowsStaged / kSegRowsBlock + 1;
+  unsigned row_starts[kLoads];
+#pragma unroll
+  for (int k = 0; k < kLoads; ++k) row_starts[k] = start[r_first + min(threadIdx.x + k * kSegRowsBlock, staged)];   // r_first + staged <= rows: start has that entry
   // The values back to their positions: four entries a thread and step, the reads of the next steps under
   // way while those of the last ones are put in place.  Range and place of a step are carried along from
   // step to step, not divided out.
@@ -1829,6 +1827,7 @@ __global__ __launch_bounds__(kSegRowsBlock) void seg_rows_kernel(const KArgs a, 
     Pair p0[kAtOnce], p1[kAtOnce];
     unsigned q0 = threadIdx.x;                                // the first step of the batch that is put in place next
     fetch(x0, p0);
+    if (threadIdx.x < listed) listed_value = table[listed_index];
     while (q0 - threadIdx.x < quads) {                        // the same for the whole workgroup
       fetch(x1, p1);
       put(q0, x0, p0);
@@ -1846,15 +1845,7 @@ __global__ __launch_bounds__(kSegRowsBlock) void seg_rows_kernel(const KArgs a, 
   // Rows: the tile's own are those that start in it; the row that reaches into it from before (if there
   // is one) comes first.  Where the first kSegRowsStaged of them start goes to LDS while the values are
   // multiplied in.
-  const unsigned staged = min(row_hi - r_first, (unsigned)kSegRowsStaged);
   {
-    constexpr int kLoads = kSegRowsStaged / kSegRowsBlock + 1;
-    unsigned at[kLoads];
-#pragma unroll
-    for (int k = 0; k < kLoads; ++k) {
-      const unsigned i = threadIdx.x + k * kSegRowsBlock;
-      at[k] = i <= staged ? start[r_first + i] : 0u;          // r_first + staged <= rows: start has that entry
-    }
 #pragma unroll
     for (int k = 0; k < kSteps; ++k) {
       const unsigned e = (threadIdx.x + k * kSegRowsBlock) * kVec;
@@ -1866,7 +1857,7 @@ __global__ __launch_bounds__(kSegRowsBlock) void seg_rows_kernel(const KArgs a, 
 #pragma unroll
     for (int k = 0; k < kLoads; ++k) {
       const unsigned i = threadIdx.x + k * kSegRowsBlock;
-      if (i <= staged) row_at[i] = at[k];
+      if (i <= staged) row_at[i] = row_starts[k];
     }
   }
   __syncthreads();

@@ -332,14 +332,15 @@ def test_spmv_column_blocked(rows, ncols, mean_len):
     run_all_modes(3, w, env)
 
 
-@pytest.mark.parametrize("shape", ["uniform", "crowded", "long rows", "empty ends", "one column", "many ranges"])
+@pytest.mark.parametrize("shape", ["uniform", "crowded", "long rows", "empty ends", "one column", "many ranges", "many tiles"])
 def test_spmv_sorted_through_lds(shape):
     # from four million elements on, over a table that no L2 holds, the segmented fold sorts its elements by
     # table range, gathers from LDS and puts the values back in place (four kernels, everything between
     # them in scratch).  Columns spread evenly, columns that crowd into few ranges or one (slots overflow:
     # those elements go through the tiles' lists), rows longer than several tiles, rows that end exactly
     # on a tile boundary, runs of empty rows at both ends and around tile boundaries, a table that is cut
-    # into many short ranges, element counts off the tile and off the 128-bit group.
+    # into many short ranges, element counts off the tile and off the 128-bit group; as many tiles as take a workgroup
+    # of the first kernel three turns (it sorts into two images in turn), columns crowded enough for lists in each.
     rng = np.random.default_rng(len(shape) * 1000 + 7)
     rows, ncols = 300001, 1500007
     lengths = rng.poisson(16.0, size=rows).astype(np.int64)
@@ -355,6 +356,8 @@ def test_spmv_sorted_through_lds(shape):
         lengths[30000:30100] = 2000
     elif shape == "many ranges":
         ncols = (1 << 24) - 3
+    elif shape == "many tiles":
+        lengths = rng.poisson(29.0, size=rows).astype(np.int64)
     w = C.spmv(lengths=lengths, seed=11, ncols=ncols)
     nnz = w.inputs["col"].shape[0]
     assert nnz >= 1 << 22
@@ -362,6 +365,9 @@ def test_spmv_sorted_through_lds(shape):
         w.inputs["col"] = np.where(rng.random(nnz) < 0.9, rng.integers(0, 3000, size=nnz), rng.integers(0, ncols, size=nnz)).astype(np.int32)
     elif shape == "one column":
         w.inputs["col"] = np.full(nnz, ncols - 1, dtype=np.int32)
+    elif shape == "many tiles":
+        w.inputs["col"] = np.where(rng.random(nnz) < 0.1, rng.integers(0, 3000, size=nnz), w.inputs["col"]).astype(np.int32)
+        assert nnz > 2 * 256 * 16384
     env = evaluate(w.graph, w.inputs)
     g, part = plan(w.graph, False)
     prog = device_program(g, w.inputs, part)
