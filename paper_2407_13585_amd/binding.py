@@ -15,6 +15,13 @@ import numpy as np
 
 from workloads.graph import Graph
 
+try:
+    from ._bound import Bound as _Bound
+except ImportError:                                 # nothing built yet
+    from . import build as _build
+    _build.build_bound()
+    from ._bound import Bound as _Bound
+
 _HERE = os.path.dirname(os.path.abspath(__file__))
 _LIB_PATH = os.path.join(_HERE, "libfc.so")
 
@@ -88,7 +95,7 @@ def _share_hip_runtime_with_torch() -> None:
 
 def lib() -> C.CDLL:
     """Loads libfc.so; builds it first only when no built library exists."""
-    global _lib
+    global _lib, _run_bound_address
     if _lib is not None:
         return _lib
     if not os.path.exists(_LIB_PATH):
@@ -119,6 +126,7 @@ def lib() -> C.CDLL:
     for f in ("fc_bind", "fc_run_bound", "fc_unbind", "fc_check", "fc_run_fused_static", "fc_num_edges", "fc_plan", "fc_plan_weighted", "fc_plan_greedy", "fc_partition_trivial", "fc_partition_check", "fc_duplicate",
               "fc_scratch_bytes", "fc_run_fused", "fc_run_unfused", "fc_cluster_kernel"):
         getattr(L, f).restype = C.c_int
+    _run_bound_address = C.cast(L.fc_run_bound, C.c_void_p).value
     _lib = L
     return L
 
@@ -384,9 +392,12 @@ class _BoundHandle:
         self._lib.fc_unbind(self.value)
 
 
-class BoundRun:
+class BoundRun(_Bound):
     """fc_run_fused / fc_run_unfused with the arguments marshalled once: for callers that run
-    one program on the same buffers many times.  partition None = fc_run_unfused."""
+    one program on the same buffers many times.  partition None = fc_run_unfused.
+
+    A call, `bound(stream=0)`, is _Bound's: the bound program issued straight from native code.  _call is for programs that
+    could not be bound, for the first call of a copy, and for arguments out of the ordinary."""
 
     def __init__(self, graph, partition: Optional[Partition], buffers: Dict[str, object], scratch):
         self._g = _cg(graph)
@@ -404,15 +415,24 @@ class BoundRun:
                                self._sp, self._sb, C.byref(handle))
         self._handle = _BoundHandle(self._lib, handle.value) if rc == 0 else None    # a copy of this object shares it
         self._run = self._lib.fc_run_bound
+        if self._handle is not None:
+            self._arm(self._handle, self._handle.value, _run_bound_address)
 
-    def __call__(self, stream: int = 0) -> None:
+    def __getstate__(self):                             # a copy is armed by its first call
+        return self.__dict__
+
+    def _call(self, stream: int = 0) -> None:
         if self._handle is not None:
             rc = self._run(self._handle.value, stream)
+            self._arm(self._handle, self._handle.value, _run_bound_address)
         elif self._cp is None:
             rc = self._lib.fc_run_unfused(self._g.ref(), self._bufs, self._sp, self._sb, stream or None)
         else:
             rc = self._lib.fc_run_fused(self._g.ref(), C.byref(self._cp), self._bufs, self._sp, self._sb,
                                         stream or None)
+        self._failed(rc)
+
+    def _failed(self, rc: int) -> None:
         if rc != 0:
             _check(rc)
 

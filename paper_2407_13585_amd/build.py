@@ -12,11 +12,13 @@ import concurrent.futures as cf
 import os
 import subprocess
 import sys
+import sysconfig
 
 HERE = os.path.dirname(os.path.abspath(__file__))
 CSRC = os.path.join(HERE, "csrc")
 OBJ = os.path.join(HERE, "_build")
 LIB = os.path.join(HERE, "libfc.so")
+BOUND = os.path.join(HERE, "_bound.so")            # the call of a bound program as a Python type (csrc/bound.c)
 
 SOURCES = ["api.hip", "run.hip", "instances.hip", "interp.hip", "generic_folds.hip", "generic_rows.hip", "generic_scans.hip", "model.cpp",
            "plan.cpp"]
@@ -55,7 +57,21 @@ def _compile(src, force):
     return obj, p.stderr
 
 
+def build_bound(force: bool = False) -> str:
+    """The extension module that binding.BoundRun is made on: host code only, against this interpreter's headers."""
+    src = os.path.join(CSRC, "bound.c")
+    if force or _stale(BOUND, [src]):
+        cmd = [os.environ.get("CC", "gcc"), "-O2", "-std=c11", "-Wall", "-shared", "-fPIC", "-I", sysconfig.get_paths()["include"], src,
+               "-o", BOUND + f".{os.getpid()}"]
+        p = subprocess.run(cmd, capture_output=True, text=True)
+        if p.returncode != 0:
+            raise RuntimeError(f"{' '.join(cmd)}\n{p.stdout}\n{p.stderr}")
+        os.replace(BOUND + f".{os.getpid()}", BOUND)
+    return BOUND
+
+
 def build(force: bool = False, verbose: bool = False) -> str:
+    build_bound(force)
     os.makedirs(OBJ, exist_ok=True)
     with cf.ThreadPoolExecutor(max_workers=min(8, len(SOURCES))) as ex:
         results = list(ex.map(lambda s: _compile(s, force), SOURCES))

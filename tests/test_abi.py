@@ -165,6 +165,37 @@ def test_a_copy_of_a_bound_program_shares_it(monkeypatch):
         copy.copy(B.BoundRun(w.graph, fc.fc_plan(w.graph, "bytes"), bufs, fake)._handle)
 
 
+def test_a_bound_program_is_called_with_a_stream_and_nothing_else():
+    # positional, by name, None and an integer beyond 32 bits reach the launch (which fails here or is not made: the
+    # program and its function are stand-ins), whatever else the Python method is left to refuse; a failing call raises
+    import copy
+    import ctypes
+    w = build(2, small=True)
+    fake = (0x10000000, 1 << 30)
+    bufs = {n.name: fake for n in w.graph.nodes if n.kind == "input" or n.output}
+    bound = B.BoundRun(w.graph, fc.fc_plan(w.graph, "bytes"), bufs, fake)
+    seen, rc = [], [0]
+
+    def run(program, stream):
+        seen.append((program, stream))
+        return rc[0]
+
+    stand_in = ctypes.CFUNCTYPE(ctypes.c_int, ctypes.c_void_p, ctypes.c_void_p)(run)
+    bound._arm(bound._handle, 5, ctypes.cast(stand_in, ctypes.c_void_p).value)
+    assert bound() is None and bound(0) is None and bound(None) is None and bound(1 << 40) is None
+    assert seen == [(5, None), (5, None), (5, None), (5, 1 << 40)]
+    rc[0] = -3
+    with pytest.raises(fc.FcError):
+        bound(0)
+    for args, kw in (((1, 2), {}), ((), {"queue": 0})):
+        with pytest.raises(TypeError):
+            bound(*args, **kw)
+    assert len(seen) == 5
+    # a copy goes its own way: it is not armed with the stand-in
+    twin = copy.copy(bound)
+    assert twin._handle is bound._handle and len(seen) == 5
+
+
 def test_scatter_that_reads_its_destination_is_refused():
     # the destination is updated in place; a scatter that took its values (or indices, or flags)
     # from the same array would read what it is overwriting
