@@ -901,11 +901,11 @@ __global__ __launch_bounds__(kBlock) void fold_binned_kernel(const KArgs a, Cont
 // XCD: 71 us for 2^24 gathers whatever else the kernel does).  Two kernels again, both with
 // workgroups of kFineBlock = 1024 threads (one per compute unit: they fill its LDS):
 //
-//  1. bin_fine_kernel cuts the table into kFineBins ranges of equal length (FineCut: the range of
+//  1. bin_fine_kernel cuts the table into 512 or 256 ranges of equal length (FineCut: the range of
 //     an index is a multiplication and a shift that the host has checked against the division,
 //     because the offsets inside a range are kept as 16-bit numbers and have to be exact) and
-//     sorts every tile of kFineTile indices by range.  A thread keeps its 32 indices in
-//     registers; every element takes a rank from an LDS counter per (wave, range) -- one LDS
+//     sorts every tile of 32768 or 16384 indices by range (FineShape).  A thread keeps its 32 or 16 indices
+//     in registers; every element takes a rank from an LDS counter per (wave, range) -- one LDS
 //     operation per element -- a scan over the ranges lays the tile out, every offset goes to its
 //     place in LDS, and the waves copy the ranges to their slots, consecutive lanes to
 //     consecutive words.  A slot is kFineCap 16-bit entries at a fixed place per (range, tile);
@@ -921,26 +921,36 @@ __global__ __launch_bounds__(kBlock) void fold_binned_kernel(const KArgs a, Cont
 // the same bits every time.
 constexpr int kFineBlock = 1024;                       // threads per workgroup of both kernels
 constexpr int kFineWaves = kFineBlock / kWave;
-constexpr int kFineBins = 512;
-constexpr int kFineTile = 32768;                       // indices per tile
-constexpr int kFineVecs = kFineTile / (kFineBlock * kVec);   // 128-bit reads per thread and tile
 constexpr int kFineCap = 96;                           // entries per slot: mean 64 + 4 standard deviations of a uniform spread
 constexpr int kFineSlotWords = kFineCap / 2;           // two entries per 32-bit word
 constexpr int kFineSlice = 32768;                      // elements of a range at most (offsets are below 2^15)
 constexpr unsigned kFineNone = kFineSlice;             // the entry of a place that holds no index
 constexpr unsigned kFineIndexLimit = 1u << 24;         // table elements at most: FineCut is exact below it
+// Ranges and indices per tile: the mean of a slot is the same for both.  Tables of up to 2^23 elements fit 256 ranges,
+// one for every compute unit in the second kernel (512 are two rounds of filling LDS), and then tiles of half the length keep twice as
+// many compute units busy in the first, or two workgroups on each: few positions are bound by the chain of one tile and one
+// range, not by their bytes (2^21 positions in as many elements: both kernels 25.4 us with 512 ranges, 20.0 with 256).
+template <int Ranges> struct FineShape {
+  static constexpr int kBins = Ranges;
+  static constexpr int kTile = Ranges * 64;
+  static constexpr int kVecs = kTile / (kFineBlock * kVec);   // 128-bit reads per thread and tile
+  static constexpr int kTogether = 512 / Ranges;              // workgroups of the first kernel a compute unit holds
+  static_assert(kBins <= kFineBlock && kVecs * kFineBlock * kVec == kTile, "a thread per range in the scan; whole reads");
+};
+using FineWide = FineShape<512>;
+using FineNarrow = FineShape<256>;
 static_assert(kFineCap % 8 == 0 && kFineSlotWords <= kWave, "a slot is whole 128-bit groups and at most a word per lane");
-static_assert(kFineBins <= kFineBlock && kFineVecs * kFineBlock * kVec == kFineTile, "a thread per range in the scan; whole reads");
-static_assert(kFineBins % 32 == 0 && kFineNone < 65536u, "a bit per range in whole words; entries are 16-bit numbers");
+static_assert(kFineNone < 65536u, "entries are 16-bit numbers");
 
 // How the table is cut: `range` elements per range (a multiple of four), `bins` ranges, and
 // j / range == __umulhi(j, magic) >> shift for every j below kFineIndexLimit.
 struct FineCut { unsigned range, bins, magic, shift; };
 
-template <class Op, class E>
-__global__ __launch_bounds__(kFineBlock) void bin_fine_kernel(const KArgs a, Control *ctl, unsigned long long *partials,
+template <class Op, class E, class Shape>
+__global__ __launch_bounds__(kFineBlock, Shape::kTogether * kFineWaves / 4) void bin_fine_kernel(const KArgs a, Control *ctl, unsigned long long *partials,
                                                               unsigned *slots, unsigned tiles, const FineCut cut) {
   using T = typename Op::T;
+  constexpr int kFineBins = Shape::kBins, kFineTile = Shape::kTile, kFineVecs = Shape::kVecs;
   using C = GatherChain<E>;
   using Raw = int __attribute__((ext_vector_type(4)));
   using Chunk = unsigned __attribute__((ext_vector_type(4)));

@@ -164,13 +164,13 @@ template <class Op, class E> hipError_t launch_fold_binned(const KArgs &a, const
 }
 
 // ---- the same fold with the table ranges in LDS: tables of more than one L2 and at most 2^24 elements ----
-// The table in kFineBins ranges of equal length (a multiple of four elements, so that every range
+// The table in max_bins ranges of equal length (a multiple of four elements, so that every range
 // starts on a 128-bit boundary) and the multiplication that stands for the division by that length.
 // With 2^k >= limit * range and magic = floor(2^k / range) + 1, umulhi(j, magic) >> (k - 32) is
 // j / range for every j < limit; the check below walks the range boundaries inside the table, where a
 // wrong quotient would show first, and an empty FineCut (bins == 0) says that this table is not to be
 // cut this way.
-inline FineCut fine_cut(size_t elems, unsigned max_bins = kFineBins, unsigned max_range = kFineSlice) {
+inline FineCut fine_cut(size_t elems, unsigned max_bins, unsigned max_range = kFineSlice) {
   const FineCut none = {0, 0, 0, 0};
   if (elems == 0 || elems > (size_t)kFineIndexLimit || max_bins == 0) return none;
   const unsigned range = (unsigned)(((elems + max_bins - 1) / max_bins + 3) / 4 * 4);
@@ -189,33 +189,45 @@ inline FineCut fine_cut(size_t elems, unsigned max_bins = kFineBins, unsigned ma
   }
   return cut;
 }
-inline unsigned fine_tiles(const KArgs &a) { return (unsigned)(((size_t)(a.n & ~3) + kFineTile - 1) / kFineTile); }
+template <class Shape> unsigned fine_tiles(const KArgs &a) { return (unsigned)(((size_t)(a.n & ~3) + Shape::kTile - 1) / Shape::kTile); }
 template <class E> bool fold_fine_accept(const KArgs &a) {
   const size_t elems = binned_table_elems<E>(a);
   // Worth it from two million positions on, for tables that no L2 holds, and while there are at
   // least half as many positions as table elements: the second kernel evaluates the whole table.
   // The index array and a range's slots are addressed with 32-bit byte offsets.
   if ((a.flags & kSinglePass) || a.n < (1 << 21) || a.n > (1 << 29) || elems * 4 <= kL2Bytes || (size_t)a.n * 2 < elems) return false;
-  return fine_cut(elems).bins != 0;
+  return fine_cut(elems, FineWide::kBins).bins != 0;
+}
+// The narrow shape for tables that it can cut and up to 6 x 2^20 positions: from there a compute unit has a tile of
+// the wide one nearly as soon, and the wide one's longer tiles cost less a position (us a pass, wide / narrow: 2^21 positions in as
+// many elements 25.4 / 20.0, 2.5 x 10^6 25.3 / 20.2, 2^22 28.1 / 25.3, 6 x 10^6 32.2 / 30.2, 7 x 10^6 33.7 / 34.2, 2^23 36.4 / 37.0; 2^24
+// in 2 x 10^6 elements 46.3 / 47.3, 2^25 in 2^22 75.5 / 80.4, 2^26 in 2^23 131 / 140).
+template <class E> bool fine_narrow(const KArgs &a) {
+  return a.n <= 6 << 20 && fine_cut(binned_table_elems<E>(a), FineNarrow::kBins).bins != 0;
 }
 template <class E> size_t fold_fine_workspace(const KArgs &a) {
-  // a slot per (range, tile) for all kFineBins ranges: the first kernel writes the empty ones past the table's end too
-  return fine_cut(binned_table_elems<E>(a)).bins != 0 ? (size_t)kFineBins * fine_tiles(a) * kFineSlotWords * sizeof(unsigned) : 0;
+  // a slot per (range, tile) for all ranges of the shape: the first kernel writes the empty ones past the table's end too
+  if (fine_cut(binned_table_elems<E>(a), FineWide::kBins).bins == 0) return 0;
+  return (fine_narrow<E>(a) ? (size_t)FineNarrow::kBins * fine_tiles<FineNarrow>(a) : (size_t)FineWide::kBins * fine_tiles<FineWide>(a)) *
+         kFineSlotWords * sizeof(unsigned);
 }
-template <class Op, class E> hipError_t launch_fold_fine(const KArgs &a, const LaunchCtx &c) {
+template <class Op, class E, class Shape> hipError_t launch_fold_fine_as(const KArgs &a, const LaunchCtx &c) {
   const unsigned elems = (unsigned)binned_table_elems<E>(a);
-  const FineCut cut = fine_cut(elems);
+  const FineCut cut = fine_cut(elems, Shape::kBins);
   if (!c.workspace || cut.bins == 0) return hipErrorInvalidValue;
-  const unsigned tiles = fine_tiles(a);
+  const unsigned tiles = fine_tiles<Shape>(a);
   unsigned *slots = static_cast<unsigned *>(c.workspace);
-  // both kernels fill the LDS of a compute unit: one workgroup of kFineBlock threads per unit
+  // one workgroup of kFineBlock threads fills the LDS of a compute unit, in the first kernel of the narrow shape two
   const int cus = device_compute_units();
   const unsigned units = (unsigned)(cus > 0 ? cus : 256);
-  const unsigned first = std::min(tiles, units);
-  hipError_t e = launch_threads(&bin_fine_kernel<Op, E>, first, c, (int)kFineBlock, a, c.ctl, c.partials, slots, tiles, cut);
+  const unsigned first = std::min(tiles, units * Shape::kTogether);
+  hipError_t e = launch_threads(&bin_fine_kernel<Op, E, Shape>, first, c, (int)kFineBlock, a, c.ctl, c.partials, slots, tiles, cut);
   if (e != hipSuccess) return e;
   return launch_threads(&fold_fine_kernel<Op, E>, std::min(cut.bins, units), c, (int)kFineBlock, a, c.ctl, c.partials,
                   static_cast<const unsigned *>(slots), tiles, cut, elems, first);
+}
+template <class Op, class E> hipError_t launch_fold_fine(const KArgs &a, const LaunchCtx &c) {
+  return fine_narrow<E>(a) ? launch_fold_fine_as<Op, E, FineNarrow>(a, c) : launch_fold_fine_as<Op, E, FineWide>(a, c);
 }
 
 // ---- segmented fold over a gathered table, sorted through LDS: tables of more than one L2 and at most 2^24 elements ----

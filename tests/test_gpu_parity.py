@@ -462,12 +462,14 @@ def test_single_pass_flag_keeps_the_gathers_in_position_order():
 @pytest.mark.parametrize("table,m", [(1048600, 1 << 21), ((1 << 24), (1 << 21) + 8192), (5000000, (1 << 21) + 4096),
                                      (1234567, (1 << 21) + 4100), ((1 << 25) + 5, (1 << 21) + 1),
                                      ((1 << 24) - 12345, (1 << 23) + 4100), ((1 << 24), (1 << 23) + 32768 + 3),
-                                     (9000001, 4500001)])
+                                     (9000001, 4500001), (1 << 23, (1 << 22) + 16384), ((1 << 23) + 1, (1 << 22) + 16385),
+                                     (8388605, 6 << 20), (2000003, (6 << 20) + 1)])
 def test_perm_gather_binned_sizes(table, m):
     # table sizes just above one L2, at 64 MiB and beyond (ranges larger than half an L2); position counts that
     # are whole tiles, whole passes, and a pass with four elements in it.  Tables of up to 2^24 elements with
     # at least half as many positions take the kernels that keep a table range in LDS (ranges of a power of
-    # two and of any other length, a last range that is shorter, a last tile that is all but empty).
+    # two and of any other length, a last range that is shorter, a last tile that is all but empty), with 256 ranges
+    # for tables of up to 2^23 elements and 6 x 2^20 positions, with 512 beyond either.
     rng = np.random.default_rng(table ^ m)
     w = C.perm_gather_fold(xs=rng.standard_normal(size=table).astype(F32), idx=rng.integers(0, table, size=m, dtype=np.int32))
     env = evaluate(w.graph, w.inputs)
