@@ -15,12 +15,38 @@ import numpy as np
 
 from workloads.graph import Graph
 
-try:
-    from ._bound import Bound as _Bound
-except ImportError:                                 # nothing built yet
-    from . import build as _build
-    _build.build_bound()
-    from ._bound import Bound as _Bound
+
+
+class _ForwardedCall:
+    """What BoundRun is made on where there is no extension module: every call goes through the Python method."""
+
+    def __call__(self, *args, **kwargs):
+        return self._call(*args, **kwargs)
+
+    def _arm(self, owner, program: int, run: int) -> None:
+        pass
+
+
+def _bound_type() -> type:
+    """The type of csrc/bound.c, compiled first where it is missing or cannot be loaded; _ForwardedCall without a
+    compiler or the headers of this interpreter, as the library itself needs neither."""
+    import importlib
+    try:
+        return importlib.import_module("._bound_call", __package__).Bound
+    except ImportError:
+        pass
+    from . import build
+    try:
+        build.build_bound(force=True)
+        importlib.invalidate_caches()
+        return importlib.import_module("._bound_call", __package__).Bound
+    except (ImportError, OSError, RuntimeError) as e:
+        import warnings
+        warnings.warn(f"bound programs are called through ctypes: {str(e).strip() or e!r}", RuntimeWarning)
+        return _ForwardedCall
+
+
+_Bound = _bound_type()
 
 _HERE = os.path.dirname(os.path.abspath(__file__))
 _LIB_PATH = os.path.join(_HERE, "libfc.so")
@@ -397,7 +423,8 @@ class BoundRun(_Bound):
     one program on the same buffers many times.  partition None = fc_run_unfused.
 
     A call, `bound(stream=0)`, is _Bound's: the bound program issued straight from native code.  _call is for programs that
-    could not be bound, for the first call of a copy, and for arguments out of the ordinary."""
+    could not be bound, for the first call of a copy, for arguments out of the ordinary, and for all calls where there is
+    no extension module."""
 
     def __init__(self, graph, partition: Optional[Partition], buffers: Dict[str, object], scratch):
         self._g = _cg(graph)

@@ -18,7 +18,8 @@ HERE = os.path.dirname(os.path.abspath(__file__))
 CSRC = os.path.join(HERE, "csrc")
 OBJ = os.path.join(HERE, "_build")
 LIB = os.path.join(HERE, "libfc.so")
-BOUND = os.path.join(HERE, "_bound.so")            # the call of a bound program as a Python type (csrc/bound.c)
+# the call of a bound program as a Python type (csrc/bound.c); the name says which interpreter it was compiled for
+BOUND = os.path.join(HERE, "_bound_call" + sysconfig.get_config_var("EXT_SUFFIX"))
 
 SOURCES = ["api.hip", "run.hip", "instances.hip", "interp.hip", "generic_folds.hip", "generic_rows.hip", "generic_scans.hip", "model.cpp",
            "plan.cpp"]
@@ -71,7 +72,10 @@ def build_bound(force: bool = False) -> str:
 
 
 def build(force: bool = False, verbose: bool = False) -> str:
-    build_bound(force)
+    try:
+        build_bound(force)
+    except (OSError, RuntimeError) as e:               # no compiler, no headers of this interpreter: binding.py does without
+        print(f"not built: {e}", file=sys.stderr)
     os.makedirs(OBJ, exist_ok=True)
     with cf.ThreadPoolExecutor(max_workers=min(8, len(SOURCES))) as ex:
         results = list(ex.map(lambda s: _compile(s, force), SOURCES))

@@ -73,7 +73,7 @@ static PyMethodDef bound_methods[] = {{"_arm", (PyCFunction)bound_arm, METH_VARA
 
 static PyTypeObject BoundType = {
     PyVarObject_HEAD_INIT(NULL, 0)
-    .tp_name = "paper_2407_13585_amd._bound.Bound",
+    .tp_name = "paper_2407_13585_amd._bound_call.Bound",
     .tp_basicsize = sizeof(Bound),
     .tp_dealloc = (destructor)bound_dealloc,
     .tp_call = (ternaryfunc)bound_call,
@@ -83,9 +83,9 @@ static PyTypeObject BoundType = {
     .tp_new = bound_new,
 };
 
-static struct PyModuleDef module = {PyModuleDef_HEAD_INIT, "_bound", NULL, -1, NULL, NULL, NULL, NULL, NULL};
+static struct PyModuleDef module = {PyModuleDef_HEAD_INIT, "_bound_call", NULL, -1, NULL, NULL, NULL, NULL, NULL};
 
-PyMODINIT_FUNC PyInit__bound(void) {
+PyMODINIT_FUNC PyInit__bound_call(void) {
   PyObject *m;
   if (PyType_Ready(&BoundType) < 0) return NULL;
   m = PyModule_Create(&module);

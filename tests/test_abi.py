@@ -196,6 +196,55 @@ def test_a_bound_program_is_called_with_a_stream_and_nothing_else():
     assert twin._handle is bound._handle and len(seen) == 5
 
 
+@pytest.mark.parametrize("state", ["absent, no compiler", "unreadable, newer than its source", "unreadable, no compiler"])
+def test_the_package_imports_without_the_extension_module(state, tmp_path):
+    # the library alone is enough for the calls of fc.h: a missing or unusable extension module is compiled again, and
+    # without a compiler (or this interpreter's headers) a bound program is called through the Python method
+    import glob
+    import shutil
+    import sys
+    import sysconfig
+    package = os.path.dirname(os.path.abspath(B.__file__))
+    there = tmp_path / "paper_2407_13585_amd"
+    (there / "csrc").mkdir(parents=True)
+    for f in glob.glob(os.path.join(package, "*.py")):
+        shutil.copy(f, there)
+    shutil.copy(os.path.join(package, "csrc", "bound.c"), there / "csrc")
+    B.lib()                                            # built by now
+    os.symlink(os.path.join(package, "libfc.so"), there / "libfc.so")
+    os.symlink(os.path.join(os.path.dirname(package), "workloads"), tmp_path / "workloads")
+    if state.startswith("unreadable"):
+        (there / ("_bound_call" + sysconfig.get_config_var("EXT_SUFFIX"))).write_text("not a library")
+    script = """
+import ctypes, os, sys, warnings
+with warnings.catch_warnings(record=True) as said:
+    warnings.simplefilter("always")
+    import paper_2407_13585_amd as fc
+from paper_2407_13585_amd import binding as B
+from workloads import build
+assert os.path.dirname(os.path.abspath(B.__file__)) == os.path.join(os.getcwd(), "paper_2407_13585_amd")
+w = build(2, small=True)
+fake = (0x10000000, 1 << 30)
+bound = B.BoundRun(w.graph, fc.fc_plan(w.graph, "bytes"), {n.name: fake for n in w.graph.nodes if n.kind == "input" or n.output}, fake)
+seen = []
+stand_in = ctypes.CFUNCTYPE(ctypes.c_int, ctypes.c_void_p, ctypes.c_void_p)(lambda program, stream: seen.append(stream) or 0)
+if B._Bound is not B._ForwardedCall:
+    bound._arm(bound._handle, 5, ctypes.cast(stand_in, ctypes.c_void_p).value)
+else:
+    bound._run = stand_in
+for args, kw in (((), {}), ((0,), {}), ((1 << 40,), {})):
+    assert bound(*args, **kw) is None
+assert seen == [None, None, 1 << 40], seen
+print(B._Bound.__name__, sum("through ctypes" in str(w.message) for w in said))
+"""
+    env = dict(os.environ, PYTHONPATH=str(tmp_path))
+    if state.endswith("no compiler"):
+        env["CC"] = "no-such-compiler"
+    p = subprocess.run([sys.executable, "-c", script], cwd=tmp_path, env=env, capture_output=True, text=True)
+    assert p.returncode == 0, p.stderr
+    assert p.stdout.split() == (["_ForwardedCall", "1"] if state.endswith("no compiler") else ["Bound", "0"])
+
+
 def test_scatter_that_reads_its_destination_is_refused():
     # the destination is updated in place; a scatter that took its values (or indices, or flags)
     # from the same array would read what it is overwriting
