@@ -1454,13 +1454,13 @@ __global__ __launch_bounds__(kBlock) void foldseg_blocked_kernel(const KArgs a, 
 // back to their positions before rows can be added up.  Four kernels, all streaming:
 //
 //  1. seg_bin_kernel sorts every tile of kSegTile positions by table range (an LDS counter per range, the
-//     tile's slots built in LDS as they go to memory, two tiles in turn so that one goes to memory while the
-//     next is sorted: one barrier a tile; 2^26 elements, before with a counter per wave and range, three passes over
-//     them and three barriers: 113 us, now 101 of which 567 MB take 90 at the rate of a copy),
-//     and keeps two 16-bit numbers per element, in two arrays: the offset inside the range and the
+//     tile's slots built in LDS as they go to memory; where two tiles' slots fit LDS, two tiles in turn, so that one goes
+//     to memory while the next is sorted: one barrier a tile, and two with one image, which costs up to a hundredth of the pass.
+//     2^26 elements, before with a counter per wave and range, three passes over them and three barriers: 113 us,
+//     now 101 of which 567 MB take 94 at the rate of a copy), and keeps two 16-bit numbers per element, in two arrays: the offset inside the range and the
 //     position inside the tile (offsets slot after slot for every range, positions tile after tile).
-//     An element that finds its slot full (a few in a thousand of evenly spread indices; most
-//     of indices that crowd into few ranges) goes onto the tile's list of (position, index) pairs.
+//     An element that finds its slot full (one to five in a hundred of evenly spread indices, as seg_plan
+//     has it; most of indices that crowd into few ranges) goes onto the tile's list of (position, index) pairs.
 //  2. seg_gather_kernel: a workgroup reads a table range into LDS and turns a stretch of the
 //     range's offsets into values, slot for slot (the slots of a range lie one behind the other).
 //  3. seg_rows_kernel: a workgroup per tile puts the tile's values (one slot per range, then those
@@ -1478,6 +1478,7 @@ constexpr int kSegWaves = kSegBlock / kWave;
 constexpr int kSegTile = 16384;                        // positions per tile: 14-bit positions, a tile of values is 64 KiB of LDS
 constexpr int kSegVecs = kSegTile / (kSegBlock * kVec);      // 128-bit reads per thread and tile
 constexpr int kSegImageWords = 18432;                  // words of a tile's slots in LDS at most (72 KiB, twice)
+constexpr int kSegOneImageWords = 24576;               // of the one image there is for more than that (96 KiB)
 constexpr int kSegMaxBins = 512;
 constexpr int kSegRowsBlock = 512;                     // threads per workgroup of the third kernel: two workgroups per compute unit
 constexpr int kSegRowsStaged = 2048;                   // row starts of a tile kept in LDS (a tile of 16-element rows has 1024)
@@ -1493,17 +1494,20 @@ struct SegPlan {
   FineCut cut;
   unsigned cap;        // entries per slot, a multiple of eight
   unsigned tiles;
+  unsigned images;     // of a tile's slots in the first kernel's LDS: two, or one
 };
 
-template <int KI>
+template <int KI, int Images>
 __global__ __launch_bounds__(kSegBlock) void seg_bin_kernel(const KArgs a, unsigned short *offsets, unsigned short *places,
                                                             unsigned short *list_place, unsigned *list_index, unsigned *list_count,
                                                             const SegPlan plan, unsigned elems) {
   using Raw = int __attribute__((ext_vector_type(4)));
   using Chunk = unsigned __attribute__((ext_vector_type(4)));
-  // Two of each, for even and odd tiles: a tile is sorted into one image while the one before goes to memory.
+  // Two of each, for even and odd tiles: a tile is sorted into one image while the one before goes to memory.  With one
+  // image its places are worked out meanwhile, and the tile waits with putting its elements there.
   __shared__ unsigned cursor[2][kSegMaxBins];               // per range: places of the slot taken so far
-  __shared__ Chunk image[2][kSegImageWords / 4];            // the tile's slots: offset | position << 16 per element
+  constexpr int kWords = Images == 2 ? kSegImageWords : kSegOneImageWords;
+  __shared__ Chunk image[Images][kWords / 4];               // the tile's slots: offset | position << 16 per element
   __shared__ unsigned listed[2];                            // elements on the tile's list so far
   __shared__ unsigned list_wait[kSegWaves][kWave][2];       // per wave: (position, index) of elements that wait to go onto the list together
   const int *index = static_cast<const int *>(a.in[KI]);
@@ -1526,7 +1530,7 @@ __global__ __launch_bounds__(kSegBlock) void seg_bin_kernel(const KArgs a, unsig
 #pragma unroll
   for (int u = 0; u < kSegVecs; ++u) v[u] = fetch_group(tile0, u);
   // where the groups of eight entries that this thread copies out lie in a range's run of slots: worked out once
-  constexpr int kCopies = (kSegImageWords / 8 + kSegBlock - 1) / kSegBlock;
+  constexpr int kCopies = (kWords / 8 + kSegBlock - 1) / kSegBlock;
   unsigned copy_to[kCopies];                                // b * tiles * cap + part, without the tile's share
 #pragma unroll
   for (int k = 0; k < kCopies; ++k) {
@@ -1535,14 +1539,15 @@ __global__ __launch_bounds__(kSegBlock) void seg_bin_kernel(const KArgs a, unsig
   }
   // a tile finds its counters zero, every place of its image holding nothing and its list empty
   for (unsigned b = threadIdx.x; b < 2u * kSegMaxBins; b += kSegBlock) cursor[b / kSegMaxBins][b % kSegMaxBins] = 0u;
-  for (unsigned q = threadIdx.x; q < words / 4u; q += kSegBlock) image[0][q] = image[1][q] = nothing;
+  for (unsigned q = threadIdx.x; q < words / 4u; q += kSegBlock) image[0][q] = image[Images - 1][q] = nothing;
   if (threadIdx.x < 2u) listed[threadIdx.x] = 0u;
   __syncthreads();
   unsigned half = 0u;
   for (unsigned tile = tile0; tile < tiles; tile += a.grid, half ^= 1u) {
     const unsigned first = threadIdx.x * kVec;              // this thread's first position in the tile, group 0
     const unsigned base = tile * kSegTile;
-    unsigned *count = cursor[half], *entry = reinterpret_cast<unsigned *>(image[half]);
+    Chunk *slots = image[Images == 2 ? half : 0u];
+    unsigned *count = cursor[half], *entry = reinterpret_cast<unsigned *>(slots);
     // The next place of its range's slot for every element (range << 16 | place is kept).  The waves take the places
     // as they come, so where in a slot an element stands differs from launch to launch, and which elements of a full slot go onto the list;
     // its value goes back to its position all the same, and the rows are added up by position.  An index
@@ -1559,6 +1564,7 @@ __global__ __launch_bounds__(kSegBlock) void seg_bin_kernel(const KArgs a, unsig
           where[u][c] |= __hip_atomic_fetch_add(&count[b], 1u, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_WORKGROUP);
       }
     }
+    if constexpr (Images == 1) __syncthreads();               // the tile before has left the image
     // Every element to its place in the image, or with its index onto the list: a wave collects such
     // elements in LDS (places from a ballot, no atomic in the way) and appends them to the tile's list sixty-
     // four at a time at most, reserving the places with one atomic.  As a group is done with, the same
@@ -1607,9 +1613,9 @@ __global__ __launch_bounds__(kSegBlock) void seg_bin_kernel(const KArgs a, unsig
     for (int k = 0; k < kCopies; ++k) {
       const unsigned q = threadIdx.x + k * kSegBlock;
       if (q < words / 8u) {
-        const Chunk lo = image[half][2u * q], hi = image[half][2u * q + 1u];
-        image[half][2u * q] = nothing;
-        image[half][2u * q + 1u] = nothing;
+        const Chunk lo = slots[2u * q], hi = slots[2u * q + 1u];
+        slots[2u * q] = nothing;
+        slots[2u * q + 1u] = nothing;
         const size_t at = (size_t)copy_to[k] + (size_t)tile * cap;
         Chunk o, p;
         o[0] = (lo[0] & 0xffffu) | (lo[1] << 16);
@@ -1624,8 +1630,8 @@ __global__ __launch_bounds__(kSegBlock) void seg_bin_kernel(const KArgs a, unsig
         *reinterpret_cast<Chunk *>(places + (size_t)tile * words + q * 8u) = p;
       }
     }
-    // The one barrier of a tile is the one above: behind it everything of this half has been written, and everything of
-    // the other half, which the next tile goes to, was read and emptied before it.
+    // The last barrier of a tile is the one above: behind it everything of this half has been written, and everything of
+    // the other half, which the next tile goes to, was read and emptied before it (the one image: before the next tile's first).
     for (unsigned b = threadIdx.x; b < bins; b += kSegBlock) count[b] = 0u;
     if (threadIdx.x == 0) {
       list_count[tile] = listed[half];

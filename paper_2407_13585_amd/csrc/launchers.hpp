@@ -231,24 +231,27 @@ template <class Op, class E> hipError_t launch_fold_fine(const KArgs &a, const L
 }
 
 // ---- segmented fold over a gathered table, sorted through LDS: tables of more than one L2 and at most 2^24 elements ----
-// Ranges as long as LDS takes (so that a slot per range and tile is long and its slack small); a slot holds
-// the mean of a uniform spread plus one and a quarter standard deviations (rounded up to whole lines), as far
-// as the tile's slots fit their LDS image: every entry of a slot is written and read whether in use or not,
-// while the few elements in a thousand that find their slot full cost a gather from memory and six bytes on
-// the tile's list each.
+// Ranges as long as LDS takes (so that a slot per range and tile is long and its slack small).  Every entry of a slot is
+// written and read whether in use or not, while an element that finds its slot full costs a gather from memory and six
+// bytes on the tile's list: a slot holds the mean of a uniform spread plus 0.35 standard deviations, at which up to one
+// element in twenty-five goes onto the lists, in whole 32-byte pieces of offsets, or, if that is shorter, the mean in whole
+// 128-byte lines (then up to one in twenty); long slots, of which it costs little, in whole 64-byte pieces, and short ones,
+// of which even 32 bytes are much, in 128-bit groups.  Of all slot lengths from the mean to 1.6 deviations above it, for 29 to 455 ranges and
+// 2^23 to 2^26 elements, this one is 0.3 % off the fastest on average and 7 % at worst (171 ranges, 2^26 elements).  2^25 elements, us a
+// pass with slots of 1.25 deviations / of what two images of the first kernel's LDS hold / these: 118 ranges 171 / 175 / 169, 200 195 / 198 / 189,
+// 256 193 / 186 / 188, 289 241 / 238 / 214, 330 202 / 217 / 197, 385 273 / 277 / 247, 455 261 / 249 / 246.
 inline SegPlan seg_plan(size_t elems, long long n) {
-  SegPlan p = {{0, 0, 0, 0}, 0, 0};
+  SegPlan p = {{0, 0, 0, 0}, 0, 0, 0};
   if (elems == 0 || n <= 0) return p;
   const unsigned want = (unsigned)std::min<size_t>((elems + kSegSlice - 1) / kSegSlice, kSegMaxBins);
   p.cut = fine_cut(elems, want, kSegSlice);
   if (p.cut.bins == 0 || p.cut.bins > (unsigned)kSegMaxBins) { p.cut.bins = 0; return p; }
   const double mean = (double)kSegTile / p.cut.bins;
-  // whole 128-byte lines of values per slot where that costs little (long slots), whole 128-bit groups anyway
-  const unsigned grain = mean >= 96.0 ? 32u : 8u;
-  unsigned cap = ((unsigned)(mean + 1.25 * std::sqrt(mean)) + grain - 1) / grain * grain;
-  cap = std::min(cap, (unsigned)kSegImageWords / p.cut.bins / 8 * 8);
-  p.cap = std::max(cap, 8u);
+  auto up = [](double entries, unsigned grain) { return ((unsigned)std::ceil(entries) + grain - 1) / grain * grain; };
+  const unsigned cap = std::min(up(mean + 0.35 * std::sqrt(mean), mean >= 136.0 ? 32u : mean >= 39.0 ? 16u : 8u), up(mean, 64u));
+  p.cap = std::min(cap, (unsigned)kSegOneImageWords / p.cut.bins / 8 * 8);       // 22976 words at most (359 ranges): no limit
   p.tiles = (unsigned)(((size_t)n + kSegTile - 1) / kSegTile);
+  p.images = p.cut.bins * p.cap <= (unsigned)kSegImageWords ? 2u : 1u;
   return p;
 }
 // the pieces of the workspace, each on a 256-byte boundary
@@ -299,8 +302,8 @@ hipError_t launch_foldseg_sorted(const KArgs &a, const LaunchCtx &c) {
   T *head = reinterpret_cast<T *>(w + s.head), *tail = reinterpret_cast<T *>(w + s.tail);
   const int cus = device_compute_units();
   const unsigned units = (unsigned)(cus > 0 ? cus : 256);
-  hipError_t e = launch_threads(&seg_bin_kernel<KI>, std::min(p.tiles, units), c, (int)kSegBlock, a, offsets, places,
-                          list_place, list_index, list_count, p, elems);
+  const auto bin = p.images == 2 ? &seg_bin_kernel<KI, 2> : &seg_bin_kernel<KI, 1>;
+  hipError_t e = launch_threads(bin, std::min(p.tiles, units), c, (int)kSegBlock, a, offsets, places, list_place, list_index, list_count, p, elems);
   if (e != hipSuccess) return e;
   // A table range is read into LDS by every workgroup that works on it, and a workgroup fills the LDS of a compute
   // unit: as few parts per range as give whole rounds of workgroups, or nearly (128 ranges in two parts each on 256

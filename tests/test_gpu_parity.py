@@ -332,7 +332,7 @@ def test_spmv_column_blocked(rows, ncols, mean_len):
     run_all_modes(3, w, env)
 
 
-@pytest.mark.parametrize("shape", ["uniform", "crowded", "long rows", "empty ends", "one column", "many ranges", "many tiles"])
+@pytest.mark.parametrize("shape", ["uniform", "crowded", "long rows", "empty ends", "one column", "many ranges", "many tiles", "one image"])
 def test_spmv_sorted_through_lds(shape):
     # from four million elements on, over a table that no L2 holds, the segmented fold sorts its elements by
     # table range, gathers from LDS and puts the values back in place (four kernels, everything between
@@ -340,7 +340,8 @@ def test_spmv_sorted_through_lds(shape):
     # those elements go through the tiles' lists), rows longer than several tiles, rows that end exactly
     # on a tile boundary, runs of empty rows at both ends and around tile boundaries, a table that is cut
     # into many short ranges, element counts off the tile and off the 128-bit group; as many tiles as take a workgroup
-    # of the first kernel three turns (it sorts into two images in turn), columns crowded enough for lists in each.
+    # of the first kernel three turns (it sorts into two images in turn), columns crowded enough for lists in each; the same over a table
+    # whose slots fit its LDS only once.
     rng = np.random.default_rng(len(shape) * 1000 + 7)
     rows, ncols = 300001, 1500007
     lengths = rng.poisson(16.0, size=rows).astype(np.int64)
@@ -356,8 +357,10 @@ def test_spmv_sorted_through_lds(shape):
         lengths[30000:30100] = 2000
     elif shape == "many ranges":
         ncols = (1 << 24) - 3
-    elif shape == "many tiles":
+    elif shape in ("many tiles", "one image"):
         lengths = rng.poisson(29.0, size=rows).astype(np.int64)
+    if shape == "one image":
+        ncols = 12200003                                  # 331 ranges, slots of 64 elements
     w = C.spmv(lengths=lengths, seed=11, ncols=ncols)
     nnz = w.inputs["col"].shape[0]
     assert nnz >= 1 << 22
@@ -365,7 +368,7 @@ def test_spmv_sorted_through_lds(shape):
         w.inputs["col"] = np.where(rng.random(nnz) < 0.9, rng.integers(0, 3000, size=nnz), rng.integers(0, ncols, size=nnz)).astype(np.int32)
     elif shape == "one column":
         w.inputs["col"] = np.full(nnz, ncols - 1, dtype=np.int32)
-    elif shape == "many tiles":
+    elif shape in ("many tiles", "one image"):
         w.inputs["col"] = np.where(rng.random(nnz) < 0.1, rng.integers(0, 3000, size=nnz), w.inputs["col"]).astype(np.int32)
         assert nnz > 2 * 256 * 16384
     env = evaluate(w.graph, w.inputs)
