@@ -2684,7 +2684,7 @@ template <> __device__ __forceinline__ void scatter_one<true, float>(float *dest
 
 template <class EI, class EV, class EF, bool Add>
 __global__ __launch_bounds__(kBlock) void scatter_kernel(const Packed<kHeadN, 1u, EI, EV, EF> packed) {
-  const KArgs &a = packed.open();
+  const KArgs &a = packed.in_place();
   using V = typename EV::R;
   struct Item { Vec4<int> f, j; Vec4<V> v; };
   V *dest = static_cast<V *>(a.out[0]);

@@ -524,3 +524,42 @@ def test_single_pass_flag_selects_the_kernel_that_keeps_position_order():
         assert marked.n_clusters == 1 and "{" not in fc.fc_cluster_kernel(g, marked, 0)
         # the single pass needs no workspace beyond the control block
         assert fc.fc_scratch_bytes(g, marked) < fc.fc_scratch_bytes(w.graph, default)
+
+
+def _kernel_metadata(path):
+    """What the compiler noted of every kernel in the library: the AMDGPU metadata of its code objects."""
+    import struct
+    msgpack = pytest.importorskip("msgpack")
+    data = open(path, "rb").read()
+    magic, at, found = b"__CLANG_OFFLOAD_BUNDLE__", 0, []
+    while (at := data.find(magic, at)) >= 0:
+        place, (count,) = at + 32, struct.unpack_from("<Q", data, at + 24)
+        for _ in range(count):
+            offset, size, length = struct.unpack_from("<QQQ", data, place)
+            triple = data[place + 24:place + 24 + length]
+            place += 24 + length
+            if not triple.endswith(b"gfx950"):
+                continue
+            elf = data[at + offset:at + offset + size]
+            sections, = struct.unpack_from("<Q", elf, 40)
+            entry, n = struct.unpack_from("<HH", elf, 58)
+            for k in range(n):
+                kind, _, _, start, length_ = struct.unpack_from("<IQQQQ", elf, sections + k * entry + 4)
+                if kind != 7:                          # SHT_NOTE
+                    continue
+                names, described, note = struct.unpack_from("<III", elf, start)
+                if note == 32:                         # NT_AMDGPU_METADATA
+                    text = start + 12 + (names + 3) // 4 * 4
+                    found += msgpack.unpackb(elf[text:text + described])["amdhsa.kernels"]
+        at += len(magic)
+    return found
+
+
+def test_no_kernel_copies_its_arguments_to_lane_memory():
+    # A kernel that reads its arguments at more places than the compiler follows gets a copy of them in every lane's own
+    # memory (KArgs: more than a kilobyte).  What is left are registers spilled on purpose, for more workgroups on a compute unit.
+    B.lib()
+    kernels = _kernel_metadata(B._LIB_PATH)
+    assert len(kernels) > 200
+    large = {k[".name"]: k[".private_segment_fixed_size"] for k in kernels if k[".private_segment_fixed_size"] > 64}
+    assert not large, large
