@@ -16,26 +16,7 @@
 
 namespace fc {
 
-// A group a lane at a time, single elements for the rest.
-__global__ __launch_bounds__(kBlock, 1) void interp_kernel(const KArgs a, Control *ctl, unsigned long long *partials) {
-  const unsigned n = (unsigned)a.n, n4 = n & ~3u;
-  const unsigned epoch = epoch_at_start(ctl);
-  unsigned acc[kInterpFolds] = {interp_identity(a.fold_op[0]), interp_identity(a.fold_op[1])};
-  constexpr unsigned kTileOf = kBlock * kVec;
-  unsigned none[kVec], none1[1];
-  for (unsigned base = blockIdx.x * kTileOf; base < n4; base += a.grid * kTileOf) {
-    const unsigned i = base + threadIdx.x * kVec;
-    if (i >= n4) break;
-    interp_run<1, kInterpDepth, kInterpGathers, kBlock, false>(a, 0, i, kTileOf, InterpAhead<1, false>(), acc, none);
-  }
-  if (blockIdx.x == 0 && threadIdx.x < n - n4)
-    interp_run<0, kInterpDepth, kInterpGathers, kBlock, false>(a, 0, n4 + threadIdx.x, 0u, InterpAhead<0, false>(), acc, none1);
-  interp_finish<kWavesPerBlock>(a, acc, ctl, partials, epoch);
-}
-
 constexpr int kShortDepth = 2;        // values below the top of the stack
-
-using Quad = unsigned __attribute__((ext_vector_type(4)));
 
 // The elements a lane works on: G groups, `apart` elements from each other, the first at `first`.  Single groups (G = 1) may be
 // cut off by the end of the array: of theirs the first `valid` exist, and the others stand for the first once more (so
@@ -45,12 +26,12 @@ template <int G> struct Span {
   __device__ __forceinline__ Span(unsigned, unsigned first_, unsigned apart_, unsigned) : first(first_), apart(apart_) {}
   __device__ __forceinline__ unsigned offset(int e) const { return (e / kVec) * apart + e % kVec; }
   __device__ __forceinline__ bool exists(int) const { return true; }
-  __device__ __forceinline__ void read(const void *array, Quad (&x)[G]) const {
+  __device__ __forceinline__ void read(const void *array, Words4 (&x)[G]) const {
     const unsigned *p = static_cast<const unsigned *>(array) + first;
 #pragma unroll
     for (int g = 0; g < G; ++g) x[g] = __builtin_nontemporal_load(reinterpret_cast<const Quad128<unsigned> *>(p + g * apart));
   }
-  template <bool Keep> __device__ __forceinline__ void write(void *array, const Quad (&x)[G]) const {
+  template <bool Keep> __device__ __forceinline__ void write(void *array, const Words4 (&x)[G]) const {
     using Raw = Quad128<unsigned>;
     unsigned *p = static_cast<unsigned *>(array) + first;
 #pragma unroll
@@ -68,24 +49,43 @@ template <> struct Span<1> {
   __device__ __forceinline__ unsigned offset(int e) const { return (unsigned)e < valid ? e : 0; }
   __device__ __forceinline__ bool exists(int e) const { return (unsigned)e < valid; }
   // a 32-bit word past the end reads as zero, and is not written
-  __device__ __forceinline__ void read(const void *array, Quad (&x)[1]) const {
+  template <bool Stream = true> __device__ __forceinline__ void read(const void *array, Words4 (&x)[1]) const {
     const __amdgpu_buffer_rsrc_t buf =
         __builtin_amdgcn_make_buffer_rsrc(const_cast<unsigned *>(static_cast<const unsigned *>(array) + base), 0, (int)bytes, 0x00020000);
-    const Raw v = __builtin_amdgcn_raw_buffer_load_b128(buf, (int)((first - base) * 4u), 0, 0x2);
+    const Raw v = __builtin_amdgcn_raw_buffer_load_b128(buf, (int)((first - base) * 4u), 0, Stream ? 0x2 : 0);
 #pragma unroll
     for (int e = 0; e < kVec; ++e) x[0][e] = (unsigned)(exists(e) ? v[e] : v[0]);
   }
-  template <bool Keep> __device__ __forceinline__ void write(void *array, const Quad (&x)[1]) const {
+  template <bool Keep> __device__ __forceinline__ void write(void *array, const Words4 (&x)[1]) const {
     const __amdgpu_buffer_rsrc_t buf = __builtin_amdgcn_make_buffer_rsrc(static_cast<unsigned *>(array) + base, 0, (int)bytes, 0x00020000);
     const Raw v = __builtin_bit_cast(Raw, x[0]);
     __builtin_amdgcn_raw_buffer_store_b128(v, buf, (int)((first - base) * 4u), 0, Keep ? 0 : 0x2);
   }
 };
 
+// The programs that are not short: a group a lane at a time, the end of the array as a group like the others.  Single elements
+// for it were a pass of their own behind a workgroup's tiles, all of its code fetched for the first time (x = exp(-a), add3(x, b, add3(b,
+// c, d * e)) stored and summed, us a pass before / now: 4099 elements 12.9 / 9.0, 300001 13.0 / 9.5, 1000003 13.3 / 11.6, 2^24 113).  All groups
+// as if they could be cut off take more instructions: 2^24 elements 118.6 us, 60000 9.8 instead of 9.0.
+__global__ __launch_bounds__(kBlock, 1) void interp_kernel(const KArgs a, Control *ctl, unsigned long long *partials) {
+  const unsigned n = (unsigned)a.n;
+  const unsigned epoch = epoch_at_start(ctl);
+  unsigned acc[kInterpFolds] = {interp_identity(a.fold_op[0]), interp_identity(a.fold_op[1])};
+  constexpr unsigned kTileOf = kBlock * kVec;
+  unsigned none[kVec], base = blockIdx.x * kTileOf;
+  const unsigned mine = threadIdx.x * kVec;
+  for (; base + kTileOf <= n; base += a.grid * kTileOf)
+    interp_run<1, kInterpDepth, kInterpGathers, kBlock, false>(a, 0, base + mine, kTileOf, InterpAhead<1, false>(), acc, none);
+  if (base + mine < n)                                   // one workgroup's, and for short arrays all that it does
+    interp_run<1, kInterpDepth, kInterpGathers, kBlock, false>(a, 0, base + mine, kTileOf, InterpAhead<1, false>(), acc, none,
+                                                               Span<1>(base, base + mine, 0u, n));
+  interp_finish<kWavesPerBlock>(a, acc, ctl, partials, epoch);
+}
+
 // The first D arrays that the program reads at the elements' own positions, read ahead of the run.
 template <int G, int D> struct ShortAhead {
   static_assert(D == 2 || D == 4, "arrays read ahead");
-  Quad v[D][G];
+  Words4 v[D][G];
   __device__ __forceinline__ void read(const KArgs &a, const Span<G> span) {
 #pragma unroll
     for (int k = 0; k < D; ++k)
@@ -109,7 +109,7 @@ __device__ __forceinline__ void interp_short(const KArgs &a, const Span<G> span,
     asm volatile("" : "+v"(first));
     return (int)(first + span.offset(e));
   };
-  Quad top[G], second[G], third[Depth > 1 ? G : 1];    // vectors of four: the compiler moves them in pairs of registers
+  Words4 top[G], second[G], third[Depth > 1 ? G : 1];    // vectors of four: the compiler moves them in pairs of registers
   int at[Enter ? V : 1];                               // the positions a gather's source is read at
   int count = 0;                                       // values on the stack: the same in every lane, as is all that branches
   bool inside = false;                                 // below a gather: the position is `at`
@@ -139,7 +139,7 @@ __device__ __forceinline__ void interp_short(const KArgs &a, const Span<G> span,
   auto take = [&](int k) {
 #pragma unroll
     for (int g = 0; g < G; ++g) {
-      const Quad v0 = ahead.v[0][g], v1 = ahead.v[1][g], v2 = ahead.v[2 % D][g], v3 = ahead.v[3 % D][g];   // values: a choice of addresses would put v into memory
+      const Words4 v0 = ahead.v[0][g], v1 = ahead.v[1][g], v2 = ahead.v[2 % D][g], v3 = ahead.v[3 % D][g];   // values: a choice of addresses would put v into memory
       top[g] = k == 0 ? v0 : D == 2 || k == 1 ? v1 : k == 2 ? v2 : v3;
     }
   };

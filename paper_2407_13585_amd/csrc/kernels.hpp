@@ -405,6 +405,8 @@ template <int G, bool Early> struct InterpAhead {
   }
 };
 
+using Words4 = unsigned __attribute__((ext_vector_type(4)));
+
 // the stack columns of a workgroup in LDS, for Columns elements a lane
 template <int Threads, int Columns>
 __device__ __forceinline__ unsigned (*interp_stack())[Columns][Threads] {
@@ -412,15 +414,32 @@ __device__ __forceinline__ unsigned (*interp_stack())[Columns][Threads] {
   return below;
 }
 
+// The elements of a run that is not cut off by the end of the array (for the others: Span<1> of interp.hpp).
+struct Uncut {};
+
 // Starts at instruction `pc`; a kCodeYield ends the run with the program's values in `result`.
 // Depth, Nest: values below the top of the stack and nested gathers that the code needs at most.  LdsThreads: threads
 // of the workgroup if the values below the top are to lie in LDS (a column per lane), or 0.
-template <int G, int Depth, int Nest, int LdsThreads, bool Early, int Columns = kVec>
+template <int G, int Depth, int Nest, int LdsThreads, bool Early, int Columns = kVec, class Cut = Uncut>
 __device__ __forceinline__ void interp_run(const KArgs &a, int pc, unsigned first, unsigned apart, const InterpAhead<G, Early> &ahead,
-                                           unsigned (&acc)[kInterpFolds], unsigned (&result)[InterpAhead<G, Early>::V]) {
+                                           unsigned (&acc)[kInterpFolds], unsigned (&result)[InterpAhead<G, Early>::V], const Cut &cut = Cut()) {
   using Raw = unsigned __attribute__((ext_vector_type(4)));
   constexpr int V = InterpAhead<G, Early>::V;
-  auto own = [&](int e) { return (int)(first + (e / kVec) * apart + e % kVec); };      // the elements' own positions
+  constexpr bool kCut = !std::is_same<Cut, Uncut>::value;
+  static_assert(!kCut || (G == 1 && !Early), "a group that may be cut off, read where the code asks");
+  auto own = [&](int e) {                              // the elements' own positions
+    if constexpr (kCut) return (int)(first + cut.offset(e)); else return (int)(first + (e / kVec) * apart + e % kVec);
+  };
+  auto read_own = [&](int array, int k, unsigned (&x)[V]) {
+    if constexpr (kCut) {
+      Words4 q[1];
+      cut.template read<false>(a.in[array], q);
+#pragma unroll
+      for (int e = 0; e < V; ++e) x[e] = q[0][e];
+    } else {
+      ahead.get(a, array, first, apart, k, x);
+    }
+  };
   int at[V];                                           // the positions element programs read at
   int suspended[Nest > 1 ? Nest - 1 : 1][V];           // of the gathers around the innermost but one; outermost: own positions
   unsigned top[V], below[LdsThreads ? 1 : Depth][V];   // an array of its own: as part of a struct it would be put into memory
@@ -463,7 +482,7 @@ __device__ __forceinline__ void interp_run(const KArgs &a, int pc, unsigned firs
       case kCodeIn: {
         push_room();
         if (c.b != 0) {
-          ahead.get(a, c.a, first, apart, c.b - 1, top);
+          read_own(c.a, c.b - 1, top);
         } else {
           const unsigned *p = static_cast<const unsigned *>(a.in[c.a]);
 #pragma unroll
@@ -474,7 +493,7 @@ __device__ __forceinline__ void interp_run(const KArgs &a, int pc, unsigned firs
       case kCodeLookup: {
         push_room();
         const unsigned *p = static_cast<const unsigned *>(a.in[c.a]);
-        ahead.get(a, c.c, first, apart, c.b - 1, top);
+        read_own(c.c, c.b - 1, top);
 #pragma unroll
         for (int e = 0; e < V; ++e) top[e] = p[(int)top[e]];
         break;
@@ -529,6 +548,12 @@ __device__ __forceinline__ void interp_run(const KArgs &a, int pc, unsigned firs
           at[e] = Nest > 2 && gathers == 2 ? suspended[Nest > 2 ? 1 : 0][e] : Nest > 1 && gathers == 1 ? suspended[0][e] : own(e);
         break;
       case kCodeStore: {
+        if constexpr (kCut) {
+          const Words4 q[1] = {{top[0], top[1], top[2], top[3]}};
+          if (a.keeps(c.a)) cut.template write<true>(a.out[c.a], q); else cut.template write<false>(a.out[c.a], q);
+          if (!(c.op & kCodeStays)) pop();
+          break;
+        }
         unsigned *p = static_cast<unsigned *>(a.out[c.a]) + first;
         if (G == 0) p[0] = top[0];
 #pragma unroll
@@ -548,7 +573,9 @@ __device__ __forceinline__ void interp_run(const KArgs &a, int pc, unsigned firs
       default: {                                        // kCodeFold
         unsigned v = c.c == 0 ? acc[0] : acc[1];
 #pragma unroll
-        for (int e = 0; e < V; ++e) v = interp_fold(c.b, v, top[e]);
+        for (int e = 0; e < V; ++e) {
+          if constexpr (kCut) v = interp_fold(c.b, v, cut.exists(e) ? top[e] : interp_identity(c.b)); else v = interp_fold(c.b, v, top[e]);
+        }
         if (c.c == 0) acc[0] = v; else acc[1] = v;
         if (!(c.op & kCodeStays)) pop();
         break;

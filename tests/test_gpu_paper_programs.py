@@ -576,6 +576,45 @@ def test_interpreted_programs_of_every_form(shape, n):
     assert abs(float(fused.fetch("s")[0]) - w.sum()) <= 1e-5 * w.sum()
 
 
+@pytest.mark.parametrize("fold", ["add", "max"])
+@pytest.mark.parametrize("shape", ["deep", "nested"])
+@pytest.mark.parametrize("n", [1, 2, 3, 5, 1023, 1024, 1025, 2 * 1024 + 1021, 300001])
+def test_long_interpreted_programs_end_with_the_array(n, shape, fold):
+    # programs of more than two values below the top of the stack and of nested gathers: the last group of four elements is cut
+    # off by the end of the array.  All values are negative, so that an element past the end would show in the maximum.
+    # Bit for bit as one kernel per combinator; the sum within 1e-5 of the sum of the magnitudes, the bound of the folds.
+    rng = np.random.default_rng(n)
+    g = Graph()
+    for k in "abcd":
+        g.add(k, "input", "f32", (n,))
+    g.add("i", "input", "i32", (n,))
+    m = lambda name, fn, *args, **kw: g.add(name, "map", "f32", (n,), fn=fn, args=args, **kw)
+    m("x", "affine", "a", fparam=(2.0, -1.0))
+    if shape == "deep":
+        m("y", "mul2", "d", "x")
+        m("z", "add3", "b", "c", "y")
+        m("w", "add3", "x", "b", "z", output=True)
+    else:
+        g.add("j", "generate", "i32", (n,), fn="iota_rev")
+        g.add("u", "gather", "f32", (n,), args=("j", "x"))
+        g.add("v", "gather", "f32", (n,), args=("i", "u"))
+        m("w", "add2", "v", "b", output=True)
+    g.add("r", "fold", "f32", (1,), fn=fold, args=("w",), output=True)
+    ins = {k: rng.uniform(-2.0, -1.0, n).astype(F32) for k in "abc"}
+    ins["d"] = rng.uniform(0.5, 1.0, n).astype(F32)
+    ins["i"] = rng.integers(0, n, n).astype(np.int32)
+    g = prune(g)
+    ins = {nd.name: ins[nd.name] for nd in g.nodes if nd.kind == "input"}
+    fused, unfused, name = fused_and_unfused(g, ins)
+    assert "interpreted" in name
+    P.assert_bit_exact(fused.fetch("w"), unfused.fetch("w"), f"{shape} n={n}")
+    w = unfused.fetch("w").astype(np.float64)
+    if fold == "max":
+        P.assert_bit_exact(fused.fetch("r"), unfused.fetch("r"), f"{shape} n={n} max")
+    else:
+        assert abs(float(fused.fetch("r")[0]) - w.sum()) <= 1e-5 * np.abs(w).sum()
+
+
 @pytest.mark.parametrize("n", [1, 3, 1020, 1024, 1025, (1 << 20) - 4, 1 << 20, (1 << 20) + 3, (1 << 20) + 1028, (1 << 20) + 2047])
 def test_interpreted_cluster_sizes(n):
     # one group of four elements a lane below 2^20 elements, two above, the rest of the last tile shared out among the
