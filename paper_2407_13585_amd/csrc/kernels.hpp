@@ -365,33 +365,32 @@ __device__ __forceinline__ unsigned interp_identity(int op) {
   }
 }
 
-// A lane runs a program for G 128-bit groups of elements at a time, which lie `apart` elements from each other,
-// or (G = 0) for one element, so that the cost of reading and decoding an instruction is shared.
+// A lane runs a program for a 128-bit group of elements at a time (G = 1), so that the cost of reading and decoding an
+// instruction is shared, or for one element (G = 0).
 // What element program `root` reads at the elements' own positions, read ahead.
 template <int G, bool Early> struct InterpAhead {
-  static constexpr int V = G ? G * kVec : 1;
+  static constexpr int V = G ? kVec : 1;
   using Group = Quad128<unsigned>;                     // a scan from the right reads groups at n - 4 - i, n of any length
   unsigned v[Early ? kInterpDirect : 1][V];
-  template <bool Stream> static __device__ __forceinline__ void read_one(const void *array, unsigned first, unsigned apart, unsigned (&x)[V]) {
+  static __device__ __forceinline__ void read_one(const void *array, unsigned first, unsigned (&x)[V]) {
     const unsigned *p = static_cast<const unsigned *>(array) + first;
-    if (G == 0) x[0] = p[0];
+    if constexpr (G == 0) {
+      x[0] = p[0];
+    } else {
+      const Group y = *reinterpret_cast<const Group *>(p);
 #pragma unroll
-    for (int g = 0; g < G; ++g) {
-      const Group *q = reinterpret_cast<const Group *>(p + g * apart);
-      const Group y = Stream ? __builtin_nontemporal_load(q) : *q;
-#pragma unroll
-      for (int c = 0; c < kVec; ++c) x[g * kVec + c] = y[c];
+      for (int c = 0; c < kVec; ++c) x[c] = y[c];
     }
   }
-  template <bool Stream> __device__ __forceinline__ void read(const KArgs &a, int root, unsigned first, unsigned apart) {
+  __device__ __forceinline__ void read(const KArgs &a, int root, unsigned first) {
     if constexpr (Early) {
 #pragma unroll
       for (int k = 0; k < kInterpDirect; ++k)
-        if (k < a.n_direct[root]) read_one<Stream>(a.in[a.direct[root][k]], first, apart, v[k]);
+        if (k < a.n_direct[root]) read_one(a.in[a.direct[root][k]], first, v[k]);
     }
   }
   // x: array number k of those read ahead, which is external array `array`; both are the same in all lanes
-  __device__ __forceinline__ void get(const KArgs &a, int array, unsigned first, unsigned apart, int k, unsigned (&x)[V]) const {
+  __device__ __forceinline__ void get(const KArgs &a, int array, unsigned first, int k, unsigned (&x)[V]) const {
     if constexpr (Early) {
       static_assert(kInterpDirect == 4, "one value per array");
 #pragma unroll
@@ -400,7 +399,7 @@ template <int G, bool Early> struct InterpAhead {
         x[e] = k == 0 ? v0 : k == 1 ? v1 : k == 2 ? v2 : v3;
       }
     } else {
-      read_one<false>(a.in[array], first, apart, x);
+      read_one(a.in[array], first, x);
     }
   }
 };
@@ -418,17 +417,15 @@ __device__ __forceinline__ unsigned (*interp_stack())[Columns][Threads] {
 struct Uncut {};
 
 // Starts at instruction `pc`; a kCodeYield ends the run with the program's values in `result`.
-// Depth, Nest: values below the top of the stack and nested gathers that the code needs at most.  LdsThreads: threads
-// of the workgroup if the values below the top are to lie in LDS (a column per lane), or 0.
-template <int G, int Depth, int Nest, int LdsThreads, bool Early, int Columns = kVec, class Cut = Uncut>
-__device__ __forceinline__ void interp_run(const KArgs &a, int pc, unsigned first, unsigned apart, const InterpAhead<G, Early> &ahead,
+// LdsThreads: threads of the workgroup if the values below the top of the stack are to lie in LDS (a column per lane), or 0.
+template <int G, int LdsThreads, bool Early, int Columns = kVec, class Cut = Uncut>
+__device__ __forceinline__ void interp_run(const KArgs &a, int pc, unsigned first, const InterpAhead<G, Early> &ahead,
                                            unsigned (&acc)[kInterpFolds], unsigned (&result)[InterpAhead<G, Early>::V], const Cut &cut = Cut()) {
-  using Raw = unsigned __attribute__((ext_vector_type(4)));
   constexpr int V = InterpAhead<G, Early>::V;
   constexpr bool kCut = !std::is_same<Cut, Uncut>::value;
   static_assert(!kCut || (G == 1 && !Early), "a group that may be cut off, read where the code asks");
   auto own = [&](int e) {                              // the elements' own positions
-    if constexpr (kCut) return (int)(first + cut.offset(e)); else return (int)(first + (e / kVec) * apart + e % kVec);
+    if constexpr (kCut) return (int)(first + cut.offset(e)); else return (int)first + e;
   };
   auto read_own = [&](int array, int k, unsigned (&x)[V]) {
     if constexpr (kCut) {
@@ -437,17 +434,18 @@ __device__ __forceinline__ void interp_run(const KArgs &a, int pc, unsigned firs
 #pragma unroll
       for (int e = 0; e < V; ++e) x[e] = q[0][e];
     } else {
-      ahead.get(a, array, first, apart, k, x);
+      ahead.get(a, array, first, k, x);
     }
   };
   int at[V];                                           // the positions element programs read at
-  int suspended[Nest > 1 ? Nest - 1 : 1][V];           // of the gathers around the innermost but one; outermost: own positions
-  unsigned top[V], below[LdsThreads ? 1 : Depth][V];   // an array of its own: as part of a struct it would be put into memory
+  static_assert(kInterpGathers == 3, "two positions suspended at most");
+  int suspended[kInterpGathers - 1][V];                // of the gathers around the innermost but one; outermost: own positions
+  unsigned top[V], below[LdsThreads ? 1 : kInterpDepth][V];   // an array of its own: as part of a struct it would be put into memory
   unsigned (*column)[Columns][LdsThreads ? LdsThreads : 1] = nullptr;
   if constexpr (LdsThreads != 0) column = interp_stack<LdsThreads, Columns>();
   static_assert(LdsThreads == 0 || V <= Columns, "a column for each element");
 #pragma unroll
-  for (int k = 0; k < (LdsThreads ? 1 : Depth); ++k)
+  for (int k = 0; k < (LdsThreads ? 1 : kInterpDepth); ++k)
 #pragma unroll
     for (int e = 0; e < V; ++e) below[k][e] = 0u;
   auto set_below = [&](int k, int e, unsigned x) { if (LdsThreads) column[k][e % Columns][threadIdx.x] = x; else below[k][e] = x; };
@@ -520,7 +518,7 @@ __device__ __forceinline__ void interp_run(const KArgs &a, int pc, unsigned firs
           for (int k = count - nargs + 1; k < count; ++k) {
 #pragma unroll
             for (int e = 0; e < V; ++e) {
-              const unsigned y = k == count - 1 ? top[e] : get_below(min(k, Depth - 1), e);
+              const unsigned y = k == count - 1 ? top[e] : get_below(min(k, kInterpDepth - 1), e);
               x[e] = (unsigned)as_bits(FnAdd2::apply(a.p[c.b], from_bits<float>((int)x[e]), from_bits<float>((int)y)));
             }
           }
@@ -533,8 +531,8 @@ __device__ __forceinline__ void interp_run(const KArgs &a, int pc, unsigned firs
       case kCodeEnter: {
 #pragma unroll
         for (int e = 0; e < V; ++e) {
-          if (Nest > 1 && gathers == 1) suspended[0][e] = at[e];
-          if (Nest > 2 && gathers == 2) suspended[Nest > 2 ? 1 : 0][e] = at[e];
+          if (gathers == 1) suspended[0][e] = at[e];
+          if (gathers == 2) suspended[1][e] = at[e];
           at[e] = (int)top[e];
         }
         ++gathers;
@@ -545,7 +543,7 @@ __device__ __forceinline__ void interp_run(const KArgs &a, int pc, unsigned firs
         --gathers;
 #pragma unroll
         for (int e = 0; e < V; ++e)
-          at[e] = Nest > 2 && gathers == 2 ? suspended[Nest > 2 ? 1 : 0][e] : Nest > 1 && gathers == 1 ? suspended[0][e] : own(e);
+          at[e] = gathers == 2 ? suspended[1][e] : gathers == 1 ? suspended[0][e] : own(e);
         break;
       case kCodeStore: {
         if constexpr (kCut) {
@@ -555,11 +553,11 @@ __device__ __forceinline__ void interp_run(const KArgs &a, int pc, unsigned firs
           break;
         }
         unsigned *p = static_cast<unsigned *>(a.out[c.a]) + first;
-        if (G == 0) p[0] = top[0];
-#pragma unroll
-        for (int g = 0; g < G; ++g) {
-          const Raw x = {top[(g * kVec) % V], top[(g * kVec + 1) % V], top[(g * kVec + 2) % V], top[(g * kVec + 3) % V]};
-          Raw *q = reinterpret_cast<Raw *>(p + g * apart);
+        if constexpr (G == 0) {
+          p[0] = top[0];
+        } else {
+          const Words4 x = {top[0], top[1], top[2], top[3]};
+          Words4 *q = reinterpret_cast<Words4 *>(p);
           if (a.keeps(c.a)) {
             asm volatile("" ::: "memory");             // keeps the two stores apart: merged, both would be ordinary
             *q = x;
@@ -640,16 +638,16 @@ struct Interp {
   template <int Base, bool Stream = false> static __device__ __forceinline__ T eval(const KArgs &a, int i) {
     unsigned r[1] = {0u}, none[kInterpFolds] = {0u, 0u};
     InterpAhead<0, Early> ahead;
-    ahead.template read<false>(a, K, (unsigned)i, 0u);
-    interp_run<0, kInterpDepth, kInterpGathers, LdsThreads, Early, Columns>(a, (int)a.root[K], (unsigned)i, 0u, ahead, none, r);
+    ahead.read(a, K, (unsigned)i);
+    interp_run<0, LdsThreads, Early, Columns>(a, (int)a.root[K], (unsigned)i, ahead, none, r);
     return from_bits<T>((int)r[0]);
   }
   // i may be any position, as for the compiled element programs
   template <int Base> static __device__ __forceinline__ Vec4<T> eval4(const KArgs &a, int i) {
     unsigned r[kVec] = {0u, 0u, 0u, 0u}, none[kInterpFolds] = {0u, 0u};
     InterpAhead<1, Early> ahead;
-    ahead.template read<false>(a, K, (unsigned)i, 0u);
-    interp_run<1, kInterpDepth, kInterpGathers, LdsThreads, Early, Columns>(a, (int)a.root[K], (unsigned)i, 0u, ahead, none, r);
+    ahead.read(a, K, (unsigned)i);
+    interp_run<1, LdsThreads, Early, Columns>(a, (int)a.root[K], (unsigned)i, ahead, none, r);
     return Vec4<T>{{from_bits<T>((int)r[0]), from_bits<T>((int)r[1]), from_bits<T>((int)r[2]), from_bits<T>((int)r[3])}};
   }
   static void sig(std::string &s) { s += std::string("*") + DtypeName<T>::s(); }
