@@ -444,7 +444,10 @@ int fc_cluster_kernel(const fc_graph *g, const fc_partition *p, int32_t cluster,
     rc = fc::plan_cluster(m, c, cl[cluster], launch, err);
     if (rc != FC_OK) return fail(rc, err);
     std::string s = launch.sig;
-    if (launch.instance && launch.instance->variant[0]) s += std::string(" {") + launch.instance->variant + "}";
+    if (launch.instance) {
+      const char *variant = launch.instance->form ? launch.instance->form(launch.args) : launch.instance->variant;
+      if (variant[0]) s += std::string(" {") + variant + "}";
+    }
     if (!name || capacity < s.size() + 1) return fail(FC_E_ARG, "name buffer too small");
     std::memcpy(name, s.c_str(), s.size() + 1);
     return FC_OK;

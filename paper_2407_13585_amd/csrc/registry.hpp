@@ -47,6 +47,7 @@ struct Instance {
   Launcher launch;
   bool (*accept)(const KArgs &) = nullptr;   // extra conditions on parameters / extents
   const char *variant = "";                  // distinguishes instances that share a signature
+  const char *(*form)(const KArgs &) = nullptr;   // the same, where one instance has several kernels to choose from
   size_t (*workspace)(const KArgs &) = nullptr;   // bytes of scratch beyond the control block a launch needs
 };
 

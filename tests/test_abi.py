@@ -165,7 +165,7 @@ def test_a_copy_of_a_bound_program_shares_it(monkeypatch):
         copy.copy(B.BoundRun(w.graph, fc.fc_plan(w.graph, "bytes"), bufs, fake)._handle)
 
 
-def test_a_bound_program_is_called_with_a_stream_and_nothing_else():
+def test_a_bound_program_is_called_with_a_stream_and_nothing_else(monkeypatch):
     # positional, by name, None and an integer beyond 32 bits reach the launch (which fails here or is not made: the
     # program and its function are stand-ins), whatever else the Python method is left to refuse; a failing call raises
     import copy
@@ -191,9 +191,37 @@ def test_a_bound_program_is_called_with_a_stream_and_nothing_else():
         with pytest.raises(TypeError):
             bound(*args, **kw)
     assert len(seen) == 5
-    # a copy goes its own way: it is not armed with the stand-in
+    # a copy goes its own way: its first call is the Python method's, which arms it with the library's own function
+    others, firsts = [], []
+    other = ctypes.CFUNCTYPE(ctypes.c_int, ctypes.c_void_p, ctypes.c_void_p)(lambda program, stream: others.append((program, stream)) or 0)
+    monkeypatch.setattr(B, "_run_bound_address", ctypes.cast(other, ctypes.c_void_p).value)
     twin = copy.copy(bound)
-    assert twin._handle is bound._handle and len(seen) == 5
+    assert twin._handle is bound._handle
+    twin._run = lambda program, stream: firsts.append((program, stream)) or 0
+    assert twin(3) is None and twin(4) is None and twin(stream=6) is None
+    handle = bound._handle.value
+    assert firsts == [(handle, 3), (handle, 6)] and others == [(handle, 4)] and len(seen) == 5
+
+
+def test_which_interpreted_programs_look_up_in_lds():
+    # the rule of the lookups from LDS: as many as pay for filling it find their element there, whatever share of all they are
+    def name(n, elems, *more):
+        g = Graph()
+        for nm, dtype, size in (("d", "f32", n), ("i", "i32", n), ("t", "f32", elems)) + tuple((k, "f32", n) for k in more):
+            g.add(nm, "input", dtype, (size,))
+        g.add("v", "gather", "f32", (n,), args=("i", "t"))
+        g.add("e", "map", "f32", (n,), fn="exp_neg", args=("d",))
+        g.add("w", "map", "f32", (n,), fn="add3" if more else "mul2", args=("e", "v") + more, output=True)
+        part = fc.fc_plan(g, "bytes")
+        assert part.n_clusters == 1
+        return fc.fc_cluster_kernel(g, part, 0)
+
+    for n, elems, lds in ((1 << 22, 1 << 16, True), (1 << 20, 39000, False), (1 << 21, 16384, True), (1 << 22, 1 << 18, False),
+                          (1 << 23, 500000, False), (1 << 25, 1000000, True), (1 << 27, 3900000, True), (1 << 24, 4000000, False),
+                          (1 << 22, 8191, False), (1 << 24, 8191, True), (1 << 24, 1, True)):
+        assert ("interpreted, lookups from LDS" in name(n, elems)) == lds, (n, elems)
+        assert "{interpreted" in name(n, elems)
+    assert "{interpreted}" in name(1 << 22, 1 << 16, "c")      # three arrays: no registers for it
 
 
 @pytest.mark.parametrize("state", ["absent, no compiler", "unreadable, newer than its source", "unreadable, no compiler"])

@@ -529,7 +529,7 @@ def test_interpreted_lookups_from_lds(n, elems):
     ins = {"i": rng.integers(0, elems, n).astype(np.int32), "t": rng.uniform(0.5, 1.0, elems).astype(F32), "d": rng.uniform(0.0, 4.0, n).astype(F32)}
     ins["i"][:4] = ins["i"][-4:] = (0, elems - 1, min(elems - 1, 39935), min(elems - 1, 39936))
     fused, unfused, name = fused_and_unfused(g, ins)
-    assert "interpreted" in name
+    assert ("lookups from LDS" in name) == (elems > 7), name
     w = unfused.fetch("w")
     for _ in range(2):
         for out in ("w", "u", "m"):
@@ -537,6 +537,60 @@ def test_interpreted_lookups_from_lds(n, elems):
         assert abs(float(fused.fetch("s")[0]) - w.astype(np.float64).sum()) <= 1e-5 * w.astype(np.float64).sum()
         fused.run()
     assert [int(x) for x in fused.control_words()[:2]] == [3, 0]
+
+
+def test_a_bound_program_called_from_two_threads():
+    # one program of one kernel, which leaves its result through the hand-over between workgroups: calls of two threads
+    # go to one stream, each a launch of its own
+    import threading
+    rng = np.random.default_rng(5)
+    n = 300001
+    g = Graph()
+    g.add("x", "input", "f32", (n,))
+    g.add("y", "map", "f32", (n,), fn="affine", fparam=(2.0, 1.0), args=("x",))
+    g.add("r", "fold", "f32", (1,), fn="add", args=("y",), output=True)
+    ins = {"x": rng.uniform(0.0, 1.0, n).astype(F32)}
+    prog = device_program(g, ins, fc().fc_plan(g, "bytes"))
+    failures = []
+
+    def calls():
+        try:
+            for _ in range(200):
+                prog.run()
+        except Exception as e:                               # shown below
+            failures.append(e)
+
+    threads = [threading.Thread(target=calls) for _ in range(2)]
+    for t in threads:
+        t.start()
+    for t in threads:
+        t.join(60)
+    assert not failures and not any(t.is_alive() for t in threads)
+    P.assert_fold(prog.fetch("r"), evaluate(g, ins)["r"], "two threads")
+    assert [int(x) for x in prog.control_words()[:2]] == [400, 0]
+
+
+@pytest.mark.parametrize("second", ["smaller", "larger", "the same"])
+def test_interpreted_program_of_two_lookups(second):
+    # the first lookup goes to LDS (its table ends behind what LDS holds of it), the second to memory, in a table of its own or in
+    # the same one; the workgroups take slabs two and one at a time
+    n, elems = 3 * 256 * 4096 + 4099, 50001
+    rng = np.random.default_rng(n)
+    others = {"smaller": 1021, "larger": 1 << 20, "the same": elems}[second]
+    g = Graph()
+    for nm, dtype, size in (("i", "i32", n), ("j", "i32", n), ("t", "f32", elems), ("u", "f32", others)):
+        if nm != "u" or second != "the same":
+            g.add(nm, "input", dtype, (size,))
+    g.add("v", "gather", "f32", (n,), args=("i", "t"))
+    g.add("r", "gather", "f32", (n,), args=("j", "t" if second == "the same" else "u"))
+    g.add("w", "map", "f32", (n,), fn="mul2", args=("v", "r"), output=True)
+    g.add("m", "fold", "f32", (1,), fn="max", args=("w",), output=True)
+    ins = {"i": rng.integers(0, elems, n).astype(np.int32), "j": rng.integers(0, others, n).astype(np.int32),
+           "t": rng.uniform(0.5, 1.0, elems).astype(F32), "u": rng.uniform(0.5, 1.0, others).astype(F32)}
+    fused, unfused, name = fused_and_unfused(g, {k: ins[k] for k in ins if k != "u" or second != "the same"})
+    assert "lookups from LDS" in name, name
+    for out in ("w", "m"):
+        P.assert_bit_exact(fused.fetch(out), unfused.fetch(out), out)
 
 
 @pytest.mark.parametrize("shape", ["three", "add3", "computed_index", "five"])
@@ -606,7 +660,7 @@ def test_long_interpreted_programs_end_with_the_array(n, shape, fold):
     g = prune(g)
     ins = {nd.name: ins[nd.name] for nd in g.nodes if nd.kind == "input"}
     fused, unfused, name = fused_and_unfused(g, ins)
-    assert "interpreted" in name
+    assert "interpreted, long" in name, name
     P.assert_bit_exact(fused.fetch("w"), unfused.fetch("w"), f"{shape} n={n}")
     w = unfused.fetch("w").astype(np.float64)
     if fold == "max":

@@ -394,12 +394,15 @@ def test_spmv_sorted_through_lds(shape):
 
 @pytest.mark.parametrize("table,m,spread", [(2200003, 2200003, "permutation"), (3000000, (1 << 21) + 4099, "uniform"),
                                             (2000001, (1 << 21) + 8197, "skewed"), (1 << 22, (1 << 21) + 2, "one"),
-                                            (3000017, (1 << 21) + 77, "middle")])
+                                            (3000017, (1 << 21) + 77, "middle"), (6500003, 6500003, "permutation"),
+                                            (9000001, 4500001, "skewed"), ((1 << 23) + 5, (1 << 22) + 4099, "one"),
+                                            (1 << 24, (1 << 23) + 77, "middle")])
 def test_perm_gather_binned(table, m, spread):
     # a fold over a gather from a table of more than one L2 sorts the indices by table range
     # first (two kernels, the entries in scratch).  A permutation, repeated indices, indices
     # that crowd into one range or one position (more than a slot takes: the remainder is
-    # evaluated on the spot), lengths off the tile and off the 128-bit group.
+    # evaluated on the spot), lengths off the tile and off the 128-bit group; tables of up to 2^23 elements
+    # and 6 x 2^20 positions in 256 ranges, the others in 512.
     rng = np.random.default_rng(table + m)
     xs = rng.standard_normal(size=table).astype(F32)
     if spread == "permutation":
