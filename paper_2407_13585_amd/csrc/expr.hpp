@@ -114,8 +114,7 @@ struct KArgs {    // arguments of one cluster launch
   // them): known before the program runs, so their reads are issued together and ahead of it.
   unsigned char direct[kMaxRoots][kInterpDirect], n_direct[kMaxRoots];
   // An instruction as one word: at an index that is the same for all lanes a scalar read, where the compiler may read
-  // four bytes through the vector unit (row scans of 2^24 interpreted elements 107 us, with words 101).  The scatters, which
-  // read ahead of the run, have scalar reads as it is.
+  // four bytes through the vector unit (row scans of 2^24 interpreted elements 107 us, with words 101).
   __device__ __forceinline__ Code code_word(int pc) const {
     unsigned word;
     __builtin_memcpy(&word, __builtin_assume_aligned(&code[pc], 4), sizeof(word));
@@ -461,7 +460,7 @@ template <int KI, class ES> struct GatherChain<Gather<In<KI, int>, ES>> {
 // asks for gridDim has another 256 bytes of arguments that the launch fills in (an empty kernel of 48 bytes of arguments
 // 2.42 us a launch without and 2.85 with them, of 64 bytes 2.42 and 3.07; a call of a bound program of one kernel
 // 2.64 to 2.70 us on the host without, 2.66 to 2.88 with them).
-template <int K, class T, int LdsThreads, bool Early, int Columns> struct Interp;        // kernels.hpp: reads KArgs::code, needs all of it
+template <int K, class T, int Threads, int Columns> struct Interp;        // kernels.hpp: reads KArgs::code, needs all of it
 
 // the fields of a Slot as words: f[0], f[1], i[0], i[1], ext[0], ext[1], m[0], m[1], m[2]
 constexpr int kSlotWords = 9;
@@ -489,7 +488,7 @@ template <class E> struct Needs {
   static constexpr bool all = false;
   template <int Base> static constexpr void words(WordList &) {}
 };
-template <int K, class T, int L, bool Early, int C> struct Needs<Interp<K, T, L, Early, C>> : Needs<void> { static constexpr bool all = true; };
+template <int K, class T, int N, int C> struct Needs<Interp<K, T, N, C>> : Needs<void> { static constexpr bool all = true; };
 template <int K, class T> struct Needs<In<K, T>> : Needs<void> { static constexpr int ins = K + 1; };
 template <class G> struct Needs<Gen<G>> : Needs<void> {
   template <int Base> static constexpr void words(WordList &l) { l.add_slot(Base, SlotUse<G>::value); }
@@ -582,7 +581,7 @@ template <unsigned Head, unsigned Outs, class... E> struct PackedArgs<Head, Outs
   __device__ __forceinline__ const KArgs &open() const { return args; }
   // The same, where the launch has put them (every kernel that takes one has it as its first argument).  From a parameter that
   // a kernel reads at more than some 300 places, as the scatters do, every lane has a copy of it made in its own memory (1336 bytes;
-  // us a pass with the copy / in place, permuted by an index array: 5003 elements 21.0 / 8.3, 300001 31.5 / 9.6, 3 x 10^6 124 / 59).
+  // us a pass with the copy / in place, permuted by an index array: 5003 elements 18.7 / 6.8, 2^22 164 / 64, 2^24 546 / 225).
   // For the other skeletons the parameter is the better one (compaction of 3 x 10^6 elements 42.3 us, in place 44.1).
   static __device__ __forceinline__ const KArgs &in_place() {
     return *(const KArgs *)(const __attribute__((address_space(4))) KArgs *)__builtin_amdgcn_kernarg_segment_ptr();

@@ -8,14 +8,12 @@ namespace fc {
 void append_generic_fold_instances(std::vector<Instance> &r) {
   const size_t first = r.size();
   // a segmented fold evaluates one element a lane
-  using XF0 = Interp<0, float, kBlock, false, 1>;
-  using XI0 = Interp<0, int, kBlock, false, 1>;
-  // scatters are bound by their destination, not by the interpreter: the stack in registers and reads ahead (histogram of
-  // 2^22 elements 312 us; without the reads ahead 324, with the stack in LDS 348)
-  using SI0 = Interp<0, int, 0, true>;
-  using SF1 = Interp<1, float, 0, true>;
-  using SI1 = Interp<1, int, 0, true>;
-  using SI2 = Interp<2, int, 0, true>;
+  using XF0 = Interp<0, float, kBlock, 1>;
+  using XI0 = Interp<0, int, kBlock, 1>;
+  using SI0 = Interp<0, int>;
+  using SF1 = Interp<1, float>;
+  using SI1 = Interp<1, int>;
+  using SI2 = Interp<2, int>;
   r.push_back(foldseg_<AddF32, XF0>());
   r.push_back(foldseg_<MaxF32, XF0>());
   r.push_back(foldseg_<AddI32, XI0>());

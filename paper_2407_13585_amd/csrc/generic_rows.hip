@@ -9,8 +9,8 @@ void append_generic_row_instances(std::vector<Instance> &r) {
   using XF0 = Interp<0, float>;
   using XI0 = Interp<0, int>;
   using XI1 = Interp<1, int>;
-  using SF0 = Interp<0, float, kBlock, false, 1>;      // the row scans evaluate one element a lane
-  using SI0 = Interp<0, int, kBlock, false, 1>;
+  using SF0 = Interp<0, float, kBlock, 1>;      // the row scans evaluate one element a lane
+  using SI0 = Interp<0, int, kBlock, 1>;
   r.push_back(rowscan_<SI0>());
   r.push_back(rowscan_<SI0, true>());
   r.push_back(rowscan_<SF0>());

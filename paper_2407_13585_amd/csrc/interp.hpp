@@ -75,9 +75,9 @@ __global__ __launch_bounds__(kBlock, 1) void interp_kernel(const KArgs a, Contro
   unsigned none[kVec], base = blockIdx.x * kTileOf;
   const unsigned mine = threadIdx.x * kVec;
   for (; base + kTileOf <= n; base += a.grid * kTileOf)
-    interp_run<1, kBlock, false>(a, 0, base + mine, InterpAhead<1, false>(), acc, none);
+    interp_run<1, kBlock>(a, 0, base + mine, acc, none);
   if (base + mine < n)                                   // one workgroup's, and for short arrays all that it does
-    interp_run<1, kBlock, false>(a, 0, base + mine, InterpAhead<1, false>(), acc, none, Span<1>(base, base + mine, 0u, n));
+    interp_run<1, kBlock>(a, 0, base + mine, acc, none, Span<1>(base, base + mine, 0u, n));
   interp_finish<kWavesPerBlock>(a, acc, ctl, partials, epoch);
 }
 

@@ -290,10 +290,8 @@ __global__ __launch_bounds__(kBlock) void store_fold_kernel(const Packed<kHeadN 
 // ------------------------------------------------------------------ interpreted elementwise clusters
 // Any cluster of maps, generates and gathers that ends in up to kMaxOut stored arrays
 // or in stored arrays and up to two folds, for which no kernel was compiled: the element
-// programs are run from KArgs::code, four elements per lane at a time.  The value stack is in LDS (or, for the
-// scatters, in registers, which the compiler indexes through the hardware's register index mode: the
-// index is the same for all lanes), the positions that gathers suspend, at most
-// kInterpGathers deep, in registers.  Every branch depends on the code only, which
+// programs are run from KArgs::code, four elements per lane at a time.  The value stack is in LDS,
+// the positions that gathers suspend, at most kInterpGathers deep, in registers.  Every branch depends on the code only, which
 // is the same for all lanes.  Results are the same as a compiled instance's: the same
 // element functions, applied in the same order.  A fallback: several times the
 // instructions of a compiled instance per element.  The kernels of such clusters are in interp.hpp.
@@ -365,45 +363,6 @@ __device__ __forceinline__ unsigned interp_identity(int op) {
   }
 }
 
-// A lane runs a program for a 128-bit group of elements at a time (G = 1), so that the cost of reading and decoding an
-// instruction is shared, or for one element (G = 0).
-// What element program `root` reads at the elements' own positions, read ahead.
-template <int G, bool Early> struct InterpAhead {
-  static constexpr int V = G ? kVec : 1;
-  using Group = Quad128<unsigned>;                     // a scan from the right reads groups at n - 4 - i, n of any length
-  unsigned v[Early ? kInterpDirect : 1][V];
-  static __device__ __forceinline__ void read_one(const void *array, unsigned first, unsigned (&x)[V]) {
-    const unsigned *p = static_cast<const unsigned *>(array) + first;
-    if constexpr (G == 0) {
-      x[0] = p[0];
-    } else {
-      const Group y = *reinterpret_cast<const Group *>(p);
-#pragma unroll
-      for (int c = 0; c < kVec; ++c) x[c] = y[c];
-    }
-  }
-  __device__ __forceinline__ void read(const KArgs &a, int root, unsigned first) {
-    if constexpr (Early) {
-#pragma unroll
-      for (int k = 0; k < kInterpDirect; ++k)
-        if (k < a.n_direct[root]) read_one(a.in[a.direct[root][k]], first, v[k]);
-    }
-  }
-  // x: array number k of those read ahead, which is external array `array`; both are the same in all lanes
-  __device__ __forceinline__ void get(const KArgs &a, int array, unsigned first, int k, unsigned (&x)[V]) const {
-    if constexpr (Early) {
-      static_assert(kInterpDirect == 4, "one value per array");
-#pragma unroll
-      for (int e = 0; e < V; ++e) {
-        const unsigned v0 = v[0][e], v1 = v[1][e], v2 = v[2][e], v3 = v[3][e];             // values: a choice of addresses would put v into memory
-        x[e] = k == 0 ? v0 : k == 1 ? v1 : k == 2 ? v2 : v3;
-      }
-    } else {
-      read_one(a.in[array], first, x);
-    }
-  }
-};
-
 using Words4 = unsigned __attribute__((ext_vector_type(4)));
 
 // the stack columns of a workgroup in LDS, for Columns elements a lane
@@ -416,40 +375,42 @@ __device__ __forceinline__ unsigned (*interp_stack())[Columns][Threads] {
 // The elements of a run that is not cut off by the end of the array (for the others: Span<1> of interp.hpp).
 struct Uncut {};
 
-// Starts at instruction `pc`; a kCodeYield ends the run with the program's values in `result`.
-// LdsThreads: threads of the workgroup if the values below the top of the stack are to lie in LDS (a column per lane), or 0.
-template <int G, int LdsThreads, bool Early, int Columns = kVec, class Cut = Uncut>
-__device__ __forceinline__ void interp_run(const KArgs &a, int pc, unsigned first, const InterpAhead<G, Early> &ahead,
-                                           unsigned (&acc)[kInterpFolds], unsigned (&result)[InterpAhead<G, Early>::V], const Cut &cut = Cut()) {
-  constexpr int V = InterpAhead<G, Early>::V;
+// Runs the program for a 128-bit group of elements (G = 1), so that the cost of reading and decoding an instruction is
+// shared, or for one element (G = 0).  Starts at instruction `pc`; a kCodeYield ends the run with the program's values in
+// `result`.  Threads: of the workgroup, a column of the stack's values below the top in LDS for each.
+template <int G, int Threads, int Columns = kVec, class Cut = Uncut>
+__device__ __forceinline__ void interp_run(const KArgs &a, int pc, unsigned first, unsigned (&acc)[kInterpFolds],
+                                           unsigned (&result)[G ? kVec : 1], const Cut &cut = Cut()) {
+  constexpr int V = G ? kVec : 1;
   constexpr bool kCut = !std::is_same<Cut, Uncut>::value;
-  static_assert(!kCut || (G == 1 && !Early), "a group that may be cut off, read where the code asks");
+  static_assert(!kCut || G == 1, "a group that may be cut off");
   auto own = [&](int e) {                              // the elements' own positions
     if constexpr (kCut) return (int)(first + cut.offset(e)); else return (int)first + e;
   };
-  auto read_own = [&](int array, int k, unsigned (&x)[V]) {
+  // x: an array at the elements' own positions
+  auto read_own = [&](int array, unsigned (&x)[V]) {
     if constexpr (kCut) {
       Words4 q[1];
       cut.template read<false>(a.in[array], q);
 #pragma unroll
       for (int e = 0; e < V; ++e) x[e] = q[0][e];
+    } else if constexpr (G == 0) {
+      x[0] = static_cast<const unsigned *>(a.in[array])[first];
     } else {
-      ahead.get(a, array, first, k, x);
+      // a scan from the right reads groups at n - 4 - i, n of any length
+      const Quad128<unsigned> y = *reinterpret_cast<const Quad128<unsigned> *>(static_cast<const unsigned *>(a.in[array]) + first);
+#pragma unroll
+      for (int e = 0; e < V; ++e) x[e] = y[e];
     }
   };
   int at[V];                                           // the positions element programs read at
   static_assert(kInterpGathers == 3, "two positions suspended at most");
   int suspended[kInterpGathers - 1][V];                // of the gathers around the innermost but one; outermost: own positions
-  unsigned top[V], below[LdsThreads ? 1 : kInterpDepth][V];   // an array of its own: as part of a struct it would be put into memory
-  unsigned (*column)[Columns][LdsThreads ? LdsThreads : 1] = nullptr;
-  if constexpr (LdsThreads != 0) column = interp_stack<LdsThreads, Columns>();
-  static_assert(LdsThreads == 0 || V <= Columns, "a column for each element");
-#pragma unroll
-  for (int k = 0; k < (LdsThreads ? 1 : kInterpDepth); ++k)
-#pragma unroll
-    for (int e = 0; e < V; ++e) below[k][e] = 0u;
-  auto set_below = [&](int k, int e, unsigned x) { if (LdsThreads) column[k][e % Columns][threadIdx.x] = x; else below[k][e] = x; };
-  auto get_below = [&](int k, int e) { return LdsThreads ? column[k][e % Columns][threadIdx.x] : below[k][e]; };
+  unsigned top[V];
+  unsigned (*column)[Columns][Threads] = interp_stack<Threads, Columns>();
+  static_assert(V <= Columns, "a column for each element");
+  auto set_below = [&](int k, int e, unsigned x) { column[k][e][threadIdx.x] = x; };
+  auto get_below = [&](int k, int e) { return column[k][e][threadIdx.x]; };
 #pragma unroll
   for (int e = 0; e < V; ++e) { at[e] = own(e); top[e] = 0u; }
   int gathers = 0, count = 0;                          // the same in every lane
@@ -467,9 +428,9 @@ __device__ __forceinline__ void interp_run(const KArgs &a, int pc, unsigned firs
       for (int e = 0; e < V; ++e) top[e] = get_below(count - 1, e);
     }
   };
-  constexpr bool kFetch = Early || V > 1;              // the next instruction is fetched while one is worked on
-  for (Code c = Early ? a.code[pc] : a.code_word(pc), next; pc < kMaxCode - 1; ++pc, c = kFetch ? next : a.code_word(pc)) {
-    if (kFetch) next = Early ? a.code[pc + 1] : a.code_word(pc + 1);             // the last entry is kCodeEnd
+  constexpr bool kFetch = V > 1;              // the next instruction is fetched while one is worked on
+  for (Code c = a.code_word(pc), next; pc < kMaxCode - 1; ++pc, c = kFetch ? next : a.code_word(pc)) {
+    if (kFetch) next = a.code_word(pc + 1);             // the last entry is kCodeEnd
     if (c.op == kCodeEnd) break;
     if (c.op == kCodeYield) {
 #pragma unroll
@@ -480,7 +441,7 @@ __device__ __forceinline__ void interp_run(const KArgs &a, int pc, unsigned firs
       case kCodeIn: {
         push_room();
         if (c.b != 0) {
-          read_own(c.a, c.b - 1, top);
+          read_own(c.a, top);
         } else {
           const unsigned *p = static_cast<const unsigned *>(a.in[c.a]);
 #pragma unroll
@@ -491,7 +452,7 @@ __device__ __forceinline__ void interp_run(const KArgs &a, int pc, unsigned firs
       case kCodeLookup: {
         push_room();
         const unsigned *p = static_cast<const unsigned *>(a.in[c.a]);
-        read_own(c.c, c.b - 1, top);
+        read_own(c.c, top);
 #pragma unroll
         for (int e = 0; e < V; ++e) top[e] = p[(int)top[e]];
         break;
@@ -625,29 +586,25 @@ __device__ __forceinline__ void interp_finish(const KArgs &a, const unsigned (&a
 // (KArgs::code from KArgs::root[K] to the kCodeYield).  With it every skeleton of this
 // file has an instance that takes any element program: what the matcher cannot pair with a
 // compiled element program runs through these.
-// LdsThreads: threads of the workgroup if the value stack is to lie in LDS, or 0; Columns: elements a lane that the
-// stack has room for (1: only eval is used).  Early: the arrays at the element's own position are read ahead of the run.
+// Threads: of the workgroup; Columns: elements a lane that the stack has room for (1: only eval is used).
 // The stack in LDS and reads where the code asks for them: in registers, stack and reads ahead leave two to four waves
 // a SIMD, too few to hide the interpreter's chain (2^24 elements: row folds of 32 elements 61 us against 115 with
-// registers and reads ahead, row scans of 32 84 / 107, segmented folds of 16 elements a row 338 / 484, fp32 scans 38 / 68).
-template <int K, class T, int LdsThreads = kBlock, bool Early = false, int Columns = kVec>
+// registers and reads ahead, row scans of 32 84 / 107, segmented folds of 16 elements a row 338 / 484, fp32 scans 38 / 68,
+// scatters by a permutation 225 / 240).
+template <int K, class T, int Threads = kBlock, int Columns = kVec>
 struct Interp {
   using R = T;
   static constexpr int kNodes = 0;                     // the code names its parameter slots itself
   static constexpr bool kMirror = false;
   template <int Base, bool Stream = false> static __device__ __forceinline__ T eval(const KArgs &a, int i) {
     unsigned r[1] = {0u}, none[kInterpFolds] = {0u, 0u};
-    InterpAhead<0, Early> ahead;
-    ahead.read(a, K, (unsigned)i);
-    interp_run<0, LdsThreads, Early, Columns>(a, (int)a.root[K], (unsigned)i, ahead, none, r);
+    interp_run<0, Threads, Columns>(a, (int)a.root[K], (unsigned)i, none, r);
     return from_bits<T>((int)r[0]);
   }
   // i may be any position, as for the compiled element programs
   template <int Base> static __device__ __forceinline__ Vec4<T> eval4(const KArgs &a, int i) {
     unsigned r[kVec] = {0u, 0u, 0u, 0u}, none[kInterpFolds] = {0u, 0u};
-    InterpAhead<1, Early> ahead;
-    ahead.read(a, K, (unsigned)i);
-    interp_run<1, LdsThreads, Early, Columns>(a, (int)a.root[K], (unsigned)i, ahead, none, r);
+    interp_run<1, Threads, Columns>(a, (int)a.root[K], (unsigned)i, none, r);
     return Vec4<T>{{from_bits<T>((int)r[0]), from_bits<T>((int)r[1]), from_bits<T>((int)r[2]), from_bits<T>((int)r[3])}};
   }
   static void sig(std::string &s) { s += std::string("*") + DtypeName<T>::s(); }
