@@ -3,13 +3,13 @@
 //
 // Short programs were bound by the instructions of the interpreter and are bound by memory where nothing is looked up (sum of exp(-x)^2 + 1, 2^24
 // elements: 54 vector instructions an element and 35 us before, 25 now; exp(-d) * t stored and summed 54 and 40 us, of 200 MB;
-// exp(-d)^2 + 1 stored 34.5 and 28; a * b + exp(-c) stored, 2^22: 19.4 and 15.1).  The value stack is named rows of registers
+// exp(-d)^2 + 1 stored 34.5 and 28; a * b + exp(-c) stored, 2^22: 18.1 and 14.1).  The value stack is named rows of registers
 // that every instruction works on from its top, not an array indexed at run time (three instructions to reach a register); the
 // rows are vectors of four, which the compiler moves in pairs where the branches of the interpreter meet (elements on their own: 24.9
 // against 26.8 us for the first of these sums); the arrays of the next tile are on their way while a tile is worked on,
 // and results really go past the caches.  Short arrays last as long as one program: every piece of code that one
 // workgroup runs after another is fetched for the first time, so the end of the array is a group like the others (42034
-// elements with a lookup 8.9 us before, with two passes more for what was left, 6.3 now).
+// elements with a lookup 9.3 us before, with two passes more for what was left, 6.4 now).
 #pragma once
 
 #include "kernels.hpp"
@@ -272,7 +272,9 @@ __device__ __forceinline__ void interp_short(const KArgs &a, const Span<G> span,
   }
 }
 
-// G groups a lane at a time, single groups for the rest.
+// G groups a lane at a time, single groups for the rest.  The widest form (two groups, four arrays, Enter) needs two registers more than
+// four workgroups a compute unit leave it, and spills them (12 bytes a lane): a * b + exp(-c) stored and summed, 2^20 elements 10.9 us, 2^24 59,
+// where the general interpreter took 16.1 and 70.
 template <int G, int D, int Depth, bool Enter, bool Next>
 __global__ __launch_bounds__(kBlock, 4) void interp_short_kernel(const KArgs a, Control *ctl, unsigned long long *partials) {
   const unsigned n = (unsigned)a.n;

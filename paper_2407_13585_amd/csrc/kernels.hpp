@@ -911,7 +911,9 @@ constexpr unsigned kFineIndexLimit = 1u << 24;         // table elements at most
 // Ranges and indices per tile: the mean of a slot is the same for both.  Tables of up to 2^23 elements fit 256 ranges,
 // one for every compute unit in the second kernel (512 are two rounds of filling LDS), and then tiles of half the length keep twice as
 // many compute units busy in the first, or two workgroups on each: few positions are bound by the chain of one tile and one
-// range, not by their bytes (2^21 positions in as many elements: both kernels 25.4 us with 512 ranges, 20.0 with 256).
+// range, not by their bytes (2^21 positions in as many elements: both kernels 25.4 us with 512 ranges, 20.0 with 256).  Two workgroups
+// leave a lane 64 registers, eleven fewer than the first kernel would like: it spills them (48 bytes a lane), also on the way of the elements that
+// find their slot full, and is the faster one there too (2^21 positions, all in one range: 53.5 us with 512 ranges, 33.6 with 256).
 template <int Ranges> struct FineShape {
   static constexpr int kBins = Ranges;
   static constexpr int kTile = Ranges * 64;
@@ -1439,10 +1441,10 @@ __global__ __launch_bounds__(kBlock) void foldseg_blocked_kernel(const KArgs a, 
 //     tile's slots built in LDS as they go to memory; where two tiles' slots fit LDS, two tiles in turn, so that one goes
 //     to memory while the next is sorted: one barrier a tile, and two with one image, which costs up to a hundredth of the pass.
 //     2^26 elements, before with a counter per wave and range, three passes over them and three barriers: 113 us,
-//     now 101 of which 567 MB take 94 at the rate of a copy), and keeps two 16-bit numbers per element, in two arrays: the offset inside the range and the
+//     now 101 of which 570 MB take 94 at the rate of a copy), and keeps two 16-bit numbers per element, in two arrays: the offset inside the range and the
 //     position inside the tile (offsets slot after slot for every range, positions tile after tile).
-//     An element that finds its slot full (one to five in a hundred of evenly spread indices, as seg_plan
-//     has it; most of indices that crowd into few ranges) goes onto the tile's list of (position, index) pairs.
+//     An element that finds its slot full (at most five in a hundred of evenly spread indices, as seg_plan
+//     has it, and for 114 ranges four in a thousand; most of indices that crowd into few ranges) goes onto the tile's list of (position, index) pairs.
 //  2. seg_gather_kernel: a workgroup reads a table range into LDS and turns a stretch of the
 //     range's offsets into values, slot for slot (the slots of a range lie one behind the other).
 //  3. seg_rows_kernel: a workgroup per tile puts the tile's values (one slot per range, then those
@@ -1647,7 +1649,6 @@ __device__ __forceinline__ unsigned wave_rows_below(const unsigned *start, unsig
 template <class T, int KT>
 __global__ __launch_bounds__(kSegBlock) void seg_gather_kernel(const KArgs a, const unsigned short *offsets, T *gathered,
                                                                unsigned *first_row, const SegPlan plan, unsigned elems, unsigned parts) {
-  using Raw = unsigned __attribute__((ext_vector_type(4)));
   using RawI = int __attribute__((ext_vector_type(4)));
   using TV = T __attribute__((ext_vector_type(4)));
   constexpr int kStream = 0x2;                                // cache policy of the buffer loads: nt
