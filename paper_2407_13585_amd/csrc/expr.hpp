@@ -458,7 +458,7 @@ template <int KI, class ES> struct GatherChain<Gather<In<KI, int>, ES>> {
 // these programs use, as Packed<...>, and open() puts them back where the program looks for them (registers:
 // every index is known when the kernel is compiled).  The number of workgroups is one of the arguments: a kernel that
 // asks for gridDim has another 256 bytes of arguments that the launch fills in (an empty kernel of 48 bytes of arguments
-// 2.42 us a launch without and 2.85 with them, of 64 bytes 2.42 and 3.07; 5003 elements stored 2.3 us a pass without, 2.8 with them).
+// 2.42 us a launch without and 2.85 with them, of 64 bytes 2.42 and 3.07).
 template <int K, class T, int Threads, int Columns> struct Interp;        // kernels.hpp: reads KArgs::code, needs all of it
 
 // the fields of a Slot as words: f[0], f[1], i[0], i[1], ext[0], ext[1], m[0], m[1], m[2]
